@@ -140,10 +140,13 @@ mpr_status mpr_build_border_transfer(int m, uint16_t *A, int64_t lda, int64_t *s
  * [0, 0xFFFE].  M, N, K >= 0 (an empty K gives an all-MPR_INF C).  C must
  * not overlap A or B.  Fast path: A, B, C 16-byte aligned and lda, ldb, ldc
  * multiples of 8; any other layout takes a slower element-wise path.  The
- * configuration comes from the tile table of the process-wide arithmetic
+ * product runs on the matrix cores when K >= 128 (values 0..30 as powers of
+ * two, the least sum read off the exponent of a sum of products; a block
+ * with a larger minimum is computed again in the f16 form), else in the
+ * configuration of the tile table of the process-wide arithmetic
  * (mpr_set_arith): packed uint16 by default; in the f16 form the result is
  * the same, but tiles whose minima reach 2048 are computed twice (about
- * 1.75x the uint16 time for such tiles). */
+ * 1.75x the uint16 time for such tiles).  The same bits in every form. */
 mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K,
                             const uint16_t *A, int64_t lda,
                             const uint16_t *B, int64_t ldb,
@@ -151,7 +154,7 @@ mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K,
                             int32_t *d_status, mpr_stream stream);
 
 /* Same with an explicit tile configuration (0 <= cfg < mpr_gemm_config_count);
- * used by the autotuner.  cfg = -1 picks from the tile table. */
+ * used by the autotuner.  cfg = -1 picks as mpr_minplus_gemm does. */
 mpr_status mpr_minplus_gemm_cfg(int cfg, int64_t M, int64_t N, int64_t K,
                                 const uint16_t *A, int64_t lda,
                                 const uint16_t *B, int64_t ldb,
@@ -167,8 +170,9 @@ mpr_status mpr_minplus_gemm_cfg(int cfg, int64_t M, int64_t N, int64_t K,
  * 128 x 128 tile of the same arithmetic.  Costs well under 1 % at the sizes
  * measured (N = 7411 to 21909).  For callers that run long products beside
  * latency-sensitive work: the query server builds its large ladders with
- * it.  cfg = -1 picks from the tile table.  Arguments and errors as
- * mpr_minplus_gemm. */
+ * it.  cfg = -1 picks as mpr_minplus_gemm does (a product of many blocks on
+ * the matrix cores then holds one of two workgroups per CU).  Arguments and
+ * errors as mpr_minplus_gemm. */
 mpr_status mpr_minplus_gemm_spare(int cfg, int64_t M, int64_t N, int64_t K,
                                   const uint16_t *A, int64_t lda,
                                   const uint16_t *B, int64_t ldb,

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "level.h"
 #include "trace_rows.h"
 
 namespace mpr {
@@ -119,7 +120,7 @@ static mpr_status gemm_norm_impl(int64_t M, int64_t N, int64_t K, const u16 *A, 
         B = Bp;
         ldb = ldp;
     }
-    e = gemm_launch(-1, M, N, K, A, lda, B, ldb, C, ldc, s);
+    e = product_launch(-1, M, N, K, A, lda, B, ldb, C, ldc, s);
     if (e != MPR_OK) return e;
     return normalise_launch(M, N, C, ldc, Ra, Rb ? s_scalar : nullptr, Rc, st, nullptr, s);
 }
@@ -423,7 +424,7 @@ extern "C" mpr_status mpr_minplus_gemm_cfg(int cfg, int64_t M, int64_t N, int64_
         if ((e = validate_launch(A, M, K, lda, d_status, s)) != MPR_OK) return e;
         if ((e = validate_launch(B, K, N, ldb, d_status, s)) != MPR_OK) return e;
     }
-    return gemm_launch(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
+    return product_launch(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
 }
 
 extern "C" mpr_status mpr_minplus_gemm_spare(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t *A,
@@ -439,7 +440,7 @@ extern "C" mpr_status mpr_minplus_gemm_spare(int cfg, int64_t M, int64_t N, int6
         if ((e = validate_launch(A, M, K, lda, d_status, s)) != MPR_OK) return e;
         if ((e = validate_launch(B, K, N, ldb, d_status, s)) != MPR_OK) return e;
     }
-    return gemm_launch_spare(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
+    return product_launch_spare(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
 }
 
 extern "C" mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K, const uint16_t *A, int64_t lda,
@@ -719,7 +720,7 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
             } else {
                 const int64_t ps = (k - 2) % M;
                 e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
-                           : gemm_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
+                           : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
                 if (e == MPR_OK)
                     e = normalise_launch(n, n, Nk, w.ld, slot_R(w, ps), nullptr, Rk, st, w.row_hash, s);
             }
@@ -785,7 +786,7 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
             if (r == MPR_OK) r = normalise_launch(n, n, Nk, w.ld, nullptr, nullptr, Rk, st, w.row_hash, s);
         } else {
             r = sparse ? sparse_step_launch(slot_N(w, prev_slot), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
-                       : gemm_launch(-1, n, n, n, slot_N(w, prev_slot), w.ld, A, lda, Nk, w.ld, s);
+                       : product_launch(-1, n, n, n, slot_N(w, prev_slot), w.ld, A, lda, Nk, w.ld, s);
             if (r == MPR_OK)
                 r = normalise_launch(n, n, Nk, w.ld, slot_R(w, prev_slot), nullptr, Rk, st, w.row_hash, s);
         }

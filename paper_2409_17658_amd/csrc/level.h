@@ -1,0 +1,465 @@
+// level.h -- the (min,+) block product on the matrix cores ("level form").
+//
+// A value v <= 30 is written as the power of two 2^(59 - 6 v) in bf16,
+// infinity (and every larger value) as 0.  The product of two such numbers
+// is 2^(118 - 6 (a + b)), and a sum of 32 of them lies in
+// [2^(118 - 6 t), 2^(118 - 6 t + 5)] with t the least a + b among them: the
+// exponent of the sum names t, because 32 equal terms raise it by 5 and one
+// level is worth 6.  So one f32 accumulator over 32 values of k (two
+// v_mfma_f32_32x32x16_bf16) holds the minimum of 32 pairs exactly, and the
+// minimum over all k is the maximum of those positive floats (an unsigned
+// integer maximum of their bits, two accumulators per v_max3_u32).  Every
+// term is a power of two and no sum loses its largest term, so rounding
+// inside the matrix core can not change the exponent's level.
+//
+// Exactness.  A result t <= 30 is exact: every pair that sums to 30 or less
+// has both values <= 30.  Any other result (t > 30, or no term at all) is
+// exact only when no finite operand of the block exceeds 30 and their
+// largest sum stays within the f32 range (LV_SUM, the smallest subnormals);
+// a block with such a result looks at its operands' largest finite values
+// once (level_clean) and, when they do not allow the conclusion, is computed
+// by the VALU forms of tile.h instead.  The product is the same bit for bit
+// on every input.
+//
+// Conversion: min(v, 31) and one multiply-add give the bf16 bit pattern
+// (the exponent field is linear in v and is 0 at v = 31), two packed
+// instructions per two values, done once per block while a slice is staged
+// into LDS.  LDS holds 16-byte chunks of 8 consecutive k: [k / 8][row] for
+// A, [k / 8][column] for B (transposed on the way by v_perm_b32), the order
+// the matrix instruction reads its operands in.
+//
+// What bounds it: per 64 k and 32 x 32 outputs a SIMD spends 128 cycles in
+// the matrix core, 64 on the maxima and (128 x 128 blocks) 80 on the
+// conversion and transposition, so matrix core and VALU are both nearly
+// busy.  N = 16384, entries 0..15: 117.0 ms (37.6 T pairs/s) in the uint16
+// form, 11.4 ms (387 T pairs/s) in this one; a bf16 library product of
+// 8192 x 8192 x 8192 reaches 604 T multiply-adds/s on the same card.
+#pragma once
+
+#include "tile.h"
+
+namespace mpr {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int LV_STEP = 6;                       // exponent bits per level
+constexpr uint32_t LV_MAX = 30;                  // largest value with a nonzero image
+constexpr int LV_BIAS = LV_STEP * (LV_MAX + 1);  // exponent field of level 0: 186 = 127 + 59
+constexpr int LV_TOP = 2 * (LV_BIAS - 127);      // exponent of a product of two level-0 images
+constexpr uint32_t LV_SUM = 44;                  // 2^(118 - 6 * 44) = 2^-146, a subnormal f32
+// Bits of the least sum that proves a result <= LV_MAX: 2^(118 - 180).
+constexpr uint32_t LV_SURE = (uint32_t)(127 + LV_TOP - LV_STEP * (int)LV_MAX) << 23;
+
+// MI x NI tiles of 32 x 32 outputs per wave, WM x WN waves per block.
+template <int MI_, int NI_, int WM_, int WN_>
+struct LevelCfg {
+    static constexpr int MI = MI_, NI = NI_, WM = WM_, WN = WN_;
+    static constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN, NT = 64 * WM * WN;
+    static constexpr int BK = 64, KC = BK / 8;
+    // Chunks per k group.  The A pitch is odd, so the 8 lanes that stage the
+    // 8 k groups of one row write to 8 different 16-byte bank groups.
+    static constexpr int PA = BM + 1, PB = BN;
+    static constexpr int STAGE = KC * (PA + PB);
+    static constexpr int LDS_CHUNKS = 2 * STAGE;
+    static constexpr int A_CPT = BM * KC / NT;   // A chunks a thread stages
+    static constexpr int B_COLS = BN * KC / NT;  // columns of 8 k a thread stages
+    static_assert(BM * KC % NT == 0 && (B_COLS == 2 || B_COLS == 4), "staging split");
+};
+
+// 2^(59 - 6 v) in bf16 for both halves; 0 for v > 30.
+__device__ __forceinline__ uint32_t level_image(uint32_t x)
+{
+    const u16x2 y = min2(as_u16x2(x), (u16x2){LV_MAX + 1, LV_MAX + 1});
+    constexpr u16 mul = (u16)(0u - (LV_STEP << 7)), add = (u16)(LV_BIAS << 7);
+    return as_u32((u16x2)(y * (u16x2){mul, mul} + (u16x2){add, add}));
+}
+
+// 16 / 8 / 4 bytes of a row that need not be aligned (global loads take any
+// 2-byte aligned address).
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+typedef u32x2 __attribute__((aligned(2))) u32x2_any;
+typedef uint32_t __attribute__((aligned(2))) u32_any;
+typedef const __attribute__((address_space(1))) unsigned char gbytes;
+__device__ __forceinline__ uint4 uload16(gbytes *base, uint32_t off)
+{
+    const u32x4 r = *(const __attribute__((address_space(1))) u32x4_any *)(base + off);
+    return make_uint4(r.x, r.y, r.z, r.w);
+}
+__device__ __forceinline__ void ustore16(gu16 *p, const uint4 &v)
+{
+    const u32x4 r = {v.x, v.y, v.z, v.w};
+    *(__attribute__((address_space(1))) u32x4_any *)p = r;
+}
+
+// 8 consecutive values shifted down by s >= 0 of them, infinity moving in.
+__device__ __forceinline__ uint4 shift_in_inf(const uint4 &v, int s)
+{
+    uint64_t lo = ~((uint64_t)v.y << 32 | v.x), hi = ~((uint64_t)v.w << 32 | v.z);
+    if (s >= 4) {
+        lo = hi;
+        hi = 0;
+        s -= 4;
+    }
+    if (s >= 4) lo = s = 0;
+    if (s > 0) lo = lo >> (16 * s) | hi << (64 - 16 * s);
+    hi >>= 16 * s;
+    return make_uint4(~(uint32_t)lo, ~(uint32_t)(lo >> 32), ~(uint32_t)hi, ~(uint32_t)(hi >> 32));
+}
+
+// Staging of the left operand, `rows` (>= 1) rows of K >= 8 values from
+// `base`: chunk q of a thread is row tid / 8 + q NT / 8, k group tid % 8 of
+// the slice.  Rows past the end read the last row (their results are not
+// used); k past the end reads as infinity.
+template <class C>
+struct LevelA {
+    gbytes *base, *at;  // the operand; the slice the next load() takes
+    int64_t K;
+    uint32_t off[C::A_CPT];  // bytes from a slice's start to each chunk
+    uint4 r[C::A_CPT];
+    __device__ __forceinline__ LevelA(const gu16 *p, int64_t ld, int rows, int64_t K_) : base((gbytes *)p), K(K_)
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) {
+            const int row = (int)threadIdx.x / C::KC + q * (C::NT / C::KC);
+            off[q] = (uint32_t)(row < rows ? row : rows - 1) * (uint32_t)ld * 2u + (threadIdx.x % C::KC) * 16u;
+        }
+    }
+    __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * 2; }
+    // a full slice; the next one is the slice before it
+    __device__ __forceinline__ void load()
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) r[q] = uload16(at, off[q]);
+        at -= C::BK * 2;
+    }
+    // the last K % BK values, in a slice of their own from k0
+    __device__ __forceinline__ void load_tail(int64_t k0)
+    {
+        gbytes *b = base + k0 * 2;
+        const int over = (int)(k0 - K) + (int)(threadIdx.x % C::KC) * 8 + 8;  // values past the end
+        const int back = over > 0 ? over : 0;
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) {
+            r[q] = uload16(b - 2 * back, off[q]);
+            r[q] = shift_in_inf(r[q], back);
+        }
+    }
+    __device__ __forceinline__ void store(uint4 *as) const
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+            as[((int)threadIdx.x % C::KC) * C::PA + (int)threadIdx.x / C::KC + q * (C::NT / C::KC)] =
+                make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
+    }
+    // largest finite value (signed: infinity is -1)
+    __device__ __forceinline__ i16x2 largest(i16x2 m) const
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(r[q], e)));
+        return m;
+    }
+};
+
+// Staging of the right operand, K rows from `base` (the block's first
+// column; `cols` >= 1 of the block's columns exist, and the row has at least
+// B_COLS up to its end): a thread takes 8 consecutive k (its k group) of
+// B_COLS consecutive columns and writes one chunk per column.  Rows past K
+// read the last row (the left operand is infinite there) and columns past
+// the end hold any values of the row (their results are not used).
+// Column n of a k group lies at chunk n ^ (n / 8 % 4): 8 consecutive lanes
+// write to 8 different bank groups, and so do 8 lanes that read consecutive
+// columns.
+template <class C>
+struct LevelB {
+    static constexpr int TPG = C::BN / C::B_COLS;  // threads per k group
+    gbytes *base, *at;
+    int64_t K;
+    uint32_t ldb2, coff;  // row bytes; byte offset of the thread's columns
+    int back;             // columns that offset was moved back by to stay in the row
+    uint32_t r[8][C::B_COLS / 2];
+    __device__ __forceinline__ LevelB(const gu16 *p, int64_t ld, int cols, int64_t K_)
+        : base((gbytes *)p), K(K_), ldb2((uint32_t)ld * 2u)
+    {
+        const int col = ((int)threadIdx.x % TPG) * C::B_COLS;
+        const int c = min(col, cols - C::B_COLS);  // may be negative: columns before the block
+        back = col - c;
+        base += min(0, cols - C::B_COLS) * 2;
+        coff = (uint32_t)(c - min(0, cols - C::B_COLS)) * 2u;
+    }
+    __device__ __forceinline__ void take(int k, gbytes *b, uint32_t o)
+    {
+        if constexpr (C::B_COLS == 4) {
+            const u32x2 v = *(const __attribute__((address_space(1))) u32x2_any *)(b + o);
+            r[k][0] = v.x;
+            r[k][1] = v.y;
+        } else {
+            r[k][0] = *(const __attribute__((address_space(1))) u32_any *)(b + o);
+        }
+    }
+    __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * ldb2; }
+    __device__ __forceinline__ void load()
+    {
+        const uint32_t o = (uint32_t)threadIdx.x / TPG * 8u * ldb2 + coff;
+#pragma unroll
+        for (int k = 0; k < 8; k++) take(k, at + (uint64_t)k * ldb2, o);
+        at -= (uint64_t)C::BK * ldb2;
+    }
+    __device__ __forceinline__ void load_tail(int64_t k0)
+    {
+        gbytes *b = base + k0 * ldb2;
+        const int kg = (int)threadIdx.x / TPG;
+        const int last = (int)(K - k0) - 1;
+#pragma unroll
+        for (int k = 0; k < 8; k++) take(k, b, (uint32_t)min(kg * 8 + k, last) * ldb2 + coff);
+    }
+    __device__ __forceinline__ void store(uint4 *bs)
+    {
+        const int kg = (int)threadIdx.x / TPG, cg = (int)threadIdx.x % TPG;
+        if (back) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                if constexpr (C::B_COLS == 4) {
+                    const uint64_t v = ((uint64_t)r[k][1] << 32 | r[k][0]) >> (16 * (back & 3));
+                    r[k][0] = (uint32_t)v;
+                    r[k][1] = (uint32_t)(v >> 32);
+                } else {
+                    r[k][0] >>= 16 * (back & 1);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < C::B_COLS; j++) {
+            uint32_t w[4];
+#pragma unroll
+            for (int p = 0; p < 4; p++)
+                w[p] = level_image(__builtin_amdgcn_perm(r[2 * p + 1][j / 2], r[2 * p][j / 2],
+                                                         (j & 1) ? 0x07060302u : 0x05040100u));
+            const int n = cg * C::B_COLS + j;
+            bs[kg * C::PB + (n ^ ((n >> 3) & 3))] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    __device__ __forceinline__ i16x2 largest(i16x2 m) const
+    {
+#pragma unroll
+        for (int k = 0; k < 8; k++)
+#pragma unroll
+            for (int e = 0; e < C::B_COLS / 2; e++)
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, r[k][e]));
+        return m;
+    }
+};
+
+template <class C>
+struct LevelAcc {
+    uint32_t v[C::MI][C::NI][16];
+};
+
+// The k loop: acc = the largest 32-term sum of each output (its f32 bits).
+// The product is taken transposed (D = B^T A^T): a lane then holds one row
+// of C and runs of 4 consecutive columns.  A partial slice at the end of K
+// is taken first, so that the loop itself has no edge.
+template <class C, class AOp, class BOp>
+__device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4 *lds, LevelAcc<C> &acc)
+{
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    const int wm = wave / C::WN, wn = wave % C::WN;
+    const int aoff = (lane >> 5) * C::PA + wm * 32 * C::MI + (lane & 31);
+    const int boff = C::KC * C::PA + (lane >> 5) * C::PB + wn * 32 * C::NI + ((lane & 31) ^ ((lane >> 3) & 3));
+#pragma unroll
+    for (int mi = 0; mi < C::MI; mi++)
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc.v[mi][ni][r] = 0;
+    int64_t left = K / C::BK;  // full slices not yet loaded
+    aop.seek((left - 1) * C::BK);
+    bop.seek((left - 1) * C::BK);
+    if (K % C::BK) {
+        aop.load_tail(left * C::BK);
+        bop.load_tail(left * C::BK);
+    } else {
+        aop.load();
+        bop.load();
+        left--;
+    }
+    aop.store(lds);
+    bop.store(lds + C::KC * C::PA);
+    __syncthreads();
+    for (int cur = 0;; cur ^= 1) {
+        const bool more = left-- > 0;
+        uint4 *next = lds + (cur ^ 1) * C::STAGE;
+        const uint4 *as = lds + cur * C::STAGE + aoff, *bs = lds + cur * C::STAGE + boff;
+        if (more) aop.load();
+        bf16x8 bf[C::NI][4];
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) bf[ni][ks] = __builtin_bit_cast(bf16x8, bs[2 * ks * C::PB + 32 * ni]);
+#pragma unroll
+        for (int mi = 0; mi < C::MI; mi++) {
+            if (C::MI > 1 && mi == C::MI / 2 && more) {
+                aop.store(next);
+                bop.load();
+            }
+            bf16x8 af[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) af[ks] = __builtin_bit_cast(bf16x8, as[2 * ks * C::PA + 32 * mi]);
+#pragma unroll
+            for (int ni = 0; ni < C::NI; ni++) {
+                f32x16 t0 = {}, t1 = {};
+                t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][0], af[0], t0, 0, 0, 0);
+                t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][2], af[2], t1, 0, 0, 0);
+                t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][1], af[1], t0, 0, 0, 0);
+                t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][3], af[3], t1, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    const float f0 = t0[r], f1 = t1[r];
+                    const uint32_t u0 = __builtin_bit_cast(uint32_t, f0), u1 = __builtin_bit_cast(uint32_t, f1);
+                    uint32_t &d = acc.v[mi][ni][r];
+                    d = max(max(d, u0), u1);
+                    // keeps the maximum here: moved past the branches below
+                    // it would hold both accumulators in registers
+                    asm volatile("" : "+v"(d));
+                }
+                __builtin_amdgcn_sched_barrier(0);  // one tile of accumulators in registers at a time
+            }
+        }
+        if (more) {
+            if (C::MI == 1) {
+                aop.store(next);
+                bop.load();
+            }
+            bop.store(next + C::KC * C::PA);
+        }
+        __syncthreads();
+        if (!more) return;
+    }
+}
+
+// Block row / first of 4 block columns that accumulator registers 4q..4q+3
+// of wave tile (mi, ni) hold.
+template <class C>
+__device__ __forceinline__ int level_row(int mi)
+{
+    return ((int)(threadIdx.x >> 6) / C::WN) * 32 * C::MI + mi * 32 + (int)(threadIdx.x & 31);
+}
+template <class C>
+__device__ __forceinline__ int level_col(int ni, int q)
+{
+    return ((int)(threadIdx.x >> 6) % C::WN) * 32 * C::NI + ni * 32 + 8 * q + 4 * (int)((threadIdx.x >> 5) & 1);
+}
+
+// The value an accumulator stands for (infinity when no term was found).
+__device__ __forceinline__ uint32_t level_value(uint32_t u)
+{
+    // u = m 2^e with m in [1/2, 1): e = 119 - 6 t .. 124 - 6 t
+    const int e = __builtin_amdgcn_frexp_expf(__builtin_bit_cast(float, u));
+    const uint32_t t = ((uint32_t)(LV_TOP + 6 - e) * 171u) >> 10;  // floor of a sixth, exact below 512
+    return u == 0 ? 0xFFFFu : t;
+}
+
+// True (block-uniform) when every result of the block inside rows x cols is
+// certainly exact: no accumulator below LV_SURE.
+template <class C>
+__device__ __forceinline__ bool level_sure(const LevelAcc<C> &acc, int rows, int cols)
+{
+    bool bad = false;
+#pragma unroll
+    for (int mi = 0; mi < C::MI; mi++) {
+        const bool rin = level_row<C>(mi) < rows;
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    bad |= rin && level_col<C>(ni, q) + j < cols && acc.v[mi][ni][4 * q + j] < LV_SURE;
+    }
+    return !__syncthreads_or(bad);
+}
+
+// True (block-uniform) when no finite operand of the block exceeds LV_MAX
+// and no finite sum exceeds LV_SUM, so every accumulator is exact.  One more
+// pass over the operands; lds is free.
+template <class C, class AOp, class BOp>
+__device__ __forceinline__ bool level_clean(int64_t K, AOp &aop, BOp &bop, uint4 *lds)
+{
+    i16x2 ma = {-1, -1}, mb = {-1, -1};
+    int64_t left = K / C::BK;
+    aop.seek((left - 1) * C::BK);
+    bop.seek((left - 1) * C::BK);
+    if (K % C::BK) {
+        aop.load_tail(left * C::BK);
+        bop.load_tail(left * C::BK);
+        ma = aop.largest(ma);
+        mb = bop.largest(mb);
+    }
+    for (; left > 0; left--) {
+        aop.load();
+        bop.load();
+        ma = aop.largest(ma);
+        mb = bop.largest(mb);
+    }
+    int *sh = (int *)lds;
+    if (threadIdx.x == 0) sh[0] = sh[1] = 0;
+    __syncthreads();
+    atomicMax(&sh[0], max((int)ma.x, (int)ma.y));
+    atomicMax(&sh[1], max((int)mb.x, (int)mb.y));
+    __syncthreads();
+    const int a = sh[0], b = sh[1];
+    __syncthreads();  // lds is reused
+    return a <= (int)LV_MAX && b <= (int)LV_MAX && a + b <= (int)LV_SUM;
+}
+
+// Writes the block's results inside rows x cols to C (row 0, column 0 of the
+// block at `out`).  Lanes l and l + 32 hold the two halves of 8 columns of
+// one row; they trade halves so that each writes 16 bytes.
+template <class C>
+__device__ __forceinline__ void level_store(gu16 *out, int64_t ldc, int rows, int cols, const LevelAcc<C> &acc)
+{
+    const int half = (int)((threadIdx.x >> 5) & 1);
+#pragma unroll
+    for (int mi = 0; mi < C::MI; mi++) {
+        const int row = level_row<C>(mi);
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+            for (int p = 0; p < 2; p++) {
+                uint32_t w[2][2];
+#pragma unroll
+                for (int e = 0; e < 2; e++)
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {
+                        const uint32_t *a = &acc.v[mi][ni][8 * p + 4 * e + 2 * h];
+                        w[e][h] = level_value(a[0]) | (level_value(a[1]) << 16);
+                    }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                const int col = level_col<C>(ni, 2 * p) - 4 * half + 8 * half;
+                if (row >= rows) continue;
+                gu16 *g = out + (int64_t)row * ldc + col;
+                const uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+                if (col + 8 <= cols) {
+                    ustore16(g, v);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        if (col + e < cols) g[e] = (u16)(comp(v, e >> 1) >> ((e & 1) * 16));
+                }
+            }
+    }
+}
+
+// The product C = A (x) B: configuration cfg of gemm.hip, or (cfg = -1) the
+// level form where it applies and the tile table's configuration elsewhere.
+mpr_status product_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                          int64_t ldb, u16 *C, int64_t ldc, hipStream_t s);
+// The same, leaving room on every CU for other launches.
+mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                                int64_t ldb, u16 *C, int64_t ldc, hipStream_t s);
+
+}  // namespace mpr

@@ -1,0 +1,112 @@
+// level.hip -- single (min,+) products on the matrix cores (level.h), and the
+// choice between them and the VALU tiles of gemm.hip.
+#include <algorithm>
+
+#include "level.h"
+
+namespace mpr {
+
+using LCfg0 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 128 x 128
+using LCfg1 = LevelCfg<1, 1, 2, 2>;  // 256 threads, 64 x 64
+
+// VALU tile (tile.h) of the same threads and block, for blocks whose values
+// leave the level range.
+template <class C> struct LevelBack;
+template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
+template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
+
+// Tile of a block: each XCD (block b runs on XCD b % 8) takes a contiguous
+// run of tiles, walked in groups of 8 tile rows, so that the 64 blocks
+// resident on one XCD share 8 row and 8 column panels in its L2.
+__device__ __forceinline__ bool level_tile(int tiles_m, int tiles_n, int &tm, int &tn)
+{
+    const int nb = (int)gridDim.x;  // a multiple of 8
+    const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
+    if (t >= tiles_m * tiles_n) return false;
+    const int first = t / (8 * tiles_n) * 8, gs = min(tiles_m - first, 8), w = t - first * tiles_n;
+    tm = first + w % gs;
+    tn = w / gs;
+    return true;
+}
+
+// The f16 form recomputes a block that the levels can not hold: at K >= 128
+// (level_config) values up to 3000 still give minima below 2048, where it is
+// exact and 4/3 as fast as the uint16 form (N = 4096, entries 0..3000: 1.88
+// ms for the wasted level pass and the f16 pass, 1.94 ms in uint16 alone).
+template <class C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void level_gemm_kernel(
+    const u16 *__restrict__ A, int64_t lda, const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ Cm, int64_t ldc,
+    int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int vec)
+{
+    using T = typename LevelBack<C>::T;
+    static_assert(T::NT == C::NT && C::BM == T::BM && C::BN == T::BN, "fallback tile");
+    constexpr int BACK = (T::LDS_ELEMS + 7) / 8;
+    __shared__ uint4 lds[C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK];
+    int tm, tn;
+    if (!level_tile(tiles_m, tiles_n, tm, tn)) return;
+    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    const int rows = (int)min<int64_t>(C::BM, M - m0), cols = (int)min<int64_t>(C::BN, N - n0);
+    LevelA<C> aop(glob(A) + m0 * lda, lda, rows, K);
+    LevelB<C> bop(glob(B) + n0, ldb, cols, K);
+    {
+        LevelAcc<C> acc;
+        level_kloop<C>(K, aop, bop, lds, acc);
+        if (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds)) {
+            level_store<C>(glob(Cm) + m0 * ldc + n0, ldc, rows, cols, acc);
+            return;
+        }
+    }
+    TileAcc<T> acc;
+    tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, (u16 *)lds, acc);
+    tile_store<T>(Cm, ldc, M, N, m0, n0, vec != 0, acc);
+}
+
+template <class C>
+static mpr_status level_launch(int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B, int64_t ldb,
+                               u16 *Cm, int64_t ldc, hipStream_t s, size_t pad_lds)
+{
+    const int64_t tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
+    const int64_t tiles = tiles_m * tiles_n;
+    if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
+    const bool vec = aligned16(A) && aligned16(B) && aligned16(Cm) && lda % 8 == 0 && ldb % 8 == 0 && ldc % 8 == 0;
+    hipLaunchKernelGGL(level_gemm_kernel<C>, dim3((unsigned)round_up(tiles, 8)), dim3(C::NT), pad_lds, s, A, lda, B,
+                       ldb, Cm, ldc, M, N, K, (int)tiles_m, (int)tiles_n, vec ? 1 : 0);
+    return check_launch();
+}
+
+// Level configuration of a product, -1 for the VALU tiles.  K >= 128: with
+// fewer pairs per output the minimum of moderate values (0..40, a third
+// infinite) often exceeds 30 and most blocks would be computed twice; at 128
+// none is expected to.  The staging uses 32-bit offsets and whole 8-byte
+// pieces of a row of B.  128 x 128 blocks once they fill the 256 CUs, where
+// they move half the operand bytes of the 64 x 64 ones (N = 2507: 72 against
+// 93 us; 1000 x 3333 x 2507: 59 against 58 us; N = 848: 21 against 11 us).
+static int level_config(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb)
+{
+    if (K < 128 || N < 4 || lda >= (1 << 22) || ldb >= (1 << 22)) return -1;
+    const int64_t tiles = ((M + LCfg0::BM - 1) / LCfg0::BM) * ((N + LCfg0::BN - 1) / LCfg0::BN);
+    return tiles >= device_cu_count() ? 0 : 1;
+}
+
+mpr_status product_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                          int64_t ldb, u16 *Cm, int64_t ldc, hipStream_t s)
+{
+    const int lc = cfg < 0 ? level_config(M, N, K, lda, ldb) : -1;
+    if (M == 0 || N == 0 || lc < 0) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
+    return lc == 0 ? level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0)
+                   : level_launch<LCfg1>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+}
+
+mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                                int64_t ldb, u16 *Cm, int64_t ldc, hipStream_t s)
+{
+    const int lc = cfg < 0 ? level_config(M, N, K, lda, ldb) : -1;
+    if (M == 0 || N == 0 || lc < 0) return gemm_launch_spare(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
+    // 128 x 128 blocks hold half of a CU's registers each: with so much LDS
+    // that a second one does not fit, the other half stays free
+    if (lc == 0)
+        return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 84 * 1024 - sizeof(uint4) * LCfg0::LDS_CHUNKS);
+    return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+}
+
+}  // namespace mpr

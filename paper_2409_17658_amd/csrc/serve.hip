@@ -40,6 +40,7 @@
 #include <vector>
 
 #include "common.h"
+#include "level.h"
 #include "trace_rows.h"
 
 namespace mpr {
@@ -490,8 +491,8 @@ static mpr_status enqueue_giants(Server &S, Ladder &L, int upto)
         const int i = L.next_giant;
         // large products leave one workgroup slot per CU to the queries
         // that run beside the build
-        e = n >= kBigLadder ? gemm_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
-                            : gemm_launch(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s);
+        e = n >= kBigLadder ? product_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
+                            : product_launch(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s);
         if (e == MPR_OK)
             e = normalise_launch(n, n, L.Ng[i], ld, L.Rg[i - 1], L.scal, L.Rg[i], L.status_dev, nullptr, s);
         if (e == MPR_OK) e = pack_build(S, L, L.Ng[i], L.Ng8[i]);

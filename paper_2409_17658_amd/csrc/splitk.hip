@@ -11,7 +11,7 @@
 // small matrices when its workspace holds the partial products.
 #include <algorithm>
 
-#include "tile.h"
+#include "level.h"
 
 namespace mpr {
 
@@ -95,7 +95,7 @@ size_t splitk_bytes(int64_t M, int64_t N, int parts)
 mpr_status splitk_launch(int parts, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                          int64_t ldb, u16 *C, int64_t ldc, u16 *P, hipStream_t s)
 {
-    if (parts <= 1 || M == 0 || N == 0 || K == 0 || !P) return gemm_launch(-1, M, N, K, A, lda, B, ldb, C, ldc, s);
+    if (parts <= 1 || M == 0 || N == 0 || K == 0 || !P) return product_launch(-1, M, N, K, A, lda, B, ldb, C, ldc, s);
     const int64_t slices = (K + SplitCfg::BK - 1) / SplitCfg::BK;
     const int64_t kchunk = ((slices + parts - 1) / parts) * SplitCfg::BK;
     const int real = (int)((K + kchunk - 1) / kchunk);  // every split non-empty

@@ -1,0 +1,65 @@
+"""The product on the matrix cores (values 0..30 as powers of two) at the
+edges of its blocks, slices and value range: the default configuration
+against the explicit uint16 configuration 0 (another kernel, itself checked
+against the oracle), bit for bit, and against the oracle on sampled rows."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import synth
+
+pytestmark = pytest.mark.gpu
+
+# (rows, columns, inner): K of whole and partial slices of 64, tiles of 64 and
+# of 128 (from 256 tiles of 128 x 128 on) with and without remainders.
+SHAPES = [(1, 4, 128), (64, 64, 129), (65, 67, 191), (130, 5, 200), (2048, 2048, 128), (2049, 2051, 135),
+          (1, 33000, 160), (33000, 4, 137)]
+# (least, largest, infinite): all sums in the levels; minima in, operands out
+# of them; sums up to 44 and 45 (the ends of the float range); minima past
+# 30; past 2048; nothing finite.
+LAWS = [(0, 15, 0.3), (0, 200, 0.25), (22, 22, 0.99), (22, 23, 0.99), (14, 40, 0.3), (1500, 0x7FFF, 0.2), (0, 1, 1.0)]
+
+
+@pytest.fixture(scope="module")
+def mpr():
+    import paper_2409_17658_amd as m
+
+    m.lib()
+    m.init(0)
+    return m
+
+
+def _law(rows, cols, seed, law):
+    lo, hi, inf = law
+    return synth.random_matrix(rows, cols, seed, lo, hi, inf)
+
+
+@pytest.mark.parametrize("padded", [True, False])
+@pytest.mark.parametrize("law", LAWS)
+def test_level_product(mpr, law, padded):
+    for i, (M, N, K) in enumerate(SHAPES):
+        print("level product", law, padded, (M, N, K), flush=True)
+        X, Y = _law(M, K, 1 + i, law), _law(K, N, 50 + i, law)
+        if padded:
+            A, B = mpr.to_device(X), mpr.to_device(Y)
+        else:
+            A, B = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+        ref = mpr.minplus_gemm(A, B, cfg=0)
+        assert torch.equal(mpr.minplus_gemm(A, B), ref)
+        assert torch.equal(mpr.minplus_gemm(A, B, spare=True), ref)
+        rows = sorted({0, M // 2, M - 1})
+        assert np.array_equal(ref.cpu().numpy()[rows], O.to_u16(O.minplus(O.from_u16(X[rows]), O.from_u16(Y))))
+
+
+def test_level_product_mixed_blocks(mpr):
+    """One block out of the levels among blocks inside them, an all-infinite
+    row and column, and single finite pairs at the ends of K."""
+    n = 300
+    X, Y = _law(n, n, 7, (0, 9, 0.5)), _law(n, n, 8, (0, 9, 0.5))
+    X[70:75] = 900
+    X[200], Y[:, 3] = mpr.INF, mpr.INF
+    X[10], X[11] = mpr.INF, mpr.INF
+    X[10, 0], X[11, n - 1] = 30, 29
+    A, B = mpr.to_device(X), mpr.to_device(Y)
+    assert np.array_equal(mpr.minplus_gemm(A, B).cpu().numpy(), O.to_u16(O.minplus(O.from_u16(X), O.from_u16(Y))))
