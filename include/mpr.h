@@ -429,13 +429,18 @@ mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count,
 /* Runs a planned batch: resets the work counter with a fill kernel and
  * launches the batch kernel, whose workgroups take the panels longest first
  * with one atomic add each (one workgroup per panel, or a persistent grid;
- * mpr_set_batch_persistent).  No memset node, no host sync, so the pair can
- * be captured into a HIP graph.  Results land in each N_out / R_out. */
+ * mpr_set_batch_persistent).  A batch whose largest chain has at least 192
+ * states, every chain at least 8 and no exponent past 4096, planned with no
+ * explicit configuration, not persistent and in a workspace of the size
+ * mpr_batch_workspace_size gives, runs on the matrix cores power by power
+ * instead: one launch per power over the tiles of all chains that reach it.
+ * No memset node, no host sync, so the launches can be captured into a HIP
+ * graph.  Results land in each N_out / R_out, the same bits in every form. */
 mpr_status mpr_batch_launch(void *ws, int32_t *d_status, mpr_stream stream);
 
 /* Describes the plan held in ws: configuration, workgroups of the grid
  * (one per panel, or the resident workgroups in the persistent form) and
- * number of panels (host ints, any may be NULL).  MPR_EINVAL if ws holds no
+ * number of panels of its panel form (host ints, any may be NULL).  MPR_EINVAL if ws holds no
  * plan. */
 mpr_status mpr_batch_plan_info(void *ws, int *cfg, int *grid, int *panels);
 

@@ -19,13 +19,24 @@
 // the raw product column tile by column tile (the shared tile routine),
 // keeps the running row minima in LDS, then rewrites the slice normalised.
 // Only workgroup barriers separate the phases: no data crosses workgroups.
+//
+// That panel form serves batches of small matrices and the explicit
+// configurations.  From LEVEL_MIN_N states on, a batch runs step by step on
+// the matrix cores instead (level.h): one launch per power takes the tiles
+// of every chain that is not yet done.  A panel that owns its rows for all
+// steps can not be fed there: 12 chains of 256 to 4096 states are about 130
+// panels of 128 rows for 256 CUs, and the largest one alone would take 170 of
+// the 967 ms that the panel form needs for the batch, while its tiles, taken
+// a step at a time, keep every CU busy.  Rows are normalised as the next step
+// reads them (LevelStep), so a step is one kernel.
 #include <algorithm>
 #include <atomic>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <vector>
 
-#include "tile.h"
+#include "level.h"
 
 namespace mpr {
 
@@ -303,6 +314,81 @@ void batch_kernel(const DevChain *__restrict__ chains, const BatchItem *__restri
 
 __global__ void reset_counter_kernel(int *counter) { *counter = 0; }
 
+// ------------------------------------------------ the batch step by step
+struct LevelItem {
+    int32_t inst;    // chain, -1 for padding
+    int16_t tm, tn;  // tile
+};
+
+// Row minima and maxima of the steps: three buffers in rotation (a step reads
+// one, writes the next and clears the third), `rows` words each.
+struct LowBufs {
+    uint32_t *low, *big;
+    int64_t rows;
+};
+
+// The chain whose rows hold row r of the batch (row0[count] = all rows).
+__device__ __forceinline__ int chain_of_row(const int64_t *row0, int count, int64_t r)
+{
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (row0[mid] <= r)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+// One row per block: FIRST writes the first power, A normalised, and prepares
+// the row's minima; otherwise the last power is normalised in place and R
+// completed.  The second read of the row comes from cache.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void batch_rows_kernel(const DevChain *__restrict__ chains, const int64_t *row0,
+                                                         int count, LowBufs lb, int32_t *st)
+{
+    __shared__ uint32_t least;
+    const int inst = chain_of_row(row0, count, blockIdx.x);
+    const DevChain c = chains[inst];
+    const int64_t i = (int64_t)blockIdx.x - row0[inst], n = c.n;
+    const bool to_p = FIRST && ((c.e - 1) & 1);
+    const u16 *src = FIRST ? c.A + i * c.lda : c.N_out + i * c.ldo;
+    u16 *dst = to_p ? c.P + i * c.ldp : c.N_out + i * c.ldo;
+    const bool vec = (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 16 == 0;
+    if (threadIdx.x == 0) {
+        least = 0xFFFFu;
+        if (FIRST) {
+            lb.low[blockIdx.x] = lb.big[blockIdx.x] = 0;  // the first power is canonical
+            lb.low[lb.rows + blockIdx.x] = LOW_NONE;
+            lb.big[lb.rows + blockIdx.x] = 0;
+        }
+    }
+    __syncthreads();
+    panel_rowmin<256>(src, 0, 0, 1, n, &least, vec);
+    __syncthreads();
+    panel_normalise<256>(src, 0, dst, 0, 0, 1, n, &least, c.R_out + i, FIRST, vec, st);
+}
+
+// Power k of every chain with e >= k: one tile per block.
+template <class C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void batch_step_kernel(
+    const DevChain *__restrict__ chains, const int64_t *__restrict__ row0, const LevelItem *__restrict__ items,
+    int64_t k, LowBufs lb, int32_t *st)
+{
+    __shared__ uint4 lds[LevelLds<C>::CHUNKS];
+    const LevelItem it = items[blockIdx.x];
+    if (it.inst < 0) return;
+    const DevChain c = chains[it.inst];
+    const bool in_p = ((c.e - k + 1) & 1) != 0;  // step k writes buffer (e - k) % 2
+    const int64_t r0 = row0[it.inst], in = (k - 2) % 3 * lb.rows + r0, out = (k - 1) % 3 * lb.rows + r0,
+                  next = k % 3 * lb.rows + r0;
+    const LevelStep p{in_p ? c.P : c.N_out, c.A, in_p ? c.N_out : c.P, in_p ? c.ldp : c.ldo, c.lda,
+                      in_p ? c.ldo : c.ldp, c.n, c.R_out, lb.low + in, lb.big + in, lb.low + out, lb.big + out,
+                      lb.low + next, lb.big + next};
+    level_step_block<C, typename LevelBack<C>::T>(p, (int64_t)it.tm * C::BM, (int64_t)it.tn * C::BN, lds, st);
+}
+
 // ------------------------------------------------------------ host side
 struct BatchCfgInfo {
     int bm, nt, arith;
@@ -320,6 +406,15 @@ static const BatchCfgInfo kBatchCfgs[] = {
 #undef MPR_BCFG
 static constexpr int kNumBatchCfgs = (int)(sizeof(kBatchCfgs) / sizeof(kBatchCfgs[0]));
 
+// A batch that runs step by step (null in a plan of the panel form).
+struct LevelPlan {
+    int count;
+    const int64_t *row0;
+    const LevelItem *items[2];            // 128 x 128 tiles, 64 x 64 tiles
+    std::vector<unsigned> active[2];      // [k]: leading items whose chains reach power k
+    LowBufs low;
+};
+
 struct BatchPlan {
     int cfg;
     int n_items;
@@ -328,6 +423,7 @@ struct BatchPlan {
     DevChain *chains;
     BatchItem *items;
     int *counter;
+    std::shared_ptr<const LevelPlan> level;
 };
 
 static std::mutex g_plan_mu;
@@ -359,6 +455,82 @@ static BatchLayout batch_layout(const mpr_chain_desc *d, int count, int bm)
         L.ldp.push_back(ldp);
         L.buf_off.push_back(take((size_t)(d[i].n * ldp) * sizeof(u16)));
     }
+    L.bytes = off + 256;
+    return L;
+}
+
+// Step-by-step batches: the matrix cores take any size, but below about 200
+// states a step is a few tiles, and its launch costs more than the panel form
+// (which keeps all steps of a panel in one workgroup) spends on it.  A step is
+// a launch, so very long chains (and captures of them) keep the panel form.
+constexpr int64_t LEVEL_MIN_N = 192, LEVEL_MAX_E = 4096;
+
+static bool level_batch(const mpr_chain_desc *d, int count)
+{
+    int64_t most = 0;
+    for (int i = 0; i < count; i++) {
+        most = std::max(most, d[i].n);
+        if (d[i].n < 8 || d[i].e > LEVEL_MAX_E) return false;
+    }
+    return most >= LEVEL_MIN_N;
+}
+
+// Tiles of size t of the chains in `order`, 8 streams interleaved: block b
+// runs on XCD b % 8, and each XCD gets an eighth of every chain's tiles, a
+// contiguous run in groups of 8 tile rows, so the blocks of one XCD share
+// panels in its L2 and all XCDs have equal work.
+static std::vector<LevelItem> level_items(const mpr_chain_desc *d, const std::vector<int> &order, int64_t t,
+                                          std::vector<unsigned> *ends)
+{
+    std::vector<LevelItem> out;
+    for (size_t o = 0; o < order.size(); o++) {
+        const int64_t side = (d[order[o]].n + t - 1) / t, tiles = side * side, per = (tiles + 7) / 8;
+        for (int64_t q = 0; q < per * 8; q++) {
+            const int64_t at = (q % 8) * per + q / 8;
+            if (at >= tiles) {
+                out.push_back(LevelItem{-1, 0, 0});
+                continue;
+            }
+            const int64_t first = at / (8 * side) * 8, gs = std::min<int64_t>(side - first, 8), w = at - first * side;
+            out.push_back(LevelItem{(int32_t)o, (int16_t)(first + w % gs), (int16_t)(w / gs)});
+        }
+        if (ends) ends->push_back((unsigned)out.size());
+    }
+    return out;
+}
+
+// Items of size t of the whole batch.
+static size_t level_item_count(const mpr_chain_desc *d, int count, int64_t t)
+{
+    size_t c = 0;
+    for (int i = 0; i < count; i++) {
+        const int64_t side = (d[i].n + t - 1) / t;
+        c += (size_t)((side * side + 7) / 8 * 8);
+    }
+    return c;
+}
+
+// Workspace of a step-by-step batch past the chains' second buffers.
+struct LevelLayout {
+    size_t row0_off, items_off[2], low_off, bytes;
+    int64_t rows = 0;
+};
+
+static LevelLayout level_layout(const mpr_chain_desc *d, int count, size_t from)
+{
+    LevelLayout L;
+    size_t off = from;
+    auto take = [&](size_t bytes) {
+        off = (size_t)round_up((int64_t)off, 256);
+        const size_t at = off;
+        off += bytes;
+        return at;
+    };
+    for (int i = 0; i < count; i++) L.rows += d[i].n;
+    L.row0_off = take(8 * (size_t)(count + 1));
+    L.items_off[0] = take(sizeof(LevelItem) * level_item_count(d, count, LCfg0::BM));
+    L.items_off[1] = take(sizeof(LevelItem) * level_item_count(d, count, LCfg1::BM));
+    L.low_off = take(6 * 4 * (size_t)L.rows);
     L.bytes = off + 256;
     return L;
 }
@@ -516,6 +688,7 @@ extern "C" mpr_status mpr_batch_workspace_size(const mpr_chain_desc *descs_host,
     if (e != MPR_OK || !bytes_host) return e != MPR_OK ? e : MPR_EINVAL;
     size_t mx = 0;
     for (int c = 0; c < kNumBatchCfgs; c++) mx = std::max(mx, batch_layout(descs_host, count, kBatchCfgs[c].bm).bytes);
+    if (level_batch(descs_host, count)) mx = level_layout(descs_host, count, mx).bytes;
     *bytes_host = mx;
     return MPR_OK;
 }
@@ -548,6 +721,44 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
     std::vector<BatchItem> flat;
     for (auto &p : items) flat.push_back(p.second);
     hipStream_t s = as_stream(stream);
+    // Step by step when no configuration is asked for and the workspace has
+    // the room (one sized for the panel form alone keeps that form).
+    std::shared_ptr<LevelPlan> level;
+    std::vector<LevelItem> tiles[2];
+    std::vector<int64_t> row0(1, 0);
+    if (forced < 0 && !g_batch_persistent && level_batch(descs_host, count)) {
+        const LevelLayout V = level_layout(descs_host, count, L.bytes);
+        if (ws_bytes >= V.bytes) {
+            level = std::make_shared<LevelPlan>();
+            std::vector<int> order(count);  // longest chains first: a step runs a prefix
+            for (int i = 0; i < count; i++) order[i] = i;
+            std::stable_sort(order.begin(), order.end(),
+                             [&](int x, int y) { return descs_host[x].e > descs_host[y].e; });
+            std::vector<DevChain> by_e;
+            for (int i : order) {
+                by_e.push_back(chains[i]);
+                row0.push_back(row0.back() + descs_host[i].n);
+            }
+            chains.swap(by_e);
+            for (int t = 0; t < 2; t++) {
+                std::vector<unsigned> ends;
+                tiles[t] = level_items(descs_host, order, t == 0 ? LCfg0::BM : LCfg1::BM, &ends);
+                level->items[t] = (LevelItem *)(base + V.items_off[t]);
+                level->active[t].assign((size_t)chains[0].e + 1, 0);
+                for (int o = 0; o < count; o++)
+                    for (int64_t k = 2; k <= chains[o].e; k++) level->active[t][k] = ends[o];
+                if (hipMemcpyAsync(base + V.items_off[t], tiles[t].data(), sizeof(LevelItem) * tiles[t].size(),
+                                   hipMemcpyHostToDevice, s) != hipSuccess)
+                    return MPR_EHIP;
+            }
+            if (hipMemcpyAsync(base + V.row0_off, row0.data(), 8 * row0.size(), hipMemcpyHostToDevice, s) !=
+                hipSuccess)
+                return MPR_EHIP;
+            level->count = count;
+            level->row0 = (const int64_t *)(base + V.row0_off);
+            level->low = LowBufs{(uint32_t *)(base + V.low_off), (uint32_t *)(base + V.low_off) + 3 * V.rows, V.rows};
+        }
+    }
     if (count && hipMemcpyAsync(base + L.chains_off, chains.data(), sizeof(DevChain) * count, hipMemcpyHostToDevice,
                                 s) != hipSuccess)
         return MPR_EHIP;
@@ -564,9 +775,32 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
     plan.chains = (DevChain *)(base + L.chains_off);
     plan.items = (BatchItem *)(base + L.items_off);
     plan.counter = (int *)(base + L.counter_off);
+    plan.level = level;
     std::lock_guard<std::mutex> lk(g_plan_mu);
     g_plans[ws] = plan;
     return MPR_OK;
+}
+
+// The launches of a step-by-step batch: first powers, one per power, last
+// normalisation.  64 x 64 tiles for a step whose 128 x 128 tiles would leave
+// CUs idle.
+static mpr_status level_batch_launch(const BatchPlan &p, int32_t *st, hipStream_t s)
+{
+    const LevelPlan &v = *p.level;
+    const unsigned fill = (unsigned)device_cu_count();
+    hipLaunchKernelGGL(batch_rows_kernel<true>, dim3((unsigned)v.low.rows), dim3(256), 0, s,
+                       (const DevChain *)p.chains, v.row0, v.count, v.low, st);
+    for (size_t k = 2; k < v.active[0].size(); k++) {
+        if (v.active[0][k] >= fill)
+            hipLaunchKernelGGL(batch_step_kernel<LCfg0>, dim3(v.active[0][k]), dim3(LCfg0::NT), 0, s,
+                               (const DevChain *)p.chains, v.row0, v.items[0], (int64_t)k, v.low, st);
+        else
+            hipLaunchKernelGGL(batch_step_kernel<LCfg1>, dim3(v.active[1][k]), dim3(LCfg1::NT), 0, s,
+                               (const DevChain *)p.chains, v.row0, v.items[1], (int64_t)k, v.low, st);
+    }
+    hipLaunchKernelGGL(batch_rows_kernel<false>, dim3((unsigned)v.low.rows), dim3(256), 0, s,
+                       (const DevChain *)p.chains, v.row0, v.count, v.low, st);
+    return check_launch();
 }
 
 extern "C" mpr_status mpr_batch_launch(void *ws, int32_t *d_status, mpr_stream stream)
@@ -580,6 +814,7 @@ extern "C" mpr_status mpr_batch_launch(void *ws, int32_t *d_status, mpr_stream s
     }
     if (p.n_items == 0) return MPR_OK;
     hipStream_t s = as_stream(stream);
+    if (p.level) return level_batch_launch(p, d_status, s);
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, p.counter);
     mpr_status e = check_launch();
     if (e != MPR_OK) return e;

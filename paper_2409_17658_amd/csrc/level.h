@@ -111,20 +111,34 @@ __device__ __forceinline__ uint4 shift_in_inf(const uint4 &v, int s)
 // Staging of the left operand, `rows` (>= 1) rows of K >= 8 values from
 // `base`: chunk q of a thread is row tid / 8 + q NT / 8, k group tid % 8 of
 // the slice.  Rows past the end read the last row (their results are not
-// used); k past the end reads as infinity.
-template <class C>
+// used); k past the end reads as infinity.  SUB: the rows still carry the
+// offsets low[row] <= 0x7FFF (each row's least value, or no finite value at
+// all), taken off while staging; infinity stays above every level.
+template <class C, bool SUB = false>
 struct LevelA {
     gbytes *base, *at;  // the operand; the slice the next load() takes
     int64_t K;
     uint32_t off[C::A_CPT];  // bytes from a slice's start to each chunk
+    uint32_t low2[SUB ? C::A_CPT : 1];
     uint4 r[C::A_CPT];
-    __device__ __forceinline__ LevelA(const gu16 *p, int64_t ld, int rows, int64_t K_) : base((gbytes *)p), K(K_)
+    __device__ __forceinline__ LevelA(const gu16 *p, int64_t ld, int rows, int64_t K_,
+                                      const uint32_t *low = nullptr)
+        : base((gbytes *)p), K(K_)
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) {
-            const int row = (int)threadIdx.x / C::KC + q * (C::NT / C::KC);
-            off[q] = (uint32_t)(row < rows ? row : rows - 1) * (uint32_t)ld * 2u + (threadIdx.x % C::KC) * 16u;
+            const int row = min((int)threadIdx.x / C::KC + q * (C::NT / C::KC), rows - 1);
+            off[q] = (uint32_t)row * (uint32_t)ld * 2u + (threadIdx.x % C::KC) * 16u;
+            if constexpr (SUB) {
+                const uint32_t v = low[row] & 0x7FFFu;  // 0xFFFF (no finite value): any offset will do
+                low2[q] = v | (v << 16);
+            }
         }
+    }
+    __device__ __forceinline__ uint32_t value2(uint32_t x, int q) const
+    {
+        if constexpr (SUB) return as_u32((u16x2)(as_u16x2(x) - as_u16x2(low2[q])));
+        return x;
     }
     __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * 2; }
     // a full slice; the next one is the slice before it
@@ -151,15 +165,17 @@ struct LevelA {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++)
             as[((int)threadIdx.x % C::KC) * C::PA + (int)threadIdx.x / C::KC + q * (C::NT / C::KC)] =
-                make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
+                make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
+                           level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
-    // largest finite value (signed: infinity is -1)
+    // largest finite value (signed: infinity is negative)
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++)
 #pragma unroll
-            for (int e = 0; e < 4; e++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(r[q], e)));
+            for (int e = 0; e < 4; e++)
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, value2(comp(r[q], e), q)));
         return m;
     }
 };
@@ -453,6 +469,131 @@ __device__ __forceinline__ void level_store(gu16 *out, int64_t ldc, int rows, in
             }
     }
 }
+
+// ------------------------------------------------ a chain step, normalised late
+// One step O = L (x) A of a chain whose rows keep their offsets until the
+// next step reads them: L holds the raw previous product, low_in[i] its row
+// minima and big_in[i] its rows' largest finite values where they can exceed
+// MPR_FMAX, so the step multiplies the canonical form L - low_in (the scalar
+// rule of Section 3) and R gains low_in.  That saves the pass over the matrix,
+// and the launch, that a normalisation after every product costs.  The step
+// leaves the row minima and maxima of O in low_out / big_out (set to LOW_NONE
+// and 0 before) and prepares low_next / big_next for the step after.
+struct LevelStep {
+    const u16 *L, *A;
+    u16 *O;
+    int64_t ldl, lda, ldo, n;
+    int64_t *R;
+    const uint32_t *low_in, *big_in;
+    uint32_t *low_out, *big_out, *low_next, *big_next;
+};
+constexpr uint32_t LOW_NONE = 0xFFFFu;  // no finite value in the row
+
+// Row minima of the block into low (the block's first row), from the largest
+// accumulator of each row.
+template <class C>
+__device__ __forceinline__ void level_row_low(const LevelAcc<C> &acc, int rows, int cols, uint32_t *low)
+{
+#pragma unroll
+    for (int mi = 0; mi < C::MI; mi++) {
+        uint32_t u = 0;
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+            for (int r = 0; r < 16; r++)
+                u = max(u, level_col<C>(ni, r / 4) + r % 4 < cols ? acc.v[mi][ni][r] : 0u);
+        u = max(u, (uint32_t)__shfl_xor((int)u, 32, 64));
+        const int row = level_row<C>(mi);
+        if ((threadIdx.x & 63) < 32 && row < rows && u) atomicMin(&low[row], level_value(u));
+    }
+}
+
+// The block of rows m0.. and columns n0.. of a step; T is the VALU tile of
+// the same shape and threads for blocks whose values leave the level range.
+template <class C, class T>
+__device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0, int64_t n0, uint4 *lds, int32_t *st)
+{
+    const int rows = (int)min<int64_t>(C::BM, p.n - m0), cols = (int)min<int64_t>(C::BN, p.n - n0);
+    bool far = false;  // offsets past 0x7FFF: no room above the levels for infinity
+    for (int r = threadIdx.x; r < rows; r += C::NT) {
+        const int64_t i = m0 + r;
+        const uint32_t l = p.low_in[i];
+        far |= l > FMAX16 && l != LOW_NONE;
+        if (n0 == 0) {  // the rows' bookkeeping, once
+            p.low_next[i] = LOW_NONE;
+            p.big_next[i] = 0;
+            p.R[i] = (l == LOW_NONE || p.R[i] == ROW_NONE) ? ROW_NONE : p.R[i] + (int64_t)l;
+            if (l != LOW_NONE && p.big_in[i] > l + FMAX16) set_status(st, MPR_EOVERFLOW);
+        }
+    }
+    if (!__syncthreads_or(far)) {
+        LevelA<C, true> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, p.n, p.low_in + m0);
+        LevelB<C> bop(glob(p.A) + n0, p.lda, cols, p.n);
+        LevelAcc<C> acc;
+        level_kloop<C>(p.n, aop, bop, lds, acc);
+        if (level_sure<C>(acc, rows, cols) || level_clean<C>(p.n, aop, bop, lds)) {
+            level_row_low<C>(acc, rows, cols, p.low_out + m0);
+            level_store<C>(glob(p.O) + m0 * p.ldo + n0, p.ldo, rows, cols, acc);
+            return;
+        }
+    }
+    const bool vec = (uintptr_t)p.L % 16 == 0 && (uintptr_t)p.A % 16 == 0 && (uintptr_t)p.O % 16 == 0 &&
+                     p.ldl % 8 == 0 && p.lda % 8 == 0 && p.ldo % 8 == 0;
+    TileAcc<T> acc;
+    tile_mainloop_with<T, true>(
+        (p.n + T::BK - 1) / T::BK,
+        [&](int64_t k0, int row, int kc) {
+            const uint4 v = load8(p.L, p.ldl, m0 + row, k0 + kc, p.n, p.n, vec);
+            const uint32_t l = row < rows ? p.low_in[m0 + row] : 0;
+            uint32_t w[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const uint32_t lo = comp(v, q) & 0xFFFFu, hi = comp(v, q) >> 16;
+                w[q] = (lo == 0xFFFFu ? lo : lo - l) | (hi == 0xFFFFu ? hi : hi - l) << 16;
+            }
+            return make_uint4(w[0], w[1], w[2], w[3]);
+        },
+        [&](int64_t k0, int kr, int jc) { return load8(p.A, p.lda, k0 + kr, n0 + jc, p.n, p.n, vec); }, (u16 *)lds,
+        acc);
+    tile_store<T>(p.O, p.ldo, p.n, p.n, m0, n0, vec, acc);
+#pragma unroll
+    for (int r = 0; r < T::TM; r++) {
+        // columns and rows past the end are infinite
+        u16x2 mn = {0xFFFF, 0xFFFF}, mx = {0, 0};  // mx: largest finite value + 1
+#pragma unroll
+        for (int q = 0; q < T::NACC; q++) {
+            mn = min2(mn, acc.v[r][q]);
+            mx = __builtin_elementwise_max(mx, (u16x2)(acc.v[r][q] + (u16x2){1, 1}));
+        }
+        uint32_t m = min((uint32_t)mn.x, (uint32_t)mn.y), x = max((uint32_t)mx.x, (uint32_t)mx.y);
+#pragma unroll
+        for (int off = 1; off < T::TX; off <<= 1) {
+            m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
+            x = max(x, (uint32_t)__shfl_xor((int)x, off, 64));
+        }
+        const int row = tile_row<T>(r);
+        if (threadIdx.x % T::TX == 0 && row < rows && x) {
+            atomicMin(&p.low_out[m0 + row], m);
+            atomicMax(&p.big_out[m0 + row], x - 1);
+        }
+    }
+}
+
+// Block shapes of the products and steps, each with the VALU tile that
+// stands in for it.
+using LCfg0 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 128 x 128
+using LCfg1 = LevelCfg<1, 1, 2, 2>;  // 256 threads, 64 x 64
+template <class C> struct LevelBack;
+template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
+template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
+// LDS of a block (16-byte chunks): its own, or the VALU tile's if larger.
+template <class C>
+struct LevelLds {
+    using T = typename LevelBack<C>::T;
+    static_assert(T::NT == C::NT && C::BM == T::BM && C::BN == T::BN, "stand-in tile");
+    static constexpr int BACK = (T::LDS_ELEMS + 7) / 8;
+    static constexpr int CHUNKS = C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK;
+};
 
 // The product C = A (x) B: configuration cfg of gemm.hip, or (cfg = -1) the
 // level form where it applies and the tile table's configuration elsewhere.

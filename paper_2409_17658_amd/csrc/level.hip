@@ -6,15 +6,6 @@
 
 namespace mpr {
 
-using LCfg0 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 128 x 128
-using LCfg1 = LevelCfg<1, 1, 2, 2>;  // 256 threads, 64 x 64
-
-// VALU tile (tile.h) of the same threads and block, for blocks whose values
-// leave the level range.
-template <class C> struct LevelBack;
-template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
-template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
-
 // Tile of a block: each XCD (block b runs on XCD b % 8) takes a contiguous
 // run of tiles, walked in groups of 8 tile rows, so that the 64 blocks
 // resident on one XCD share 8 row and 8 column panels in its L2.
@@ -39,9 +30,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int vec)
 {
     using T = typename LevelBack<C>::T;
-    static_assert(T::NT == C::NT && C::BM == T::BM && C::BN == T::BN, "fallback tile");
-    constexpr int BACK = (T::LDS_ELEMS + 7) / 8;
-    __shared__ uint4 lds[C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK];
+    __shared__ uint4 lds[LevelLds<C>::CHUNKS];
     int tm, tn;
     if (!level_tile(tiles_m, tiles_n, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;

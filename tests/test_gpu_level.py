@@ -63,3 +63,56 @@ def test_level_product_mixed_blocks(mpr):
     X[10, 0], X[11, n - 1] = 30, 29
     A, B = mpr.to_device(X), mpr.to_device(Y)
     assert np.array_equal(mpr.minplus_gemm(A, B).cpu().numpy(), O.to_u16(O.minplus(O.from_u16(X), O.from_u16(Y))))
+
+
+# Chains whose rows stay in the levels; leave them (f16, then uint16 blocks);
+# carry offsets past 0x7FFF; have no finite value at all.
+STEP_LAWS = [(0, 31, 0.25), (0, 60, 0.9), (2100, 3000, 0.2), (0x7000, 0x7FFF, 0.3), (0, 9, 0.997)]
+
+
+@pytest.mark.parametrize("law", STEP_LAWS)
+def test_level_batch_steps(mpr, law):
+    """A batch run step by step on the matrix cores (largest chain >= 192
+    states), tile edges and chains of different lengths, against the
+    oracle's chains."""
+    print("level batch", law, flush=True)
+    sizes = [(257, 5), (129, 7), (8, 3), (320, 1), (65, 2), (192, 6)]
+    chains, refs = [], []
+    for i, (n, e) in enumerate(sizes):
+        X = _law(n, n, 900 + i, law)
+        if i % 2:  # rows that are not 16-byte aligned
+            A, N = torch.from_numpy(X).cuda(), torch.empty((n, n), dtype=torch.int16, device="cuda").view(torch.uint16)
+        else:
+            A, N = mpr.to_device(X), mpr.alloc_matrix(n, n)
+        chains.append((A, e, N, torch.empty(n, dtype=torch.int64, device="cuda")))
+        refs.append(O.power_chain(O.from_u16(X), e))
+    ws = mpr.workspace(mpr.batch_workspace_size(chains))
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    mpr.batch_plan(chains, ws)
+    for _ in range(2):  # the launch prepares all its state itself
+        mpr.batch_launch(ws, st)
+        assert int(st.item()) == 0
+        for (_, _, N, R), (Nr, Rr) in zip(chains, refs):
+            assert np.array_equal(N.cpu().numpy(), O.to_u16(Nr)) and np.array_equal(R.cpu().numpy(), Rr)
+
+
+def test_level_batch_overflow_is_reported(mpr):
+    """A row whose canonical values pass 0x7FFF: refused by the panel form
+    (configuration 0) and by the step-by-step form alike."""
+    n, e = 200, 4
+    X = np.full((n, n), mpr.INF, dtype=np.uint16)
+    X[np.arange(n), (np.arange(n) + 1) % n] = 0x7FFF
+    X[np.arange(n), np.arange(n)] = 0
+    status = []
+    for cfg in (0, -1):
+        mpr.set_batch_config(cfg)
+        try:
+            chain = (mpr.to_device(X), e, mpr.alloc_matrix(n, n), torch.empty(n, dtype=torch.int64, device="cuda"))
+            ws = mpr.workspace(mpr.batch_workspace_size([chain]))
+            st = torch.zeros(1, dtype=torch.int32, device="cuda")
+            mpr.batch_plan([chain], ws)
+            mpr.batch_launch(ws, st)
+            status.append(int(st.item()))
+        finally:
+            mpr.set_batch_config(-1)
+    assert status == [3, 3]
