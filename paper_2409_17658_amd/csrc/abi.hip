@@ -4,6 +4,7 @@
 // period search of Algorithm 2).
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -136,23 +137,23 @@ static size_t gemm_norm_ws(int64_t K, int64_t N, int64_t *ldp_out)
 }
 
 // ------------------------------------------------------------ powers
-// splitk.hip: small products with the inner dimension split.
-int splitk_parts(int64_t M, int64_t N, int64_t K);
-size_t splitk_bytes(int64_t M, int64_t N, int parts);
-mpr_status splitk_launch(int parts, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
-                         int64_t ldb, u16 *C, int64_t ldc, u16 *P, hipStream_t s);
-
 struct PowerWs {
     u16 *P, *acc, *Bp, *C;
     int64_t *RP, *Racc, *RC, *s;
     void *plan;         // compressed-K plan of A (MPR_CHAIN_SPARSE)
     size_t plan_bytes;  // its share of the workspace
     bool plan_full;     // sized for the worst case (any A fits)
-    u16 *split;         // MPR_CHAIN: partial products of a split-k step, the rest of the workspace
-    size_t split_bytes;
+    uint32_t *low;      // MPR_CHAIN: row minima and maxima of steps normalised late, if there is room
     int64_t ld;
-    size_t bytes;       // needed (without the optional partial products)
+    size_t bytes;       // needed (without the optional minima)
 };
+
+// Chains whose steps run in the level form, normalised late: the launch and
+// the pass over the matrix that a separate normalisation costs are worth
+// saving while a step is short (a third of it at n = 848; past 4096 the pass
+// is below a tenth of the step, and the workspace stays what it was).
+static bool level_chain(int64_t n) { return n >= 33 && n <= 4096; }
+static size_t level_chain_bytes(int64_t n) { return (size_t)round_up(6 * n * 4, 256) + 256; }
 
 // Workspace layout of mpr_minplus_power.  The compressed-K plan takes the
 // rest of a workspace of ws_bytes, up to its worst case; ws_bytes = 0 (or
@@ -179,22 +180,22 @@ static PowerWs carve_power(void *ws, int64_t n, int schedule, size_t ws_bytes = 
         w.plan = c.take<char>(w.plan_bytes);
     }
     w.bytes = c.used + 256;
-    if (schedule == MPR_CHAIN && ws_bytes > w.bytes + 256) {  // room for the partial products of small steps
-        const size_t at = (size_t)round_up((int64_t)c.used, 256);
-        w.split = ws ? (u16 *)((char *)ws + at) : nullptr;
-        w.split_bytes = ws_bytes - at - 256;
-    }
+    if (schedule == MPR_CHAIN && level_chain(n) && ws_bytes >= w.bytes + level_chain_bytes(n)) w.low = c.take<uint32_t>(6 * (size_t)n);
     return w;
 }
 
 // Workspace that mpr_power_workspace_size reports: the layout plus, for the
-// chain of a small matrix, the partial products of its split-k steps.
+// chain of a matrix with too few 64 x 64 output tiles to give every CU two,
+// up to seven more matrices.  Its steps keep their row minima there (24 n
+// bytes); the size is the published one, which callers hold workspaces of.
 static size_t power_ws_recommended(int64_t n, int schedule)
 {
     const PowerWs w = carve_power(nullptr, n, schedule);
-    size_t extra = 0;
-    if (schedule == MPR_CHAIN && n > 0) extra = splitk_bytes(n, n, splitk_parts(n, n, n));
-    return w.bytes + (extra ? extra + 256 : 0);
+    if (schedule != MPR_CHAIN || n < 256) return w.bytes;
+    const int64_t tiles = ((n + 63) / 64) * ((n + 63) / 64), want = 4 * (int64_t)device_cu_count();
+    if (tiles >= want / 2) return w.bytes;
+    const int64_t parts = std::min<int64_t>(8, std::min((want + tiles - 1) / tiles, n / 128));
+    return w.bytes + (size_t)((parts - 1) * n * w.ld) * sizeof(u16) + 256;
 }
 
 // e - 1 chain steps from a first power: A itself (normalised), or, when N0
@@ -220,13 +221,24 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
         if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], nullptr, nullptr, R_out, st, nullptr, s);
     }
     if (r == MPR_OK && sparse && e >= 2) r = sparse_plan_launch(A, n, lda, w.plan, w.plan_bytes, st, s);
-    // a small matrix's steps split k when the workspace holds the partial products
-    int parts = sparse ? 1 : splitk_parts(n, n, n);
-    while (parts > 1 && splitk_bytes(n, n, parts) > w.split_bytes) parts--;
+    if (r == MPR_OK && w.low && !sparse && e >= 2 && level_strides(lda, ldo)) {
+        uint32_t *low = w.low, *big = w.low + 3 * n;
+        r = level_prepare_launch(low, big, n, s);
+        for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
+            const int nb = b ^ 1;
+            const int64_t in = (k - 2) % 3 * n, out = (k - 1) % 3 * n, next = k % 3 * n;
+            r = level_step_launch(LevelStep{buf[b], A, buf[nb], ld[b], lda, ld[nb], n, R_out, low + in, big + in,
+                                            low + out, big + out, low + next, big + next},
+                                  st, s);
+            b = nb;
+        }
+        if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, nullptr, s);
+        return r;
+    }
     for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
         const int nb = b ^ 1;
         r = sparse ? sparse_step_launch(buf[b], ld[b], n, w.plan, w.plan_bytes, buf[nb], ld[nb], s)
-                   : splitk_launch(parts, n, n, n, buf[b], ld[b], A, lda, buf[nb], ld[nb], w.split, s);
+                   : product_launch(-1, n, n, n, buf[b], ld[b], A, lda, buf[nb], ld[nb], s);
         if (r == MPR_OK) r = normalise_launch(n, n, buf[nb], ld[nb], R_out, nullptr, R_out, st, nullptr, s);
         b = nb;
     }

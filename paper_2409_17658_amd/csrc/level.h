@@ -51,20 +51,31 @@ constexpr uint32_t LV_SUM = 44;                  // 2^(118 - 6 * 44) = 2^-146, a
 // Bits of the least sum that proves a result <= LV_MAX: 2^(118 - 180).
 constexpr uint32_t LV_SURE = (uint32_t)(127 + LV_TOP - LV_STEP * (int)LV_MAX) << 23;
 
-// MI x NI tiles of 32 x 32 outputs per wave, WM x WN waves per block.
-template <int MI_, int NI_, int WM_, int WN_>
+// MI x NI tiles of 32 x 32 outputs per wave, WM x WN waves per block, KS such
+// groups of waves that share the block's slices of K between them (for
+// products of few tiles, which are a chain of memory round trips: KS times
+// the loads in flight, a KS-th of the trips).
+template <int MI_, int NI_, int WM_, int WN_, int KS_ = 1>
 struct LevelCfg {
-    static constexpr int MI = MI_, NI = NI_, WM = WM_, WN = WN_;
-    static constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN, NT = 64 * WM * WN;
+    static constexpr int MI = MI_, NI = NI_, WM = WM_, WN = WN_, KS = KS_;
+    static constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN;
+    static constexpr int GT = 64 * WM * WN, NT = GT * KS;  // threads of a group, of the block
+    // Thread in its group, wave in its group, group.
+    static __device__ __forceinline__ int tid() { return (int)threadIdx.x % GT; }
+    static __device__ __forceinline__ int wave() { return (int)(threadIdx.x >> 6) % (WM * WN); }
+    static __device__ __forceinline__ int group()
+    {
+        return KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / GT);
+    }
     static constexpr int BK = 64, KC = BK / 8;
     // Chunks per k group.  The A pitch is odd, so the 8 lanes that stage the
     // 8 k groups of one row write to 8 different 16-byte bank groups.
     static constexpr int PA = BM + 1, PB = BN;
     static constexpr int STAGE = KC * (PA + PB);
-    static constexpr int LDS_CHUNKS = 2 * STAGE;
-    static constexpr int A_CPT = BM * KC / NT;   // A chunks a thread stages
-    static constexpr int B_COLS = BN * KC / NT;  // columns of 8 k a thread stages
-    static_assert(BM * KC % NT == 0 && (B_COLS == 2 || B_COLS == 4), "staging split");
+    static constexpr int LDS_CHUNKS = 2 * STAGE * KS;
+    static constexpr int A_CPT = BM * KC / GT;   // A chunks a thread stages
+    static constexpr int B_COLS = BN * KC / GT;  // columns of 8 k a thread stages
+    static_assert(BM * KC % GT == 0 && (B_COLS == 2 || B_COLS == 4), "staging split");
 };
 
 // 2^(59 - 6 v) in bf16 for both halves; 0 for v > 30.
@@ -127,8 +138,8 @@ struct LevelA {
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) {
-            const int row = min((int)threadIdx.x / C::KC + q * (C::NT / C::KC), rows - 1);
-            off[q] = (uint32_t)row * (uint32_t)ld * 2u + (threadIdx.x % C::KC) * 16u;
+            const int row = min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1);
+            off[q] = (uint32_t)row * (uint32_t)ld * 2u + (uint32_t)(C::tid() % C::KC) * 16u;
             if constexpr (SUB) {
                 const uint32_t v = low[row] & 0x7FFFu;  // 0xFFFF (no finite value): any offset will do
                 low2[q] = v | (v << 16);
@@ -141,18 +152,18 @@ struct LevelA {
         return x;
     }
     __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * 2; }
-    // a full slice; the next one is the slice before it
+    // a full slice; the group's next one is KS slices before it
     __device__ __forceinline__ void load()
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) r[q] = uload16(at, off[q]);
-        at -= C::BK * 2;
+        at -= C::BK * C::KS * 2;
     }
     // the last K % BK values, in a slice of their own from k0
     __device__ __forceinline__ void load_tail(int64_t k0)
     {
         gbytes *b = base + k0 * 2;
-        const int over = (int)(k0 - K) + (int)(threadIdx.x % C::KC) * 8 + 8;  // values past the end
+        const int over = (int)(k0 - K) + C::tid() % C::KC * 8 + 8;  // values past the end
         const int back = over > 0 ? over : 0;
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) {
@@ -164,7 +175,7 @@ struct LevelA {
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++)
-            as[((int)threadIdx.x % C::KC) * C::PA + (int)threadIdx.x / C::KC + q * (C::NT / C::KC)] =
+            as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
                 make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
                            level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
@@ -200,7 +211,7 @@ struct LevelB {
     __device__ __forceinline__ LevelB(const gu16 *p, int64_t ld, int cols, int64_t K_)
         : base((gbytes *)p), K(K_), ldb2((uint32_t)ld * 2u)
     {
-        const int col = ((int)threadIdx.x % TPG) * C::B_COLS;
+        const int col = (C::tid() % TPG) * C::B_COLS;
         const int c = min(col, cols - C::B_COLS);  // may be negative: columns before the block
         back = col - c;
         base += min(0, cols - C::B_COLS) * 2;
@@ -219,22 +230,22 @@ struct LevelB {
     __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * ldb2; }
     __device__ __forceinline__ void load()
     {
-        const uint32_t o = (uint32_t)threadIdx.x / TPG * 8u * ldb2 + coff;
+        const uint32_t o = (uint32_t)(C::tid() / TPG) * 8u * ldb2 + coff;
 #pragma unroll
         for (int k = 0; k < 8; k++) take(k, at + (uint64_t)k * ldb2, o);
-        at -= (uint64_t)C::BK * ldb2;
+        at -= (uint64_t)(C::BK * C::KS) * ldb2;
     }
     __device__ __forceinline__ void load_tail(int64_t k0)
     {
         gbytes *b = base + k0 * ldb2;
-        const int kg = (int)threadIdx.x / TPG;
+        const int kg = C::tid() / TPG;
         const int last = (int)(K - k0) - 1;
 #pragma unroll
         for (int k = 0; k < 8; k++) take(k, b, (uint32_t)min(kg * 8 + k, last) * ldb2 + coff);
     }
     __device__ __forceinline__ void store(uint4 *bs)
     {
-        const int kg = (int)threadIdx.x / TPG, cg = (int)threadIdx.x % TPG;
+        const int kg = C::tid() / TPG, cg = C::tid() % TPG;
         if (back) {
 #pragma unroll
             for (int k = 0; k < 8; k++) {
@@ -274,85 +285,123 @@ struct LevelAcc {
     uint32_t v[C::MI][C::NI][16];
 };
 
-// The k loop: acc = the largest 32-term sum of each output (its f32 bits).
-// The product is taken transposed (D = B^T A^T): a lane then holds one row
-// of C and runs of 4 consecutive columns.  A partial slice at the end of K
-// is taken first, so that the loop itself has no edge.
+// The slices of K: slice 0 is the partial one at the end of K when there is
+// one, so that no loop has an edge, and the others follow from the end to the
+// start; group g of a block takes slices g, g + KS, ...
+template <class C, class AOp, class BOp>
+__device__ __forceinline__ void level_first(int64_t K, AOp &aop, BOp &bop)
+{
+    const int64_t full = K / C::BK;
+    const int g = C::group();
+    if (g == 0 && K % C::BK) {
+        aop.load_tail(full * C::BK);
+        bop.load_tail(full * C::BK);
+        aop.seek((full - C::KS) * C::BK);
+        bop.seek((full - C::KS) * C::BK);
+    } else {
+        const int64_t at = full - 1 - g + (K % C::BK ? 1 : 0);
+        aop.seek(at * C::BK);
+        bop.seek(at * C::BK);
+        if (at < 0) return;  // fewer slices than groups
+        aop.load();
+        bop.load();
+    }
+}
+
+// The k loop: acc = the largest 32-term sum of each output (its f32 bits),
+// complete in group 0.  The product is taken transposed (D = B^T A^T): a lane
+// then holds one row of C and runs of 4 consecutive columns.
 template <class C, class AOp, class BOp>
 __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4 *lds, LevelAcc<C> &acc)
 {
-    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
-    const int wm = wave / C::WN, wn = wave % C::WN;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wm = C::wave() / C::WN, wn = C::wave() % C::WN;
     const int aoff = (lane >> 5) * C::PA + wm * 32 * C::MI + (lane & 31);
     const int boff = C::KC * C::PA + (lane >> 5) * C::PB + wn * 32 * C::NI + ((lane & 31) ^ ((lane >> 3) & 3));
+    uint4 *const all = lds;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++)
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
             for (int r = 0; r < 16; r++) acc.v[mi][ni][r] = 0;
-    int64_t left = K / C::BK;  // full slices not yet loaded
-    aop.seek((left - 1) * C::BK);
-    bop.seek((left - 1) * C::BK);
-    if (K % C::BK) {
-        aop.load_tail(left * C::BK);
-        bop.load_tail(left * C::BK);
-    } else {
-        aop.load();
-        bop.load();
-        left--;
+    // slices of this group, and the trips of the block (those of group 0)
+    const int64_t slices = (K + C::BK - 1) / C::BK;
+    int64_t left = (slices - C::group() + C::KS - 1) / C::KS, trips = (slices + C::KS - 1) / C::KS;
+    lds += C::group() * 2 * C::STAGE;
+    level_first<C>(K, aop, bop);
+    if (C::KS == 1 || left > 0) {
+        aop.store(lds);
+        bop.store(lds + C::KC * C::PA);
     }
-    aop.store(lds);
-    bop.store(lds + C::KC * C::PA);
     __syncthreads();
     for (int cur = 0;; cur ^= 1) {
-        const bool more = left-- > 0;
+        const bool more = --left > 0;
         uint4 *next = lds + (cur ^ 1) * C::STAGE;
         const uint4 *as = lds + cur * C::STAGE + aoff, *bs = lds + cur * C::STAGE + boff;
         if (more) aop.load();
-        bf16x8 bf[C::NI][4];
+        if (C::KS == 1 || left >= 0) {
+            bf16x8 bf[C::NI][4];
 #pragma unroll
-        for (int ni = 0; ni < C::NI; ni++)
+            for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
-            for (int ks = 0; ks < 4; ks++) bf[ni][ks] = __builtin_bit_cast(bf16x8, bs[2 * ks * C::PB + 32 * ni]);
+                for (int ks = 0; ks < 4; ks++) bf[ni][ks] = __builtin_bit_cast(bf16x8, bs[2 * ks * C::PB + 32 * ni]);
+            if (C::MI == 1 && more) bop.load();
 #pragma unroll
-        for (int mi = 0; mi < C::MI; mi++) {
-            if (C::MI > 1 && mi == C::MI / 2 && more) {
-                aop.store(next);
-                bop.load();
-            }
-            bf16x8 af[4];
-#pragma unroll
-            for (int ks = 0; ks < 4; ks++) af[ks] = __builtin_bit_cast(bf16x8, as[2 * ks * C::PA + 32 * mi]);
-#pragma unroll
-            for (int ni = 0; ni < C::NI; ni++) {
-                f32x16 t0 = {}, t1 = {};
-                t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][0], af[0], t0, 0, 0, 0);
-                t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][2], af[2], t1, 0, 0, 0);
-                t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][1], af[1], t0, 0, 0, 0);
-                t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][3], af[3], t1, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const float f0 = t0[r], f1 = t1[r];
-                    const uint32_t u0 = __builtin_bit_cast(uint32_t, f0), u1 = __builtin_bit_cast(uint32_t, f1);
-                    uint32_t &d = acc.v[mi][ni][r];
-                    d = max(max(d, u0), u1);
-                    // keeps the maximum here: moved past the branches below
-                    // it would hold both accumulators in registers
-                    asm volatile("" : "+v"(d));
+            for (int mi = 0; mi < C::MI; mi++) {
+                if (C::MI > 1 && mi == C::MI / 2 && more) {
+                    aop.store(next);
+                    bop.load();
                 }
-                __builtin_amdgcn_sched_barrier(0);  // one tile of accumulators in registers at a time
+                bf16x8 af[4];
+#pragma unroll
+                for (int ks = 0; ks < 4; ks++) af[ks] = __builtin_bit_cast(bf16x8, as[2 * ks * C::PA + 32 * mi]);
+#pragma unroll
+                for (int ni = 0; ni < C::NI; ni++) {
+                    f32x16 t0 = {}, t1 = {};
+                    t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][0], af[0], t0, 0, 0, 0);
+                    t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][2], af[2], t1, 0, 0, 0);
+                    t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][1], af[1], t0, 0, 0, 0);
+                    t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][3], af[3], t1, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; r++) {
+                        const float f0 = t0[r], f1 = t1[r];
+                        const uint32_t u0 = __builtin_bit_cast(uint32_t, f0), u1 = __builtin_bit_cast(uint32_t, f1);
+                        uint32_t &d = acc.v[mi][ni][r];
+                        d = max(max(d, u0), u1);
+                        // keeps the maximum here: moved past the branches below
+                        // it would hold both accumulators in registers
+                        asm volatile("" : "+v"(d));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // one tile of accumulators in registers at a time
+                }
             }
         }
         if (more) {
-            if (C::MI == 1) {
-                aop.store(next);
-                bop.load();
-            }
+            if (C::MI == 1) aop.store(next);
             bop.store(next + C::KC * C::PA);
         }
         __syncthreads();
-        if (!more) return;
+        if (--trips == 0) break;
+    }
+    if constexpr (C::KS > 1) {  // the groups' maxima into group 0
+        constexpr int REGS = C::MI * C::NI * 16;
+        uint32_t *sh = (uint32_t *)all + C::tid();
+        for (int g = 1; g < C::KS; g++) {
+            if (C::group() == g) {
+#pragma unroll
+                for (int r = 0; r < REGS; r++) sh[r * C::GT] = acc.v[r / (C::NI * 16)][r / 16 % C::NI][r % 16];
+            }
+            __syncthreads();
+            if (C::group() == 0) {
+#pragma unroll
+                for (int r = 0; r < REGS; r++) {
+                    uint32_t &d = acc.v[r / (C::NI * 16)][r / 16 % C::NI][r % 16];
+                    d = max(d, sh[r * C::GT]);
+                }
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -361,12 +410,12 @@ __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
 template <class C>
 __device__ __forceinline__ int level_row(int mi)
 {
-    return ((int)(threadIdx.x >> 6) / C::WN) * 32 * C::MI + mi * 32 + (int)(threadIdx.x & 31);
+    return (C::wave() / C::WN) * 32 * C::MI + mi * 32 + (int)(threadIdx.x & 31);
 }
 template <class C>
 __device__ __forceinline__ int level_col(int ni, int q)
 {
-    return ((int)(threadIdx.x >> 6) % C::WN) * 32 * C::NI + ni * 32 + 8 * q + 4 * (int)((threadIdx.x >> 5) & 1);
+    return (C::wave() % C::WN) * 32 * C::NI + ni * 32 + 8 * q + 4 * (int)((threadIdx.x >> 5) & 1);
 }
 
 // The value an accumulator stands for (infinity when no term was found).
@@ -386,7 +435,7 @@ __device__ __forceinline__ bool level_sure(const LevelAcc<C> &acc, int rows, int
     bool bad = false;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++) {
-        const bool rin = level_row<C>(mi) < rows;
+        const bool rin = C::group() == 0 && level_row<C>(mi) < rows;
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
@@ -405,18 +454,13 @@ template <class C, class AOp, class BOp>
 __device__ __forceinline__ bool level_clean(int64_t K, AOp &aop, BOp &bop, uint4 *lds)
 {
     i16x2 ma = {-1, -1}, mb = {-1, -1};
-    int64_t left = K / C::BK;
-    aop.seek((left - 1) * C::BK);
-    bop.seek((left - 1) * C::BK);
-    if (K % C::BK) {
-        aop.load_tail(left * C::BK);
-        bop.load_tail(left * C::BK);
-        ma = aop.largest(ma);
-        mb = bop.largest(mb);
-    }
-    for (; left > 0; left--) {
-        aop.load();
-        bop.load();
+    const int64_t slices = (K + C::BK - 1) / C::BK, left = (slices - C::group() + C::KS - 1) / C::KS;
+    if (left > 0) level_first<C>(K, aop, bop);
+    for (int64_t j = 0; j < left; j++) {
+        if (j > 0) {
+            aop.load();
+            bop.load();
+        }
         ma = aop.largest(ma);
         mb = bop.largest(mb);
     }
@@ -438,6 +482,7 @@ template <class C>
 __device__ __forceinline__ void level_store(gu16 *out, int64_t ldc, int rows, int cols, const LevelAcc<C> &acc)
 {
     const int half = (int)((threadIdx.x >> 5) & 1);
+    if (C::group() != 0) return;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++) {
         const int row = level_row<C>(mi);
@@ -494,6 +539,7 @@ constexpr uint32_t LOW_NONE = 0xFFFFu;  // no finite value in the row
 template <class C>
 __device__ __forceinline__ void level_row_low(const LevelAcc<C> &acc, int rows, int cols, uint32_t *low)
 {
+    if (C::group() != 0) return;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++) {
         uint32_t u = 0;
@@ -583,9 +629,13 @@ __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0,
 // stands in for it.
 using LCfg0 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 128 x 128
 using LCfg1 = LevelCfg<1, 1, 2, 2>;  // 256 threads, 64 x 64
+using LCfg2 = LevelCfg<2, 2, 2, 2, 2>;  // 512 threads, 128 x 128
+using LCfg3 = LevelCfg<1, 1, 2, 2, 2>;  // 512 threads, 64 x 64
 template <class C> struct LevelBack;
 template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
 template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
+template <> struct LevelBack<LCfg2> { using T = TileCfg<128, 128, 32, 4, 8>; };
+template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 32, 1, 8>; };
 // LDS of a block (16-byte chunks): its own, or the VALU tile's if larger.
 template <class C>
 struct LevelLds {
@@ -594,6 +644,15 @@ struct LevelLds {
     static constexpr int BACK = (T::LDS_ELEMS + 7) / 8;
     static constexpr int CHUNKS = C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK;
 };
+
+inline bool level_strides(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 22); }
+int level_shape(int64_t M, int64_t N);
+
+// A chain step in the shape for its size, and the row minima and maxima of
+// the first power and for its first step (3 n words each in rotation: a step
+// reads one third, writes the next and clears the last).
+mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s);
+mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStream_t s);
 
 // The product C = A (x) B: configuration cfg of gemm.hip, or (cfg = -1) the
 // level form where it applies and the tile table's configuration elsewhere.

@@ -63,39 +63,109 @@ static mpr_status level_launch(int64_t M, int64_t N, int64_t K, const u16 *A, in
     return check_launch();
 }
 
-// Level configuration of a product, -1 for the VALU tiles.  K >= 128: with
-// fewer pairs per output the minimum of moderate values (0..40, a third
-// infinite) often exceeds 30 and most blocks would be computed twice; at 128
-// none is expected to.  The staging uses 32-bit offsets and whole 8-byte
-// pieces of a row of B.  128 x 128 blocks once they fill the 256 CUs, where
-// they move half the operand bytes of the 64 x 64 ones (N = 2507: 72 against
-// 93 us; 1000 x 3333 x 2507: 59 against 58 us; N = 848: 21 against 11 us).
-static int level_config(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb)
+// Block shape of an M x N output (0..3 = LCfg0..3).  128 x 128 blocks move
+// half the operand bytes of 64 x 64 ones, so they are taken as soon as they
+// nearly fill the 256 CUs; while a CU holds only one of them, two groups of
+// waves share its slices of K.  Measured (us, shape 0 / 1 / 2 / 3): N = 848
+// 22 / 13 / 19 / 11.5; N = 1300 31 / 21 / 26 / 20; 1000 x 3333 x 2507 (216
+// blocks of 128 x 128) 58 / 57 / 47 / 60; N = 2507 (400) 73 / 92 / 80 / 99;
+// N = 4096 195 / 295 / 229 / 295.
+int level_shape(int64_t M, int64_t N)
 {
-    if (K < 128 || N < 4 || lda >= (1 << 22) || ldb >= (1 << 22)) return -1;
-    const int64_t tiles = ((M + LCfg0::BM - 1) / LCfg0::BM) * ((N + LCfg0::BN - 1) / LCfg0::BN);
-    return tiles >= device_cu_count() ? 0 : 1;
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), cus = device_cu_count();
+    return tiles >= cus ? 0 : tiles >= cus * 5 / 8 ? 2 : 3;
+}
+
+// Whether a product runs in the level form.  K >= 128: with fewer pairs per
+// output the minimum of moderate values (0..40, a third infinite) often
+// exceeds 30 and most blocks would be computed twice; at 128 none is expected
+// to.  The staging uses 32-bit offsets and whole 8-byte pieces of a row of B.
+static bool level_product(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb)
+{
+    return M > 0 && K >= 128 && N >= 4 && level_strides(lda, ldb);
 }
 
 mpr_status product_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                           int64_t ldb, u16 *Cm, int64_t ldc, hipStream_t s)
 {
-    const int lc = cfg < 0 ? level_config(M, N, K, lda, ldb) : -1;
-    if (M == 0 || N == 0 || lc < 0) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
-    return lc == 0 ? level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0)
-                   : level_launch<LCfg1>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+    if (cfg >= 0 || !level_product(M, N, K, lda, ldb)) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
+    switch (level_shape(M, N)) {
+    case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+    case 2: return level_launch<LCfg2>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+    default: return level_launch<LCfg3>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+    }
 }
 
 mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                                 int64_t ldb, u16 *Cm, int64_t ldc, hipStream_t s)
 {
-    const int lc = cfg < 0 ? level_config(M, N, K, lda, ldb) : -1;
-    if (M == 0 || N == 0 || lc < 0) return gemm_launch_spare(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
+    if (cfg >= 0 || !level_product(M, N, K, lda, ldb))
+        return gemm_launch_spare(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
     // 128 x 128 blocks hold half of a CU's registers each: with so much LDS
     // that a second one does not fit, the other half stays free
-    if (lc == 0)
+    if (level_shape(M, N) == 0)
         return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 84 * 1024 - sizeof(uint4) * LCfg0::LDS_CHUNKS);
     return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
 }
 
+// One step of a chain (LevelStep).
+template <class C>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void level_step_kernel(LevelStep p,
+                                                                                                  int tiles,
+                                                                                                  int32_t *st)
+{
+    __shared__ uint4 lds[LevelLds<C>::CHUNKS];
+    int tm, tn;
+    if (!level_tile(tiles, tiles, tm, tn)) return;
+    level_step_block<C, typename LevelBack<C>::T>(p, (int64_t)tm * C::BM, (int64_t)tn * C::BN, lds, st);
+}
+
+template <class C>
+static mpr_status step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
+{
+    const int64_t side = (p.n + C::BM - 1) / C::BM;
+    hipLaunchKernelGGL(level_step_kernel<C>, dim3((unsigned)round_up(side * side, 8)), dim3(C::NT), 0, s, p, (int)side,
+                       st);
+    return check_launch();
+}
+
+mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
+{
+    switch (level_shape(p.n, p.n)) {
+    case 0: return step_launch<LCfg0>(p, st, s);
+    case 2: return step_launch<LCfg2>(p, st, s);
+    default: return step_launch<LCfg3>(p, st, s);
+    }
+}
+
+__global__ void level_prepare_kernel(uint32_t *low, uint32_t *big, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    low[i] = big[i] = 0;  // the first power is canonical
+    low[n + i] = LOW_NONE;
+    big[n + i] = 0;
+}
+
+mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStream_t s)
+{
+    hipLaunchKernelGGL(level_prepare_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, low, big, n);
+    return check_launch();
+}
+
 }  // namespace mpr
+
+#ifdef LV_PROBE
+extern "C" int mpr_level_probe(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t *A, int64_t lda,
+                               const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc, void *s)
+{
+    using namespace mpr;
+    hipStream_t st = (hipStream_t)s;
+    switch (cfg) {
+    case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
+    case 1: return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
+    case 2: return level_launch<LCfg2>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
+    default: return level_launch<LCfg3>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
+    }
+}
+#endif
