@@ -461,13 +461,14 @@ mpr_status mpr_batch_power(const mpr_chain_desc *descs_host, int count,
 mpr_status mpr_set_sparse_arith(int arith);
 
 /* Form of the compressed-K chain steps (Algorithm 2's step restricted to
- * the rows L_J of A that reach each block J of 64 output columns):
+ * the rows L_J of A that reach each block J of 64 output columns, in whole
+ * groups of 8 rows):
  * MPR_SPARSE_TILES multiplies N[:, L_J] by the dense rows A[L_J, J];
  * MPR_SPARSE_ENTRIES (uint16 arithmetic only; the f16 form always takes
  * the tiles) visits only the finite entries of A[L_J, J], one output
- * column per wave; MPR_SPARSE_AUTO (the default) picks by the matrix's
- * size.  Both give the same powers bit for bit.  MPR_EINVAL for other
- * values.  Process-wide setting. */
+ * column per wave; MPR_SPARSE_AUTO (the default) multiplies the tiles on the
+ * matrix cores, as mpr_minplus_gemm does.  All give the same powers bit for
+ * bit.  MPR_EINVAL for other values.  Process-wide setting. */
 #define MPR_SPARSE_AUTO 0
 #define MPR_SPARSE_TILES 1
 #define MPR_SPARSE_ENTRIES 2

@@ -14,16 +14,13 @@
 #include <algorithm>
 #include <atomic>
 
-#include "tile.h"
+#include "level.h"
 
 namespace mpr {
 
 using SCfg = TileCfg<64, 64, 32, 4, 8>;  // 128 threads; 64-column blocks
 constexpr int SBN = SCfg::BN;
 constexpr int SBK = SCfg::BK;
-// The entry-list form from this size on (m >= 8 transfer matrices); below
-// it the tile form is faster (too few 512-row tiles to fill the device).
-constexpr int64_t kEntryFormMinN = 7000;
 
 // Does row l of A have a finite entry in columns [j0, j0 + SBN)?
 __device__ __forceinline__ bool row_hits_block(const u16 *A, int64_t lda, int64_t l, int64_t j0, int64_t n, bool vec)
@@ -41,13 +38,24 @@ __device__ __forceinline__ bool row_hits_block(const u16 *A, int64_t lda, int64_
     return false;
 }
 
+// The lists take whole aligned groups of 8 rows (those below n) once one row
+// of the group hits the block: a transfer matrix's rows hit a block in runs
+// of about 80, so the groups add about a tenth, and they make 8 consecutive
+// entries of a list 8 consecutive rows.  `ball`: the hits of 64 consecutive
+// rows, one bit per lane.
+__device__ __forceinline__ bool group_hit(uint64_t ball, int lane) { return (ball >> (lane & 56) & 0xFF) != 0; }
+
 // counts[J] = |L_J| rounded up to a multiple of SBK.
 __global__ __launch_bounds__(256) void sp_count_kernel(const u16 *A, int64_t lda, int64_t n, int64_t *counts, int vec)
 {
     __shared__ uint64_t sh[4];
     const int64_t j0 = (int64_t)blockIdx.x * SBN;
     uint64_t c = 0;
-    for (int64_t l = threadIdx.x; l < n; l += 256) c += row_hits_block(A, lda, l, j0, n, vec != 0);
+    for (int64_t l0 = 0; l0 < n; l0 += 256) {
+        const int64_t l = l0 + threadIdx.x;
+        const uint64_t ball = __ballot(l < n && row_hits_block(A, lda, l, j0, n, vec != 0));
+        c += l < n && group_hit(ball, (int)(threadIdx.x & 63));
+    }
     c = wave_sum_u64(c);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -122,7 +130,7 @@ __global__ __launch_bounds__(256) void sp_fill_kernel(const u16 *A, int64_t lda,
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (int64_t l0 = 0; l0 < n; l0 += 256) {
         const int64_t l = l0 + threadIdx.x;
-        const bool hit = l < n && row_hits_block(A, lda, l, j0, n, vec != 0);
+        const bool hit = l < n && group_hit(__ballot(l < n && row_hits_block(A, lda, l, j0, n, vec != 0)), lane);
         const uint64_t ball = __ballot(hit);
         const int before = __popcll(ball & ((1ull << lane) - 1ull));
         if (lane == 0) wsum[w] = __popcll(ball);
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(SCfg::NT) __attribute__((amdgpu_waves_per_eu(4))) v
 }
 
 // ------------------------------------------- entry-list form of the step
-// The tile above multiplies whole 64-column rows of A[L_J, J]; for a
+// (by request: MPR_SPARSE_ENTRIES.)  The tile above multiplies whole 64-column rows of A[L_J, J]; for a
 // transfer matrix about nine in ten of those entries are infinite (a
 // column has 25 to 120 finite entries, its block's L_J ten times as many),
 // so nine in ten of its pairs cannot win.  This form visits the finite
@@ -256,7 +264,6 @@ __global__ __launch_bounds__(SCfg::NT) __attribute__((amdgpu_waves_per_eu(4))) v
 // entry, rows where neither has one skipped).  The same
 // plan, the same minimum over the same entries: the same bits as the tile
 // form.
-typedef const __attribute__((address_space(1))) unsigned char gbytes;
 constexpr int EBM = 512;                 // rows per block
 constexpr int ENT = 512;                 // threads: 8 waves
 constexpr int ECOLS = SBN / (ENT / 64);  // columns per wave
@@ -448,6 +455,121 @@ __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void s
         entry_tile<false>(Np, ldn, n, m0, j0, idx, Bp, kbeg, nk, C, ldc, vec, nt);
 }
 
+// ------------------------------------------- level form of the step
+// The tile product on the matrix cores (level.h).  The lists L_J hold whole
+// aligned groups of 8 rows, so 8 consecutive k are 8 consecutive columns of
+// N: one 16-byte load, as in a plain product.  Each XCD takes a contiguous
+// run of the tiles in row-panel order: the column blocks of one panel run
+// together and their 128 rows of N (1.9 MB at m = 8) stay in that XCD's L2,
+// where every block reads its |L_J| columns of them.
+using PCfg = LevelCfg<2, 1, 2, 2>;  // 256 threads, 128 x 64
+using PBack = TileCfg<128, 64, 32, 4, 8>;
+static_assert(PCfg::BM == PBack::BM && PCfg::BN == SBN && PBack::BN == SBN && PCfg::NT == PBack::NT, "stand-in tile");
+
+// Staging of N[m0 .., L_J]: LevelA with the k groups of the list.
+template <class C>
+struct LevelGather {
+    gbytes *base;
+    const __attribute__((address_space(1))) int32_t *idx, *at;
+    int64_t n, K;
+    uint32_t off[C::A_CPT];
+    int col;  // first column of the thread's k group in the slice that load() takes
+    uint4 r[C::A_CPT];
+    __device__ __forceinline__ LevelGather(const gu16 *p, int64_t ld, int rows, int64_t n_, const int32_t *list,
+                                           int64_t K_)
+        : base((gbytes *)p), idx(glob(list) + C::tid() % C::KC * 8), n(n_), K(K_)
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+            off[q] = (uint32_t)min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1) * (uint32_t)ld * 2u;
+    }
+    __device__ __forceinline__ void seek(int64_t k0)
+    {
+        at = idx + k0;
+        col = k0 >= 0 ? *at : 0;
+    }
+    __device__ __forceinline__ void take()
+    {
+        // The last group of the matrix may end before its 8th column: read
+        // back from the end of the row and shift (its rows of A past the end
+        // are infinite, so any value will do there).
+        const int back = max(0, (int)(col + 8 - n));
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) {
+            r[q] = uload16(base, off[q] + (uint32_t)(col - back) * 2u);
+            if (back) r[q] = shift_in_inf(r[q], back);
+        }
+    }
+    __device__ __forceinline__ void load()
+    {
+        take();
+        at -= C::BK * C::KS;
+        col = at >= idx ? *at : 0;
+    }
+    __device__ __forceinline__ void load_tail(int64_t k0)  // K is a multiple of SBK = 32
+    {
+        col = k0 + C::tid() % C::KC * 8 < K ? idx[k0] : 0;
+        take();
+        if (k0 + C::tid() % C::KC * 8 >= K) {
+#pragma unroll
+            for (int q = 0; q < C::A_CPT; q++)
+                r[q] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+        }
+    }
+    __device__ __forceinline__ void store(uint4 *as) const
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+            as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+                make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
+    }
+    __device__ __forceinline__ i16x2 largest(i16x2 m) const
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(r[q], e)));
+        return m;
+    }
+};
+
+__global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level_kernel(
+    const u16 *__restrict__ Np, int64_t ldn, int64_t n, const int64_t *__restrict__ off, const int32_t *__restrict__ idx,
+    const u16 *__restrict__ Bp, u16 *__restrict__ Cm, int64_t ldc, int tiles_m, int nblk, int64_t cap, int vec)
+{
+    using C = PCfg;
+    constexpr int BACK = (PBack::LDS_ELEMS + 7) / 8;
+    __shared__ uint4 lds[C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK];
+    const int nb = (int)gridDim.x;  // a multiple of 8
+    const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
+    if (t >= tiles_m * nblk) return;
+    const int64_t m0 = (int64_t)(t / nblk) * C::BM, j0 = (int64_t)(t % nblk) * SBN;
+    const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
+    const int64_t kbeg = off[t % nblk], K = off[nblk] > cap ? 0 : off[t % nblk + 1] - kbeg;
+    gu16 *out = glob(Cm) + m0 * ldc + j0;
+    if (K == 0) {  // no finite entry in these columns, or a plan that did not fit: infinite
+        for (int e = (int)threadIdx.x; e < rows * SBN; e += C::NT)
+            if (e % SBN < cols) out[(int64_t)(e / SBN) * ldc + e % SBN] = 0xFFFF;
+        return;
+    }
+    {
+        LevelGather<C> aop(glob(Np) + m0 * ldn, ldn, rows, n, idx + kbeg, K);
+        LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
+        LevelAcc<C> acc;
+        level_kloop<C>(K, aop, bop, lds, acc);
+        if (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds)) {
+            level_store<C>(out, ldc, rows, cols, acc);
+            return;
+        }
+    }
+    const gu16 *gB = glob(Bp) + kbeg * SBN;
+    TileAcc<PBack> acc;
+    GatherA<PBack> aop{glob(Np), ldn, n, m0, glob(idx) + kbeg, rows == C::BM, {}};
+    auto bop = chunk_b<PBack>([&](int64_t k0, int kr, int jc) { return gload16(gB + (k0 + kr) * SBN + jc); });
+    tile_product<PBack, true>(K / PBack::BK, aop, bop, (u16 *)lds, acc);
+    tile_store<PBack>(Cm, ldc, n, n, m0, j0, vec != 0, acc);
+}
+
 // ------------------------------------------------------------ host side
 // Plan layout: counts[nblk + 1] | off[nblk + 1] | order[nblk] | idx[cap] |
 // Bp[cap * SBN], every piece 256-byte aligned; cap (rows) follows from the
@@ -544,22 +666,21 @@ mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, si
 static std::atomic<int> g_sparse_arith{MPR_ARITH_U16};  // process-wide, set from any thread
 static std::atomic<int> g_sparse_form{MPR_SPARSE_AUTO};
 
-// The form a step of an n x n matrix takes: the entry-list form in uint16
-// once it has enough blocks to fill the device, else the tile form.
-static bool use_entry_form(int64_t n)
-{
-    if (g_sparse_arith == MPR_ARITH_F16) return false;
-    const int form = g_sparse_form;
-    if (form != MPR_SPARSE_AUTO) return form == MPR_SPARSE_ENTRIES;
-    return n >= kEntryFormMinN;
-}
-
 mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, size_t bytes, u16 *C, int64_t ldc,
                               hipStream_t s)
 {
     SparsePlan p = carve_plan(ws, n, bytes);
     const int vec = aligned16(C) && ldc % 8 == 0;
-    if (use_entry_form(n) && (int64_t)EBM * ldn * 2 < ((int64_t)1 << 32)) {
+    const int form = g_sparse_form;
+    if (form == MPR_SPARSE_AUTO && n >= 8 && level_strides(ldn, ldc)) {
+        const int64_t tiles_m = (n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
+        if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
+        hipLaunchKernelGGL(sp_level_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, Np, ldn, n,
+                           (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, C, ldc, (int)tiles_m,
+                           (int)p.nblk, p.cap, vec);
+        return check_launch();
+    }
+    if (form == MPR_SPARSE_ENTRIES && g_sparse_arith == MPR_ARITH_U16 && (int64_t)EBM * ldn * 2 < ((int64_t)1 << 32)) {
         const int64_t tiles_m = (n + EBM - 1) / EBM;
         const int64_t tiles = tiles_m * p.nblk;
         if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
