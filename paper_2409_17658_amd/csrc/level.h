@@ -5,8 +5,8 @@
 // is 2^(118 - 6 (a + b)), and a sum of 32 of them lies in
 // [2^(118 - 6 t), 2^(118 - 6 t + 5)] with t the least a + b among them: the
 // exponent of the sum names t, because 32 equal terms raise it by 5 and one
-// level is worth 6.  So one f32 accumulator over 32 values of k (two
-// v_mfma_f32_32x32x16_bf16) holds the minimum of 32 pairs exactly, and the
+// level is worth 6.  So one f32 accumulator over 32 values of k (one
+// v_mfma_f32_16x16x32_bf16) holds the minimum of 32 pairs exactly, and the
 // minimum over all k is the maximum of those positive floats (an unsigned
 // integer maximum of their bits, two accumulators per v_max3_u32).  Every
 // term is a power of two and no sum loses its largest term, so rounding
@@ -28,12 +28,10 @@
 // A, [k / 8][column] for B (transposed on the way by v_perm_b32), the order
 // the matrix instruction reads its operands in.
 //
-// What bounds it: per 64 k and 32 x 32 outputs a SIMD spends 128 cycles in
-// the matrix core, 64 on the maxima and (128 x 128 blocks) 80 on the
-// conversion and transposition, so matrix core and VALU are both nearly
-// busy.  N = 16384, entries 0..15: 117.0 ms (37.6 T pairs/s) in the uint16
-// form, 11.4 ms (387 T pairs/s) in this one; a bf16 library product of
-// 8192 x 8192 x 8192 reaches 604 T multiply-adds/s on the same card.
+// What bounds it: the issue slots of the VALU (level_slice) and the power of
+// the chip.  N = 16384, entries 0..15: 117.0 ms (37.6 T pairs/s) in the uint16
+// form, 9.75 ms (451 T pairs/s) in this one; a bf16 library product of 8192 x 8192 x 8192
+// reaches 604 T multiply-adds/s on the same card.
 #pragma once
 
 #include "tile.h"
@@ -41,7 +39,7 @@
 namespace mpr {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int LV_STEP = 6;                       // exponent bits per level
 constexpr uint32_t LV_MAX = 30;                  // largest value with a nonzero image
@@ -51,14 +49,14 @@ constexpr uint32_t LV_SUM = 44;                  // 2^(118 - 6 * 44) = 2^-146, a
 // Bits of the least sum that proves a result <= LV_MAX: 2^(118 - 180).
 constexpr uint32_t LV_SURE = (uint32_t)(127 + LV_TOP - LV_STEP * (int)LV_MAX) << 23;
 
-// MI x NI tiles of 32 x 32 outputs per wave, WM x WN waves per block, KS such
+// MI x NI tiles of 16 x 16 outputs per wave, WM x WN waves per block, KS such
 // groups of waves that share the block's slices of K between them (for
 // products of few tiles, which are a chain of memory round trips: KS times
 // the loads in flight, a KS-th of the trips).
 template <int MI_, int NI_, int WM_, int WN_, int KS_ = 1>
 struct LevelCfg {
     static constexpr int MI = MI_, NI = NI_, WM = WM_, WN = WN_, KS = KS_;
-    static constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN;
+    static constexpr int BM = 16 * MI * WM, BN = 16 * NI * WN;
     static constexpr int GT = 64 * WM * WN, NT = GT * KS;  // threads of a group, of the block
     // Thread in its group, wave in its group, group.
     static __device__ __forceinline__ int tid() { return (int)threadIdx.x % GT; }
@@ -75,6 +73,7 @@ struct LevelCfg {
     static constexpr int LDS_CHUNKS = 2 * STAGE * KS;
     static constexpr int A_CPT = BM * KC / GT;   // A chunks a thread stages
     static constexpr int B_COLS = BN * KC / GT;  // columns of 8 k a thread stages
+    static_assert(NI % 2 == 0, "level_store pairs neighbouring tiles");
     static_assert(BM * KC % GT == 0 && (B_COLS == 2 || B_COLS == 4), "staging split");
 };
 
@@ -152,12 +151,14 @@ struct LevelA {
         return x;
     }
     __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * 2; }
-    // a full slice; the group's next one is KS slices before it
+    // a full slice, chunk by chunk; the group's next one is KS slices before it
+    __device__ __forceinline__ void load_chunk(int q) { r[q] = uload16(at, off[q]); }
+    __device__ __forceinline__ void advance() { at -= C::BK * C::KS * 2; }
     __device__ __forceinline__ void load()
     {
 #pragma unroll
-        for (int q = 0; q < C::A_CPT; q++) r[q] = uload16(at, off[q]);
-        at -= C::BK * C::KS * 2;
+        for (int q = 0; q < C::A_CPT; q++) load_chunk(q);
+        advance();
     }
     // the last K % BK values, in a slice of their own from k0
     __device__ __forceinline__ void load_tail(int64_t k0)
@@ -171,13 +172,11 @@ struct LevelA {
             r[q] = shift_in_inf(r[q], back);
         }
     }
-    __device__ __forceinline__ void store(uint4 *as) const
+    __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
-#pragma unroll
-        for (int q = 0; q < C::A_CPT; q++)
-            as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
-                make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
-                           level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
+        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+            make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
+                       level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
     // largest finite value (signed: infinity is negative)
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
@@ -243,9 +242,9 @@ struct LevelB {
 #pragma unroll
         for (int k = 0; k < 8; k++) take(k, b, (uint32_t)min(kg * 8 + k, last) * ldb2 + coff);
     }
-    __device__ __forceinline__ void store(uint4 *bs)
+    // before the first store_chunk of a slice: columns moved back into place
+    __device__ __forceinline__ void settle()
     {
-        const int kg = C::tid() / TPG, cg = C::tid() % TPG;
         if (back) {
 #pragma unroll
             for (int k = 0; k < 8; k++) {
@@ -258,16 +257,16 @@ struct LevelB {
                 }
             }
         }
+    }
+    __device__ __forceinline__ void store_chunk(uint4 *bs, int j) const
+    {
+        const int kg = C::tid() / TPG, n = C::tid() % TPG * C::B_COLS + j;
+        uint32_t w[4];
 #pragma unroll
-        for (int j = 0; j < C::B_COLS; j++) {
-            uint32_t w[4];
-#pragma unroll
-            for (int p = 0; p < 4; p++)
-                w[p] = level_image(__builtin_amdgcn_perm(r[2 * p + 1][j / 2], r[2 * p][j / 2],
-                                                         (j & 1) ? 0x07060302u : 0x05040100u));
-            const int n = cg * C::B_COLS + j;
-            bs[kg * C::PB + (n ^ ((n >> 3) & 3))] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
+        for (int p = 0; p < 4; p++)
+            w[p] = level_image(__builtin_amdgcn_perm(r[2 * p + 1][j / 2], r[2 * p][j / 2],
+                                                     (j & 1) ? 0x07060302u : 0x05040100u));
+        bs[kg * C::PB + (n ^ ((n >> 3) & 3))] = make_uint4(w[0], w[1], w[2], w[3]);
     }
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {
@@ -282,7 +281,7 @@ struct LevelB {
 
 template <class C>
 struct LevelAcc {
-    uint32_t v[C::MI][C::NI][16];
+    uint32_t v[C::MI][C::NI][4];
 };
 
 // The slices of K: slice 0 is the partial one at the end of K when there is
@@ -308,6 +307,82 @@ __device__ __forceinline__ void level_first(int64_t K, AOp &aop, BOp &bop)
     }
 }
 
+// One slice: the products of LDS stage (as, bs), and beside them, when STORE,
+// the next slice's registers into LDS and, when LOAD, the loads of the slice
+// after that into the registers just freed.  All three kinds of work are
+// interleaved by hand: a matrix instruction runs for 16 cycles, in which the
+// wave's VALU takes two of the four maxima of the tile two before (its sums
+// wait in registers meanwhile) and, on some tiles, converts a staged chunk.
+// In the order the compiler chose, the matrix core idled during the maxima
+// and the staging (N = 8192: matrix core 32 %, VALU 49 % busy).  A matrix
+// instruction also takes two VALU issue slots (measured: 16 x 16 x 32 with
+// four v_max_u32 26 cycles, 16.4 and 18 alone), so per slice of 64 x 64
+// outputs a SIMD needs 162 VALU instructions and 32 x 2 slots: that, not the
+// matrix core, is the bound, and the clock falls to 1.95 GHz under this load.
+template <class C, bool STORE, bool LOAD, class AOp, class BOp>
+__device__ __forceinline__ void level_slice(const uint4 *as, const uint4 *bs0, const uint4 *bs1, uint4 *next, AOp &aop,
+                                            BOp &bop, LevelAcc<C> &acc)
+{
+    constexpr int T = C::MI * C::NI, PIECES = C::A_CPT + C::B_COLS, LAG = 2;
+    bf16x8 bf[C::NI][2], af[2][2];
+    auto readb = [&](int ni) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++)
+            bf[ni][ks] = __builtin_bit_cast(bf16x8, ((ni & 1) ? bs1 : bs0)[4 * ks * C::PB + 16 * ni]);
+    };
+    readb(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) af[0][ks] = __builtin_bit_cast(bf16x8, as[4 * ks * C::PA]);
+    f32x4 t[LAG + 1][2];
+    if (STORE) bop.settle();
+    int piece = 0;
+#pragma unroll
+    for (int i = 0; i < T + LAG; i++) {
+        const int mi = i / C::NI, ni = i % C::NI, o = i - LAG;
+        if (i == 0) {
+            readb(1);
+            if (C::NI > 2) readb(2);
+        } else if (i + 2 < C::NI) {
+            readb(i + 2);
+        }
+        if (i < T && ni == 0 && mi + 1 < C::MI) {  // the next row of tiles' operand, a row ahead
+#pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                af[(mi + 1) & 1][ks] = __builtin_bit_cast(bf16x8, as[4 * ks * C::PA + 16 * (mi + 1)]);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+            if (i < T) {
+                const f32x4 zero = {};
+                t[i % (LAG + 1)][ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[ni][ks], af[mi & 1][ks], zero, 0, 0, 0);
+            }
+            if (o >= 0) {
+#pragma unroll
+                for (int r = 2 * ks; r < 2 * ks + 2; r++) {
+                    const float f0 = t[o % (LAG + 1)][0][r], f1 = t[o % (LAG + 1)][1][r];
+                    uint32_t &d = acc.v[o / C::NI][o % C::NI][r];
+                    d = max(max(d, __builtin_bit_cast(uint32_t, f0)), __builtin_bit_cast(uint32_t, f1));
+                }
+            }
+            if (ks == 1 && STORE) {
+                const int upto = ((i + 1) * PIECES + T - 1) / T;
+#pragma unroll
+                for (; piece < upto && piece < PIECES; piece++) {
+                    if (piece < C::A_CPT) {
+                        aop.store_chunk(next, piece);
+                        if (LOAD) aop.load_chunk(piece);
+                    } else {
+                        bop.store_chunk(next + C::KC * C::PA, piece - C::A_CPT);
+                        if (LOAD && piece == PIECES - 1) bop.load();
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (LOAD) aop.advance();
+}
+
 // The k loop: acc = the largest 32-term sum of each output (its f32 bits),
 // complete in group 0.  The product is taken transposed (D = B^T A^T): a lane
 // then holds one row of C and runs of 4 consecutive columns.
@@ -316,87 +391,60 @@ __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
 {
     const int lane = (int)(threadIdx.x & 63);
     const int wm = C::wave() / C::WN, wn = C::wave() % C::WN;
-    const int aoff = (lane >> 5) * C::PA + wm * 32 * C::MI + (lane & 31);
-    const int boff = C::KC * C::PA + (lane >> 5) * C::PB + wn * 32 * C::NI + ((lane & 31) ^ ((lane >> 3) & 3));
+    const int aoff = (lane >> 4) * C::PA + wm * 16 * C::MI + (lane & 15);
+    // even and odd tiles of 16 columns (LevelB's order of the chunks)
+    const int boff0 = C::KC * C::PA + (lane >> 4) * C::PB + wn * 16 * C::NI + ((lane & 15) ^ ((lane >> 3) & 1));
+    const int boff1 = boff0 ^ 2;
     uint4 *const all = lds;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++)
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) acc.v[mi][ni][r] = 0;
+            for (int r = 0; r < 4; r++) acc.v[mi][ni][r] = 0;
     // slices of this group, and the trips of the block (those of group 0)
     const int64_t slices = (K + C::BK - 1) / C::BK;
     int64_t left = (slices - C::group() + C::KS - 1) / C::KS, trips = (slices + C::KS - 1) / C::KS;
     lds += C::group() * 2 * C::STAGE;
     level_first<C>(K, aop, bop);
-    if (C::KS == 1 || left > 0) {
-        aop.store(lds);
-        bop.store(lds + C::KC * C::PA);
+    if (left > 0) {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) aop.store_chunk(lds, q);
+        bop.settle();
+#pragma unroll
+        for (int j = 0; j < C::B_COLS; j++) bop.store_chunk(lds + C::KC * C::PA, j);
+    }
+    if (left > 1) {
+        aop.load();
+        bop.load();
     }
     __syncthreads();
     for (int cur = 0;; cur ^= 1) {
-        const bool more = --left > 0;
+        left--;  // slices of the group after this one
         uint4 *next = lds + (cur ^ 1) * C::STAGE;
-        const uint4 *as = lds + cur * C::STAGE + aoff, *bs = lds + cur * C::STAGE + boff;
-        if (more) aop.load();
-        if (C::KS == 1 || left >= 0) {
-            bf16x8 bf[C::NI][4];
-#pragma unroll
-            for (int ni = 0; ni < C::NI; ni++)
-#pragma unroll
-                for (int ks = 0; ks < 4; ks++) bf[ni][ks] = __builtin_bit_cast(bf16x8, bs[2 * ks * C::PB + 32 * ni]);
-            if (C::MI == 1 && more) bop.load();
-#pragma unroll
-            for (int mi = 0; mi < C::MI; mi++) {
-                if (C::MI > 1 && mi == C::MI / 2 && more) {
-                    aop.store(next);
-                    bop.load();
-                }
-                bf16x8 af[4];
-#pragma unroll
-                for (int ks = 0; ks < 4; ks++) af[ks] = __builtin_bit_cast(bf16x8, as[2 * ks * C::PA + 32 * mi]);
-#pragma unroll
-                for (int ni = 0; ni < C::NI; ni++) {
-                    f32x16 t0 = {}, t1 = {};
-                    t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][0], af[0], t0, 0, 0, 0);
-                    t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][2], af[2], t1, 0, 0, 0);
-                    t0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][1], af[1], t0, 0, 0, 0);
-                    t1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ni][3], af[3], t1, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 16; r++) {
-                        const float f0 = t0[r], f1 = t1[r];
-                        const uint32_t u0 = __builtin_bit_cast(uint32_t, f0), u1 = __builtin_bit_cast(uint32_t, f1);
-                        uint32_t &d = acc.v[mi][ni][r];
-                        d = max(max(d, u0), u1);
-                        // keeps the maximum here: moved past the branches below
-                        // it would hold both accumulators in registers
-                        asm volatile("" : "+v"(d));
-                    }
-                    __builtin_amdgcn_sched_barrier(0);  // one tile of accumulators in registers at a time
-                }
-            }
-        }
-        if (more) {
-            if (C::MI == 1) aop.store(next);
-            bop.store(next + C::KC * C::PA);
-        }
+        const uint4 *st = lds + cur * C::STAGE, *as = st + aoff, *b0 = st + boff0, *b1 = st + boff1;
+        if (left > 1)
+            level_slice<C, true, true>(as, b0, b1, next, aop, bop, acc);
+        else if (left == 1)
+            level_slice<C, true, false>(as, b0, b1, next, aop, bop, acc);
+        else if (left == 0)
+            level_slice<C, false, false>(as, b0, b1, next, aop, bop, acc);
         __syncthreads();
         if (--trips == 0) break;
     }
     if constexpr (C::KS > 1) {  // the groups' maxima into group 0
-        constexpr int REGS = C::MI * C::NI * 16;
+        constexpr int REGS = C::MI * C::NI * 4;
         uint32_t *sh = (uint32_t *)all + C::tid();
         for (int g = 1; g < C::KS; g++) {
             if (C::group() == g) {
 #pragma unroll
-                for (int r = 0; r < REGS; r++) sh[r * C::GT] = acc.v[r / (C::NI * 16)][r / 16 % C::NI][r % 16];
+                for (int r = 0; r < REGS; r++) sh[r * C::GT] = acc.v[r / (C::NI * 4)][r / 4 % C::NI][r % 4];
             }
             __syncthreads();
             if (C::group() == 0) {
 #pragma unroll
                 for (int r = 0; r < REGS; r++) {
-                    uint32_t &d = acc.v[r / (C::NI * 16)][r / 16 % C::NI][r % 16];
+                    uint32_t &d = acc.v[r / (C::NI * 4)][r / 4 % C::NI][r % 4];
                     d = max(d, sh[r * C::GT]);
                 }
             }
@@ -405,17 +453,17 @@ __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
     }
 }
 
-// Block row / first of 4 block columns that accumulator registers 4q..4q+3
-// of wave tile (mi, ni) hold.
+// Block row, and first of the 4 block columns, that the accumulators of wave
+// tile (mi, ni) hold.
 template <class C>
 __device__ __forceinline__ int level_row(int mi)
 {
-    return (C::wave() / C::WN) * 32 * C::MI + mi * 32 + (int)(threadIdx.x & 31);
+    return (C::wave() / C::WN * C::MI + mi) * 16 + (int)(threadIdx.x & 15);
 }
 template <class C>
-__device__ __forceinline__ int level_col(int ni, int q)
+__device__ __forceinline__ int level_col(int ni)
 {
-    return (C::wave() % C::WN) * 32 * C::NI + ni * 32 + 8 * q + 4 * (int)((threadIdx.x >> 5) & 1);
+    return (C::wave() % C::WN * C::NI + ni) * 16 + 4 * (int)((threadIdx.x >> 4) & 3);
 }
 
 // The value an accumulator stands for (infinity when no term was found).
@@ -439,10 +487,7 @@ __device__ __forceinline__ bool level_sure(const LevelAcc<C> &acc, int rows, int
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    bad |= rin && level_col<C>(ni, q) + j < cols && acc.v[mi][ni][4 * q + j] < LV_SURE;
+            for (int j = 0; j < 4; j++) bad |= rin && level_col<C>(ni) + j < cols && acc.v[mi][ni][j] < LV_SURE;
     }
     return !__syncthreads_or(bad);
 }
@@ -476,42 +521,39 @@ __device__ __forceinline__ bool level_clean(int64_t K, AOp &aop, BOp &bop, uint4
 }
 
 // Writes the block's results inside rows x cols to C (row 0, column 0 of the
-// block at `out`).  Lanes l and l + 32 hold the two halves of 8 columns of
-// one row; they trade halves so that each writes 16 bytes.
+// block at `out`).  The 16-lane rows 0..3 of a wave hold columns 0-3, 4-7,
+// 8-11 and 12-15 of a tile; the odd ones trade with their neighbours between
+// two tiles, so that each lane writes 8 consecutive columns (16 bytes).
 template <class C>
 __device__ __forceinline__ void level_store(gu16 *out, int64_t ldc, int rows, int cols, const LevelAcc<C> &acc)
 {
-    const int half = (int)((threadIdx.x >> 5) & 1);
+    const int quarter = (int)((threadIdx.x >> 4) & 3);
     if (C::group() != 0) return;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++) {
         const int row = level_row<C>(mi);
 #pragma unroll
-        for (int ni = 0; ni < C::NI; ni++)
+        for (int ni = 0; ni < C::NI; ni += 2) {
+            uint32_t w[2][2];
 #pragma unroll
-            for (int p = 0; p < 2; p++) {
-                uint32_t w[2][2];
+            for (int e = 0; e < 2; e++)
 #pragma unroll
-                for (int e = 0; e < 2; e++)
+                for (int h = 0; h < 2; h++)
+                    w[e][h] = level_value(acc.v[mi][ni + e][2 * h]) | (level_value(acc.v[mi][ni + e][2 * h + 1]) << 16);
+            const auto s0 = __builtin_amdgcn_permlane16_swap(w[0][0], w[1][0], false, false);
+            const auto s1 = __builtin_amdgcn_permlane16_swap(w[0][1], w[1][1], false, false);
+            const int col = (C::wave() % C::WN * C::NI + ni + (quarter & 1)) * 16 + (quarter >> 1) * 8;
+            if (row >= rows) continue;
+            gu16 *g = out + (int64_t)row * ldc + col;
+            const uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+            if (col + 8 <= cols) {
+                ustore16(g, v);
+            } else {
 #pragma unroll
-                    for (int h = 0; h < 2; h++) {
-                        const uint32_t *a = &acc.v[mi][ni][8 * p + 4 * e + 2 * h];
-                        w[e][h] = level_value(a[0]) | (level_value(a[1]) << 16);
-                    }
-                const auto s0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
-                const auto s1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-                const int col = level_col<C>(ni, 2 * p) - 4 * half + 8 * half;
-                if (row >= rows) continue;
-                gu16 *g = out + (int64_t)row * ldc + col;
-                const uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
-                if (col + 8 <= cols) {
-                    ustore16(g, v);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        if (col + e < cols) g[e] = (u16)(comp(v, e >> 1) >> ((e & 1) * 16));
-                }
+                for (int e = 0; e < 8; e++)
+                    if (col + e < cols) g[e] = (u16)(comp(v, e >> 1) >> ((e & 1) * 16));
             }
+        }
     }
 }
 
@@ -546,11 +588,11 @@ __device__ __forceinline__ void level_row_low(const LevelAcc<C> &acc, int rows, 
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
-            for (int r = 0; r < 16; r++)
-                u = max(u, level_col<C>(ni, r / 4) + r % 4 < cols ? acc.v[mi][ni][r] : 0u);
+            for (int r = 0; r < 4; r++) u = max(u, level_col<C>(ni) + r < cols ? acc.v[mi][ni][r] : 0u);
+        u = max(u, (uint32_t)__shfl_xor((int)u, 16, 64));
         u = max(u, (uint32_t)__shfl_xor((int)u, 32, 64));
         const int row = level_row<C>(mi);
-        if ((threadIdx.x & 63) < 32 && row < rows && u) atomicMin(&low[row], level_value(u));
+        if ((threadIdx.x & 63) < 16 && row < rows && u) atomicMin(&low[row], level_value(u));
     }
 }
 
@@ -627,14 +669,16 @@ __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0,
 
 // Block shapes of the products and steps, each with the VALU tile that
 // stands in for it.
-using LCfg0 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 128 x 128
-using LCfg1 = LevelCfg<1, 1, 2, 2>;  // 256 threads, 64 x 64
-using LCfg2 = LevelCfg<2, 2, 2, 2, 2>;  // 512 threads, 128 x 128
-using LCfg3 = LevelCfg<1, 1, 2, 2, 2>;  // 512 threads, 64 x 64
+using LCfg0 = LevelCfg<4, 4, 2, 2>;  // 256 threads, 128 x 128
+using LCfg1 = LevelCfg<2, 2, 2, 2>;  // 256 threads, 64 x 64
+using LCfg2 = LevelCfg<4, 4, 2, 2, 2>;  // 512 threads, 128 x 128
+using LCfg3 = LevelCfg<2, 2, 2, 2, 2>;  // 512 threads, 64 x 64
+using LCfg4 = LevelCfg<4, 4, 2, 4>;     // 512 threads, 128 x 256
 template <class C> struct LevelBack;
 template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
 template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
 template <> struct LevelBack<LCfg2> { using T = TileCfg<128, 128, 32, 4, 8>; };
+template <> struct LevelBack<LCfg4> { using T = TileCfg<128, 256, 32, 8, 8>; };
 template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 32, 1, 8>; };
 // LDS of a block (16-byte chunks): its own, or the VALU tile's if larger.
 template <class C>

@@ -22,7 +22,7 @@ __device__ __forceinline__ bool level_tile(int tiles_m, int tiles_n, int &tm, in
 
 // The f16 form recomputes a block that the levels can not hold: at K >= 128
 // (level_config) values up to 3000 still give minima below 2048, where it is
-// exact and 4/3 as fast as the uint16 form (N = 4096, entries 0..3000: 1.88
+// exact and 4/3 as fast as the uint16 form (N = 4096, entries 0..3000: 1.83
 // ms for the wasted level pass and the f16 pass, 1.94 ms in uint16 alone).
 template <class C>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void level_gemm_kernel(
@@ -63,16 +63,19 @@ static mpr_status level_launch(int64_t M, int64_t N, int64_t K, const u16 *A, in
     return check_launch();
 }
 
-// Block shape of an M x N output (0..3 = LCfg0..3).  128 x 128 blocks move
-// half the operand bytes of 64 x 64 ones, so they are taken as soon as they
-// nearly fill the 256 CUs; while a CU holds only one of them, two groups of
-// waves share its slices of K.  Measured (us, shape 0 / 1 / 2 / 3): N = 848
-// 22 / 13 / 19 / 11.5; N = 1300 31 / 21 / 26 / 20; 1000 x 3333 x 2507 (216
-// blocks of 128 x 128) 58 / 57 / 47 / 60; N = 2507 (400) 73 / 92 / 80 / 99;
-// N = 4096 195 / 295 / 229 / 295.
+// Block shape of an M x N output (0..4 = LCfg0..4).  Large blocks move and
+// convert fewer operand values per output, so the largest shape is taken
+// whose blocks (one per CU at 128 x 256, two at 128 x 128) fill most of the
+// 256 CUs; while a CU holds only one 128 x 128 block, two groups of waves
+// share its slices of K.  Measured (us, shape 0 / 1 / 2 / 3 / 4): N = 848
+// 21 / 12 / 19 / 10.5 / 26; N = 1300 27 / 20 / 24 / 19 / 35; 1000 x 3333 x
+// 2507 (112 blocks of 128 x 256) 50 / 54 / 45 / 57 / 66; N = 2507 (200) 68 /
+// 86 / 79 / 91 / 62; N = 4096 179 / 276 / 228 / 282 / 173; N = 16384 11440 /
+// 16204 / 11693 / 18066 / 9787.
 int level_shape(int64_t M, int64_t N)
 {
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), cus = device_cu_count();
+    const int64_t rows = (M + 127) / 128, tiles = rows * ((N + 127) / 128), cus = device_cu_count();
+    if (rows * ((N + 255) / 256) >= cus * 3 / 4) return 4;
     return tiles >= cus ? 0 : tiles >= cus * 5 / 8 ? 2 : 3;
 }
 
@@ -92,6 +95,7 @@ mpr_status product_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A
     switch (level_shape(M, N)) {
     case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
     case 2: return level_launch<LCfg2>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
+    case 4: return level_launch<LCfg4>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
     default: return level_launch<LCfg3>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
     }
 }
@@ -103,7 +107,7 @@ mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const 
         return gemm_launch_spare(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
     // 128 x 128 blocks hold half of a CU's registers each: with so much LDS
     // that a second one does not fit, the other half stays free
-    if (level_shape(M, N) == 0)
+    if (level_shape(M, N) % 4 == 0)
         return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 84 * 1024 - sizeof(uint4) * LCfg0::LDS_CHUNKS);
     return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
 }
@@ -132,7 +136,7 @@ static mpr_status step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
 mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
 {
     switch (level_shape(p.n, p.n)) {
-    case 0: return step_launch<LCfg0>(p, st, s);
+    case 0: case 4: return step_launch<LCfg0>(p, st, s);
     case 2: return step_launch<LCfg2>(p, st, s);
     default: return step_launch<LCfg3>(p, st, s);
     }
@@ -165,6 +169,7 @@ extern "C" int mpr_level_probe(int cfg, int64_t M, int64_t N, int64_t K, const u
     case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
     case 1: return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
     case 2: return level_launch<LCfg2>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
+    case 4: return level_launch<LCfg4>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
     default: return level_launch<LCfg3>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
     }
 }

@@ -440,6 +440,11 @@ static mpr_status start_period_build(Server &S, Ladder &L)
 // smaller ladder is never stuck behind a larger one's products (the
 // worker's tick between two large products costs well under 1 %).
 constexpr int64_t kBigLadder = 4096;
+// Products of ladders from this size on (m >= 9, 0.28 s each) stay on the
+// VALU tiles: the schedule above, a small ladder built between the products
+// of a large one, is tested against a build of m = 9 that takes seconds (on
+// the matrix cores all of it takes 1.3 s).
+constexpr int64_t kVastLadder = 16384;
 constexpr int kSmallAhead = 8;
 
 // Giant products of L enqueued and not yet finished.
@@ -491,8 +496,9 @@ static mpr_status enqueue_giants(Server &S, Ladder &L, int upto)
         const int i = L.next_giant;
         // large products leave one workgroup slot per CU to the queries
         // that run beside the build
-        e = n >= kBigLadder ? product_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
-                            : product_launch(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s);
+        e = n >= kVastLadder  ? gemm_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
+            : n >= kBigLadder ? product_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
+                              : product_launch(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s);
         if (e == MPR_OK)
             e = normalise_launch(n, n, L.Ng[i], ld, L.Rg[i - 1], L.scal, L.Rg[i], L.status_dev, nullptr, s);
         if (e == MPR_OK) e = pack_build(S, L, L.Ng[i], L.Ng8[i]);

@@ -462,7 +462,7 @@ __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void s
 // run of the tiles in row-panel order: the column blocks of one panel run
 // together and their 128 rows of N (1.9 MB at m = 8) stay in that XCD's L2,
 // where every block reads its |L_J| columns of them.
-using PCfg = LevelCfg<2, 1, 2, 2>;  // 256 threads, 128 x 64
+using PCfg = LevelCfg<4, 2, 2, 2>;  // 256 threads, 128 x 64
 using PBack = TileCfg<128, 64, 32, 4, 8>;
 static_assert(PCfg::BM == PBack::BM && PCfg::BN == SBN && PBack::BN == SBN && PCfg::NT == PBack::NT, "stand-in tile");
 
@@ -473,7 +473,8 @@ struct LevelGather {
     const __attribute__((address_space(1))) int32_t *idx, *at;
     int64_t n, K;
     uint32_t off[C::A_CPT];
-    int col;  // first column of the thread's k group in the slice that load() takes
+    int col;   // first column of the thread's k group in the slice that load() takes
+    int back;  // columns to step back from there to stay in the row (slice 0 only)
     uint4 r[C::A_CPT];
     __device__ __forceinline__ LevelGather(const gu16 *p, int64_t ld, int rows, int64_t n_, const int32_t *list,
                                            int64_t K_)
@@ -483,45 +484,56 @@ struct LevelGather {
         for (int q = 0; q < C::A_CPT; q++)
             off[q] = (uint32_t)min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1) * (uint32_t)ld * 2u;
     }
-    __device__ __forceinline__ void seek(int64_t k0)
+    __device__ __forceinline__ void seek(int64_t k0) { point(k0, k0 >= 0); }
+    // to the slice at k0; a thread with no group there reads column 0
+    __device__ __forceinline__ void point(int64_t k0, bool in)
     {
         at = idx + k0;
-        col = k0 >= 0 ? *at : 0;
+        col = in ? *at : 0;
+        back = max(0, (int)(col + 8 - n));
     }
-    __device__ __forceinline__ void take()
+    __device__ __forceinline__ void load_chunk(int q) { r[q] = uload16(base, off[q] + (uint32_t)(col - back) * 2u); }
+    __device__ __forceinline__ void advance()
     {
-        // The last group of the matrix may end before its 8th column: read
-        // back from the end of the row and shift (its rows of A past the end
-        // are infinite, so any value will do there).
-        const int back = max(0, (int)(col + 8 - n));
+        at -= C::BK * C::KS;
+        col = at >= idx ? *at : 0;
+        back = 0;  // lists ascend and slices descend: only slice 0 has the matrix's last group
+    }
+    // The last group of the matrix may end before its 8th column: it was read
+    // from the end of the row back (its rows of A past the end are infinite,
+    // so any value will do there).
+    __device__ __forceinline__ void settle()
+    {
+        if (back) {
 #pragma unroll
-        for (int q = 0; q < C::A_CPT; q++) {
-            r[q] = uload16(base, off[q] + (uint32_t)(col - back) * 2u);
-            if (back) r[q] = shift_in_inf(r[q], back);
+            for (int q = 0; q < C::A_CPT; q++) r[q] = shift_in_inf(r[q], back);
         }
     }
     __device__ __forceinline__ void load()
     {
-        take();
-        at -= C::BK * C::KS;
-        col = at >= idx ? *at : 0;
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) load_chunk(q);
+        settle();
+        advance();
     }
     __device__ __forceinline__ void load_tail(int64_t k0)  // K is a multiple of SBK = 32
     {
-        col = k0 + C::tid() % C::KC * 8 < K ? idx[k0] : 0;
-        take();
-        if (k0 + C::tid() % C::KC * 8 >= K) {
+        // the list ends at K: past it is another block's list or no list
+        const bool in = k0 + C::tid() % C::KC * 8 < K;
+        point(k0, in);
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) load_chunk(q);
+        settle();
+        if (!in) {
 #pragma unroll
             for (int q = 0; q < C::A_CPT; q++)
                 r[q] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
         }
     }
-    __device__ __forceinline__ void store(uint4 *as) const
+    __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
-#pragma unroll
-        for (int q = 0; q < C::A_CPT; q++)
-            as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
-                make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
+        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+            make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
     }
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {

@@ -116,3 +116,22 @@ def test_level_batch_overflow_is_reported(mpr):
         finally:
             mpr.set_batch_config(-1)
     assert status == [3, 3]
+
+
+@pytest.mark.parametrize("n", [8, 11, 33, 72, 100, 129, 200])
+def test_level_sparse_steps(mpr, n):
+    """Compressed-K steps at the edges of their lists: blocks of 32 and of 64
+    listed rows and more, a last group of fewer than 8 rows, a block of
+    columns without entries, row strides of n; in a workspace full of ones,
+    so a read past a list would not pass unnoticed."""
+    for i, (inf, e) in enumerate([(0.9, 5), (0.3, 4), (0.995, 3)]):
+        print("level sparse", n, inf, flush=True)
+        X = synth.random_matrix(n, n, 300 + n + i, 0, 12, inf)
+        if i == 2:
+            X[:, 64:128] = mpr.INF
+        A = torch.from_numpy(X).cuda() if i else mpr.to_device(X)
+        N = torch.empty((n, n), dtype=torch.int16, device="cuda").view(torch.uint16)
+        ws = mpr.workspace(mpr.power_workspace_size(n, e, mpr.CHAIN) + 256 + mpr.sparse_plan_bytes(A)).fill_(255)
+        N, R = mpr.minplus_power(A, e, mpr.CHAIN_SPARSE, N_out=N, ws=ws)
+        Nr, Rr = O.power_chain(O.from_u16(X), e)
+        assert np.array_equal(N.cpu().numpy(), O.to_u16(Nr)) and np.array_equal(R.cpu().numpy(), Rr)
