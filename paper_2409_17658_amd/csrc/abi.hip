@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -90,6 +91,62 @@ int device_cu_count()
     if (hipGetDevice(&dev) != hipSuccess) return 256;
     std::lock_guard<std::mutex> lk(g_init_mu);
     return (dev < (int)g_cus.size() && g_cus[dev] > 0) ? g_cus[dev] : 256;
+}
+
+// ------------------------------------------------------------ host records
+// At most kRecords pinned records stay allocated while no call uses them.
+static std::mutex g_records_mu;
+static std::vector<int64_t *> g_records;
+constexpr size_t kRecords = 16;
+
+HostRecord::HostRecord() : p(nullptr)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_records_mu);
+        if (!g_records.empty()) {
+            p = g_records.back();
+            g_records.pop_back();
+        }
+    }
+    if (!p && hipHostMalloc((void **)&p, 16 * sizeof(int64_t), hipHostMallocPortable) != hipSuccess) p = nullptr;
+    if (p) p[7] = p[15] = 0;  // no record yet
+}
+
+HostRecord::~HostRecord()
+{
+    if (!p || failed) return;
+    {
+        std::lock_guard<std::mutex> lk(g_records_mu);
+        if (g_records.size() < kRecords) {
+            g_records.push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+// Waits until a kernel on stream s has written `seq` (never 0) into the
+// record: a look at host memory (6 us from launch to here, 21 us with a copy
+// and a synchronisation).  A stream that ends or fails without writing it is
+// an error, so the wait ends in every case.
+mpr_status HostRecord::wait(const int64_t *rec, int64_t seq, hipStream_t s)
+{
+    auto there = [&] { return __atomic_load_n(&rec[7], __ATOMIC_ACQUIRE) == seq; };
+    for (;;) {
+        for (int k = 0; k < 4096; k++) {
+            if (there()) return MPR_OK;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) {
+            std::this_thread::yield();
+            continue;
+        }
+        if (e == hipSuccess && there()) return MPR_OK;
+        (void)hipGetLastError();
+        failed = true;
+        return MPR_EHIP;
+    }
 }
 
 // ------------------------------------------------------------ workspace carving
@@ -301,11 +358,11 @@ static void report_progress(int64_t k, int64_t trace)
 constexpr int kPeriodFlagsAll = MPR_PERIOD_SPARSE | MPR_PERIOD_EXTEND | MPR_PERIOD_REUSE_A | MPR_PERIOD_PIPELINE;
 
 struct PeriodWs {
-    uint64_t *row_hash;
+    void *acc;        // what the rows of a power fold into (period.hip)
     int64_t *hold_R;  // offsets of the power kept in A's buffer (MPR_PERIOD_REUSE_A)
     void *plan;
     size_t plan_bytes;
-    int64_t *scal;  // [0] hash, [1] trace, [2] status (int32 in low half), [3..5] compare
+    int64_t *scal;  // [2] status (int32 in low half), [3..5] compare
     int64_t slots;
     int64_t ld;
     size_t slot_elems;  // u16 per slot (matrix) + R follows after padding
@@ -314,7 +371,7 @@ struct PeriodWs {
     size_t fixed;
 };
 
-// Workspace layout of the period search: the per-row hashes and scalars,
+// Workspace layout of the period search: the accumulator and scalars,
 // then (MPR_PERIOD_SPARSE) the compressed-K plan of plan_bytes (the worst
 // case when 0), then the ring of power slots.
 static PeriodWs carve_period(void *ws, int64_t n, size_t ws_bytes, int64_t slots_req, int flags,
@@ -323,7 +380,7 @@ static PeriodWs carve_period(void *ws, int64_t n, size_t ws_bytes, int64_t slots
     PeriodWs w{};
     w.ld = round_up(n > 0 ? n : 1, 8);
     Carver c(ws);
-    w.row_hash = c.take<uint64_t>((size_t)n);
+    w.acc = c.take<char>(period_acc_bytes());
     w.scal = c.take<int64_t>(8);
     w.hold_R = (flags & MPR_PERIOD_REUSE_A) ? c.take<int64_t>((size_t)n) : nullptr;
     if (flags & MPR_PERIOD_SPARSE) {
@@ -585,7 +642,7 @@ extern "C" mpr_status mpr_sparse_plan_bytes(const uint16_t *A, int64_t n, int64_
     if (hipMallocAsync(&tmp, tmp_bytes, s) != hipSuccess) return MPR_ENOMEM;
     int64_t rows = 0;
     r = sparse_plan_rows(A, n, lda, tmp, s, &rows);
-    if (hipFreeAsync(tmp, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
+    if (hipFreeAsync(tmp, s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
     if (r == MPR_OK) *bytes_host = sparse_plan_bytes_rows(n, rows);
     return r;
 }
@@ -667,8 +724,9 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     if (w.slots < (pipeline ? 3 : 2)) return MPR_ENOMEM;
     int32_t *st = (int32_t *)&w.scal[2];
     if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK) return r;
-    if ((r = validate_launch(A, n, n, lda, st, s)) != MPR_OK) return r;
-    if (sparse && (r = sparse_plan_launch(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
+    if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
+    // the counts that sized the plan lie where it begins (same carving)
+    if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
     if (traces_host) traces_host[0] = MPR_ROW_NONE;
 
     // Power k lives in slot (k - 1) % slots (a ring), so a repeat of the class
@@ -679,7 +737,6 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     std::unordered_multimap<uint64_t, int64_t> seen;  // class hash -> k
     bool found = false;
     int64_t mu = 0, lam = 0, cval = 0;
-    int64_t prev_slot = -1;
     bool held = false;           // a power waits in A's buffer
     int64_t held_k = 0, held_lam = 0;
     u16 *hold_N = reuse_a ? const_cast<u16 *>(A) : nullptr;
@@ -700,57 +757,37 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
         c = no_rows ? 0 : cmp[1];
         return MPR_OK;
     };
+    HostRecord host;  // two records of 8 words, powers in turn
+    if (!host.p) return MPR_ENOMEM;
+    // Power k into slot (k - 1) % M, its record on the way to the host.
+    auto enqueue = [&](int64_t k, int64_t M) -> mpr_status {
+        const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M;
+        u16 *Nk = slot_N(w, slot);
+        int64_t *Rk = slot_R(w, slot), *rec = host.p + 8 * (k & 1);
+        if (k == 1) return period_rows_launch(A, lda, Nk, w.ld, n, nullptr, Rk, true, w.acc, st, rec, k, s);
+        mpr_status e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
+                              : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
+        if (e == MPR_OK) e = period_rows_launch(Nk, w.ld, Nk, w.ld, n, slot_R(w, ps), Rk, false, w.acc, st, rec, k, s);
+        return e;
+    };
     if (pipeline) {
         // Power k + 1 is enqueued before the host waits for the class hash
-        // and trace of power k (copied to pinned memory, each with its
-        // event), so the round trip overlaps a power's work instead of
-        // following it.  Power k + 1 overwrites power k + 1 - M of the ring
-        // of M buffers, so a repeat of power j is confirmed while
+        // and trace of power k, so the round trip overlaps a power's work
+        // instead of following it.  Power k + 1 overwrites power k + 1 - M of
+        // the ring of M buffers, so a repeat of power j is confirmed while
         // k - j < M - 1: the workspace of `slots` holds M = slots + 1.
         const int64_t M = w.slots;
-        int64_t *pin = nullptr;  // two records of the 8 scalar words
-        hipEvent_t ev[2] = {nullptr, nullptr};
         auto finish = [&](mpr_status e) {
             if (hipStreamSynchronize(s) != hipSuccess && e == MPR_OK) e = MPR_EHIP;  // the power computed ahead
-            for (hipEvent_t x : ev)
-                if (x) (void)hipEventDestroy(x);
-            if (pin) (void)hipHostFree(pin);
             return e;
         };
-        if (hipHostMalloc((void **)&pin, 2 * 8 * sizeof(int64_t)) != hipSuccess) return MPR_ENOMEM;
-        if (hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) != hipSuccess)
-            return finish(MPR_EHIP);
-        auto enqueue = [&](int64_t k) -> mpr_status {
-            const int64_t slot = (k - 1) % M;
-            u16 *Nk = slot_N(w, slot);
-            int64_t *Rk = slot_R(w, slot);
-            mpr_status e;
-            if (k == 1) {
-                e = copy_launch(A, lda, Nk, w.ld, n, n, s);
-                if (e == MPR_OK) e = normalise_launch(n, n, Nk, w.ld, nullptr, nullptr, Rk, st, w.row_hash, s);
-            } else {
-                const int64_t ps = (k - 2) % M;
-                e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
-                           : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
-                if (e == MPR_OK)
-                    e = normalise_launch(n, n, Nk, w.ld, slot_R(w, ps), nullptr, Rk, st, w.row_hash, s);
-            }
-            if (e == MPR_OK) e = class_hash_launch(w.row_hash, Rk, n, (uint64_t *)&w.scal[0], s);
-            if (e == MPR_OK) e = trace_launch(Nk, n, w.ld, Rk, &w.scal[1], s);
-            if (e == MPR_OK && (hipMemcpyAsync(pin + 8 * (k & 1), w.scal, 8 * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                               s) != hipSuccess ||
-                                hipEventRecord(ev[k & 1], s) != hipSuccess))
-                e = MPR_EHIP;
-            return e;
-        };
-        if ((r = enqueue(1)) != MPR_OK) return finish(r);
+        if ((r = enqueue(1, M)) != MPR_OK) return finish(r);
         for (int64_t k = 1; k <= kmax; k++) {
-            if (k + 1 <= kmax && (r = enqueue(k + 1)) != MPR_OK) return finish(r);
-            if (hipEventSynchronize(ev[k & 1]) != hipSuccess) return finish(MPR_EHIP);
-            const volatile int64_t *rec = pin + 8 * (k & 1);
+            if (k + 1 <= kmax && (r = enqueue(k + 1, M)) != MPR_OK) return finish(r);
+            const int64_t *rec = host.p + 8 * (k & 1);
+            if ((r = host.wait(rec, k, s)) != MPR_OK) return finish(r);
             const int64_t hash = rec[0], trace = rec[1];
-            const int32_t stv = (int32_t)(rec[2] & 0xFFFFFFFF);
+            const int32_t stv = (int32_t)rec[2];
             if (stv != 0) return finish((mpr_status)stv);
             if (traces_host) traces_host[k] = trace;
             report_progress(k, trace);
@@ -793,26 +830,12 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
         const int64_t slot = (k - 1) % w.slots;
         u16 *Nk = slot_N(w, slot);
         int64_t *Rk = slot_R(w, slot);
-        if (k == 1) {
-            r = copy_launch(A, lda, Nk, w.ld, n, n, s);
-            if (r == MPR_OK) r = normalise_launch(n, n, Nk, w.ld, nullptr, nullptr, Rk, st, w.row_hash, s);
-        } else {
-            r = sparse ? sparse_step_launch(slot_N(w, prev_slot), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
-                       : product_launch(-1, n, n, n, slot_N(w, prev_slot), w.ld, A, lda, Nk, w.ld, s);
-            if (r == MPR_OK)
-                r = normalise_launch(n, n, Nk, w.ld, slot_R(w, prev_slot), nullptr, Rk, st, w.row_hash, s);
-        }
-        if (r == MPR_OK) r = class_hash_launch(w.row_hash, Rk, n, (uint64_t *)&w.scal[0], s);
-        if (r == MPR_OK) r = trace_launch(Nk, n, w.ld, Rk, &w.scal[1], s);
-        if (r != MPR_OK) return r;
-        int64_t host[3];
-        if (hipMemcpyAsync(host, w.scal, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return MPR_EHIP;
-        if ((int32_t)(host[2] & 0xFFFFFFFF) != 0) return (mpr_status)(int32_t)(host[2] & 0xFFFFFFFF);
-        if (traces_host) traces_host[k] = host[1];
-        report_progress(k, host[1]);
-        prev_slot = slot;
+        const int64_t *rec = host.p + 8 * (k & 1);
+        if ((r = enqueue(k, w.slots)) != MPR_OK || (r = host.wait(rec, k, s)) != MPR_OK) return r;
+        const int64_t hash = rec[0], trace = rec[1];
+        if ((int32_t)rec[2] != 0) return (mpr_status)(int32_t)rec[2];
+        if (traces_host) traces_host[k] = trace;
+        report_progress(k, trace);
         if (!found && held && k == held_k + held_lam) {
             // the power kept one period ago: the relation A^(k) = c (x)
             // A^(k - lam) confirmed exactly at n0 = k - lam
@@ -828,7 +851,7 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
             }
         }
         if (!found) {
-            const uint64_t h = (uint64_t)host[0];
+            const uint64_t h = (uint64_t)hash;
             auto range = seen.equal_range(h);
             for (auto it = range.first; it != range.second && !found; ++it) {
                 const int64_t j = it->second;

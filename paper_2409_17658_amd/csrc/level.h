@@ -689,6 +689,33 @@ struct LevelLds {
     static constexpr int CHUNKS = C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK;
 };
 
+// sparse.hip: the rows of a plan whose counts sparse_plan_rows left in ws.
+mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st, hipStream_t s);
+
+// period.hip: one pass over a power of a period search (canonical form to dst,
+// offsets, and into rec the class hash, trace, status and seq), and the
+// accumulator it folds into (cleared once; every pass leaves it clear).
+size_t period_acc_bytes();
+mpr_status period_clear_launch(void *acc, hipStream_t s);
+mpr_status period_rows_launch(const u16 *src, int64_t lds_, u16 *dst, int64_t ldd, int64_t n, const int64_t *R_in,
+                              int64_t *R_out, bool raw, void *acc, int32_t *st, int64_t *rec, int64_t seq, hipStream_t s);
+
+// abi.hip: 16 words of pinned host memory that a kernel writes records of 8
+// words to (the last one, word 7, when the others are in place), and the wait
+// for one.  A few stay allocated between calls (a pinned allocation and its
+// release take 50 us); taken and given back from any thread.
+struct HostRecord {
+    int64_t *p;
+    HostRecord();
+    ~HostRecord();
+    HostRecord(const HostRecord &) = delete;
+    HostRecord &operator=(const HostRecord &) = delete;
+    mpr_status wait(const int64_t *rec, int64_t seq, hipStream_t s);
+
+private:
+    bool failed = false;  // a kernel of a failed stream could still write here: not used again
+};
+
 inline bool level_strides(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 22); }
 int level_shape(int64_t M, int64_t N);
 

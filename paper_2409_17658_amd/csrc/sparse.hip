@@ -22,87 +22,128 @@ using SCfg = TileCfg<64, 64, 32, 4, 8>;  // 128 threads; 64-column blocks
 constexpr int SBN = SCfg::BN;
 constexpr int SBK = SCfg::BK;
 
-// Does row l of A have a finite entry in columns [j0, j0 + SBN)?
-__device__ __forceinline__ bool row_hits_block(const u16 *A, int64_t lda, int64_t l, int64_t j0, int64_t n, bool vec)
+// ------------------------------------------------ the plan
+// The lists take whole aligned groups of 8 rows (those below n) once one row
+// of the group has a finite entry in the block's columns: a transfer matrix's
+// rows hit a block in runs of about 80, so the groups add about a tenth, and
+// they make 8 consecutive entries of a list 8 consecutive rows.
+//
+// One workgroup of 16 waves per column block.  A wave reads a group's 8 rows
+// x 64 columns with one 16-byte load per lane (whole 128-byte lines, PU groups
+// in flight), so a pass reads A once, coalesced; one thread per row, each
+// walking its own line, took 0.57 ms to count and 1.80 ms to fill at m = 9
+// (0.10 and 0.50 at m = 8; TIMES).
+constexpr int PT = 1024;       // threads
+constexpr int PW = PT / 64;    // waves
+constexpr int PWIN = 8 * PT;   // groups per window (65536 rows)
+constexpr int PU = 4;
+
+// Lane (r, c) = (lane / 8, lane % 8): values 8 c .. 8 c + 7 of row 8 g + r in
+// columns [j0, j0 + SBN); infinite outside the matrix.
+__device__ __forceinline__ uint4 plan_load(const u16 *A, int64_t lda, int64_t n, int64_t g, int64_t j0, bool vec)
 {
-    const gu16 *row = glob(A) + l * lda;
-    for (int64_t j = j0; j < j0 + SBN && j < n; j += 8) {
-        if (vec && j + 8 <= n) {
-            const uint4 v = gload16(row + j);
-            if ((v.x & v.y & v.z & v.w) != 0xFFFFFFFFu) return true;
-        } else {
-            for (int64_t e = j; e < j + 8 && e < n; e++)
-                if (row[e] != 0xFFFF) return true;
-        }
-    }
-    return false;
+    const int lane = (int)(threadIdx.x & 63);
+    return load8(A, lda, g * 8 + (lane >> 3), j0 + (lane & 7) * 8, n, n, vec);
+}
+__device__ __forceinline__ bool plan_hit(const uint4 &v)
+{
+    return __ballot((v.x & v.y & v.z & v.w) != 0xFFFFFFFFu) != 0;
 }
 
-// The lists take whole aligned groups of 8 rows (those below n) once one row
-// of the group hits the block: a transfer matrix's rows hit a block in runs
-// of about 80, so the groups add about a tenth, and they make 8 consecutive
-// entries of a list 8 consecutive rows.  `ball`: the hits of 64 consecutive
-// rows, one bit per lane.
-__device__ __forceinline__ bool group_hit(uint64_t ball, int lane) { return (ball >> (lane & 56) & 0xFF) != 0; }
+// rows[g] = rows of group g0 + g in the list of column block j0 / SBN (0 when
+// none hits it), for the window's `groups` groups; ends with a barrier.
+__device__ __forceinline__ void plan_window(const u16 *A, int64_t lda, int64_t n, int64_t g0, int groups, int64_t j0,
+                                            bool vec, uint8_t *rows)
+{
+    const int w = (int)(threadIdx.x >> 6);
+    for (int g = w * PU; g < groups; g += PW * PU) {
+        uint4 v[PU];
+#pragma unroll
+        for (int u = 0; u < PU; u++) v[u] = plan_load(A, lda, n, g0 + g + u, j0, vec);  // past the end: infinite
+#pragma unroll
+        for (int u = 0; u < PU; u++) {
+            const bool hit = plan_hit(v[u]);
+            if ((threadIdx.x & 63) == 0 && g + u < groups)
+                rows[g + u] = hit ? (uint8_t)min<int64_t>(8, n - (g0 + g + u) * 8) : 0;
+        }
+    }
+    __syncthreads();
+}
+
+// Exclusive sum of v over the workgroup (and the total); ends with a barrier.
+__device__ __forceinline__ int plan_scan(int v, int *wsum, int &total)
+{
+    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
+    int x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(x, off, 64);
+        x += lane >= off ? y : 0;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int q = 0; q < PW; q++) {
+        before += q < w ? wsum[q] : 0;
+        total += wsum[q];
+    }
+    __syncthreads();
+    return before + x - v;
+}
 
 // counts[J] = |L_J| rounded up to a multiple of SBK.
-__global__ __launch_bounds__(256) void sp_count_kernel(const u16 *A, int64_t lda, int64_t n, int64_t *counts, int vec)
+__global__ __launch_bounds__(PT) void sp_count_kernel(const u16 *A, int64_t lda, int64_t n, int64_t *counts, int vec)
 {
-    __shared__ uint64_t sh[4];
-    const int64_t j0 = (int64_t)blockIdx.x * SBN;
-    uint64_t c = 0;
-    for (int64_t l0 = 0; l0 < n; l0 += 256) {
-        const int64_t l = l0 + threadIdx.x;
-        const uint64_t ball = __ballot(l < n && row_hits_block(A, lda, l, j0, n, vec != 0));
-        c += l < n && group_hit(ball, (int)(threadIdx.x & 63));
+    __shared__ uint8_t rows[PWIN];
+    __shared__ int wsum[PW];
+    const int64_t j0 = (int64_t)blockIdx.x * SBN, groups = (n + 7) / 8;
+    int64_t all = 0;
+    for (int64_t g0 = 0; g0 < groups; g0 += PWIN) {
+        const int cnt = (int)min<int64_t>(PWIN, groups - g0);
+        plan_window(A, lda, n, g0, cnt, j0, vec != 0, rows);
+        int c = 0, total;
+        for (int g = (int)threadIdx.x; g < cnt; g += PT) c += rows[g];
+        plan_scan(c, wsum, total);
+        all += total;
     }
-    c = wave_sum_u64(c);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint64_t t = sh[0] + sh[1] + sh[2] + sh[3];
-        counts[blockIdx.x] = (int64_t)((t + SBK - 1) / SBK * SBK);
-    }
+    if (threadIdx.x == 0) counts[blockIdx.x] = (all + SBK - 1) / SBK * SBK;
 }
 
-// off[J] = sum of counts before J; off[nblk] = total.  One block.
-__global__ __launch_bounds__(1024) void sp_scan_kernel(const int64_t *counts, int64_t nblk, int64_t *off)
+// off[J] = sum of counts before J, off[nblk] = total; order[r] = the column
+// block with the r-th largest |L_J| (ties by index): the tile and entry forms
+// launch the costliest blocks first so the launch does not end on a few long
+// blocks (|L_J| varies by 50x within one transfer matrix).  One block, the
+// counts in LDS when they fit; the total also goes to rec when given.
+constexpr int PCOUNTS = 8 * PT;
+__global__ __launch_bounds__(PT) void sp_scan_kernel(const int64_t *counts, int64_t nblk, int64_t *off, int32_t *order,
+                                                     int64_t *rec)
 {
-    __shared__ int64_t part[1024];
-    const int64_t per = (nblk + 1023) / 1024;
-    const int64_t b0 = threadIdx.x * per;
-    int64_t s = 0;
-    for (int64_t b = b0; b < b0 + per && b < nblk; b++) s += counts[b];
-    part[threadIdx.x] = s;
-    __syncthreads();
+    __shared__ int wsum[PW];
+    __shared__ int cs[PCOUNTS];
+    const bool fits = nblk <= PCOUNTS;
+    int64_t run = 0;
+    for (int64_t b0 = 0; b0 < nblk; b0 += PT) {
+        const int64_t b = b0 + threadIdx.x;
+        const int c = b < nblk ? (int)counts[b] : 0;  // at most n + SBK
+        if (fits && b < nblk) cs[b] = c;
+        int total;
+        const int before = plan_scan(c, wsum, total);
+        if (b < nblk) off[b] = run + before;
+        run += total;
+    }
     if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int t = 0; t < 1024; t++) {
-            const int64_t v = part[t];
-            part[t] = run;
-            run += v;
-        }
         off[nblk] = run;
+        if (rec) {
+            rec[0] = run;
+            __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
     __syncthreads();
-    int64_t run = part[threadIdx.x];
-    for (int64_t b = b0; b < b0 + per && b < nblk; b++) {
-        off[b] = run;
-        run += counts[b];
-    }
-}
-
-// order[r] = the column block with the r-th largest |L_J| (ties by index):
-// the step launches the costliest blocks first so the launch does not end
-// on a few long blocks (|L_J| varies by 50x within one transfer matrix).
-// One block.
-__global__ __launch_bounds__(1024) void sp_order_kernel(const int64_t *counts, int64_t nblk, int32_t *order)
-{
-    for (int64_t J = threadIdx.x; J < nblk; J += 1024) {
-        const int64_t c = counts[J];
+    for (int64_t J = threadIdx.x; J < nblk; J += PT) {
+        const int c = fits ? cs[J] : (int)counts[J];
         int64_t rank = 0;
         for (int64_t K = 0; K < nblk; K++) {
-            const int64_t d = counts[K];
+            const int d = fits ? cs[K] : (int)counts[K];
             rank += (d > c) || (d == c && K < J);
         }
         order[rank] = (int32_t)J;
@@ -113,46 +154,52 @@ __global__ __launch_bounds__(1024) void sp_order_kernel(const int64_t *counts, i
 // Bp[(off[J] + t) * SBN + c] = A[l][j0 + c]; padding rows are row 0 / infinite.
 // A plan whose rows (off[nblk]) exceed the capacity `cap` of its workspace
 // is not written: *st = MPR_ENOMEM, and the step kernel then does nothing.
-__global__ __launch_bounds__(256) void sp_fill_kernel(const u16 *A, int64_t lda, int64_t n, const int64_t *off,
-                                                      int64_t nblk, int64_t cap, int32_t *idx, u16 *Bp, int vec,
-                                                      int32_t *st)
+__global__ __launch_bounds__(PT) void sp_fill_kernel(const u16 *A, int64_t lda, int64_t n, const int64_t *off,
+                                                     int64_t nblk, int64_t cap, int32_t *idx, u16 *Bp, int vec,
+                                                     int32_t *st)
 {
-    __shared__ int wsum[4];
-    __shared__ int64_t run;
+    __shared__ uint8_t rows[PWIN];
+    __shared__ int pos[PWIN];
+    __shared__ int wsum[PW];
     if (off[nblk] > cap) {  // uniform over the grid
         if (blockIdx.x == 0 && threadIdx.x == 0) set_status(st, MPR_ENOMEM);
         return;
     }
-    const int64_t J = blockIdx.x, j0 = J * SBN;
-    const int64_t base = off[J], end = off[J + 1];
-    if (threadIdx.x == 0) run = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int64_t l0 = 0; l0 < n; l0 += 256) {
-        const int64_t l = l0 + threadIdx.x;
-        const bool hit = l < n && group_hit(__ballot(l < n && row_hits_block(A, lda, l, j0, n, vec != 0)), lane);
-        const uint64_t ball = __ballot(hit);
-        const int before = __popcll(ball & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[w] = __popcll(ball);
-        __syncthreads();
-        int pre = 0;
-        for (int q = 0; q < w; q++) pre += wsum[q];
-        const int64_t t = base + run + pre + before;
-        if (hit) {
-            idx[t] = (int32_t)l;
-            const gu16 *src = glob(A) + l * lda;
-            gu16 *dst = glob(Bp) + t * SBN;
-            for (int c = 0; c < SBN; c++) dst[c] = (j0 + c < n) ? src[j0 + c] : (u16)0xFFFF;
+    const int64_t J = blockIdx.x, j0 = J * SBN, base = off[J], end = off[J + 1], groups = (n + 7) / 8;
+    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
+    int64_t run = 0;
+    for (int64_t g0 = 0; g0 < groups; g0 += PWIN) {
+        const int cnt = (int)min<int64_t>(PWIN, groups - g0);
+        plan_window(A, lda, n, g0, cnt, j0, vec != 0, rows);
+        const int per = PWIN / PT, first = (int)threadIdx.x * per;
+        int mine = 0, total;
+        for (int g = first; g < first + per && g < cnt; g++) mine += rows[g];
+        int at = plan_scan(mine, wsum, total);
+        for (int g = first; g < first + per && g < cnt; g++) {
+            pos[g] = at;
+            at += rows[g];
         }
         __syncthreads();
-        if (threadIdx.x == 0) run += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        for (int g = w * PU; g < cnt; g += PW * PU) {
+            uint4 v[PU];
+#pragma unroll
+            for (int u = 0; u < PU; u++)
+                if (g + u < cnt && rows[g + u]) v[u] = plan_load(A, lda, n, g0 + g + u, j0, vec != 0);
+#pragma unroll
+            for (int u = 0; u < PU; u++)
+                if (g + u < cnt && (lane >> 3) < rows[g + u]) {
+                    const int64_t t = base + run + pos[g + u] + (lane >> 3);
+                    gstore16(glob(Bp) + t * SBN + (lane & 7) * 8, v[u]);
+                    if ((lane & 7) == 0) idx[t] = (int32_t)((g0 + g + u) * 8 + (lane >> 3));
+                }
+        }
+        run += total;
         __syncthreads();
     }
     // padding up to the multiple of SBK
-    for (int64_t t = base + run + threadIdx.x; t < end; t += 256) {
-        idx[t] = 0;
-        gu16 *dst = glob(Bp) + t * SBN;
-        for (int c = 0; c < SBN; c++) dst[c] = 0xFFFF;
+    for (int64_t e = (base + run) * 8 + threadIdx.x; e < end * 8; e += PT) {
+        gstore16(glob(Bp) + e * 8, make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu));
+        if (e % 8 == 0) idx[e / 8] = 0;
     }
 }
 
@@ -644,35 +691,44 @@ static SparsePlan carve_plan(void *ws, int64_t n, size_t bytes)
     return p;
 }
 
-// The counts and their prefix sums only (off[nblk] = the plan's rows).
-static void plan_count(const u16 *A, int64_t n, int64_t lda, const SparsePlan &p, hipStream_t s)
+// The counts, their prefix sums (off[nblk] = the plan's rows) and the order
+// of the blocks: the part of a plan that needs no room for rows.
+static void plan_count(const u16 *A, int64_t n, int64_t lda, const SparsePlan &p, int64_t *rec, hipStream_t s)
 {
     const int vec = aligned16(A) && lda % 8 == 0;
-    hipLaunchKernelGGL(sp_count_kernel, dim3((unsigned)p.nblk), dim3(256), 0, s, A, lda, n, p.counts, vec);
-    hipLaunchKernelGGL(sp_scan_kernel, dim3(1), dim3(1024), 0, s, (const int64_t *)p.counts, p.nblk, p.off);
+    hipLaunchKernelGGL(sp_count_kernel, dim3((unsigned)p.nblk), dim3(PT), 0, s, A, lda, n, p.counts, vec);
+    hipLaunchKernelGGL(sp_scan_kernel, dim3(1), dim3(PT), 0, s, (const int64_t *)p.counts, p.nblk, p.off,
+                       p.order, rec);
 }
 
 mpr_status sparse_plan_rows(const u16 *A, int64_t n, int64_t lda, void *ws, hipStream_t s, int64_t *rows)
 {
     SparsePlan p = carve_plan(ws, n, 0);
-    plan_count(A, n, lda, p, s);
-    if (check_launch() != MPR_OK) return MPR_EHIP;
-    if (hipMemcpyAsync(rows, p.off + p.nblk, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return MPR_EHIP;
-    return MPR_OK;
+    HostRecord rec;
+    if (!rec.p) return MPR_ENOMEM;
+    plan_count(A, n, lda, p, rec.p, s);
+    const mpr_status e = check_launch();
+    if (e != MPR_OK) return e;
+    const mpr_status w = rec.wait(rec.p, 1, s);
+    if (w == MPR_OK) *rows = rec.p[0];
+    return w;
+}
+
+mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st, hipStream_t s)
+{
+    SparsePlan p = carve_plan(ws, n, bytes);
+    const int vec = aligned16(A) && lda % 8 == 0;
+    hipLaunchKernelGGL(sp_fill_kernel, dim3((unsigned)p.nblk), dim3(PT), 0, s, A, lda, n, (const int64_t *)p.off,
+                       p.nblk, p.cap, p.idx, p.Bp, vec, st);
+    return check_launch();
 }
 
 mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st,
                               hipStream_t s)
 {
-    SparsePlan p = carve_plan(ws, n, bytes);
-    const int vec = aligned16(A) && lda % 8 == 0;
-    plan_count(A, n, lda, p, s);
-    hipLaunchKernelGGL(sp_order_kernel, dim3(1), dim3(1024), 0, s, (const int64_t *)p.counts, p.nblk, p.order);
-    hipLaunchKernelGGL(sp_fill_kernel, dim3((unsigned)p.nblk), dim3(256), 0, s, A, lda, n, (const int64_t *)p.off,
-                       p.nblk, p.cap, p.idx, p.Bp, vec, st);
-    return check_launch();
+    const SparsePlan p = carve_plan(ws, n, bytes);
+    plan_count(A, n, lda, p, nullptr, s);
+    return sparse_plan_fill(A, n, lda, ws, bytes, st, s);
 }
 
 static std::atomic<int> g_sparse_arith{MPR_ARITH_U16};  // process-wide, set from any thread

@@ -77,24 +77,86 @@ __host__ __device__ __forceinline__ uint32_t unrank(const WordTable &t, int64_t 
 __device__ __constant__ uint8_t kAlways[4] = {(1 << 0) | (1 << 2), (1 << 3), (1 << 0) | (1 << 1) | (1 << 3), (1 << 0)};
 __device__ __constant__ uint8_t kWithA[4] = {0, (1 << 2), (1 << 2), 0};
 
-__global__ __launch_bounds__(256) void transfer_kernel(WordTable t, int64_t n, u16 *A, int64_t lda)
+// The rule lists for all rows of a column at once.  blocked(p) has, for each
+// letter x of the previous column, the rows i where p_i may not follow
+// q_i = x (16 bits a letter); letters(q) has the rows where q_i = x.  p can
+// follow q when the two have no bit in common.
+__device__ __forceinline__ uint64_t letters(uint32_t w, int m)
 {
-    const int64_t q = blockIdx.x;
-    const uint32_t wq = unrank(t, q);
-    const int m = t.m;
-    for (int64_t p = threadIdx.x; p < n; p += blockDim.x) {
-        const uint32_t wp = unrank(t, p);
-        bool ok = true;
-        uint32_t weight = 0;
-        for (int i = 0; i < m; i++) {
-            const int qi = (wq >> (2 * i)) & 3, pi = (wp >> (2 * i)) & 3;
-            const bool a_up = i > 0 && ((wp >> (2 * (i - 1))) & 3) == 0;
-            const bool a_down = i + 1 < m && ((wp >> (2 * (i + 1))) & 3) == 0;
-            const uint32_t allowed = kAlways[qi] | ((a_up || a_down) ? kWithA[qi] : 0);
-            ok = ok && ((allowed >> pi) & 1u);
-            weight += pi == 0 ? 2u : (pi == 1 ? 1u : 0u);
+    uint64_t r = 0;
+    for (int i = 0; i < m; i++) r |= (uint64_t)(1u << i) << (16 * ((w >> (2 * i)) & 3u));
+    return r;
+}
+__device__ __forceinline__ uint64_t blocked(uint32_t w, int m)
+{
+    uint32_t is[4] = {0, 0, 0, 0};
+    for (int i = 0; i < m; i++) {
+        const uint32_t x = (w >> (2 * i)) & 3u;
+#pragma unroll
+        for (uint32_t y = 0; y < 4; y++) is[y] |= (x == y ? 1u : 0u) << i;
+    }
+    const uint32_t near_a = is[0] << 1 | is[0] >> 1, rows = (1u << m) - 1u;
+    uint64_t r = 0;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        uint32_t ok = 0;
+#pragma unroll
+        for (int y = 0; y < 4; y++) {
+            if (kAlways[q] >> y & 1u) ok |= is[y];
+            if (kWithA[q] >> y & 1u) ok |= is[y] & near_a;
         }
-        A[q * lda + p] = ok ? (u16)weight : (u16)0xFFFF;
+        r |= (uint64_t)(rows & ~ok) << (16 * q);
+    }
+    return r;
+}
+
+// A block writes TROWS rows of TCOLS columns, 8 columns per thread: each word
+// of its rows and columns is unranked once, into LDS; an entry is then two
+// ANDs and a compare, and the kernel is bound by its writes (one thread per
+// entry, unranking both words each time, took 10.2 ms at m = 9 and 1.10 ms at
+// m = 8; now TIMES).
+constexpr int TROWS = 64, TCOLS = 256 * 8;
+__global__ __launch_bounds__(256) void transfer_kernel(WordTable t, int64_t n, u16 *A, int64_t lda, int vec)
+{
+    __shared__ uint64_t q_letters[TROWS], p_blocked[TCOLS];
+    __shared__ uint8_t p_weight[TCOLS];
+    const int64_t q0 = (int64_t)blockIdx.y * TROWS, c0 = (int64_t)blockIdx.x * TCOLS;
+    const int rows = (int)min<int64_t>(TROWS, n - q0), cols = (int)min<int64_t>(TCOLS, n - c0);
+    for (int r = (int)threadIdx.x; r < rows; r += 256) q_letters[r] = letters(unrank(t, q0 + r), t.m);
+    for (int c = (int)threadIdx.x; c < cols; c += 256) {
+        const uint32_t w = unrank(t, c0 + c);
+        uint32_t weight = 0;
+        for (int i = 0; i < t.m; i++) {
+            const uint32_t x = (w >> (2 * i)) & 3u;
+            weight += x == 0 ? 2u : x == 1 ? 1u : 0u;
+        }
+        p_blocked[c] = blocked(w, t.m);
+        p_weight[c] = (uint8_t)weight;
+    }
+    __syncthreads();
+    const int p0 = (int)threadIdx.x * 8;
+    if (p0 >= cols) return;
+    uint64_t block[8];
+    uint32_t weight[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const int c = p0 + e < cols ? p0 + e : p0;
+        block[e] = p_blocked[c];
+        weight[e] = p_weight[c];
+    }
+    gu16 *out = glob(A) + q0 * lda + c0 + p0;
+    for (int r = 0; r < rows; r++, out += lda) {
+        const uint64_t q = q_letters[r];
+        uint32_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) v[e] = (q & block[e]) == 0 ? weight[e] : 0xFFFFu;
+        if (vec && p0 + 8 <= cols) {
+            gstore16(out, make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                if (p0 + e < cols) out[e] = (u16)v[e];
+        }
     }
 }
 
@@ -153,7 +215,8 @@ mpr_status transfer_launch(int m, u16 *A, int64_t lda, hipStream_t s)
     make_table(m, t);
     const int64_t n = word_count(t);
     if (lda < n) return MPR_EINVAL;
-    hipLaunchKernelGGL(transfer_kernel, dim3((unsigned)n), dim3(256), 0, s, t, n, A, lda);
+    hipLaunchKernelGGL(transfer_kernel, dim3((unsigned)((n + TCOLS - 1) / TCOLS), (unsigned)((n + TROWS - 1) / TROWS)),
+                       dim3(256), 0, s, t, n, A, lda, aligned16(A) && lda % 8 == 0 ? 1 : 0);
     return check_launch();
 }
 
