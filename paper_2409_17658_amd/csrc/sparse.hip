@@ -506,9 +506,12 @@ __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void s
 // The tile product on the matrix cores (level.h).  The lists L_J hold whole
 // aligned groups of 8 rows, so 8 consecutive k are 8 consecutive columns of
 // N: one 16-byte load, as in a plain product.  Each XCD takes a contiguous
-// run of the tiles in row-panel order: the column blocks of one panel run
-// together and their 128 rows of N (1.9 MB at m = 8) stay in that XCD's L2,
-// where every block reads its |L_J| columns of them.
+// run of the tiles, two row panels at a time, both panels of a column block in
+// turn: neighbouring column blocks read overlapping columns of the panels
+// from that XCD's L2 and each block's entries serve both (us a step with 1 /
+// 2 / 4 / 8 panels together, normalisation included: m = 8 295 / 265 / 267 /
+// 278, m = 9 3594 / 3532 / 3857 / 4323).  At m = 9 the panels (5.6 MB each) do
+// not fit: 20 GB a step miss L2, 5.7 TB/s, which is the bound there.
 using PCfg = LevelCfg<4, 2, 2, 2>;  // 256 threads, 128 x 64
 using PBack = TileCfg<128, 64, 32, 4, 8>;
 static_assert(PCfg::BM == PBack::BM && PCfg::BN == SBN && PBack::BN == SBN && PCfg::NT == PBack::NT, "stand-in tile");
@@ -602,9 +605,11 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     const int nb = (int)gridDim.x;  // a multiple of 8
     const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
     if (t >= tiles_m * nblk) return;
-    const int64_t m0 = (int64_t)(t / nblk) * C::BM, j0 = (int64_t)(t % nblk) * SBN;
+    const int first = t / (2 * nblk) * 2, gs = min(tiles_m - first, 2), w = t - first * nblk;
+    const int64_t m0 = (int64_t)(first + w % gs) * C::BM, j0 = (int64_t)(w / gs) * SBN;
+    const int J = w / gs;
     const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
-    const int64_t kbeg = off[t % nblk], K = off[nblk] > cap ? 0 : off[t % nblk + 1] - kbeg;
+    const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;
     gu16 *out = glob(Cm) + m0 * ldc + j0;
     if (K == 0) {  // no finite entry in these columns, or a plan that did not fit: infinite
         for (int e = (int)threadIdx.x; e < rows * SBN; e += C::NT)
