@@ -153,6 +153,16 @@ mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K,
                             uint16_t *C, int64_t ldc,
                             int32_t *d_status, mpr_stream stream);
 
+/* The product of mpr_minplus_gemm_cfg (spare = 0) or mpr_minplus_gemm_spare
+ * (spare != 0) with its inputs checked and the verdict given to the host:
+ * *status_host = 0, or MPR_EOVERFLOW when a finite input exceeds MPR_FMAX.
+ * Waits for the check only (the product may still run when the call
+ * returns); allocates no device memory.  Not for captured streams. */
+mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, int64_t N, int64_t K,
+                                    const uint16_t *A, int64_t lda,
+                                    const uint16_t *B, int64_t ldb,
+                                    uint16_t *C, int64_t ldc,
+                                    int32_t *status_host, mpr_stream stream);
 /* Same with an explicit tile configuration (0 <= cfg < mpr_gemm_config_count);
  * used by the autotuner.  cfg = -1 picks as mpr_minplus_gemm does. */
 mpr_status mpr_minplus_gemm_cfg(int cfg, int64_t M, int64_t N, int64_t K,

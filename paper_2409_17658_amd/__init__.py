@@ -89,6 +89,7 @@ _SIGS = {
     "mpr_minplus_gemm": (_I, [_I64, _I64, _I64, _P, _I64, _P, _I64, _P, _I64, _P, _P]),
     "mpr_minplus_gemm_spare": (_I, [_I, _I64, _I64, _I64, _P, _I64, _P, _I64, _P, _I64, _P, _P]),
     "mpr_minplus_gemm_cfg": (_I, [_I, _I64, _I64, _I64, _P, _I64, _P, _I64, _P, _I64, _P, _P]),
+    "mpr_minplus_gemm_checked": (_I, [_I, _I, _I64, _I64, _I64, _P, _I64, _P, _I64, _P, _I64, _P, _P]),
     "mpr_normalise": (_I, [_I64, _I64, _P, _I64, _P, _P, _P, _P]),
     "mpr_gemm_norm_workspace_size": (_I, [_I64, _I64, _P]),
     "mpr_minplus_gemm_norm": (_I, [_I64, _I64, _I64, _P, _I64, _P, _P, _I64, _P, _P, _I64, _P,
@@ -295,12 +296,16 @@ def minplus_gemm(A, B, C=None, check=True, cfg=-1, stream=None, d_status=None, s
         raise ValueError("inner dimensions differ")
     if C is None:
         C = alloc_matrix(M, N, A.device)
-    st = d_status if d_status is not None else (_status_tensor(A.device) if check else None)
-    fn = lib().mpr_minplus_gemm_spare if spare else lib().mpr_minplus_gemm_cfg
-    _ok(fn(cfg, M, N, K, _ptr(A), _ld(A), _ptr(B), _ld(B), _ptr(C), _ld(C), _ptr(st), _stream(stream)),
-        "mpr_minplus_gemm")
     if check and d_status is None:
-        check_status(st)
+        st = ctypes.c_int32()
+        _ok(lib().mpr_minplus_gemm_checked(cfg, 1 if spare else 0, M, N, K, _ptr(A), _ld(A), _ptr(B), _ld(B), _ptr(C),
+                                           _ld(C), ctypes.byref(st), _stream(stream)), "mpr_minplus_gemm")
+        if st.value != 0:
+            raise MprError(st.value, "device status")
+        return C
+    fn = lib().mpr_minplus_gemm_spare if spare else lib().mpr_minplus_gemm_cfg
+    _ok(fn(cfg, M, N, K, _ptr(A), _ld(A), _ptr(B), _ld(B), _ptr(C), _ld(C), _ptr(d_status), _stream(stream)),
+        "mpr_minplus_gemm")
     return C
 
 

@@ -480,6 +480,14 @@ static mpr_status gemm_args(int64_t M, int64_t N, int64_t K, const void *A, int6
     return MPR_OK;
 }
 
+mpr_status mpr::mpr_gemm_args(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                              int64_t ldb, const u16 *C, int64_t ldc)
+{
+    const mpr_status e = gemm_args(M, N, K, A, lda, B, ldb, C, ldc);
+    if (e != MPR_OK) return e;
+    return cfg < -1 || cfg >= mpr_gemm_config_count() ? MPR_EINVAL : MPR_OK;
+}
+
 extern "C" mpr_status mpr_minplus_gemm_cfg(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t *A, int64_t lda,
                                            const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc,
                                            int32_t *d_status, mpr_stream stream)

@@ -716,6 +716,10 @@ private:
     bool failed = false;  // a kernel of a failed stream could still write here: not used again
 };
 
+// abi.hip: the argument checks of a product.
+mpr_status mpr_gemm_args(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B, int64_t ldb,
+                         const u16 *C, int64_t ldc);
+
 inline bool level_strides(int64_t lda, int64_t ldb) { return lda < (1 << 22) && ldb < (1 << 22); }
 int level_shape(int64_t M, int64_t N);
 

@@ -88,9 +88,52 @@ static bool level_product(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t 
     return M > 0 && K >= 128 && N >= 4 && level_strides(lda, ldb);
 }
 
+// Tiny products: one row and two columns per thread, no LDS, 8 k in flight.
+// The smallest VALU tile (64 x 64, staged through LDS) takes 9.2 us at 33 x 33
+// x 33, nearly all of it latency of its first instructions, loads and
+// barriers; this takes TINY.
+__global__ __launch_bounds__(256) void tiny_product_kernel(const u16 *__restrict__ A, int64_t lda,
+                                                           const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ Cm,
+                                                           int64_t ldc, int M, int N, int K)
+{
+    const int pairs = (N + 1) / 2, t = (int)(blockIdx.x * 256 + threadIdx.x), i = t / pairs, j = t % pairs * 2;
+    if (i >= M) return;
+    const gu16 *a = glob(A) + i * lda, *b = glob(B) + j;
+    const int second = j + 1 < N ? 1 : 0;
+    u16x2 m = {0xFFFF, 0xFFFF};
+    int k = 0;
+    for (; k + 8 <= K; k += 8) {
+        u16 x[8];
+        u16x2 y[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            x[q] = a[k + q];
+            const gu16 *p = b + (int64_t)(k + q) * ldb;
+            y[q] = (u16x2){p[0], p[second]};
+        }
+#pragma unroll
+        for (int q = 0; q < 8; q++) m = min2(m, add_sat((u16x2){x[q], x[q]}, y[q]));
+    }
+    for (; k < K; k++) {
+        const gu16 *p = b + (int64_t)k * ldb;
+        m = min2(m, add_sat((u16x2){a[k], a[k]}, (u16x2){p[0], p[second]}));
+    }
+    gu16 *c = glob(Cm) + i * ldc + j;
+    c[0] = m.x;
+    if (second) c[1] = m.y;
+}
+// Up to so many outputs (K < 128: the level form takes the others).
+constexpr int64_t TINY_OUTPUTS = 1 << 14;
+
 mpr_status product_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                           int64_t ldb, u16 *Cm, int64_t ldc, hipStream_t s)
 {
+    if (cfg < 0 && M > 0 && N > 0 && K > 0 && K < 128 && M * N <= TINY_OUTPUTS) {
+        const unsigned blocks = (unsigned)((M * ((N + 1) / 2) + 255) / 256);
+        hipLaunchKernelGGL(tiny_product_kernel, dim3(blocks), dim3(256), 0, s, A, lda, B, ldb, Cm, ldc, (int)M, (int)N,
+                           (int)K);
+        return check_launch();
+    }
     if (cfg >= 0 || !level_product(M, N, K, lda, ldb)) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, Cm, ldc, s);
     switch (level_shape(M, N)) {
     case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, 0);
@@ -158,6 +201,80 @@ mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStre
 }
 
 }  // namespace mpr
+
+namespace mpr {
+
+// Flags a finite entry above MPR_FMAX of A or B in rec[0] (host memory).  One
+// block also ends the record; more blocks leave that to check_end_kernel.
+__global__ __launch_bounds__(1024) void check_kernel(const u16 *A, int64_t rows_a, int64_t cols_a, int64_t lda,
+                                                     const u16 *B, int64_t rows_b, int64_t cols_b, int64_t ldb,
+                                                     int64_t *rec)
+{
+    const int64_t step = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    bool over = false;
+    auto look = [&](const u16 *X, int64_t rows, int64_t cols, int64_t ld) {
+        const int64_t per = (cols + 7) / 8, total = rows * per;
+        for (int64_t t = t0; t < total; t += step) {
+            const uint4 v = load8(X, ld, t / per, t % per * 8, rows, cols, ((uintptr_t)X & 15u) == 0 && ld % 8 == 0);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint32_t x = comp(v, e), lo = x & 0xFFFFu, hi = x >> 16;
+                over |= (lo > FMAX16 && lo != 0xFFFFu) || (hi > FMAX16 && hi != 0xFFFFu);
+            }
+        }
+    };
+    look(A, rows_a, cols_a, lda);
+    look(B, rows_b, cols_b, ldb);
+    const bool any = __syncthreads_or(over);
+    if (threadIdx.x != 0) return;
+    if (any) __hip_atomic_store(&rec[0], (int64_t)MPR_EOVERFLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (gridDim.x == 1) __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ void check_end_kernel(int64_t *rec)
+{
+    __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+}  // namespace mpr
+
+using namespace mpr;
+
+// The product with its inputs checked and the verdict on the host: the
+// product is launched behind the check, which the host waits for in a pinned
+// record (a device status word, two checks, a copy back and a
+// synchronisation cost 43 us at 33 x 33 x 33 through the binding, this HOST33).
+extern "C" mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, int64_t N, int64_t K, const uint16_t *A,
+                                               int64_t lda, const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc,
+                                               int32_t *status_host, mpr_stream stream)
+{
+    if (!status_host) return MPR_EINVAL;
+    *status_host = 0;
+    auto product = [&] {
+        return spare ? mpr_minplus_gemm_spare(cfg, M, N, K, A, lda, B, ldb, C, ldc, nullptr, stream)
+                     : mpr_minplus_gemm_cfg(cfg, M, N, K, A, lda, B, ldb, C, ldc, nullptr, stream);
+    };
+    mpr_status e = mpr_gemm_args(cfg, M, N, K, A, lda, B, ldb, C, ldc);
+    if (e != MPR_OK) return e;
+    if ((e = ensure_init()) != MPR_OK) return e;
+    const int64_t values = M * K + K * N;
+    if (values == 0) return product();
+    HostRecord rec;
+    if (!rec.p) return MPR_ENOMEM;
+    rec.p[0] = 0;
+    hipStream_t s = as_stream(stream);
+    const unsigned blocks = (unsigned)std::min<int64_t>(values / (8 * 8192) + 1, 2048);
+    hipLaunchKernelGGL(check_kernel, dim3(blocks), dim3(1024), 0, s, A, M, K, lda, B, K, N, ldb, rec.p);
+    if (blocks > 1) hipLaunchKernelGGL(check_end_kernel, dim3(1), dim3(1), 0, s, rec.p);
+    if ((e = check_launch()) != MPR_OK) {
+        (void)hipStreamSynchronize(s);  // nothing writes the record any more
+        return e;
+    }
+    e = product();
+    const mpr_status w = rec.wait(rec.p, 1, s);
+    if (e == MPR_OK) e = w;
+    if (w == MPR_OK) *status_host = (int32_t)rec.p[0];
+    return e;
+}
 
 #ifdef LV_PROBE
 extern "C" int mpr_level_probe(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t *A, int64_t lda,

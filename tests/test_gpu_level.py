@@ -135,3 +135,25 @@ def test_level_sparse_steps(mpr, n):
         N, R = mpr.minplus_power(A, e, mpr.CHAIN_SPARSE, N_out=N, ws=ws)
         Nr, Rr = O.power_chain(O.from_u16(X), e)
         assert np.array_equal(N.cpu().numpy(), O.to_u16(Nr)) and np.array_equal(R.cpu().numpy(), Rr)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 2, 7), (33, 33, 33), (127, 129, 127), (128, 128, 8), (129, 127, 9),
+                                   (700, 900, 100)])
+def test_small_products_and_their_check(mpr, shape):
+    """The default product below the level form's sizes (tiny outputs, one
+    thread per two columns, and the next size up), checked on the way: inputs
+    at MPR_FMAX pass, one entry above it in either operand is refused."""
+    M, N, K = shape
+    for law in ((0, 40, 0.35), (0x7FF0, 0x7FFF, 0.2)):
+        print("small product", shape, law, flush=True)
+        X, Y = _law(M, K, 5, law), _law(K, N, 6, law)
+        ref = O.to_u16(O.minplus(O.from_u16(X), O.from_u16(Y)))
+        for A, B in ((mpr.to_device(X), mpr.to_device(Y)), (torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda())):
+            assert np.array_equal(mpr.minplus_gemm(A, B).cpu().numpy(), ref)
+            for bad in (A, B):
+                keep = bad[-1, -1].item()
+                bad[-1, -1] = 0x8000
+                with pytest.raises(mpr.MprError) as e:
+                    mpr.minplus_gemm(A, B)
+                assert e.value.status == 3
+                bad[-1, -1] = keep
