@@ -200,7 +200,7 @@ struct PowerWs {
     void *plan;         // compressed-K plan of A (MPR_CHAIN_SPARSE)
     size_t plan_bytes;  // its share of the workspace
     bool plan_full;     // sized for the worst case (any A fits)
-    uint32_t *low;      // MPR_CHAIN: row minima and maxima of steps normalised late, if there is room
+    uint32_t *low;      // chains: row minima and maxima of steps normalised late, if there is room
     int64_t ld;
     size_t bytes;       // needed (without the optional minima)
 };
@@ -232,9 +232,18 @@ static PowerWs carve_power(void *ws, int64_t n, int schedule, size_t ws_bytes = 
     }
     if (schedule == MPR_CHAIN_SPARSE) {
         const size_t at = (size_t)round_up((int64_t)c.used, 256), worst = sparse_plan_bytes(n);
-        w.plan_bytes = (ws_bytes > at + 256 && ws_bytes - at - 256 < worst) ? ws_bytes - at - 256 : worst;
+        const size_t given = ws_bytes > at + 256 ? ws_bytes - at - 256 : 0, low = level_chain_bytes(n);
+        w.plan_bytes = given && given < worst ? given : worst;
+        // the row minima of steps normalised late: past a plan of the worst
+        // case, or the part that mpr_sparse_plan_bytes adds for them
+        const bool room = n >= 8 && (given >= worst + low || (given < worst && given >= sparse_plan_bytes_rows(n, 32) + low));
+        if (room && given < worst) w.plan_bytes = given - low;
         w.plan_full = w.plan_bytes == worst;
         w.plan = c.take<char>(w.plan_bytes);
+        if (room) {
+            w.low = (uint32_t *)((char *)ws + round_up((int64_t)c.used, 256));
+            if (!ws) w.low = nullptr;
+        }
     }
     w.bytes = c.used + 256;
     if (schedule == MPR_CHAIN && level_chain(n) && ws_bytes >= w.bytes + level_chain_bytes(n)) w.low = c.take<uint32_t>(6 * (size_t)n);
@@ -278,15 +287,16 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
         if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], nullptr, nullptr, R_out, st, nullptr, s);
     }
     if (r == MPR_OK && sparse && e >= 2) r = sparse_plan_launch(A, n, lda, w.plan, w.plan_bytes, st, s);
-    if (r == MPR_OK && w.low && !sparse && e >= 2 && level_strides(lda, ldo)) {
+    if (r == MPR_OK && w.low && e >= 2 &&
+        (sparse ? sparse_step_late(n, w.ld, ldo) : level_strides(lda, ldo) && level_strides(w.ld, ldo))) {
         uint32_t *low = w.low, *big = w.low + 3 * n;
         r = level_prepare_launch(low, big, n, s);
         for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
             const int nb = b ^ 1;
             const int64_t in = (k - 2) % 3 * n, out = (k - 1) % 3 * n, next = k % 3 * n;
-            r = level_step_launch(LevelStep{buf[b], A, buf[nb], ld[b], lda, ld[nb], n, R_out, low + in, big + in,
-                                            low + out, big + out, low + next, big + next},
-                                  st, s);
+            const LevelStep p{buf[b], A, buf[nb], ld[b], lda, ld[nb], n, R_out, low + in, big + in, low + out,
+                              big + out, low + next, big + next};
+            r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, st, s) : level_step_launch(p, st, s);
             b = nb;
         }
         if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, nullptr, s);
@@ -651,7 +661,7 @@ extern "C" mpr_status mpr_sparse_plan_bytes(const uint16_t *A, int64_t n, int64_
     int64_t rows = 0;
     r = sparse_plan_rows(A, n, lda, tmp, s, &rows);
     if (hipFreeAsync(tmp, s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
-    if (r == MPR_OK) *bytes_host = sparse_plan_bytes_rows(n, rows);
+    if (r == MPR_OK) *bytes_host = sparse_plan_bytes_rows(n, rows) + (n >= 8 ? level_chain_bytes(n) : 0);
     return r;
 }
 

@@ -596,53 +596,40 @@ __device__ __forceinline__ void level_row_low(const LevelAcc<C> &acc, int rows, 
     }
 }
 
-// The block of rows m0.. and columns n0.. of a step; T is the VALU tile of
-// the same shape and threads for blocks whose values leave the level range.
-template <class C, class T>
-__device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0, int64_t n0, uint4 *lds, int32_t *st)
+// The rows' bookkeeping, by the block of column 0: the offsets they lost to
+// the previous step move into R, and the buffers of the step after are
+// cleared.  Returns (to every thread) whether an offset of the block's rows
+// passes 0x7FFF: no room above the levels for infinity then.
+template <class C>
+__device__ __forceinline__ bool level_step_rows(const LevelStep &p, int64_t m0, int rows, bool first, int32_t *st)
 {
-    const int rows = (int)min<int64_t>(C::BM, p.n - m0), cols = (int)min<int64_t>(C::BN, p.n - n0);
-    bool far = false;  // offsets past 0x7FFF: no room above the levels for infinity
+    bool far = false;
     for (int r = threadIdx.x; r < rows; r += C::NT) {
         const int64_t i = m0 + r;
         const uint32_t l = p.low_in[i];
         far |= l > FMAX16 && l != LOW_NONE;
-        if (n0 == 0) {  // the rows' bookkeeping, once
+        if (first) {
             p.low_next[i] = LOW_NONE;
             p.big_next[i] = 0;
             p.R[i] = (l == LOW_NONE || p.R[i] == ROW_NONE) ? ROW_NONE : p.R[i] + (int64_t)l;
             if (l != LOW_NONE && p.big_in[i] > l + FMAX16) set_status(st, MPR_EOVERFLOW);
         }
     }
-    if (!__syncthreads_or(far)) {
-        LevelA<C, true> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, p.n, p.low_in + m0);
-        LevelB<C> bop(glob(p.A) + n0, p.lda, cols, p.n);
-        LevelAcc<C> acc;
-        level_kloop<C>(p.n, aop, bop, lds, acc);
-        if (level_sure<C>(acc, rows, cols) || level_clean<C>(p.n, aop, bop, lds)) {
-            level_row_low<C>(acc, rows, cols, p.low_out + m0);
-            level_store<C>(glob(p.O) + m0 * p.ldo + n0, p.ldo, rows, cols, acc);
-            return;
-        }
-    }
-    const bool vec = (uintptr_t)p.L % 16 == 0 && (uintptr_t)p.A % 16 == 0 && (uintptr_t)p.O % 16 == 0 &&
-                     p.ldl % 8 == 0 && p.lda % 8 == 0 && p.ldo % 8 == 0;
-    TileAcc<T> acc;
-    tile_mainloop_with<T, true>(
-        (p.n + T::BK - 1) / T::BK,
-        [&](int64_t k0, int row, int kc) {
-            const uint4 v = load8(p.L, p.ldl, m0 + row, k0 + kc, p.n, p.n, vec);
-            const uint32_t l = row < rows ? p.low_in[m0 + row] : 0;
-            uint32_t w[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const uint32_t lo = comp(v, q) & 0xFFFFu, hi = comp(v, q) >> 16;
-                w[q] = (lo == 0xFFFFu ? lo : lo - l) | (hi == 0xFFFFu ? hi : hi - l) << 16;
-            }
-            return make_uint4(w[0], w[1], w[2], w[3]);
-        },
-        [&](int64_t k0, int kr, int jc) { return load8(p.A, p.lda, k0 + kr, n0 + jc, p.n, p.n, vec); }, (u16 *)lds,
-        acc);
+    return __syncthreads_or(far);
+}
+
+// Takes the offset l off the halves of x; infinity stays.
+__device__ __forceinline__ uint32_t take_low(uint32_t x, uint32_t l)
+{
+    const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
+    return (lo == 0xFFFFu ? lo : lo - l) | (hi == 0xFFFFu ? hi : hi - l) << 16;
+}
+
+// A block that the VALU tile computed: its results, row minima and maxima.
+template <class T>
+__device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, int64_t n0, int rows, bool vec,
+                                                const TileAcc<T> &acc)
+{
     tile_store<T>(p.O, p.ldo, p.n, p.n, m0, n0, vec, acc);
 #pragma unroll
     for (int r = 0; r < T::TM; r++) {
@@ -665,6 +652,38 @@ __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0,
             atomicMax(&p.big_out[m0 + row], x - 1);
         }
     }
+}
+
+// The block of rows m0.. and columns n0.. of a step; T is the VALU tile of
+// the same shape and threads for blocks whose values leave the level range.
+template <class C, class T>
+__device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0, int64_t n0, uint4 *lds, int32_t *st)
+{
+    const int rows = (int)min<int64_t>(C::BM, p.n - m0), cols = (int)min<int64_t>(C::BN, p.n - n0);
+    if (!level_step_rows<C>(p, m0, rows, n0 == 0, st)) {
+        LevelA<C, true> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, p.n, p.low_in + m0);
+        LevelB<C> bop(glob(p.A) + n0, p.lda, cols, p.n);
+        LevelAcc<C> acc;
+        level_kloop<C>(p.n, aop, bop, lds, acc);
+        if (level_sure<C>(acc, rows, cols) || level_clean<C>(p.n, aop, bop, lds)) {
+            level_row_low<C>(acc, rows, cols, p.low_out + m0);
+            level_store<C>(glob(p.O) + m0 * p.ldo + n0, p.ldo, rows, cols, acc);
+            return;
+        }
+    }
+    const bool vec = (uintptr_t)p.L % 16 == 0 && (uintptr_t)p.A % 16 == 0 && (uintptr_t)p.O % 16 == 0 &&
+                     p.ldl % 8 == 0 && p.lda % 8 == 0 && p.ldo % 8 == 0;
+    TileAcc<T> acc;
+    tile_mainloop_with<T, true>(
+        (p.n + T::BK - 1) / T::BK,
+        [&](int64_t k0, int row, int kc) {
+            const uint4 v = load8(p.L, p.ldl, m0 + row, k0 + kc, p.n, p.n, vec);
+            const uint32_t l = row < rows ? p.low_in[m0 + row] : 0;
+            return make_uint4(take_low(v.x, l), take_low(v.y, l), take_low(v.z, l), take_low(v.w, l));
+        },
+        [&](int64_t k0, int kr, int jc) { return load8(p.A, p.lda, k0 + kr, n0 + jc, p.n, p.n, vec); }, (u16 *)lds,
+        acc);
+    level_step_back<T>(p, m0, n0, rows, vec, acc);
 }
 
 // Block shapes of the products and steps, each with the VALU tile that
@@ -715,6 +734,10 @@ struct HostRecord {
 private:
     bool failed = false;  // a kernel of a failed stream could still write here: not used again
 };
+
+// The compressed-K step (sparse.hip) in the same way; p.A is not read.
+bool sparse_step_late(int64_t n, int64_t ldl, int64_t ldo);  // whether it applies
+mpr_status sparse_step_late_launch(const LevelStep &p, void *ws, size_t bytes, int32_t *st, hipStream_t s);
 
 // abi.hip: the argument checks of a product.
 mpr_status mpr_gemm_args(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B, int64_t ldb,

@@ -225,6 +225,7 @@ struct GatherA {
     int64_t ldn, n, m0;
     const __attribute__((address_space(1))) int32_t *idx;
     bool full;  // all BM rows of the block are < n (block-uniform)
+    const uint32_t *low;  // offsets to take off the rows from m0 on, or null
     uint32_t v[PER];
     __device__ __forceinline__ void load(int64_t k0)
     {
@@ -233,12 +234,17 @@ struct GatherA {
         if (full) {
 #pragma unroll
             for (int e = 0; e < PER; e++) v[e] = N[(m0 + r0 + e * RSTEP) * ldn + col];
-            return;
-        }
+        } else {
 #pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const int64_t r = m0 + r0 + e * RSTEP;
-            v[e] = r < n ? (uint32_t)N[r * ldn + col] : 0xFFFFu;
+            for (int e = 0; e < PER; e++) {
+                const int64_t r = m0 + r0 + e * RSTEP;
+                v[e] = r < n ? (uint32_t)N[r * ldn + col] : 0xFFFFu;
+            }
+        }
+        if (low) {
+#pragma unroll
+            for (int e = 0; e < PER; e++)
+                if (v[e] != 0xFFFFu) v[e] -= low[r0 + e * RSTEP];
         }
     }
     template <bool H>
@@ -285,7 +291,7 @@ __global__ __launch_bounds__(SCfg::NT) __attribute__((amdgpu_waves_per_eu(4))) v
     const __attribute__((address_space(1))) int32_t *gi = glob(idx) + kbeg;
     const gu16 *gB = glob(Bp) + kbeg * SBN;
     TileAcc<SCfg> acc;
-    GatherA<SCfg> aop{gN, ldn, n, m0, gi, m0 + SCfg::BM <= n, {}};
+    GatherA<SCfg> aop{gN, ldn, n, m0, gi, m0 + SCfg::BM <= n, nullptr, {}};
     auto bop = chunk_b<SCfg>([&](int64_t k0, int kr, int jc) { return gload16(gB + (k0 + kr) * SBN + jc); });
     tile_product<SCfg, H>(K / SBK, aop, bop, lds, acc);
     tile_store<SCfg>(C, ldc, n, n, m0, n0, vec != 0, acc);
@@ -516,8 +522,8 @@ using PCfg = LevelCfg<4, 2, 2, 2>;  // 256 threads, 128 x 64
 using PBack = TileCfg<128, 64, 32, 4, 8>;
 static_assert(PCfg::BM == PBack::BM && PCfg::BN == SBN && PBack::BN == SBN && PCfg::NT == PBack::NT, "stand-in tile");
 
-// Staging of N[m0 .., L_J]: LevelA with the k groups of the list.
-template <class C>
+// Staging of N[m0 .., L_J]: LevelA with the k groups of the list (SUB as there).
+template <class C, bool SUB = false>
 struct LevelGather {
     gbytes *base;
     const __attribute__((address_space(1))) int32_t *idx, *at;
@@ -525,14 +531,26 @@ struct LevelGather {
     uint32_t off[C::A_CPT];
     int col;   // first column of the thread's k group in the slice that load() takes
     int back;  // columns to step back from there to stay in the row (slice 0 only)
+    uint32_t low2[SUB ? C::A_CPT : 1];
     uint4 r[C::A_CPT];
     __device__ __forceinline__ LevelGather(const gu16 *p, int64_t ld, int rows, int64_t n_, const int32_t *list,
-                                           int64_t K_)
+                                           int64_t K_, const uint32_t *low = nullptr)
         : base((gbytes *)p), idx(glob(list) + C::tid() % C::KC * 8), n(n_), K(K_)
     {
 #pragma unroll
-        for (int q = 0; q < C::A_CPT; q++)
-            off[q] = (uint32_t)min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1) * (uint32_t)ld * 2u;
+        for (int q = 0; q < C::A_CPT; q++) {
+            const int row = min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1);
+            off[q] = (uint32_t)row * (uint32_t)ld * 2u;
+            if constexpr (SUB) {
+                const uint32_t v = low[row] & 0x7FFFu;  // 0xFFFF (no finite value): any offset will do
+                low2[q] = v | (v << 16);
+            }
+        }
+    }
+    __device__ __forceinline__ uint32_t value2(uint32_t x, int q) const
+    {
+        if constexpr (SUB) return as_u32((u16x2)(as_u16x2(x) - as_u16x2(low2[q])));
+        return x;
     }
     __device__ __forceinline__ void seek(int64_t k0) { point(k0, k0 >= 0); }
     // to the slice at k0; a thread with no group there reads column 0
@@ -583,21 +601,27 @@ struct LevelGather {
     __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
         as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
-            make_uint4(level_image(r[q].x), level_image(r[q].y), level_image(r[q].z), level_image(r[q].w));
+            make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
+                       level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++)
 #pragma unroll
-            for (int e = 0; e < 4; e++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(r[q], e)));
+            for (int e = 0; e < 4; e++)
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, value2(comp(r[q], e), q)));
         return m;
     }
 };
 
+// One 128 x 64 tile of a step.  LATE: the rows of p.L are normalised on the
+// way in and their minima left behind (LevelStep); otherwise p.L is canonical
+// and only L, O, their strides and n of p are used.
+template <bool LATE>
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level_kernel(
-    const u16 *__restrict__ Np, int64_t ldn, int64_t n, const int64_t *__restrict__ off, const int32_t *__restrict__ idx,
-    const u16 *__restrict__ Bp, u16 *__restrict__ Cm, int64_t ldc, int tiles_m, int nblk, int64_t cap, int vec)
+    LevelStep p, const int64_t *__restrict__ off, const int32_t *__restrict__ idx, const u16 *__restrict__ Bp,
+    int tiles_m, int nblk, int64_t cap, int vec, int32_t *st)
 {
     using C = PCfg;
     constexpr int BACK = (PBack::LDS_ELEMS + 7) / 8;
@@ -605,33 +629,38 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     const int nb = (int)gridDim.x;  // a multiple of 8
     const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
     if (t >= tiles_m * nblk) return;
-    const int first = t / (2 * nblk) * 2, gs = min(tiles_m - first, 2), w = t - first * nblk;
-    const int64_t m0 = (int64_t)(first + w % gs) * C::BM, j0 = (int64_t)(w / gs) * SBN;
-    const int J = w / gs;
+    const int first = t / (2 * nblk) * 2, gs = min(tiles_m - first, 2), w = t - first * nblk, J = w / gs;
+    const int64_t n = p.n, m0 = (int64_t)(first + w % gs) * C::BM, j0 = (int64_t)J * SBN;
     const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
     const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;
-    gu16 *out = glob(Cm) + m0 * ldc + j0;
+    gu16 *out = glob(p.O) + m0 * p.ldo + j0;
+    bool far = false;
+    if constexpr (LATE) far = level_step_rows<C>(p, m0, rows, J == 0, st);
     if (K == 0) {  // no finite entry in these columns, or a plan that did not fit: infinite
         for (int e = (int)threadIdx.x; e < rows * SBN; e += C::NT)
-            if (e % SBN < cols) out[(int64_t)(e / SBN) * ldc + e % SBN] = 0xFFFF;
+            if (e % SBN < cols) out[(int64_t)(e / SBN) * p.ldo + e % SBN] = 0xFFFF;
         return;
     }
-    {
-        LevelGather<C> aop(glob(Np) + m0 * ldn, ldn, rows, n, idx + kbeg, K);
+    if (!far) {
+        LevelGather<C, LATE> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, n, idx + kbeg, K, LATE ? p.low_in + m0 : nullptr);
         LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
         LevelAcc<C> acc;
         level_kloop<C>(K, aop, bop, lds, acc);
         if (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds)) {
-            level_store<C>(out, ldc, rows, cols, acc);
+            if constexpr (LATE) level_row_low<C>(acc, rows, cols, p.low_out + m0);
+            level_store<C>(out, p.ldo, rows, cols, acc);
             return;
         }
     }
     const gu16 *gB = glob(Bp) + kbeg * SBN;
     TileAcc<PBack> acc;
-    GatherA<PBack> aop{glob(Np), ldn, n, m0, glob(idx) + kbeg, rows == C::BM, {}};
+    GatherA<PBack> aop{glob(p.L), p.ldl, n, m0, glob(idx) + kbeg, rows == C::BM, LATE ? p.low_in + m0 : nullptr, {}};
     auto bop = chunk_b<PBack>([&](int64_t k0, int kr, int jc) { return gload16(gB + (k0 + kr) * SBN + jc); });
     tile_product<PBack, true>(K / PBack::BK, aop, bop, (u16 *)lds, acc);
-    tile_store<PBack>(Cm, ldc, n, n, m0, j0, vec != 0, acc);
+    if constexpr (LATE)
+        level_step_back<PBack>(p, m0, j0, rows, vec != 0, acc);
+    else
+        tile_store<PBack>(p.O, p.ldo, n, n, m0, j0, vec != 0, acc);
 }
 
 // ------------------------------------------------------------ host side
@@ -739,19 +768,41 @@ mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, si
 static std::atomic<int> g_sparse_arith{MPR_ARITH_U16};  // process-wide, set from any thread
 static std::atomic<int> g_sparse_form{MPR_SPARSE_AUTO};
 
+bool sparse_step_late(int64_t n, int64_t ldl, int64_t ldo)
+{
+    return g_sparse_form == MPR_SPARSE_AUTO && n >= 8 && level_strides(ldl, ldo);
+}
+
+template <bool LATE>
+static mpr_status level_step(const LevelStep &q, const SparsePlan &p, int vec, int32_t *st, hipStream_t s)
+{
+    const int64_t tiles_m = (q.n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
+    if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
+    hipLaunchKernelGGL(sp_level_kernel<LATE>, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, q,
+                       (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, (int)tiles_m, (int)p.nblk,
+                       p.cap, vec, st);
+    return check_launch();
+}
+
+mpr_status sparse_step_late_launch(const LevelStep &q, void *ws, size_t bytes, int32_t *st, hipStream_t s)
+{
+    return level_step<true>(q, carve_plan(ws, q.n, bytes), aligned16(q.O) && q.ldo % 8 == 0, st, s);
+}
+
 mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, size_t bytes, u16 *C, int64_t ldc,
                               hipStream_t s)
 {
     SparsePlan p = carve_plan(ws, n, bytes);
     const int vec = aligned16(C) && ldc % 8 == 0;
     const int form = g_sparse_form;
-    if (form == MPR_SPARSE_AUTO && n >= 8 && level_strides(ldn, ldc)) {
-        const int64_t tiles_m = (n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
-        if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
-        hipLaunchKernelGGL(sp_level_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, Np, ldn, n,
-                           (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, C, ldc, (int)tiles_m,
-                           (int)p.nblk, p.cap, vec);
-        return check_launch();
+    if (sparse_step_late(n, ldn, ldc)) {
+        LevelStep q{};
+        q.L = Np;
+        q.O = C;
+        q.ldl = ldn;
+        q.ldo = ldc;
+        q.n = n;
+        return level_step<false>(q, p, vec, nullptr, s);
     }
     if (form == MPR_SPARSE_ENTRIES && g_sparse_arith == MPR_ARITH_U16 && (int64_t)EBM * ldn * 2 < ((int64_t)1 << 32)) {
         const int64_t tiles_m = (n + EBM - 1) / EBM;
