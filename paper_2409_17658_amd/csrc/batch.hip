@@ -315,6 +315,11 @@ void batch_kernel(const DevChain *__restrict__ chains, const BatchItem *__restri
 __global__ void reset_counter_kernel(int *counter) { *counter = 0; }
 
 // ------------------------------------------------ the batch step by step
+// Tiles of a step: 128 x 256 while they fill the CUs, else 64 x 64 (12 chains
+// of 256 to 4096 states: 33.7 ms; with 128 x 128 instead 37.3; with 128 x 256
+// and 128 x 128 34.0, and 6 chains up to 1500 states 2.73 / 2.97 / 3.98 ms).
+using BStep0 = LCfg4;
+using BStep1 = LCfg1;
 struct LevelItem {
     int32_t inst;    // chain, -1 for padding
     int16_t tm, tn;  // tile
@@ -410,7 +415,7 @@ static constexpr int kNumBatchCfgs = (int)(sizeof(kBatchCfgs) / sizeof(kBatchCfg
 struct LevelPlan {
     int count;
     const int64_t *row0;
-    const LevelItem *items[2];            // 128 x 128 tiles, 64 x 64 tiles
+    const LevelItem *items[2];            // tiles of BStep0, of BStep1
     std::vector<unsigned> active[2];      // [k]: leading items whose chains reach power k
     LowBufs low;
 };
@@ -475,23 +480,25 @@ static bool level_batch(const mpr_chain_desc *d, int count)
     return most >= LEVEL_MIN_N;
 }
 
-// Tiles of size t of the chains in `order`, 8 streams interleaved: block b
+// bm x bn tiles of the chains in `order`, 8 streams interleaved: block b
 // runs on XCD b % 8, and each XCD gets an eighth of every chain's tiles, a
 // contiguous run in groups of 8 tile rows, so the blocks of one XCD share
 // panels in its L2 and all XCDs have equal work.
-static std::vector<LevelItem> level_items(const mpr_chain_desc *d, const std::vector<int> &order, int64_t t,
-                                          std::vector<unsigned> *ends)
+static std::vector<LevelItem> level_items(const mpr_chain_desc *d, const std::vector<int> &order, int64_t bm,
+                                          int64_t bn, std::vector<unsigned> *ends)
 {
     std::vector<LevelItem> out;
     for (size_t o = 0; o < order.size(); o++) {
-        const int64_t side = (d[order[o]].n + t - 1) / t, tiles = side * side, per = (tiles + 7) / 8;
+        const int64_t n = d[order[o]].n, down = (n + bm - 1) / bm, across = (n + bn - 1) / bn;
+        const int64_t tiles = down * across, per = (tiles + 7) / 8;
         for (int64_t q = 0; q < per * 8; q++) {
             const int64_t at = (q % 8) * per + q / 8;
             if (at >= tiles) {
                 out.push_back(LevelItem{-1, 0, 0});
                 continue;
             }
-            const int64_t first = at / (8 * side) * 8, gs = std::min<int64_t>(side - first, 8), w = at - first * side;
+            const int64_t first = at / (8 * across) * 8, gs = std::min<int64_t>(down - first, 8),
+                          w = at - first * across;
             out.push_back(LevelItem{(int32_t)o, (int16_t)(first + w % gs), (int16_t)(w / gs)});
         }
         if (ends) ends->push_back((unsigned)out.size());
@@ -499,14 +506,11 @@ static std::vector<LevelItem> level_items(const mpr_chain_desc *d, const std::ve
     return out;
 }
 
-// Items of size t of the whole batch.
-static size_t level_item_count(const mpr_chain_desc *d, int count, int64_t t)
+// Items of bm x bn tiles of the whole batch.
+static size_t level_item_count(const mpr_chain_desc *d, int count, int64_t bm, int64_t bn)
 {
     size_t c = 0;
-    for (int i = 0; i < count; i++) {
-        const int64_t side = (d[i].n + t - 1) / t;
-        c += (size_t)((side * side + 7) / 8 * 8);
-    }
+    for (int i = 0; i < count; i++) c += (size_t)round_up((d[i].n + bm - 1) / bm * ((d[i].n + bn - 1) / bn), 8);
     return c;
 }
 
@@ -528,8 +532,8 @@ static LevelLayout level_layout(const mpr_chain_desc *d, int count, size_t from)
     };
     for (int i = 0; i < count; i++) L.rows += d[i].n;
     L.row0_off = take(8 * (size_t)(count + 1));
-    L.items_off[0] = take(sizeof(LevelItem) * level_item_count(d, count, LCfg0::BM));
-    L.items_off[1] = take(sizeof(LevelItem) * level_item_count(d, count, LCfg1::BM));
+    L.items_off[0] = take(sizeof(LevelItem) * level_item_count(d, count, BStep0::BM, BStep0::BN));
+    L.items_off[1] = take(sizeof(LevelItem) * level_item_count(d, count, BStep1::BM, BStep1::BN));
     L.low_off = take(6 * 4 * (size_t)L.rows);
     L.bytes = off + 256;
     return L;
@@ -742,7 +746,8 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
             chains.swap(by_e);
             for (int t = 0; t < 2; t++) {
                 std::vector<unsigned> ends;
-                tiles[t] = level_items(descs_host, order, t == 0 ? LCfg0::BM : LCfg1::BM, &ends);
+                tiles[t] = t == 0 ? level_items(descs_host, order, BStep0::BM, BStep0::BN, &ends)
+                                  : level_items(descs_host, order, BStep1::BM, BStep1::BN, &ends);
                 level->items[t] = (LevelItem *)(base + V.items_off[t]);
                 level->active[t].assign((size_t)chains[0].e + 1, 0);
                 for (int o = 0; o < count; o++)
@@ -782,8 +787,7 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
 }
 
 // The launches of a step-by-step batch: first powers, one per power, last
-// normalisation.  64 x 64 tiles for a step whose 128 x 128 tiles would leave
-// CUs idle.
+// normalisation.
 static mpr_status level_batch_launch(const BatchPlan &p, int32_t *st, hipStream_t s)
 {
     const LevelPlan &v = *p.level;
@@ -792,10 +796,10 @@ static mpr_status level_batch_launch(const BatchPlan &p, int32_t *st, hipStream_
                        (const DevChain *)p.chains, v.row0, v.count, v.low, st);
     for (size_t k = 2; k < v.active[0].size(); k++) {
         if (v.active[0][k] >= fill)
-            hipLaunchKernelGGL(batch_step_kernel<LCfg0>, dim3(v.active[0][k]), dim3(LCfg0::NT), 0, s,
+            hipLaunchKernelGGL(batch_step_kernel<BStep0>, dim3(v.active[0][k]), dim3(BStep0::NT), 0, s,
                                (const DevChain *)p.chains, v.row0, v.items[0], (int64_t)k, v.low, st);
         else
-            hipLaunchKernelGGL(batch_step_kernel<LCfg1>, dim3(v.active[1][k]), dim3(LCfg1::NT), 0, s,
+            hipLaunchKernelGGL(batch_step_kernel<BStep1>, dim3(v.active[1][k]), dim3(BStep1::NT), 0, s,
                                (const DevChain *)p.chains, v.row0, v.items[1], (int64_t)k, v.low, st);
     }
     hipLaunchKernelGGL(batch_rows_kernel<false>, dim3((unsigned)v.low.rows), dim3(256), 0, s,
