@@ -710,23 +710,17 @@ extern "C" mpr_status mpr_period_workspace_size(int64_t n, int64_t slots, size_t
     return mpr_period_workspace_size_ex(n, slots, 0, bytes_host);
 }
 
-extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t lda, int64_t kmax, int flags,
-                                         int64_t *mu_host, int64_t *lam_host, int64_t *c_host, int64_t *traces_host,
-                                         void *ws, size_t ws_bytes, mpr_stream stream)
+// The search; bytes: the powers are kept in bytes (sparse.hip), and *restart
+// tells that a value left their range, so that the search has to start again
+// without.  reported: powers the observer has heard of.
+static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, int64_t kmax, int flags, bool bytes,
+                                   bool *restart, int64_t *reported, int64_t *mu_host, int64_t *lam_host,
+                                   int64_t *c_host, int64_t *traces_host, void *ws, size_t ws_bytes, mpr_stream stream)
 {
-    if (n < 1 || kmax < 1 || !A || !mu_host || !lam_host || !c_host || !ld_ok(lda, n)) return MPR_EINVAL;
-    if (flags & ~kPeriodFlagsAll) return MPR_EINVAL;
     const bool sparse = (flags & MPR_PERIOD_SPARSE) != 0;
     const bool reuse_a = (flags & MPR_PERIOD_REUSE_A) != 0;
     const bool pipeline = (flags & MPR_PERIOD_PIPELINE) != 0;
-    if (pipeline && reuse_a) return MPR_EINVAL;
-    // A's buffer can hold a power only once nothing reads A any more (the
-    // compressed-K plan replaces it after the first power) and only in the
-    // ring's layout (the compare reads both powers with one row stride).
-    if (reuse_a && (!sparse || lda != round_up(n, 8))) return MPR_EINVAL;
-    if (!ws) return MPR_ENOMEM;
-    mpr_status r = ensure_init();
-    if (r != MPR_OK) return r;
+    mpr_status r = MPR_OK;
     hipStream_t s = as_stream(stream);
     // The compressed-K plan is sized for this A (its rows are counted first,
     // one host round trip), so the ring gets every byte the plan does not use.
@@ -740,8 +734,10 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     }
     PeriodWs w = carve_period(ws, n, ws_bytes, 0, flags, plan_bytes);
     if (w.slots < (pipeline ? 3 : 2)) return MPR_ENOMEM;
-    int32_t *st = (int32_t *)&w.scal[2];
-    if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK) return r;
+    // status, a value past the bytes' range, the largest value in them
+    int32_t *st = (int32_t *)&w.scal[2], *wide = st + 1, *big = (int32_t *)&w.scal[6];
+    if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK || (r = fill_i32_launch(big, 1, 0, s)) != MPR_OK) return r;
+    const int64_t ld8 = round_up(n, 16);  // <= 2 w.ld: a power in bytes fits its slot
     if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
     // the counts that sized the plan lie where it begins (same carving)
     if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
@@ -764,7 +760,8 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     auto same_class = [&](const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, bool &eq,
                           int64_t &c) -> mpr_status {
         int64_t *out3 = &w.scal[3];
-        mpr_status e = compare_launch(X, RX, Y, RY, n, w.ld, out3, s);
+        mpr_status e = bytes ? compare_rows_launch(X, RX, Y, RY, n, ld8 / 2, ld8 / 2, out3, s)
+                             : compare_rows_launch(X, RX, Y, RY, n, n, w.ld, out3, s);
         if (e != MPR_OK) return e;
         int64_t cmp[3];
         if (hipMemcpyAsync(cmp, out3, sizeof(cmp), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -782,6 +779,16 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
         const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M;
         u16 *Nk = slot_N(w, slot);
         int64_t *Rk = slot_R(w, slot), *rec = host.p + 8 * (k & 1);
+        if (bytes) {
+            uint8_t *N8 = (uint8_t *)Nk;
+            mpr_status e = k == 1 ? MPR_OK
+                                  : sparse_step8_launch((const uint8_t *)slot_N(w, ps), ld8, n, w.plan, w.plan_bytes, N8,
+                                                        wide, big, s);
+            if (e == MPR_OK)
+                e = period_rows8_launch(k == 1 ? A : nullptr, lda, N8, ld8, n, k == 1 ? nullptr : slot_R(w, ps), Rk,
+                                        w.acc, st, wide, big, rec, k, s);
+            return e;
+        }
         if (k == 1) return period_rows_launch(A, lda, Nk, w.ld, n, nullptr, Rk, true, w.acc, st, rec, k, s);
         mpr_status e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
                               : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
@@ -807,8 +814,12 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
             const int64_t hash = rec[0], trace = rec[1];
             const int32_t stv = (int32_t)rec[2];
             if (stv != 0) return finish((mpr_status)stv);
+            if (bytes && rec[3] != 0) {
+                *restart = true;
+                return finish(MPR_OK);
+            }
             if (traces_host) traces_host[k] = trace;
-            report_progress(k, trace);
+            if (k > *reported) report_progress(*reported = k, trace);
             if (!found) {
                 const uint64_t h = (uint64_t)hash;
                 auto range = seen.equal_range(h);
@@ -852,8 +863,12 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
         if ((r = enqueue(k, w.slots)) != MPR_OK || (r = host.wait(rec, k, s)) != MPR_OK) return r;
         const int64_t hash = rec[0], trace = rec[1];
         if ((int32_t)rec[2] != 0) return (mpr_status)(int32_t)rec[2];
+        if (bytes && rec[3] != 0) {
+            *restart = true;
+            return MPR_OK;
+        }
         if (traces_host) traces_host[k] = trace;
-        report_progress(k, trace);
+        if (k > *reported) report_progress(*reported = k, trace);
         if (!found && held && k == held_k + held_lam) {
             // the power kept one period ago: the relation A^(k) = c (x)
             // A^(k - lam) confirmed exactly at n0 = k - lam
@@ -909,6 +924,36 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     *lam_host = lam;
     *c_host = cval;
     return MPR_OK;
+}
+
+extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t lda, int64_t kmax, int flags,
+                                         int64_t *mu_host, int64_t *lam_host, int64_t *c_host, int64_t *traces_host,
+                                         void *ws, size_t ws_bytes, mpr_stream stream)
+{
+    if (n < 1 || kmax < 1 || !A || !mu_host || !lam_host || !c_host || !ld_ok(lda, n)) return MPR_EINVAL;
+    if (flags & ~kPeriodFlagsAll) return MPR_EINVAL;
+    const bool sparse = (flags & MPR_PERIOD_SPARSE) != 0;
+    const bool reuse_a = (flags & MPR_PERIOD_REUSE_A) != 0;
+    const bool pipeline = (flags & MPR_PERIOD_PIPELINE) != 0;
+    if (pipeline && reuse_a) return MPR_EINVAL;
+    // A's buffer can hold a power only once nothing reads A any more (the
+    // compressed-K plan replaces it after the first power) and only in the
+    // ring's layout (the compare reads both powers with one row stride).
+    if (reuse_a && (!sparse || lda != round_up(n, 8))) return MPR_EINVAL;
+    if (!ws) return MPR_ENOMEM;
+    const mpr_status r = ensure_init();
+    if (r != MPR_OK) return r;
+    // In bytes where the steps allow it (and A, which a restart reads again,
+    // is not given up): half the traffic of every step and pass.
+    int64_t reported = 0;
+    if (sparse && !reuse_a && sparse_step_late(n, lda, lda)) {
+        bool restart = false;
+        const mpr_status e = find_period_impl(A, n, lda, kmax, flags, true, &restart, &reported, mu_host, lam_host,
+                                              c_host, traces_host, ws, ws_bytes, stream);
+        if (!restart) return e;
+    }
+    return find_period_impl(A, n, lda, kmax, flags, false, nullptr, &reported, mu_host, lam_host, c_host, traces_host,
+                            ws, ws_bytes, stream);
 }
 
 extern "C" mpr_status mpr_set_period_progress(void (*fn)(int64_t k, int64_t trace, void *user), void *user)

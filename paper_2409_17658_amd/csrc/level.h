@@ -492,31 +492,43 @@ __device__ __forceinline__ bool level_sure(const LevelAcc<C> &acc, int rows, int
     return !__syncthreads_or(bad);
 }
 
+// Largest finite value over the block of what `fold` makes of m (a pair of
+// signed halves, infinity negative); lds is free before and after.
+template <class C, class Fold>
+__device__ __forceinline__ int level_largest(uint4 *lds, Fold fold)
+{
+    const i16x2 m = fold((i16x2){-1, -1});
+    int *sh = (int *)lds;
+    if (threadIdx.x == 0) sh[0] = 0;
+    __syncthreads();
+    atomicMax(&sh[0], max((int)m.x, (int)m.y));
+    __syncthreads();
+    const int a = sh[0];
+    __syncthreads();
+    return a;
+}
+
 // True (block-uniform) when no finite operand of the block exceeds LV_MAX
 // and no finite sum exceeds LV_SUM, so every accumulator is exact.  One more
 // pass over the operands; lds is free.
 template <class C, class AOp, class BOp>
 __device__ __forceinline__ bool level_clean(int64_t K, AOp &aop, BOp &bop, uint4 *lds)
 {
-    i16x2 ma = {-1, -1}, mb = {-1, -1};
     const int64_t slices = (K + C::BK - 1) / C::BK, left = (slices - C::group() + C::KS - 1) / C::KS;
-    if (left > 0) level_first<C>(K, aop, bop);
-    for (int64_t j = 0; j < left; j++) {
-        if (j > 0) {
-            aop.load();
-            bop.load();
+    i16x2 mb = {-1, -1};
+    const int a = level_largest<C>(lds, [&](i16x2 ma) {
+        if (left > 0) level_first<C>(K, aop, bop);
+        for (int64_t j = 0; j < left; j++) {
+            if (j > 0) {
+                aop.load();
+                bop.load();
+            }
+            ma = aop.largest(ma);
+            mb = bop.largest(mb);
         }
-        ma = aop.largest(ma);
-        mb = bop.largest(mb);
-    }
-    int *sh = (int *)lds;
-    if (threadIdx.x == 0) sh[0] = sh[1] = 0;
-    __syncthreads();
-    atomicMax(&sh[0], max((int)ma.x, (int)ma.y));
-    atomicMax(&sh[1], max((int)mb.x, (int)mb.y));
-    __syncthreads();
-    const int a = sh[0], b = sh[1];
-    __syncthreads();  // lds is reused
+        return ma;
+    });
+    const int b = level_largest<C>(lds, [&](i16x2 m) { return __builtin_elementwise_max(m, mb); });
     return a <= (int)LV_MAX && b <= (int)LV_MAX && a + b <= (int)LV_SUM;
 }
 
@@ -716,6 +728,22 @@ mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size
 // accumulator it folds into (cleared once; every pass leaves it clear).
 size_t period_acc_bytes();
 mpr_status period_clear_launch(void *acc, hipStream_t s);
+// The same over a power in bytes (row stride ld8, a multiple of 16): raw sums
+// with 255 = infinity (or, first = true, the u16 matrix `first`, row stride
+// lda) become level bytes, 186 - 6 v for v <= 30 and 0 for infinity, padding
+// included.  A larger value raises *wide; *big receives the largest v.
+// rec[3] = *wide.
+mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t ld8, int64_t n, const int64_t *R_in,
+                               int64_t *R_out, void *acc, int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
+                               int64_t seq, hipStream_t s);
+// rowops.hip: exact compare of two canonical forms up to a scalar shift, n rows
+// of `cols` values.
+mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t cols,
+                               int64_t ld, int64_t *out3, hipStream_t s);
+// sparse.hip: the compressed-K step from level bytes to raw bytes; raises
+// *wide when a block can not be decided from values up to *big.
+mpr_status sparse_step8_launch(const uint8_t *N, int64_t ld8, int64_t n, void *ws, size_t bytes, uint8_t *O,
+                               int32_t *wide, const int32_t *big, hipStream_t s);
 mpr_status period_rows_launch(const u16 *src, int64_t lds_, u16 *dst, int64_t ldd, int64_t n, const int64_t *R_in,
                               int64_t *R_out, bool raw, void *acc, int32_t *st, int64_t *rec, int64_t seq, hipStream_t s);
 

@@ -663,6 +663,128 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
         tile_store<PBack>(p.O, p.ldo, n, n, m0, j0, vec != 0, acc);
 }
 
+#ifndef SP8G
+#define SP8G 2
+#endif
+// ------------------------------------------- the step in bytes
+// For the period search, which owns its powers: a canonical value v <= 30 is
+// kept as the exponent field 186 - 6 v of its image in one byte (0 for
+// infinity), and a raw result as the byte t (255 for infinity).  A step reads
+// and writes half the bytes, and the image of two values is a byte
+// permutation and a shift.  At m = 9 the 128 rows of N that a panel reads are
+// 2.8 MB and fit an XCD's L2.  A result that the levels do not prove raises a
+// flag, and the search starts again in u16.
+template <class C>
+struct LevelGather8 {
+    gbytes *base;
+    const __attribute__((address_space(1))) int32_t *idx, *at;
+    int64_t K;
+    uint32_t off[C::A_CPT];
+    int col;
+    uint2 r[C::A_CPT];
+    __device__ __forceinline__ LevelGather8(const uint8_t *p, int64_t ld8, int rows, const int32_t *list, int64_t K_)
+        : base((gbytes *)p), idx(glob(list) + C::tid() % C::KC * 8), K(K_)
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++)
+            off[q] = (uint32_t)min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1) * (uint32_t)ld8;
+    }
+    __device__ __forceinline__ void seek(int64_t k0)
+    {
+        at = idx + k0;
+        col = k0 >= 0 ? *at : 0;
+    }
+    __device__ __forceinline__ void load_chunk(int q)  // a group's 8 bytes lie inside the padded row
+    {
+        const u32x2 v = *(const __attribute__((address_space(1))) u32x2 *)(base + (off[q] + (uint32_t)col));
+        r[q] = make_uint2(v.x, v.y);
+    }
+    __device__ __forceinline__ void advance()
+    {
+        at -= C::BK * C::KS;
+        col = at >= idx ? *at : 0;
+    }
+    __device__ __forceinline__ void load()
+    {
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) load_chunk(q);
+        advance();
+    }
+    __device__ __forceinline__ void load_tail(int64_t k0)  // the list ends at K, a multiple of SBK = 32
+    {
+        const bool in = k0 + C::tid() % C::KC * 8 < K;
+        col = in ? idx[k0] : 0;
+#pragma unroll
+        for (int q = 0; q < C::A_CPT; q++) {
+            load_chunk(q);
+            if (!in) r[q] = make_uint2(0, 0);
+        }
+    }
+    __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
+    {
+        auto image = [](uint32_t w, uint32_t sel) { return __builtin_amdgcn_perm(w, w, sel) << 7; };
+        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+            make_uint4(image(r[q].x, 0x0C010C00u), image(r[q].x, 0x0C030C02u), image(r[q].y, 0x0C010C00u),
+                       image(r[q].y, 0x0C030C02u));
+    }
+};
+
+__global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level8_kernel(
+    const uint8_t *__restrict__ N, int64_t ld8, int64_t n, const int64_t *__restrict__ off,
+    const int32_t *__restrict__ idx, const u16 *__restrict__ Bp, uint8_t *__restrict__ O, int tiles_m, int nblk,
+    int64_t cap, int32_t *wide, const int32_t *big)
+{
+    using C = PCfg;
+    __shared__ uint4 lds[C::LDS_CHUNKS];
+    const int nb = (int)gridDim.x;  // a multiple of 8
+    const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
+    if (t >= tiles_m * nblk) return;
+    const int first = t / (SP8G * nblk) * SP8G, gs = min(tiles_m - first, SP8G), w = t - first * nblk, J = w / gs;
+    const int64_t m0 = (int64_t)(first + w % gs) * C::BM, j0 = (int64_t)J * SBN;
+    const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
+    const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;
+    LevelAcc<C> acc;
+    if (K > 0) {
+        LevelGather8<C> aop(N + m0 * ld8, ld8, rows, idx + kbeg, K);
+        LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
+        level_kloop<C>(K, aop, bop, lds, acc);
+        if (!level_sure<C>(acc, rows, cols)) {
+            // exact when the largest values of N and of these columns sum to
+            // what the float range holds
+            const int b = level_largest<C>(lds, [&](i16x2 m) {
+                for (int64_t e = threadIdx.x; e < K * SBN / 8; e += C::NT) {
+                    const uint4 v = gload16(glob(Bp) + kbeg * SBN + e * 8);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(v, q)));
+                }
+                return m;
+            });
+            if (threadIdx.x == 0 && (b > (int)LV_MAX || *big + b > (int)LV_SUM)) set_status(wide, 1);
+        }
+    } else {  // no finite entry in these columns, or a plan that did not fit
+#pragma unroll
+        for (int mi = 0; mi < C::MI; mi++)
+#pragma unroll
+            for (int ni = 0; ni < C::NI; ni++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) acc.v[mi][ni][r] = 0;
+    }
+    __attribute__((address_space(1))) uint8_t *out = glob(O) + m0 * ld8 + j0;
+#pragma unroll
+    for (int mi = 0; mi < C::MI; mi++) {
+        const int row = level_row<C>(mi);
+#pragma unroll
+        for (int ni = 0; ni < C::NI; ni++) {
+            const int col = level_col<C>(ni);
+            uint32_t x = 0;
+#pragma unroll
+            for (int r = 0; r < 4; r++) x |= (level_value(acc.v[mi][ni][r]) & 0xFFu) << (8 * r);
+            if (row < rows && j0 + col < ld8)  // columns past n, up to the stride, are infinite
+                *(__attribute__((address_space(1))) uint32_t *)(out + (int64_t)row * ld8 + col) = x;
+        }
+    }
+}
+
 // ------------------------------------------------------------ host side
 // Plan layout: counts[nblk + 1] | off[nblk + 1] | order[nblk] | idx[cap] |
 // Bp[cap * SBN], every piece 256-byte aligned; cap (rows) follows from the
@@ -781,6 +903,18 @@ static mpr_status level_step(const LevelStep &q, const SparsePlan &p, int vec, i
     hipLaunchKernelGGL(sp_level_kernel<LATE>, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, q,
                        (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, (int)tiles_m, (int)p.nblk,
                        p.cap, vec, st);
+    return check_launch();
+}
+
+mpr_status sparse_step8_launch(const uint8_t *N, int64_t ld8, int64_t n, void *ws, size_t bytes, uint8_t *O,
+                               int32_t *wide, const int32_t *big, hipStream_t s)
+{
+    const SparsePlan p = carve_plan(ws, n, bytes);
+    const int64_t tiles_m = (n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
+    if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
+    hipLaunchKernelGGL(sp_level8_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, N, ld8, n,
+                       (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, O, (int)tiles_m, (int)p.nblk,
+                       p.cap, wide, big);
     return check_launch();
 }
 

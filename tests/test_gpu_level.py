@@ -157,3 +157,33 @@ def test_small_products_and_their_check(mpr, shape):
                     mpr.minplus_gemm(A, B)
                 assert e.value.status == 3
                 bad[-1, -1] = keep
+
+
+@pytest.mark.parametrize("pipeline", [False, True])
+@pytest.mark.parametrize("spread", [0, 25, 40, 300])
+def test_period_search_in_bytes_and_past_them(mpr, spread, pipeline):
+    """A period search keeps its powers in bytes while their values stay
+    within 30 (spread 0, 25) and starts again when one does not (40: past the
+    first power, 300: at once); period, traces and the observer's calls equal
+    those of the dense search, which holds 16 bits throughout."""
+    n, kmax = 75, 40
+    X = np.full((n, n), mpr.INF, dtype=np.uint16)
+    rng = np.random.default_rng(spread)
+    for i in range(n):  # strongly connected, period 3, sparse
+        X[i, (i + 1) % n] = rng.integers(0, 3)
+        X[i, rng.integers(0, n)] = rng.integers(0, max(spread, 3) // 2 + 1)
+    X[5, 6] = spread
+    A = mpr.to_device(X)
+    mpr.set_period_progress(lambda k, t: heard.append((k, t)))
+    try:
+        got = []
+        for sparse in (False, True):
+            heard = []
+            mu, lam, c, tr = mpr.find_period(A, kmax, slots=30, sparse=sparse, pipeline=pipeline)
+            assert [k for k, _ in heard] == list(range(1, kmax + 1))
+            got.append((mu, lam, c, tr.tolist(), heard))
+        assert got[0] == got[1]
+    finally:
+        mpr.set_period_progress(None)
+    On = O.power_chain(O.from_u16(X), 7)
+    assert int(O.trace(*On)) == got[1][3][7] if got[1][3][7] != mpr.ROW_NONE else True
