@@ -24,7 +24,7 @@ constexpr int RT = 256;  // threads per row
 struct PeriodSlot {
     uint64_t hash, offsets, keys;  // sums over the rows
     int64_t least, trace;          // minima over the rows
-    uint32_t done, pad[5];         // rows folded in
+    uint32_t done, pad[5];         // blocks folded in
 };
 static_assert(sizeof(PeriodSlot) == 64, "a slot to a half line");
 struct PeriodAcc {
@@ -78,41 +78,53 @@ __device__ __forceinline__ uint4 row8(const gu16 *row, int64_t c, int64_t n)
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// The row's part in its power, by every thread of its block (m: least value,
-// diag: diagonal value, h: hash of its entries, refuse: out of range; of
-// thread 0).  wide: a second status word for the record, or null.
-__device__ __forceinline__ void period_fold(int64_t i, uint32_t m, uint32_t diag, uint64_t h, int refuse,
-                                            const int64_t *R_in, int64_t *R_out, PeriodAcc *acc, int32_t *st,
-                                            int32_t *wide, int64_t *rec, int64_t seq, int *last)
+// One row's part in its power (m: least value, diag: diagonal value, h: hash
+// of its entries); its offset goes to R_out.
+struct RowPart {
+    uint64_t hash, offsets, keys;
+    int64_t least, trace;
+};
+__device__ __forceinline__ RowPart period_row(int64_t i, uint32_t m, uint32_t diag, uint64_t h, const int64_t *R_in,
+                                              int64_t *R_out)
+{
+    const int64_t rin = R_in ? R_in[i] : 0;
+    const bool none = m == 0xFFFFu || rin == ROW_NONE;
+    const int64_t R = none ? ROW_NONE : rin + (int64_t)m;
+    R_out[i] = R;
+    const uint64_t rh = mix64(h ^ mix64((uint64_t)i ^ 0x6A09E667F3BCC909ull));
+    const uint64_t key = mix64((uint64_t)i ^ 0xBB67AE8584CAA73Bull);
+    if (none) return RowPart{rh + 1, 0, 0, ROW_NONE, ROW_NONE};
+    return RowPart{rh, key * (uint64_t)R, key, R, diag != 0xFFFFu ? R + (int64_t)(diag - m) : ROW_NONE};
+}
+
+// Folds a block's rows into the power, called by every thread (x and refuse
+// of thread 0; refuse: 1 out of range, 2 wide).  wide: a second status word
+// for the record, or null.
+__device__ __forceinline__ void period_fold(const RowPart &x, int refuse, PeriodAcc *acc, int32_t *st, int32_t *wide,
+                                            int64_t *rec, int64_t seq, int *last)
 {
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
     if (threadIdx.x == 0) {
-        const int64_t rin = R_in ? R_in[i] : 0;
-        const bool none = m == 0xFFFFu || rin == ROW_NONE;
-        const int64_t R = none ? ROW_NONE : rin + (int64_t)m;
-        R_out[i] = R;
-        const uint64_t rh = mix64(h ^ mix64((uint64_t)i ^ 0x6A09E667F3BCC909ull));
-        const uint64_t key = mix64((uint64_t)i ^ 0xBB67AE8584CAA73Bull);
         PeriodSlot *s = &acc->slot[blockIdx.x % PSLOTS];
-        // every fold completes (its old value arrives) before the row counts
-        uint64_t seen = agent_add(&s->hash, none ? rh + 1 : rh);
-        if (!none) {
-            seen |= agent_add(&s->offsets, key * (uint64_t)R) | agent_add(&s->keys, key);
-            seen |= (uint64_t)agent_min(&s->least, R);
-            if (diag != 0xFFFFu) seen |= (uint64_t)agent_min(&s->trace, R + (int64_t)(diag - m));
+        // every fold completes (its old value arrives) before the block counts
+        uint64_t seen = agent_add(&s->hash, x.hash);
+        if (x.least != ROW_NONE) {
+            seen |= agent_add(&s->offsets, x.offsets) | agent_add(&s->keys, x.keys);
+            seen |= (uint64_t)agent_min(&s->least, x.least);
+            if (x.trace != ROW_NONE) seen |= (uint64_t)agent_min(&s->trace, x.trace);
         }
         if (refuse & 1)
             seen |= (uint64_t)__hip_atomic_exchange(st, MPR_EOVERFLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (refuse & 2) seen |= (uint64_t)__hip_atomic_exchange(wide, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" : : "v"(seen) : "memory");
-        const uint32_t rows = ((uint32_t)gridDim.x + PSLOTS - 1 - blockIdx.x % PSLOTS) / PSLOTS;  // of this slot
+        const uint32_t blocks = ((uint32_t)gridDim.x + PSLOTS - 1 - blockIdx.x % PSLOTS) / PSLOTS;  // of this slot
         const uint32_t slots = min((uint32_t)gridDim.x, (uint32_t)PSLOTS);
         *last = 0;
-        if (agent_add(&s->done, 1u) + 1 == rows) *last = agent_add(&acc->full, 1u) + 1 == slots;
+        if (agent_add(&s->done, 1u) + 1 == blocks) *last = agent_add(&acc->full, 1u) + 1 == slots;
     }
     __syncthreads();
     if (!*last || w != 0) return;
-    // The last row of the power: one lane per slot (reads at the place where
+    // The last block of the power: one lane per slot (reads at the place where
     // the folds happened), then the record and a clear accumulator.
     PeriodSlot *s = &acc->slot[lane % PSLOTS];
     uint64_t hs = lane < PSLOTS ? agent_add(&s->hash, (uint64_t)0) : 0;
@@ -219,136 +231,160 @@ __global__ __launch_bounds__(RT) void period_rows_kernel(const u16 *src, int64_t
     h = wave_sum_u64(h);
     if (lane == 0) hsum[w] = h;
     __syncthreads();
-    period_fold(i, m, diag, hsum[0] + hsum[1] + hsum[2] + hsum[3], refuse, R_in, R_out, acc, st, nullptr, rec, seq, &last);
+    RowPart x{};
+    if (threadIdx.x == 0) x = period_row(i, m, diag, hsum[0] + hsum[1] + hsum[2] + hsum[3], R_in, R_out);
+    period_fold(x, refuse, acc, st, nullptr, rec, seq, &last);
 }
 
-// The same in bytes (level bytes, sparse.hip): 16 columns per thread and
-// chunk.  FIRST: the source is the u16 matrix X.  *big receives the largest
-// canonical value of the power, for the step that reads it.
+// The same in bytes (level bytes, sparse.hip), a wave per row: lane t takes
+// the 16 columns at 16 t, 16 t + 1024, ..., NCH of them in registers (0: the
+// row is read twice).  FIRST: the source is the u16 matrix X.  *big receives
+// the largest canonical value, for the step that reads it.  Four rows share
+// one fold: with one each, the atomics bound the pass (m = 9: 300 us).
 template <int NCH, bool FIRST>
 __global__ __launch_bounds__(RT) void period_rows8_kernel(const u16 *X, int64_t ldx, uint8_t *N, int64_t ld8, int64_t n,
                                                           const int64_t *R_in, int64_t *R_out, PeriodAcc *acc,
                                                           int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
                                                           int64_t seq)
 {
-    __shared__ uint32_t least[RT / 64], most[RT / 64];
-    __shared__ uint64_t hsum[RT / 64];
-    __shared__ uint32_t diag;
-    __shared__ int last, refuse;
+    __shared__ RowPart part[RT / 64];
+    __shared__ int refused[RT / 64], most[RT / 64];
+    __shared__ int last;
     constexpr u16 INFV = FIRST ? 0xFFFF : 0xFF;
-    constexpr int Q = NCH > 0 ? NCH : 1;
-    const int64_t i = blockIdx.x;
-    const gu16 *xrow = glob(X) + (FIRST ? i * ldx : 0);
-    __attribute__((address_space(1))) uint8_t *row = glob(N) + i * ld8;
+    constexpr int W = FIRST ? 8 : 4;  // dwords of 16 columns
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-    // values 0, 2 / 4, 6 / .. and 1, 3 / 5, 7 / .. of 16 columns from c
-    auto load = [&](int64_t c, u16x2 ev[4], u16x2 od[4]) {
-        if constexpr (FIRST) {
-            const uint4 a = row8(xrow, c, n), b = c + 8 < n ? row8(xrow, c + 8, n)
-                                                            : make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-            const uint32_t d[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const int64_t i = (int64_t)blockIdx.x * (RT / 64) + w;
+    if (lane == 0) {
+        part[w] = RowPart{0, 0, 0, ROW_NONE, ROW_NONE};
+        refused[w] = most[w] = 0;
+    }
+    if (i < n) {  // wave-uniform
+        const gu16 *xrow = glob(X) + (FIRST ? i * ldx : 0);
+        __attribute__((address_space(1))) uint8_t *row = glob(N) + i * ld8;
+        auto load = [&](int64_t c, uint32_t d[W]) {
+            if constexpr (FIRST) {
+                const uint4 inf = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+                const uint4 a = row8(xrow, c, n), b = c + 8 < n ? row8(xrow, c + 8, n) : inf;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    d[q] = comp(a, q);
+                    d[4 + q] = comp(b, q);
+                }
+            } else {
+                const u32x4 v = *(const __attribute__((address_space(1))) u32x4 *)(row + c);
+                d[0] = v.x;
+                d[1] = v.y;
+                d[2] = v.z;
+                d[3] = v.w;
+            }
+        };
+        // values 4q, 4q + 2 and 4q + 1, 4q + 3 of 16 columns
+        auto split = [&](const uint32_t d[W], int q, u16x2 &ev, u16x2 &od) {
+            if constexpr (FIRST) {
+                ev = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u));
+                od = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u));
+            } else {
+                ev = as_u16x2(d[q] & 0x00FF00FFu);
+                od = as_u16x2(d[q] >> 8 & 0x00FF00FFu);
+            }
+        };
+        uint32_t keep[NCH > 0 ? NCH : 1][W];
+        u16x2 mn = {0xFFFF, 0xFFFF}, mx = {0, 0};  // mx: largest finite value + 1 (infinity + 1 is 0)
+        auto fold = [&](const uint32_t d[W]) {
+            const u16x2 one = {1, 1}, mask = {INFV, INFV};
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                ev[q] = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u));
-                od[q] = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u));
+                u16x2 ev, od;
+                split(d, q, ev, od);
+                mn = min2(mn, min2(ev, od));
+                mx = __builtin_elementwise_max(mx, __builtin_elementwise_max((u16x2)((ev + one) & mask),
+                                                                             (u16x2)((od + one) & mask)));
+            }
+        };
+        const int64_t c0 = (int64_t)lane * 16;
+        if constexpr (NCH > 0) {
+#pragma unroll
+            for (int k = 0; k < NCH; k++) {
+                const int64_t c = c0 + (int64_t)k * 1024;
+#pragma unroll
+                for (int q = 0; q < W; q++) keep[k][q] = 0xFFFFFFFFu;
+                if (c < n) load(c, keep[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < NCH; k++) fold(keep[k]);
+        } else {
+            for (int64_t c = c0; c < n; c += 1024) {
+                load(c, keep[0]);
+                fold(keep[0]);
+            }
+        }
+        uint32_t diag = FIRST ? (uint32_t)xrow[i] : (uint32_t)row[i];
+        if (diag == INFV) diag = 0xFFFFu;
+        uint32_t m = wave_min_u32(min((uint32_t)mn.x, (uint32_t)mn.y));
+        const uint32_t top1 = ~wave_min_u32(~max((uint32_t)mx.x, (uint32_t)mx.y));  // largest finite value + 1, or 0
+        if (m == INFV) m = 0xFFFFu;
+        // v = x - m (infinity apart) as the level byte 186 - 6 v
+        const u16 base = (u16)(LV_BIAS + LV_STEP * m), mul = (u16)(0u - LV_STEP);
+        uint64_t h = 0;
+        auto image = [&](u16x2 x) {
+            const u16x2 e = x * (u16x2){mul, mul} + (u16x2){base, base};
+            if constexpr (FIRST) {
+                return (u16x2){(u16)(x.x == INFV ? 0 : e.x & 0xFF), (u16)(x.y == INFV ? 0 : e.y & 0xFF)};
+            } else {
+                // all ones where x is 255: only there x + 1 carries into bit 8
+                const u16x2 inf = (u16x2){0, 0} - (u16x2)((x + (u16x2){1, 1}) >> (u16x2){8, 8});
+                return (u16x2)(e & ~inf & (u16x2){0xFF, 0xFF});
+            }
+        };
+        auto finish = [&](const uint32_t d[W], int64_t c) {
+            uint32_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                u16x2 ev, od;
+                split(d, q, ev, od);
+                x[q] = as_u32(image(ev)) | as_u32(image(od)) << 8;
+            }
+            h += nh4(x, (uint32_t)(c >> 4));
+            *(__attribute__((address_space(1))) u32x4 *)(row + c) = (u32x4){x[0], x[1], x[2], x[3]};
+        };
+        if constexpr (NCH > 0) {
+#pragma unroll
+            for (int k = 0; k < NCH; k++) {
+                const int64_t c = c0 + (int64_t)k * 1024;
+                if (c < n) finish(keep[k], c);
             }
         } else {
-            const u32x4 v = *(const __attribute__((address_space(1))) u32x4 *)(row + c);
-            const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                ev[q] = as_u16x2(d[q] & 0x00FF00FFu);
-                od[q] = as_u16x2(d[q] >> 8 & 0x00FF00FFu);
+            for (int64_t c = c0; c < n; c += 1024) {
+                load(c, keep[0]);
+                finish(keep[0], c);
             }
         }
-    };
-    u16x2 ke[Q][4], ko[Q][4];
-    u16x2 mn = {0xFFFF, 0xFFFF};
-    bool over = false;
-    const int64_t c0 = (int64_t)threadIdx.x * 16;
-    auto fold = [&](const u16x2 ev[4], const u16x2 od[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            mn = min2(mn, min2(ev[q], od[q]));
-            if (FIRST) {
-                const uint32_t x[4] = {ev[q].x, ev[q].y, od[q].x, od[q].y};
-#pragma unroll
-                for (int e = 0; e < 4; e++) over |= x[e] > FMAX16 && x[e] != 0xFFFFu;
-            }
+        h = wave_sum_u64(h);
+        if (lane == 0) {
+            part[w] = period_row(i, m, diag, h, R_in, R_out);
+            const uint32_t v = top1 ? top1 - 1 - m : 0;  // the row's largest canonical value
+            refused[w] = (FIRST && top1 > FMAX16 + 1u ? 1 : 0) | (v > LV_MAX ? 2 : 0);
+            most[w] = (int)min(v, (uint32_t)LV_MAX);
         }
-    };
-    if constexpr (NCH > 0) {
-#pragma unroll
-        for (int k = 0; k < NCH; k++) {
-            const int64_t c = c0 + (int64_t)k * RT * 16;
-            if (c < n) {
-                load(c, ke[k], ko[k]);
-                fold(ke[k], ko[k]);
-            }
-        }
-    } else {
-        for (int64_t c = c0; c < n; c += RT * 16) {
-            load(c, ke[0], ko[0]);
-            fold(ke[0], ko[0]);
-        }
-    }
-    uint32_t m = wave_min_u32(min((uint32_t)mn.x, (uint32_t)mn.y));
-    if (lane == 0) least[w] = m;
-    if (threadIdx.x == 0) {
-        diag = FIRST ? (uint32_t)xrow[i] : (uint32_t)row[i];  // before the row is rewritten
-        if (diag == INFV) diag = 0xFFFFu;
-        refuse = 0;
     }
     __syncthreads();
-    m = min(min(least[0], least[1]), min(least[2], least[3]));
-    if (m == INFV) m = 0xFFFFu;
-    // 186 - 6 (x - m), a level byte when x - m <= 30
-    const u16 top = (u16)(LV_BIAS + LV_STEP * m);
-    uint64_t h = 0;
-    u16x2 small = {0xFFFF, 0xFFFF};  // least nonzero image: the largest value
-    bool far = false;
-    auto image = [&](u16x2 x) {
-        const u16x2 e = x * (u16x2){(u16)(0u - LV_STEP), (u16)(0u - LV_STEP)} + (u16x2){top, top};
-        const bool fx = x.x != INFV, fy = x.y != INFV;
-        far |= (fx && (uint32_t)x.x - m > LV_MAX) || (fy && (uint32_t)x.y - m > LV_MAX);
-        small = min2(small, (u16x2){fx ? e.x : (u16)0xFFFF, fy ? e.y : (u16)0xFFFF});
-        return (u16x2){(u16)(fx ? e.x & 0xFF : 0), (u16)(fy ? e.y & 0xFF : 0)};
-    };
-    auto finish = [&](const u16x2 ev[4], const u16x2 od[4], int64_t c) {
-        uint32_t x[4];
-#pragma unroll
-        for (int q = 0; q < 4; q++) x[q] = as_u32(image(ev[q])) | as_u32(image(od[q])) << 8;
-        h += nh4(x, (uint32_t)(c >> 4));
-        *(__attribute__((address_space(1))) u32x4 *)(row + c) = (u32x4){x[0], x[1], x[2], x[3]};
-    };
-    if constexpr (NCH > 0) {
-#pragma unroll
-        for (int k = 0; k < NCH; k++) {
-            const int64_t c = c0 + (int64_t)k * RT * 16;
-            if (c < n) finish(ke[k], ko[k], c);
-        }
-    } else {
-        for (int64_t c = c0; c < n; c += RT * 16) {
-            load(c, ke[0], ko[0]);
-            finish(ke[0], ko[0], c);
-        }
-    }
-    if (over) atomicOr(&refuse, 1);
-    if (far) atomicOr(&refuse, 2);
-    h = wave_sum_u64(h);
-    const uint32_t lo = wave_min_u32(min((uint32_t)small.x, (uint32_t)small.y));
-    if (lane == 0) {
-        hsum[w] = h;
-        most[w] = lo;
-    }
-    __syncthreads();
+    RowPart x{0, 0, 0, ROW_NONE, ROW_NONE};
+    int refuse = 0;
     if (threadIdx.x == 0) {
-        const uint32_t e = min(min(most[0], most[1]), min(most[2], most[3]));
-        // read by the next step, a later kernel; few rows raise it
-        const int32_t v = e <= LV_BIAS ? (int32_t)((LV_BIAS - e) / LV_STEP) : 0;
+        int v = 0;
+        for (int k = 0; k < RT / 64; k++) {
+            x.hash += part[k].hash;
+            x.offsets += part[k].offsets;
+            x.keys += part[k].keys;
+            x.least = min(x.least, part[k].least);
+            x.trace = min(x.trace, part[k].trace);
+            refuse |= refused[k];
+            v = max(v, most[k]);
+        }
+        // read by the next step, a later kernel; few blocks raise it
         if (v > __hip_atomic_load(big, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(big, v);
     }
-    period_fold(i, m, diag, hsum[0] + hsum[1] + hsum[2] + hsum[3], refuse, R_in, R_out, acc, st, wide, rec, seq, &last);
+    period_fold(x, refuse, acc, st, wide, rec, seq, &last);
 }
 
 mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t ld8, int64_t n, const int64_t *R_in,
@@ -356,12 +392,12 @@ mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_
                                int64_t seq, hipStream_t s)
 {
     if (n > INT32_MAX) return MPR_EUNSUPPORTED;
-    auto kernel = first             ? period_rows8_kernel<0, true>
-                  : n <= RT * 16     ? period_rows8_kernel<1, false>
-                  : n <= 2 * RT * 16 ? period_rows8_kernel<2, false>
-                  : n <= 6 * RT * 16 ? period_rows8_kernel<6, false>
-                                     : period_rows8_kernel<0, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(RT), 0, s, first, lda, N, ld8, n, R_in, R_out, (PeriodAcc *)acc,
+    auto kernel = first          ? period_rows8_kernel<0, true>
+                  : n <= 1024     ? period_rows8_kernel<1, false>
+                  : n <= 8 * 1024 ? period_rows8_kernel<8, false>
+                  : n <= 24 * 1024 ? period_rows8_kernel<24, false>
+                                   : period_rows8_kernel<0, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 3) / 4)), dim3(RT), 0, s, first, lda, N, ld8, n, R_in, R_out, (PeriodAcc *)acc,
                        st, wide, big, rec, seq);
     return check_launch();
 }
