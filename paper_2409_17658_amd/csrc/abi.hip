@@ -736,11 +736,16 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
     if (w.slots < (pipeline ? 3 : 2)) return MPR_ENOMEM;
     // status, a value past the bytes' range, the largest value in them
     int32_t *st = (int32_t *)&w.scal[2], *wide = st + 1, *big = (int32_t *)&w.scal[6];
-    if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK || (r = fill_i32_launch(big, 1, 0, s)) != MPR_OK) return r;
     const int64_t ld8 = round_up(n, 16);  // <= 2 w.ld: a power in bytes fits its slot
-    if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
-    // the counts that sized the plan lie where it begins (same carving)
-    if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
+    // Powers of at most 64 states: one workgroup takes one from the power
+    // before and A, and needs none of what the others share.
+    const bool small = bytes && n <= PERIOD_SMALL_N;
+    if (!small) {
+        if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK || (r = fill_i32_launch(big, 1, 0, s)) != MPR_OK) return r;
+        if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
+        // the counts that sized the plan lie where it begins (same carving)
+        if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
+    }
     if (traces_host) traces_host[0] = MPR_ROW_NONE;
 
     // Power k lives in slot (k - 1) % slots (a ring), so a repeat of the class
@@ -779,6 +784,9 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M;
         u16 *Nk = slot_N(w, slot);
         int64_t *Rk = slot_R(w, slot), *rec = host.p + 8 * (k & 1);
+        if (small)
+            return period_small_launch(A, lda, k == 1 ? nullptr : (const uint8_t *)slot_N(w, ps), (uint8_t *)Nk, ld8, n,
+                                       k == 1 ? nullptr : slot_R(w, ps), Rk, rec, k, s);
         if (bytes) {
             uint8_t *N8 = (uint8_t *)Nk;
             mpr_status e = k == 1 ? MPR_OK

@@ -736,6 +736,11 @@ mpr_status period_clear_launch(void *acc, hipStream_t s);
 mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t ld8, int64_t n, const int64_t *R_in,
                                int64_t *R_out, void *acc, int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
                                int64_t seq, hipStream_t s);
+// The step and that pass at once, for n <= PERIOD_SMALL_N: N the power before
+// (null: the power is A itself), O the next.
+constexpr int64_t PERIOD_SMALL_N = 64;
+mpr_status period_small_launch(const u16 *A, int64_t lda, const uint8_t *N, uint8_t *O, int64_t ld8, int64_t n,
+                               const int64_t *R_in, int64_t *R_out, int64_t *rec, int64_t seq, hipStream_t s);
 // rowops.hip: exact compare of two canonical forms up to a scalar shift, n rows
 // of `cols` values.
 mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t cols,

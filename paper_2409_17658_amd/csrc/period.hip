@@ -11,9 +11,9 @@
 // and for the offsets a linear sum, whose shift by the least offset can be
 // taken off at the end.  Each block folds its row into one of PSLOTS records
 // and the last block combines them, where two more kernels of one block used
-// to read n words each (m = 8: 68 + 13 + 9 us, now ROWS8; m = 9: 410 + 51 +
-// 24 us, now ROWS9; m = 3: 6.0 + 3.4 + 3.3 us and a copy to the host, now
-// ROWS3).
+// to read n words each (m = 8: 68 + 13 + 9 us, in bytes 31; m = 9: 410 + 51 +
+// 24 us, in bytes 280; m = 3: 6.0 + 3.4 + 3.3 us and a copy to the host, now
+// within the 6.7 us of a whole power).
 #include "level.h"
 
 namespace mpr {
@@ -399,6 +399,88 @@ mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_
                                    : period_rows8_kernel<0, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 3) / 4)), dim3(RT), 0, s, first, lda, N, ld8, n, R_in, R_out, (PeriodAcc *)acc,
                        st, wide, big, rec, seq);
+    return check_launch();
+}
+
+// A whole power of up to SMALL_N states, step and pass, by one workgroup: the
+// power before (bytes) and A in LDS, a half wave to a row and a lane to two
+// columns, sums in 16 bits (no value passes 30 + FMAX), nothing left to
+// atomics.  Two kernels whose blocks meet in an accumulator are latency alone
+// at this size (n = 33: 4.5 + 8.8 us a power, now 6.7).
+constexpr int SMALL_N = PERIOD_SMALL_N, SMALL_T = 1024;
+__global__ __launch_bounds__(SMALL_T) void period_small_kernel(const u16 *A, int64_t lda, const uint8_t *N, uint8_t *O,
+                                                               int ld8, int n, const int64_t *R_in, int64_t *R_out,
+                                                               int64_t *rec, int64_t seq)
+{
+    constexpr int HP = SMALL_N / 2;  // lanes of a row: column pairs
+    static_assert(HP == 32, "a half wave to a row");
+    __shared__ uint32_t a[SMALL_N][HP + 1];
+    __shared__ u16 l[SMALL_N][SMALL_N + 2];
+    __shared__ RowPart part[SMALL_N];
+    __shared__ int refused;
+    const int t = (int)threadIdx.x, lane = t & 63, half = t / HP, p = t % HP;
+    if (t == 0) refused = 0;
+    if (t < SMALL_N) part[t] = RowPart{0, 0, 0, ROW_NONE, ROW_NONE};
+    for (int e = t; e < SMALL_N * HP; e += SMALL_T) {
+        const int i = e / HP, c = e % HP * 2;
+        const gu16 *row = glob(A) + (int64_t)i * lda;
+        const uint32_t lo = i < n && c < n ? row[c] : 0xFFFFu, hi = i < n && c + 1 < n ? row[c + 1] : 0xFFFFu;
+        a[i][c / 2] = lo | hi << 16;
+    }
+    if (N) {
+        for (int e = t; e < n * n; e += SMALL_T) {
+            const int i = e / n, c = e - i * n;
+            const uint32_t b = glob(N)[i * ld8 + c];
+            l[i][c] = b ? (u16)((LV_BIAS - b) * 43 >> 8) : INF16;  // v <= 30: 43 / 256 is 1 / 6 there
+        }
+    }
+    __syncthreads();
+    for (int i = half; i < n; i += SMALL_T / HP) {  // uniform in a half wave
+        u16x2 v = as_u16x2(a[i][p]);
+        if (N) {
+            v = (u16x2){0xFFFF, 0xFFFF};
+#pragma unroll 8
+            for (int k = 0; k < n; k++) v = min2(v, add_sat((u16x2){l[i][k], l[i][k]}, as_u16x2(a[k][p])));
+        }
+        const int c = 2 * p;
+        uint32_t m = min((uint32_t)v.x, (uint32_t)v.y);
+        // largest finite value + 1, or 0
+        uint32_t top1 = max(v.x == 0xFFFF ? 0u : v.x + 1u, v.y == 0xFFFF ? 0u : v.y + 1u);
+        for (int off = HP / 2; off > 0; off >>= 1) {
+            m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
+            top1 = max(top1, (uint32_t)__shfl_xor((int)top1, off, 64));
+        }
+        auto image = [&](uint32_t x) { return x == 0xFFFFu ? 0u : (LV_BIAS - LV_STEP * (x - m)) & 0xFFu; };
+        const uint32_t x = image(v.x) | image(v.y) << 8;
+        uint64_t h = mix64((uint64_t)(p + 1) << 32 | x);
+        for (int off = HP / 2; off > 0; off >>= 1) h += __shfl_xor(h, off, 64);
+        const uint32_t pair = (uint32_t)__shfl((int)as_u32(v), (lane & HP) + i / 2, 64);
+        if (c < ld8) *(__attribute__((address_space(1))) u16 *)(glob(O) + i * ld8 + c) = (u16)x;  // ld8 is even
+        if (p == 0) {
+            part[i] = period_row(i, m, i & 1 ? pair >> 16 : pair & 0xFFFFu, h, R_in, R_out);
+            const int r = (!N && top1 > FMAX16 + 1u ? 1 : 0) | (top1 && top1 - 1 - m > LV_MAX ? 2 : 0);
+            if (r) atomicOr(&refused, r);
+        }
+    }
+    __syncthreads();
+    if (t >= 64) return;
+    const RowPart x = part[lane];
+    const uint64_t hs = wave_sum_u64(x.hash), os = wave_sum_u64(x.offsets), ks = wave_sum_u64(x.keys);
+    const int64_t lo = wave_min_i64(x.least), tr = wave_min_i64(x.trace);
+    if (lane != 0) return;
+    rec[0] = (int64_t)mix64(hs + mix64(os - (lo == ROW_NONE ? 0 : (uint64_t)lo * ks)));
+    rec[1] = tr;
+    rec[2] = refused & 1 ? MPR_EOVERFLOW : MPR_OK;
+    rec[3] = refused >> 1;
+    __hip_atomic_store(&rec[7], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+mpr_status period_small_launch(const u16 *A, int64_t lda, const uint8_t *N, uint8_t *O, int64_t ld8, int64_t n,
+                               const int64_t *R_in, int64_t *R_out, int64_t *rec, int64_t seq, hipStream_t s)
+{
+    if (n > SMALL_N || ld8 > SMALL_N) return MPR_EUNSUPPORTED;
+    hipLaunchKernelGGL(period_small_kernel, dim3(1), dim3(SMALL_T), 0, s, A, lda, N, O, (int)ld8, (int)n, R_in, R_out, rec,
+                       seq);
     return check_launch();
 }
 

@@ -663,9 +663,6 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
         tile_store<PBack>(p.O, p.ldo, n, n, m0, j0, vec != 0, acc);
 }
 
-#ifndef SP8G
-#define SP8G 2
-#endif
 // ------------------------------------------- the step in bytes
 // For the period search, which owns its powers: a canonical value v <= 30 is
 // kept as the exponent field 186 - 6 v of its image in one byte (0 for
@@ -729,6 +726,11 @@ struct LevelGather8 {
     }
 };
 
+// Row panels that run side by side over the column blocks (whole searches with
+// 1, 2, 3, 4: m = 8 7.45, 6.79, 6.87, 6.62 ms, m = 9 85.4, 79.8, 82.1, 80.3).  A
+// block that took 2 neighbouring column blocks, the second's first loads ahead
+// of the first's stores, left too few blocks: 8.40 and 91.8 ms.
+constexpr int PANELS8 = 2;
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level8_kernel(
     const uint8_t *__restrict__ N, int64_t ld8, int64_t n, const int64_t *__restrict__ off,
     const int32_t *__restrict__ idx, const u16 *__restrict__ Bp, uint8_t *__restrict__ O, int tiles_m, int nblk,
@@ -739,7 +741,7 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     const int nb = (int)gridDim.x;  // a multiple of 8
     const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
     if (t >= tiles_m * nblk) return;
-    const int first = t / (SP8G * nblk) * SP8G, gs = min(tiles_m - first, SP8G), w = t - first * nblk, J = w / gs;
+    const int first = t / (PANELS8 * nblk) * PANELS8, gs = min(tiles_m - first, PANELS8), w = t - first * nblk, J = w / gs;
     const int64_t m0 = (int64_t)(first + w % gs) * C::BM, j0 = (int64_t)J * SBN;
     const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
     const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;

@@ -187,3 +187,26 @@ def test_period_search_in_bytes_and_past_them(mpr, spread, pipeline):
         mpr.set_period_progress(None)
     On = O.power_chain(O.from_u16(X), 7)
     assert int(O.trace(*On)) == got[1][3][7] if got[1][3][7] != mpr.ROW_NONE else True
+
+
+@pytest.mark.parametrize("n", [8, 9, 15, 16, 17, 33, 63, 64, 65])
+@pytest.mark.parametrize("top", [7, 30, 60])
+def test_small_period_search(mpr, n, top):
+    """Searches of at most 64 states take a power in one workgroup (65: not):
+    the same period and traces as the dense search, the traces of the oracle's
+    powers, for odd and even n, empty rows, and values past the byte range."""
+    kmax = 24
+    rng = np.random.default_rng(n + top)
+    X = np.full((n, n + 5), mpr.INF, dtype=np.uint16)
+    for i in range(n - 1):  # the last row is empty
+        X[i, (i + 1) % (n - 2)] = rng.integers(0, 4)
+        X[i, rng.integers(0, n)] = rng.integers(0, top + 1)
+    X[n // 2, 0] = top
+    A = mpr.to_device(X)[:, :n]
+    want = mpr.find_period(A, kmax, slots=30, sparse=False)
+    On = O.from_u16(X[:, :n])
+    for pipeline in (False, True):
+        got = mpr.find_period(A, kmax, slots=30, sparse=True, pipeline=pipeline)
+        assert got[:3] == want[:3] and got[3].tolist() == want[3].tolist()
+    for k in (1, 2, 5):
+        assert got[3][k] == int(O.trace(*O.power_chain(On, k)))  # one value for "none" on both sides
