@@ -736,7 +736,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
     if (w.slots < (pipeline ? 3 : 2)) return MPR_ENOMEM;
     // status, a value past the bytes' range, the largest value in them
     int32_t *st = (int32_t *)&w.scal[2], *wide = st + 1, *big = (int32_t *)&w.scal[6];
-    const int64_t ld8 = round_up(n, 16);  // <= 2 w.ld: a power in bytes fits its slot
+    const int64_t ld8 = round_up(n, 16);  // row stride of a small power
     // Powers of at most 64 states: one workgroup takes one from the power
     // before and A, and needs none of what the others share.
     const bool small = bytes && n <= PERIOD_SMALL_N;
@@ -765,8 +765,10 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
     auto same_class = [&](const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, bool &eq,
                           int64_t &c) -> mpr_status {
         int64_t *out3 = &w.scal[3];
-        mpr_status e = bytes ? compare_rows_launch(X, RX, Y, RY, n, ld8 / 2, ld8 / 2, out3, s)
-                             : compare_rows_launch(X, RX, Y, RY, n, n, w.ld, out3, s);
+        const int64_t group = level_group8(n) / 2;
+        mpr_status e = small   ? compare_rows_launch(X, RX, Y, RY, n, n, ld8 / 2, ld8 / 2, out3, s)
+                       : bytes ? compare_rows_launch(X, RX, Y, RY, n, (n + 7) / 8, group, group, out3, s)
+                               : compare_rows_launch(X, RX, Y, RY, n, n, n, w.ld, out3, s);
         if (e != MPR_OK) return e;
         int64_t cmp[3];
         if (hipMemcpyAsync(cmp, out3, sizeof(cmp), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -790,10 +792,10 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         if (bytes) {
             uint8_t *N8 = (uint8_t *)Nk;
             mpr_status e = k == 1 ? MPR_OK
-                                  : sparse_step8_launch((const uint8_t *)slot_N(w, ps), ld8, n, w.plan, w.plan_bytes, N8,
+                                  : sparse_step8_launch((const uint8_t *)slot_N(w, ps), n, w.plan, w.plan_bytes, N8,
                                                         wide, big, s);
             if (e == MPR_OK)
-                e = period_rows8_launch(k == 1 ? A : nullptr, lda, N8, ld8, n, k == 1 ? nullptr : slot_R(w, ps), Rk,
+                e = period_rows8_launch(k == 1 ? A : nullptr, lda, N8, n, k == 1 ? nullptr : slot_R(w, ps), Rk,
                                         w.acc, st, wide, big, rec, k, s);
             return e;
         }

@@ -728,26 +728,28 @@ mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size
 // accumulator it folds into (cleared once; every pass leaves it clear).
 size_t period_acc_bytes();
 mpr_status period_clear_launch(void *acc, hipStream_t s);
-// The same over a power in bytes (row stride ld8, a multiple of 16): raw sums
-// with 255 = infinity (or, first = true, the u16 matrix `first`, row stride
-// lda) become level bytes, 186 - 6 v for v <= 30 and 0 for infinity, padding
-// included.  A larger value raises *wide; *big receives the largest v.
-// rec[3] = *wide.
-mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t ld8, int64_t n, const int64_t *R_in,
+// The same over a power in bytes, in groups of 8 columns: [column / 8][row]
+// [column % 8], the rows padded to whole lines, at most as large as its n rows
+// of u16.  Raw sums with 255 = infinity (or, first not null, the u16 matrix
+// `first`, row stride lda) become level bytes, 93 - 3 v for v <= 30 and 0 for
+// infinity, padding included.  A larger value raises *wide; *big receives the
+// largest v.  rec[3] = *wide.
+inline int64_t level_group8(int64_t n) { return 8 * round_up(n, 16); }  // bytes of a group
+mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t n, const int64_t *R_in,
                                int64_t *R_out, void *acc, int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
                                int64_t seq, hipStream_t s);
 // The step and that pass at once, for n <= PERIOD_SMALL_N: N the power before
-// (null: the power is A itself), O the next.
+// (null: the power is A itself), O the next, level bytes in rows of ld8 >= n.
 constexpr int64_t PERIOD_SMALL_N = 64;
 mpr_status period_small_launch(const u16 *A, int64_t lda, const uint8_t *N, uint8_t *O, int64_t ld8, int64_t n,
                                const int64_t *R_in, int64_t *R_out, int64_t *rec, int64_t seq, hipStream_t s);
-// rowops.hip: exact compare of two canonical forms up to a scalar shift, n rows
-// of `cols` values.
-mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t cols,
-                               int64_t ld, int64_t *out3, hipStream_t s);
+// rowops.hip: exact compare of two canonical forms up to a scalar shift, `rows`
+// <= n rows of `cols` values and n offsets.
+mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t rows,
+                               int64_t cols, int64_t ld, int64_t *out3, hipStream_t s);
 // sparse.hip: the compressed-K step from level bytes to raw bytes; raises
 // *wide when a block can not be decided from values up to *big.
-mpr_status sparse_step8_launch(const uint8_t *N, int64_t ld8, int64_t n, void *ws, size_t bytes, uint8_t *O,
+mpr_status sparse_step8_launch(const uint8_t *N, int64_t n, void *ws, size_t bytes, uint8_t *O,
                                int32_t *wide, const int32_t *big, hipStream_t s);
 mpr_status period_rows_launch(const u16 *src, int64_t lds_, u16 *dst, int64_t ldd, int64_t n, const int64_t *R_in,
                               int64_t *R_out, bool raw, void *acc, int32_t *st, int64_t *rec, int64_t seq, hipStream_t s);

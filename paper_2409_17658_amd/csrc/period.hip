@@ -236,169 +236,230 @@ __global__ __launch_bounds__(RT) void period_rows_kernel(const u16 *src, int64_t
     period_fold(x, refuse, acc, st, nullptr, rec, seq, &last);
 }
 
-// The same in bytes (level bytes, sparse.hip), a wave per row: lane t takes
-// the 16 columns at 16 t, 16 t + 1024, ..., NCH of them in registers (0: the
-// row is read twice).  FIRST: the source is the u16 matrix X.  *big receives
-// the largest canonical value, for the step that reads it.  Four rows share
-// one fold: with one each, the atomics bound the pass (m = 9: 300 us).
-template <int NCH, bool FIRST>
-__global__ __launch_bounds__(RT) void period_rows8_kernel(const u16 *X, int64_t ldx, uint8_t *N, int64_t ld8, int64_t n,
-                                                          const int64_t *R_in, int64_t *R_out, PeriodAcc *acc,
-                                                          int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
-                                                          int64_t seq)
+// The same in bytes (level bytes in column groups, sparse.hip), 16 rows to a
+// block, whose bytes of a group are one 128-byte line: a lane takes 2 rows of
+// 8 columns, 8 lanes a line, NCH groups a thread in registers (0: read
+// twice).  FIRST: the source is the u16 matrix X.  *big receives the largest
+// canonical value, for the step that reads it.  With a row to a fold, the
+// atomics bound the pass (m = 9: 300 us).
+constexpr int GROWS = 16;
+template <int T, int NCH, bool FIRST>
+__global__ __launch_bounds__(T) void period_rows8_kernel(const u16 *X, int64_t ldx, uint8_t *N, int64_t group8, int64_t n,
+                                                         const int64_t *R_in, int64_t *R_out, PeriodAcc *acc,
+                                                         int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
+                                                         int64_t seq)
 {
-    __shared__ RowPart part[RT / 64];
-    __shared__ int refused[RT / 64], most[RT / 64];
+    constexpr int W = T / 64, GSTEP = T / 8;  // groups of a sweep
+    __shared__ uint32_t least[W][GROWS], most[W][GROWS], diag[GROWS];
+    __shared__ uint64_t hash[W][GROWS];
     __shared__ int last;
-    constexpr u16 INFV = FIRST ? 0xFFFF : 0xFF;
-    constexpr int W = FIRST ? 8 : 4;  // dwords of 16 columns
-    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-    const int64_t i = (int64_t)blockIdx.x * (RT / 64) + w;
-    if (lane == 0) {
-        part[w] = RowPart{0, 0, 0, ROW_NONE, ROW_NONE};
-        refused[w] = most[w] = 0;
+    const int t = (int)threadIdx.x, lane = t & 63, w = t >> 6, pr = t & 7;
+    const int64_t i0 = (int64_t)blockIdx.x * GROWS, i = i0 + 2 * pr, groups = (n + 7) / 8;
+    // a sweep's first byte is the same for all threads; 127 groups span 32 bits
+    const uint32_t at = (uint32_t)(i * 8 + (t >> 3) * group8);
+    if (t < GROWS) {
+        const int64_t d = i0 + t;
+        uint32_t v = 0xFFFF;
+        if (d < n) {
+            v = FIRST ? (uint32_t)glob(X)[d * ldx + d] : (uint32_t)glob(N)[(d >> 3) * group8 + d * 8 + (d & 7)];
+            if (!FIRST && v == 0xFF) v = 0xFFFF;
+        }
+        diag[t] = v;
     }
-    if (i < n) {  // wave-uniform
-        const gu16 *xrow = glob(X) + (FIRST ? i * ldx : 0);
-        __attribute__((address_space(1))) uint8_t *row = glob(N) + i * ld8;
-        auto load = [&](int64_t c, uint32_t d[W]) {
-            if constexpr (FIRST) {
-                const uint4 inf = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-                const uint4 a = row8(xrow, c, n), b = c + 8 < n ? row8(xrow, c + 8, n) : inf;
+    // even and odd columns 2 q, 2 q + 1 of 4: u[2 row + half] = columns 4 half ..
+    struct Piece {
+        u16x2 ev[4], od[4];
+    };
+    typedef __attribute__((address_space(1))) u32x4 piece_bytes;
+    auto split = [&](u32x4 d) {
+        Piece x;
+        const uint32_t u[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    d[q] = comp(a, q);
-                    d[4 + q] = comp(b, q);
+        for (int q = 0; q < 4; q++) {
+            x.ev[q] = as_u16x2(u[q] & 0x00FF00FFu);
+            x.od[q] = as_u16x2(u[q] >> 8 & 0x00FF00FFu);
+        }
+        return x;
+    };
+    auto first = [&](int64_t g) {
+        Piece x;
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            uint4 v = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+            if (i + r < n) v = row8(glob(X) + (i + r) * ldx, g * 8, n);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const uint32_t lo = h ? v.z : v.x, hi = h ? v.w : v.y;
+                x.ev[2 * r + h] = as_u16x2(__builtin_amdgcn_perm(hi, lo, 0x05040100u));
+                x.od[2 * r + h] = as_u16x2(__builtin_amdgcn_perm(hi, lo, 0x07060302u));
+            }
+        }
+        return x;
+    };
+    constexpr u16 INFV = FIRST ? 0xFFFF : 0xFF;
+    u16x2 mn[2], mx[2];  // mx: largest finite value + 1 (infinity + 1 is 0)
+    mn[0] = mn[1] = (u16x2){0xFFFF, 0xFFFF};
+    mx[0] = mx[1] = (u16x2){0, 0};
+    auto fold = [&](const Piece &x) {
+        const u16x2 one = {1, 1}, mask = {INFV, INFV};
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            mn[q / 2] = min2(mn[q / 2], min2(x.ev[q], x.od[q]));
+            mx[q / 2] = __builtin_elementwise_max(mx[q / 2], __builtin_elementwise_max((u16x2)((x.ev[q] + one) & mask),
+                                                                                      (u16x2)((x.od[q] + one) & mask)));
+        }
+    };
+    const int64_t g0 = t >> 3;
+    auto piece = [&](int64_t sweep) { return (piece_bytes *)(glob(N) + sweep * group8 + at); };
+    u32x4 keep[NCH > 0 ? NCH : 1];
+    if constexpr (NCH > 0) {
+#pragma unroll
+        for (int k = 0; k < NCH; k++) {
+            const int64_t g = g0 + (int64_t)k * GSTEP;
+            keep[k] = (u32x4){0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+            if (g < groups) keep[k] = *piece((int64_t)k * GSTEP);
+        }
+#pragma unroll
+        for (int k = 0; k < NCH; k++) {
+            fold(split(keep[k]));
+            __builtin_amdgcn_sched_barrier(0);  // else many are split at once and their registers spill
+        }
+    } else {
+        for (int64_t g = g0; g < groups; g += GSTEP) {
+            if constexpr (FIRST)
+                fold(first(g));
+            else
+                fold(split(*piece(g - g0)));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 2; r++) {
+        uint32_t m = min((uint32_t)mn[r].x, (uint32_t)mn[r].y), top1 = max((uint32_t)mx[r].x, (uint32_t)mx[r].y);
+        for (int off = 8; off < 64; off <<= 1) {
+            m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
+            top1 = max(top1, (uint32_t)__shfl_xor((int)top1, off, 64));
+        }
+        if (lane < 8) {
+            least[w][2 * pr + r] = m;
+            most[w][2 * pr + r] = top1;
+        }
+    }
+    __syncthreads();
+    uint32_t m[2];
+    u16 base_of[2];
+#pragma unroll
+    for (int r = 0; r < 2; r++) {
+        m[r] = least[0][2 * pr + r];
+        for (int k = 1; k < W; k++) m[r] = min(m[r], least[k][2 * pr + r]);
+        // v = x - m (infinity apart) as the level byte 93 - 3 v
+        base_of[r] = (u16)(LV_BIAS / 2 + LV_STEP / 2 * m[r]);
+    }
+    uint64_t h[2] = {0, 0};
+    auto finish = [&](const Piece &x, int64_t g) {
+        constexpr u16 mul = (u16)(0u - LV_STEP / 2);
+        uint32_t o[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const u16 b = base_of[q / 2];
+            auto image = [&](u16x2 v) {
+                const u16x2 e = v * (u16x2){mul, mul} + (u16x2){b, b};
+                if constexpr (FIRST) {
+                    return (u16x2){(u16)(v.x == INFV ? 0 : e.x & 0xFF), (u16)(v.y == INFV ? 0 : e.y & 0xFF)};
+                } else {
+                    // all ones where v is 255: only there v + 1 carries into bit 8
+                    const u16x2 inf = (u16x2){0, 0} - (u16x2)((v + (u16x2){1, 1}) >> (u16x2){8, 8});
+                    return (u16x2)(e & ~inf & (u16x2){0xFF, 0xFF});
                 }
-            } else {
-                const u32x4 v = *(const __attribute__((address_space(1))) u32x4 *)(row + c);
-                d[0] = v.x;
-                d[1] = v.y;
-                d[2] = v.z;
-                d[3] = v.w;
-            }
-        };
-        // values 4q, 4q + 2 and 4q + 1, 4q + 3 of 16 columns
-        auto split = [&](const uint32_t d[W], int q, u16x2 &ev, u16x2 &od) {
-            if constexpr (FIRST) {
-                ev = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x05040100u));
-                od = as_u16x2(__builtin_amdgcn_perm(d[2 * q + 1], d[2 * q], 0x07060302u));
-            } else {
-                ev = as_u16x2(d[q] & 0x00FF00FFu);
-                od = as_u16x2(d[q] >> 8 & 0x00FF00FFu);
-            }
-        };
-        uint32_t keep[NCH > 0 ? NCH : 1][W];
-        u16x2 mn = {0xFFFF, 0xFFFF}, mx = {0, 0};  // mx: largest finite value + 1 (infinity + 1 is 0)
-        auto fold = [&](const uint32_t d[W]) {
-            const u16x2 one = {1, 1}, mask = {INFV, INFV};
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                u16x2 ev, od;
-                split(d, q, ev, od);
-                mn = min2(mn, min2(ev, od));
-                mx = __builtin_elementwise_max(mx, __builtin_elementwise_max((u16x2)((ev + one) & mask),
-                                                                             (u16x2)((od + one) & mask)));
-            }
-        };
-        const int64_t c0 = (int64_t)lane * 16;
-        if constexpr (NCH > 0) {
-#pragma unroll
-            for (int k = 0; k < NCH; k++) {
-                const int64_t c = c0 + (int64_t)k * 1024;
-#pragma unroll
-                for (int q = 0; q < W; q++) keep[k][q] = 0xFFFFFFFFu;
-                if (c < n) load(c, keep[k]);
-            }
-#pragma unroll
-            for (int k = 0; k < NCH; k++) fold(keep[k]);
-        } else {
-            for (int64_t c = c0; c < n; c += 1024) {
-                load(c, keep[0]);
-                fold(keep[0]);
-            }
+            };
+            o[q] = as_u32(image(x.ev[q])) | as_u32(image(x.od[q])) << 8;
+            if (i + q / 2 >= n) o[q] = 0;  // rows past n: infinite, as two powers are compared with them
         }
-        uint32_t diag = FIRST ? (uint32_t)xrow[i] : (uint32_t)row[i];
-        if (diag == INFV) diag = 0xFFFFu;
-        uint32_t m = wave_min_u32(min((uint32_t)mn.x, (uint32_t)mn.y));
-        const uint32_t top1 = ~wave_min_u32(~max((uint32_t)mx.x, (uint32_t)mx.y));  // largest finite value + 1, or 0
-        if (m == INFV) m = 0xFFFFu;
-        // v = x - m (infinity apart) as the level byte 186 - 6 v
-        const u16 base = (u16)(LV_BIAS + LV_STEP * m), mul = (u16)(0u - LV_STEP);
-        uint64_t h = 0;
-        auto image = [&](u16x2 x) {
-            const u16x2 e = x * (u16x2){mul, mul} + (u16x2){base, base};
-            if constexpr (FIRST) {
-                return (u16x2){(u16)(x.x == INFV ? 0 : e.x & 0xFF), (u16)(x.y == INFV ? 0 : e.y & 0xFF)};
-            } else {
-                // all ones where x is 255: only there x + 1 carries into bit 8
-                const u16x2 inf = (u16x2){0, 0} - (u16x2)((x + (u16x2){1, 1}) >> (u16x2){8, 8});
-                return (u16x2)(e & ~inf & (u16x2){0xFF, 0xFF});
-            }
-        };
-        auto finish = [&](const uint32_t d[W], int64_t c) {
-            uint32_t x[4];
+        const uint32_t k = ((uint32_t)g + 1u) * 0x9E3779B1u;
+        h[0] += (uint64_t)(o[0] + k) * (o[1] + (k ^ 0x85EBCA6Bu));
+        h[1] += (uint64_t)(o[2] + k) * (o[3] + (k ^ 0x85EBCA6Bu));
+        *piece(g - g0) = (u32x4){o[0], o[1], o[2], o[3]};
+    };
+    if constexpr (NCH > 0) {
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                u16x2 ev, od;
-                split(d, q, ev, od);
-                x[q] = as_u32(image(ev)) | as_u32(image(od)) << 8;
-            }
-            h += nh4(x, (uint32_t)(c >> 4));
-            *(__attribute__((address_space(1))) u32x4 *)(row + c) = (u32x4){x[0], x[1], x[2], x[3]};
-        };
-        if constexpr (NCH > 0) {
+        for (int k = 0; k < NCH; k++) {
+            const int64_t g = g0 + (int64_t)k * GSTEP;
+            asm volatile("" : "+v"(keep[k]));  // split again rather than kept split, in twice the registers
+            if (g < groups) finish(split(keep[k]), g);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        for (int64_t g = g0; g < groups; g += GSTEP) {
+            if constexpr (FIRST)
+                finish(first(g), g);
+            else
+                finish(split(*piece(g - g0)), g);
+        }
+    }
 #pragma unroll
-            for (int k = 0; k < NCH; k++) {
-                const int64_t c = c0 + (int64_t)k * 1024;
-                if (c < n) finish(keep[k], c);
-            }
-        } else {
-            for (int64_t c = c0; c < n; c += 1024) {
-                load(c, keep[0]);
-                finish(keep[0], c);
-            }
-        }
-        h = wave_sum_u64(h);
-        if (lane == 0) {
-            part[w] = period_row(i, m, diag, h, R_in, R_out);
-            const uint32_t v = top1 ? top1 - 1 - m : 0;  // the row's largest canonical value
-            refused[w] = (FIRST && top1 > FMAX16 + 1u ? 1 : 0) | (v > LV_MAX ? 2 : 0);
-            most[w] = (int)min(v, (uint32_t)LV_MAX);
-        }
+    for (int r = 0; r < 2; r++) {
+        for (int off = 8; off < 64; off <<= 1) h[r] += __shfl_xor(h[r], off, 64);
+        if (lane < 8) hash[w][2 * pr + r] = h[r];
     }
     __syncthreads();
     RowPart x{0, 0, 0, ROW_NONE, ROW_NONE};
     int refuse = 0;
-    if (threadIdx.x == 0) {
-        int v = 0;
-        for (int k = 0; k < RT / 64; k++) {
-            x.hash += part[k].hash;
-            x.offsets += part[k].offsets;
-            x.keys += part[k].keys;
-            x.least = min(x.least, part[k].least);
-            x.trace = min(x.trace, part[k].trace);
-            refuse |= refused[k];
-            v = max(v, most[k]);
+    if (w == 0) {  // lane t: row i0 + t
+        const int64_t row = i0 + lane;
+        uint32_t v = 0;
+        if (lane < GROWS && row < n) {
+            uint32_t mr = least[0][lane], top1 = most[0][lane];
+            uint64_t hr = hash[0][lane];
+            for (int k = 1; k < W; k++) {
+                mr = min(mr, least[k][lane]);
+                top1 = max(top1, most[k][lane]);
+                hr += hash[k][lane];
+            }
+            if (mr == INFV) mr = 0xFFFFu;
+            x = period_row(row, mr, diag[lane], hr, R_in, R_out);
+            v = top1 ? top1 - 1 - mr : 0;  // the row's largest canonical value
+            refuse = (FIRST && top1 > FMAX16 + 1u ? 1 : 0) | (v > LV_MAX ? 2 : 0);
         }
+        for (int off = GROWS / 2; off > 0; off >>= 1) {
+            x.hash += __shfl_xor(x.hash, off, 64);
+            x.offsets += __shfl_xor(x.offsets, off, 64);
+            x.keys += __shfl_xor(x.keys, off, 64);
+            x.least = min(x.least, (int64_t)__shfl_xor((long long)x.least, off, 64));
+            x.trace = min(x.trace, (int64_t)__shfl_xor((long long)x.trace, off, 64));
+            v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
+        }
+        refuse = (__any(refuse & 1) ? 1 : 0) | (__any(refuse & 2) ? 2 : 0);
+        v = min(v, LV_MAX);
         // read by the next step, a later kernel; few blocks raise it
-        if (v > __hip_atomic_load(big, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(big, v);
+        if (lane == 0 && (int)v > __hip_atomic_load(big, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(big, (int)v);
     }
     period_fold(x, refuse, acc, st, wide, rec, seq, &last);
 }
 
-mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t ld8, int64_t n, const int64_t *R_in,
+mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t n, const int64_t *R_in,
                                int64_t *R_out, void *acc, int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
                                int64_t seq, hipStream_t s)
 {
     if (n > INT32_MAX) return MPR_EUNSUPPORTED;
-    auto kernel = first          ? period_rows8_kernel<0, true>
-                  : n <= 1024     ? period_rows8_kernel<1, false>
-                  : n <= 8 * 1024 ? period_rows8_kernel<8, false>
-                  : n <= 24 * 1024 ? period_rows8_kernel<24, false>
-                                   : period_rows8_kernel<0, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 3) / 4)), dim3(RT), 0, s, first, lda, N, ld8, n, R_in, R_out, (PeriodAcc *)acc,
-                       st, wide, big, rec, seq);
+    const dim3 grid((unsigned)((n + GROWS - 1) / GROWS));
+    const int64_t group8 = level_group8(n), groups = (n + 7) / 8;
+#define ROWS8(T, NCH, FIRST)                                                                                           \
+    hipLaunchKernelGGL((period_rows8_kernel<T, NCH, FIRST>), grid, dim3(T), 0, s, first, lda, N, group8, n, R_in, R_out, \
+                       (PeriodAcc *)acc, st, wide, big, rec, seq)
+    // as many threads as keep the registers of a row's groups within 128
+    if (first)
+        ROWS8(512, 0, true);
+    else if (groups <= 2 * 64)
+        ROWS8(512, 2, false);
+    else if (groups <= 4 * 128)
+        ROWS8(1024, 4, false);
+    else if (groups <= 16 * 64)
+        ROWS8(512, 16, false);
+    else if (groups <= 22 * 128)
+        ROWS8(1024, 22, false);
+    else
+        ROWS8(1024, 0, false);
+#undef ROWS8
     return check_launch();
 }
 
@@ -431,7 +492,7 @@ __global__ __launch_bounds__(SMALL_T) void period_small_kernel(const u16 *A, int
         for (int e = t; e < n * n; e += SMALL_T) {
             const int i = e / n, c = e - i * n;
             const uint32_t b = glob(N)[i * ld8 + c];
-            l[i][c] = b ? (u16)((LV_BIAS - b) * 43 >> 8) : INF16;  // v <= 30: 43 / 256 is 1 / 6 there
+            l[i][c] = b ? (u16)((LV_BIAS / 2 - b) * 86 >> 8) : INF16;  // v <= 30: 86 / 256 is 1 / 3 there
         }
     }
     __syncthreads();
@@ -450,7 +511,7 @@ __global__ __launch_bounds__(SMALL_T) void period_small_kernel(const u16 *A, int
             m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
             top1 = max(top1, (uint32_t)__shfl_xor((int)top1, off, 64));
         }
-        auto image = [&](uint32_t x) { return x == 0xFFFFu ? 0u : (LV_BIAS - LV_STEP * (x - m)) & 0xFFu; };
+        auto image = [&](uint32_t x) { return x == 0xFFFFu ? 0u : (LV_BIAS / 2 - LV_STEP / 2 * (x - m)) & 0xFFu; };
         const uint32_t x = image(v.x) | image(v.y) << 8;
         uint64_t h = mix64((uint64_t)(p + 1) << 32 | x);
         for (int off = HP / 2; off > 0; off >>= 1) h += __shfl_xor(h, off, 64);

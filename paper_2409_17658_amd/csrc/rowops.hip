@@ -483,12 +483,13 @@ mpr_status class_hash_launch(const uint64_t *row_hash, const int64_t *R, int64_t
 // out3[0] = number of differing entries of N plus rows whose emptiness
 // differs, out3[1] / out3[2] = min / max of RY[i] - RX[i] over non-empty rows.
 __global__ __launch_bounds__(RB) void compare_kernel(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY,
-                                                     int64_t n, int64_t cols, int64_t ld, int vec, int64_t *out3)
+                                                     int64_t n, int64_t rows, int64_t cols, int64_t ld, int vec,
+                                                     int64_t *out3)
 {
     __shared__ int64_t sh[RB / 64];
     int64_t diff = 0, lo = ROW_NONE, hi = -ROW_NONE;
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        for (int64_t c = (int64_t)threadIdx.x * 8; c < cols; c += RB * 8) {
+        for (int64_t c = (int64_t)threadIdx.x * 8; i < rows && c < cols; c += RB * 8) {
             const uint4 x = chunk8(glob(X) + i * ld, c, cols, vec != 0), y = chunk8(glob(Y) + i * ld, c, cols, vec != 0);
 #pragma unroll
             for (int e = 0; e < 4; e++) {
@@ -520,15 +521,15 @@ __global__ void compare_init_kernel(int64_t *out3)
     out3[2] = -ROW_NONE;
 }
 
-mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t cols,
-                          int64_t ld, int64_t *out3, hipStream_t s)
+mpr_status compare_rows_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n, int64_t rows,
+                               int64_t cols, int64_t ld, int64_t *out3, hipStream_t s)
 {
     hipLaunchKernelGGL(compare_init_kernel, dim3(1), dim3(1), 0, s, out3);
     mpr_status e = check_launch();
     if (e != MPR_OK || n == 0) return e;
     const int vec = aligned16(X) && aligned16(Y) && ld % 8 == 0;
     const unsigned blocks = (unsigned)std::min<int64_t>(n, 2048);  // three atomics each
-    hipLaunchKernelGGL(compare_kernel, dim3(blocks), dim3(RB), 0, s, X, RX, Y, RY, n, cols, ld, vec, out3);
+    hipLaunchKernelGGL(compare_kernel, dim3(blocks), dim3(RB), 0, s, X, RX, Y, RY, n, rows, cols, ld, vec, out3);
     return check_launch();
 }
 

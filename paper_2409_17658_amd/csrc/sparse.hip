@@ -665,41 +665,51 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
 
 // ------------------------------------------- the step in bytes
 // For the period search, which owns its powers: a canonical value v <= 30 is
-// kept as the exponent field 186 - 6 v of its image in one byte (0 for
-// infinity), and a raw result as the byte t (255 for infinity).  A step reads
-// and writes half the bytes, and the image of two values is a byte
-// permutation and a shift.  At m = 9 the 128 rows of N that a panel reads are
+// kept as the byte 93 - 3 v (0 for infinity), half the exponent field of its
+// image and so the image's upper byte (the lower is 0), and a raw result as
+// the byte t (255 for infinity).  A step reads and writes half the bytes, and
+// the image of two values is one byte permutation.  At m = 9 the 128 rows of N that a panel reads are
 // 2.8 MB and fit an XCD's L2.  A result that the levels do not prove raises a
 // flag, and the search starts again in u16.
+// A power lies in column groups: [column / 8][row][column % 8].  The gathered
+// columns are whole groups, so the 64 rows of a wave's load are 512 bytes one
+// after the other, and the group is the same for the whole wave.  With rows
+// one after the other a load touched up to 64 lines: whole searches of m = 9
+// 79.0 ms, now 73.1, m = 8 6.63 and 6.55, m = 6 0.68 and 0.71.
 template <class C>
 struct LevelGather8 {
     gbytes *base;
-    const __attribute__((address_space(1))) int32_t *idx, *at;
-    int64_t K;
-    uint32_t off[C::A_CPT];
-    int col;
+    const int32_t *idx, *at;
+    int64_t K, group8;  // bytes of a column group
+    uint32_t off;
+    int32_t col[C::A_CPT];
     uint2 r[C::A_CPT];
-    __device__ __forceinline__ LevelGather8(const uint8_t *p, int64_t ld8, int rows, const int32_t *list, int64_t K_)
-        : base((gbytes *)p), idx(glob(list) + C::tid() % C::KC * 8), K(K_)
+    static_assert(C::GT % C::BM == 0 && C::BM % 64 == 0 && C::KC % C::A_CPT == 0, "a wave's chunk in one group");
+    static __device__ __forceinline__ int row() { return C::tid() % C::BM; }
+    static __device__ __forceinline__ int first() { return __builtin_amdgcn_readfirstlane(C::tid() / C::BM) * C::A_CPT; }
+    __device__ __forceinline__ LevelGather8(const uint8_t *p, int64_t group8_, int rows, const int32_t *list, int64_t K_)
+        : base((gbytes *)p), idx(list + first() * 8), K(K_), group8(group8_), off((uint32_t)min(row(), rows - 1) * 8u)
+    {
+    }
+    __device__ __forceinline__ void fetch()
     {
 #pragma unroll
-        for (int q = 0; q < C::A_CPT; q++)
-            off[q] = (uint32_t)min(C::tid() / C::KC + q * (C::GT / C::KC), rows - 1) * (uint32_t)ld8;
+        for (int q = 0; q < C::A_CPT; q++) col[q] = at >= idx ? at[8 * q] : 0;
     }
     __device__ __forceinline__ void seek(int64_t k0)
     {
         at = idx + k0;
-        col = k0 >= 0 ? *at : 0;
+        fetch();
     }
-    __device__ __forceinline__ void load_chunk(int q)  // a group's 8 bytes lie inside the padded row
+    __device__ __forceinline__ void load_chunk(int q)
     {
-        const u32x2 v = *(const __attribute__((address_space(1))) u32x2 *)(base + (off[q] + (uint32_t)col));
+        const u32x2 v = *(const __attribute__((address_space(1))) u32x2 *)(base + (col[q] >> 3) * group8 + off);
         r[q] = make_uint2(v.x, v.y);
     }
     __device__ __forceinline__ void advance()
     {
         at -= C::BK * C::KS;
-        col = at >= idx ? *at : 0;
+        fetch();
     }
     __device__ __forceinline__ void load()
     {
@@ -709,20 +719,20 @@ struct LevelGather8 {
     }
     __device__ __forceinline__ void load_tail(int64_t k0)  // the list ends at K, a multiple of SBK = 32
     {
-        const bool in = k0 + C::tid() % C::KC * 8 < K;
-        col = in ? idx[k0] : 0;
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) {
+            const bool in = k0 + (first() + q) * 8 < K;
+            col[q] = in ? idx[k0 + 8 * q] : 0;
             load_chunk(q);
             if (!in) r[q] = make_uint2(0, 0);
         }
     }
     __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
-        auto image = [](uint32_t w, uint32_t sel) { return __builtin_amdgcn_perm(w, w, sel) << 7; };
-        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
-            make_uint4(image(r[q].x, 0x0C010C00u), image(r[q].x, 0x0C030C02u), image(r[q].y, 0x0C010C00u),
-                       image(r[q].y, 0x0C030C02u));
+        auto image = [](uint32_t w, uint32_t sel) { return __builtin_amdgcn_perm(w, w, sel); };
+        as[(first() + q) * C::PA + row()] =
+            make_uint4(image(r[q].x, 0x010C000Cu), image(r[q].x, 0x030C020Cu), image(r[q].y, 0x010C000Cu),
+                       image(r[q].y, 0x030C020Cu));
     }
 };
 
@@ -732,7 +742,7 @@ struct LevelGather8 {
 // of the first's stores, left too few blocks: 8.40 and 91.8 ms.
 constexpr int PANELS8 = 2;
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level8_kernel(
-    const uint8_t *__restrict__ N, int64_t ld8, int64_t n, const int64_t *__restrict__ off,
+    const uint8_t *__restrict__ N, int64_t group8, int64_t n, const int64_t *__restrict__ off,
     const int32_t *__restrict__ idx, const u16 *__restrict__ Bp, uint8_t *__restrict__ O, int tiles_m, int nblk,
     int64_t cap, int32_t *wide, const int32_t *big)
 {
@@ -747,7 +757,7 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;
     LevelAcc<C> acc;
     if (K > 0) {
-        LevelGather8<C> aop(N + m0 * ld8, ld8, rows, idx + kbeg, K);
+        LevelGather8<C> aop(N + m0 * 8, group8, rows, idx + kbeg, K);
         LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
         level_kloop<C>(K, aop, bop, lds, acc);
         if (!level_sure<C>(acc, rows, cols)) {
@@ -771,7 +781,7 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
 #pragma unroll
                 for (int r = 0; r < 4; r++) acc.v[mi][ni][r] = 0;
     }
-    __attribute__((address_space(1))) uint8_t *out = glob(O) + m0 * ld8 + j0;
+    __attribute__((address_space(1))) uint8_t *out = glob(O) + (j0 >> 3) * group8 + m0 * 8;
 #pragma unroll
     for (int mi = 0; mi < C::MI; mi++) {
         const int row = level_row<C>(mi);
@@ -781,8 +791,8 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
             uint32_t x = 0;
 #pragma unroll
             for (int r = 0; r < 4; r++) x |= (level_value(acc.v[mi][ni][r]) & 0xFFu) << (8 * r);
-            if (row < rows && j0 + col < ld8)  // columns past n, up to the stride, are infinite
-                *(__attribute__((address_space(1))) uint32_t *)(out + (int64_t)row * ld8 + col) = x;
+            if (row < rows && j0 + col < (n + 7 & ~(int64_t)7))  // columns past n, up to the group's end, are infinite
+                *(__attribute__((address_space(1))) uint32_t *)(out + (col >> 3) * group8 + row * 8 + (col & 7)) = x;
         }
     }
 }
@@ -908,13 +918,13 @@ static mpr_status level_step(const LevelStep &q, const SparsePlan &p, int vec, i
     return check_launch();
 }
 
-mpr_status sparse_step8_launch(const uint8_t *N, int64_t ld8, int64_t n, void *ws, size_t bytes, uint8_t *O,
+mpr_status sparse_step8_launch(const uint8_t *N, int64_t n, void *ws, size_t bytes, uint8_t *O,
                                int32_t *wide, const int32_t *big, hipStream_t s)
 {
     const SparsePlan p = carve_plan(ws, n, bytes);
     const int64_t tiles_m = (n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
     if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
-    hipLaunchKernelGGL(sp_level8_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, N, ld8, n,
+    hipLaunchKernelGGL(sp_level8_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, N, level_group8(n), n,
                        (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, O, (int)tiles_m, (int)p.nblk,
                        p.cap, wide, big);
     return check_launch();

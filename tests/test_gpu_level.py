@@ -210,3 +210,21 @@ def test_small_period_search(mpr, n, top):
         assert got[:3] == want[:3] and got[3].tolist() == want[3].tolist()
     for k in (1, 2, 5):
         assert got[3][k] == int(O.trace(*O.power_chain(On, k)))  # one value for "none" on both sides
+
+
+@pytest.mark.parametrize("n", [66, 80, 1023, 1025, 4095, 4097, 8193])
+def test_period_search_byte_passes(mpr, n):
+    """The pass over a power in bytes at the ends of the sizes of its forms
+    (2, 4 and 16 groups a thread, and more), with ragged last groups and rows:
+    traces and period equal the dense search's."""
+    kmax = 7
+    rng = np.random.default_rng(n)
+    X = np.full((n, n), mpr.INF, dtype=np.uint16)
+    r = np.arange(n - 1)  # the last row is empty
+    X[r, (r + 1) % 5 + (r // 5) * 5 % (n - 5)] = rng.integers(0, 4, n - 1)
+    X[r, rng.integers(0, n, n - 1)] = rng.integers(0, 6, n - 1)
+    A = mpr.to_device(X)
+    want = mpr.find_period(A, kmax, slots=9, sparse=False)
+    got = mpr.find_period(A, kmax, slots=9, sparse=True, pipeline=True)
+    assert got[:3] == want[:3] and got[3].tolist() == want[3].tolist()
+    assert any(t != mpr.ROW_NONE for t in got[3][1:])
