@@ -11,8 +11,8 @@
 // and for the offsets a linear sum, whose shift by the least offset can be
 // taken off at the end.  Each block folds its row into one of PSLOTS records
 // and the last block combines them, where two more kernels of one block used
-// to read n words each (m = 8: 68 + 13 + 9 us, in bytes 31; m = 9: 410 + 51 +
-// 24 us, in bytes 280; m = 3: 6.0 + 3.4 + 3.3 us and a copy to the host, now
+// to read n words each (m = 8: 68 + 13 + 9 us, in bytes 30; m = 9: 410 + 51 +
+// 24 us, in bytes 246; m = 3: 6.0 + 3.4 + 3.3 us and a copy to the host, now
 // within the 6.7 us of a whole power).
 #include "level.h"
 
@@ -240,8 +240,8 @@ __global__ __launch_bounds__(RT) void period_rows_kernel(const u16 *src, int64_t
 // block, whose bytes of a group are one 128-byte line: a lane takes 2 rows of
 // 8 columns, 8 lanes a line, NCH groups a thread in registers (0: read
 // twice).  FIRST: the source is the u16 matrix X.  *big receives the largest
-// canonical value, for the step that reads it.  With a row to a fold, the
-// atomics bound the pass (m = 9: 300 us).
+// canonical value, for the step that reads it.  A row to a fold left the pass
+// to its atomics (m = 8 47 us, m = 9 300; now 30 and 246, 0.96 GB at 3.9 TB/s).
 constexpr int GROWS = 16;
 template <int T, int NCH, bool FIRST>
 __global__ __launch_bounds__(T) void period_rows8_kernel(const u16 *X, int64_t ldx, uint8_t *N, int64_t group8, int64_t n,
@@ -446,7 +446,8 @@ mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_
 #define ROWS8(T, NCH, FIRST)                                                                                           \
     hipLaunchKernelGGL((period_rows8_kernel<T, NCH, FIRST>), grid, dim3(T), 0, s, first, lda, N, group8, n, R_in, R_out, \
                        (PeriodAcc *)acc, st, wide, big, rec, seq)
-    // as many threads as keep the registers of a row's groups within 128
+    // the forms keep a row's groups in registers (m = 9: 1024 threads spilled,
+    // 301 us; 512 with twice the groups each do not, 246)
     if (first)
         ROWS8(512, 0, true);
     else if (groups <= 2 * 64)
@@ -455,8 +456,8 @@ mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_
         ROWS8(1024, 4, false);
     else if (groups <= 16 * 64)
         ROWS8(512, 16, false);
-    else if (groups <= 22 * 128)
-        ROWS8(1024, 22, false);
+    else if (groups <= 44 * 64)
+        ROWS8(512, 44, false);
     else
         ROWS8(1024, 0, false);
 #undef ROWS8
