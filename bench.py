@@ -7,14 +7,16 @@ seeds 1 and 2), i.e. one (min,+) product, its row-min normalisation and the
 trace (Corollary 7) per step.  Throughput counts N^3 add+min pairs per step.
 
 Prints ONE JSON line with the value, the roofline of the dominant kernel
-(the product; VALU-bound, peak = CUs x 64 lanes x 2.4 GHz pairs/s, measured
-with HIP events on the launch stream) and the CPU oracle timed on a bounded
-sample of the same workload.
+(the product, against the matrix cores' dense bf16 peak; measured with HIP
+events on the launch stream) and the CPU oracle timed on a bounded sample of
+the same workload.
 
-The headline runs in the packed uint16 form (the library's default
-arithmetic) against the packed-int16 VALU peak; "f16_form" times the same
-step in the exact f16 form (a labelled experiment with its own peak) and a
-product whose minima all reach 2048 (its slow path).
+The headline is the product the library chooses, on the matrix cores and
+equal to the uint16 form bit for bit; pct_valu_peak sets it against the
+packed-int16 VALU peak (CUs x 64 lanes x 2.4 GHz pairs/s), which it passes.
+"u16_form" and "f16_form" time the same step in the two VALU forms, each
+with its own peak, and a product whose minima all reach 2048 (the f16 form's
+slow path).
 
 The default run then adds compact legs of the other workloads, each with
 the oracle timed on a bounded sample as its CPU baseline: config1 (m = 3,
@@ -93,12 +95,20 @@ def _events(torch, k):
     return [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(k)]
 
 
+def mfma_peak_gpairs(cus: int) -> float:
+    """Matrix-core peak in G pairs/s for the product in levels, where a pair
+    is one bf16 multiply-add: v_mfma_f32_16x16x32_bf16 does 8192 in 16 clocks
+    on each of the 4 SIMDs of a CU."""
+    return cus * 4 * 8192 / 16 * PEAK_CLOCK_GHZ
+
+
 def bench_gemm(args, mpr, torch):
-    """The headline: the N = 16384 chain step in the packed uint16 form
-    (the library's default arithmetic), against the packed-int16 VALU peak;
-    the same step in the exact f16 form is reported beside it as a labelled
-    experiment, with a product whose minima all reach 2048 (the f16 form's
-    slow path: every tile recomputed in uint16)."""
+    """The headline: the N = 16384 chain step as the library chooses it (on
+    the matrix cores), against the matrix cores' dense bf16 peak, or in the
+    VALU configuration --cfg against the packed-int16 VALU peak.  The same step
+    in the two VALU forms (packed uint16, exact f16) is reported beside it,
+    with a product whose minima all reach 2048 (the f16 form's slow path:
+    every tile recomputed in uint16)."""
     import synth
 
     n = args.n
@@ -149,13 +159,14 @@ def bench_gemm(args, mpr, torch):
     mpr.normalise(P[0], None, R)
     pairs = float(n) ** 3
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    cfg = args.cfg if args.cfg >= 0 else mpr.gemm_pick_config(n, n, n)
-    info = mpr.gemm_config_info(cfg)
+    cfg = args.cfg
+    info = mpr.gemm_config_info(cfg) if cfg >= 0 else None
     ms_step, kern_avg = timed_steps(cfg, args.steps, args.warmup)
     value = pairs / (ms_step * 1e-3) / 1e9
     achieved = pairs / (kern_avg * 1e-3) / 1e9
-    peak = valu_peak_gpairs(cus, info["arith"])
-    dtype = _dtype(info["arith"])
+    arith = info["arith"] if info else "u16"
+    peak = valu_peak_gpairs(cus, arith) if info else mfma_peak_gpairs(cus)
+    dtype = _dtype(arith)
 
     def tile_name(i):
         return "%dx%d, %dx%d per lane, %d threads, %s arithmetic" % (i["bm"], i["bn"], i["tm"], i["tn"],
@@ -167,17 +178,20 @@ def bench_gemm(args, mpr, torch):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": dtype,
         "data": "synthetic (SplitMix64 seeds 1, 2; uniform [0,15], 30% infinity)",
         "config": {"workload": "minplus chain step N=16384 uint16 (product + row-min normalisation + trace)",
-                   "n": n, "tile_config": cfg, "tile": tile_name(info),
+                   "n": n, "tile_config": cfg,
+                   "tile": tile_name(info) if info else "128x256, 64x64 per wave, 512 threads, levels as powers of two",
                    "storage": "uint16 in and out"},
-        "pct_valu_peak": round(100.0 * value / peak, 2),
-        "roofline": {"bound": "alu", "achieved": round(achieved, 1), "peak": round(peak, 1), "unit": "G pairs/s",
+        "pct_valu_peak": round(100.0 * value / valu_peak_gpairs(cus, arith), 2),
+        "roofline": {"bound": "alu" if info else "matrix cores", "achieved": round(achieved, 1), "peak": round(peak, 1), "unit": "G pairs/s",
                      "frac": round(achieved / peak, 4), "traffic": load_traffic(args.traffic_json, cfg),
                      "kernel": "gemm_kernel<%d,%d,%d,%d,%d>, %s" % (info["bm"], info["bn"], info["bk"], info["tm"],
-                                                                    info["tn"], info["arith"]),
+                                                                    info["tn"], arith)
+                     if info else "level_gemm_kernel<4,4,2,4>, exact in bf16 powers of two",
                      "kernel_avg_ms": round(kern_avg, 3),
-                     "peak_basis": "%d CUs x 64 lanes x 2.4 GHz; %s" % (
+                     "peak_basis": "%d CUs x 4 x 8192 pairs per 16 clocks (v_mfma_f32_16x16x32_bf16) x 2.4 GHz" % cus
+                     if not info else "%d CUs x 64 lanes x 2.4 GHz; %s" % (
                          cus, "v_pk_add_u16 clamp + v_pk_min_u16: 2 pairs per 2 lane-instructions"
-                         if info["arith"] == "u16" else "2 v_pk_add_f16 + 1 v_pk_minimum3_f16: 4 pairs per 3")},
+                         if arith == "u16" else "2 v_pk_add_f16 + 1 v_pk_minimum3_f16: 4 pairs per 3")},
         "input_gen_s": round(gen_s, 1),
     }
     if args.probe:
@@ -193,7 +207,16 @@ def bench_gemm(args, mpr, torch):
                         "clock_ghz": round(ghz, 3), "pairs_per_cu_clock": round(rate / (cus * ghz * 1e9), 2),
                         "nominal_pairs_per_cu_clock": round(nominal / (cus * PEAK_CLOCK_GHZ), 2)}
         out["valu_probe"] = probe
-    if args.f16_form and info["arith"] == "u16":
+    if args.f16_form and not info:
+        ucfg = mpr.gemm_pick_config(n, n, n)
+        ums, ukern = timed_steps(ucfg, max(1, args.steps // 2), max(1, args.warmup // 2))
+        upeak = valu_peak_gpairs(cus, "u16")
+        uach = pairs / (ukern * 1e-3) / 1e9
+        out["u16_form"] = {"tile_config": ucfg, "tile": tile_name(mpr.gemm_config_info(ucfg)),
+                           "ms_per_step": round(ums, 3), "kernel_avg_ms": round(ukern, 3), "achieved": round(uach, 1),
+                           "peak": round(upeak, 1), "frac": round(uach / upeak, 4),
+                           "traffic": load_traffic(args.traffic_json, ucfg)}
+    if args.f16_form and arith == "u16":
         out["f16_form"] = bench_f16_form(args, mpr, torch, timed_steps, tile_name, cus, pairs, n, L, sptr)
     if not args.skip_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline_gemm(X, Y, args.cpu_seconds)
@@ -251,7 +274,7 @@ def kernel_source_digest() -> str:
     import hashlib
 
     h = hashlib.sha256()
-    for f in ("tile.h", "gemm.hip", "common.h"):
+    for f in ("tile.h", "gemm.hip", "common.h", "level.h", "level.hip"):
         with open(os.path.join(ROOT, "paper_2409_17658_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -1068,7 +1091,7 @@ def main():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=3)
     ap.add_argument("--n", type=int, default=16384)
-    ap.add_argument("--cfg", type=int, default=-1, help="tile configuration (-1: tile table)")
+    ap.add_argument("--cfg", type=int, default=-1, help="VALU tile configuration (-1: the library's choice)")
     ap.add_argument("--workload", default="gemm",
                     choices=["gemm", "config2", "config3", "config4", "serve", "m10", "m11"])
     ap.add_argument("--m11-kmax", type=int, default=45)

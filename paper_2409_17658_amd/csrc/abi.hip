@@ -180,7 +180,7 @@ static mpr_status gemm_norm_impl(int64_t M, int64_t N, int64_t K, const u16 *A, 
     }
     e = product_launch(-1, M, N, K, A, lda, B, ldb, C, ldc, s);
     if (e != MPR_OK) return e;
-    return normalise_launch(M, N, C, ldc, Ra, Rb ? s_scalar : nullptr, Rc, st, nullptr, s);
+    return normalise_launch(M, N, C, ldc, Ra, Rb ? s_scalar : nullptr, Rc, st, s);
 }
 
 static size_t gemm_norm_ws(int64_t K, int64_t N, int64_t *ldp_out)
@@ -284,7 +284,7 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
             r = MPR_EHIP;
     } else {
         r = copy_launch(A, lda, buf[b], ld[b], n, n, s);
-        if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], nullptr, nullptr, R_out, st, nullptr, s);
+        if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], nullptr, nullptr, R_out, st, s);
     }
     if (r == MPR_OK && sparse && e >= 2) r = sparse_plan_launch(A, n, lda, w.plan, w.plan_bytes, st, s);
     if (r == MPR_OK && w.low && e >= 2 &&
@@ -299,14 +299,14 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
             r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, st, s) : level_step_launch(p, st, s);
             b = nb;
         }
-        if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, nullptr, s);
+        if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, s);
         return r;
     }
     for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
         const int nb = b ^ 1;
         r = sparse ? sparse_step_launch(buf[b], ld[b], n, w.plan, w.plan_bytes, buf[nb], ld[nb], s)
                    : product_launch(-1, n, n, n, buf[b], ld[b], A, lda, buf[nb], ld[nb], s);
-        if (r == MPR_OK) r = normalise_launch(n, n, buf[nb], ld[nb], R_out, nullptr, R_out, st, nullptr, s);
+        if (r == MPR_OK) r = normalise_launch(n, n, buf[nb], ld[nb], R_out, nullptr, R_out, st, s);
         b = nb;
     }
     return r;
@@ -319,7 +319,7 @@ static mpr_status power_square(const u16 *A, int64_t n, int64_t lda, int64_t e, 
     int64_t *RP = w.RP, *Racc = w.Racc, *RC = w.RC;
     const int64_t ld = w.ld;
     mpr_status r = copy_launch(A, lda, P, ld, n, n, s);
-    if (r == MPR_OK) r = normalise_launch(n, n, P, ld, nullptr, nullptr, RP, st, nullptr, s);
+    if (r == MPR_OK) r = normalise_launch(n, n, P, ld, nullptr, nullptr, RP, st, s);
     bool have = false;
     while (r == MPR_OK) {
         if (e & 1) {
@@ -543,7 +543,7 @@ extern "C" mpr_status mpr_normalise(int64_t M, int64_t N, uint16_t *C, int64_t l
     if (M < 0 || N < 0 || (M && (!C || !R_out)) || !ld_ok(ldc, N)) return MPR_EINVAL;
     mpr_status e = ensure_init();
     if (e != MPR_OK) return e;
-    return normalise_launch(M, N, C, ldc, R_in, nullptr, R_out, d_status, nullptr, as_stream(stream));
+    return normalise_launch(M, N, C, ldc, R_in, nullptr, R_out, d_status, as_stream(stream));
 }
 
 extern "C" mpr_status mpr_gemm_norm_workspace_size(int64_t K, int64_t N, size_t *bytes_host)

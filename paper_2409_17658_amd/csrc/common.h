@@ -77,7 +77,7 @@ __device__ __forceinline__ uint32_t comp(const uint4 &v, int q)
 }
 
 // SplitMix64 finaliser (Steele, Lea, Flood 2014), used only to hash the
-// class of a power for the period search.
+// class of a power for the period search (period.hip).
 __device__ __forceinline__ uint64_t mix64(uint64_t z)
 {
     z ^= z >> 30;
@@ -149,17 +149,12 @@ mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, s
 // rowops.hip
 mpr_status validate_launch(const u16 *X, int64_t rows, int64_t cols, int64_t ld, int32_t *st, hipStream_t s);
 mpr_status normalise_launch(int64_t M, int64_t N, u16 *C, int64_t ldc, const int64_t *R_in,
-                            const int64_t *add_scalar, int64_t *R_out, int32_t *st,
-                            uint64_t *row_hash, hipStream_t s);
+                            const int64_t *add_scalar, int64_t *R_out, int32_t *st, hipStream_t s);
 mpr_status copy_launch(const u16 *src, int64_t lds, u16 *dst, int64_t ldd, int64_t rows, int64_t cols,
                        hipStream_t s);
 mpr_status fold_launch(const u16 *B, int64_t ldb, const int64_t *Rb, int64_t K, int64_t N, u16 *Bp,
                        int64_t ldp, int64_t *s_out, int32_t *st, hipStream_t s);
 mpr_status trace_launch(const u16 *N, int64_t n, int64_t ld, const int64_t *R, int64_t *out, hipStream_t s);
-mpr_status class_hash_launch(const uint64_t *row_hash, const int64_t *R, int64_t n, uint64_t *out,
-                             hipStream_t s);
-mpr_status compare_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n,
-                          int64_t ld, int64_t *out3, hipStream_t s);
 mpr_status fill_i32_launch(int32_t *p, int64_t count, int32_t v, hipStream_t s);
 mpr_status trace_product_launch(const u16 *X, const int64_t *RX, const u16 *Y, const int64_t *RY, int64_t n,
                                 int64_t ld, int64_t *out, hipStream_t s);

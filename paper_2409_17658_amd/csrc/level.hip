@@ -91,7 +91,7 @@ static bool level_product(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t 
 // Tiny products: one row and two columns per thread, no LDS, 8 k in flight.
 // The smallest VALU tile (64 x 64, staged through LDS) takes 9.2 us at 33 x 33
 // x 33, nearly all of it latency of its first instructions, loads and
-// barriers; this takes TINY.
+// barriers; this takes 3.8.
 __global__ __launch_bounds__(256) void tiny_product_kernel(const u16 *__restrict__ A, int64_t lda,
                                                            const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ Cm,
                                                            int64_t ldc, int M, int N, int K)
@@ -242,7 +242,7 @@ using namespace mpr;
 // The product with its inputs checked and the verdict on the host: the
 // product is launched behind the check, which the host waits for in a pinned
 // record (a device status word, two checks, a copy back and a
-// synchronisation cost 43 us at 33 x 33 x 33 through the binding, this HOST33).
+// synchronisation cost 43 us at 33 x 33 x 33 through the binding, this 18.8).
 extern "C" mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, int64_t N, int64_t K, const uint16_t *A,
                                                int64_t lda, const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc,
                                                int32_t *status_host, mpr_stream stream)
@@ -275,19 +275,3 @@ extern "C" mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, in
     if (w == MPR_OK) *status_host = (int32_t)rec.p[0];
     return e;
 }
-
-#ifdef LV_PROBE
-extern "C" int mpr_level_probe(int cfg, int64_t M, int64_t N, int64_t K, const uint16_t *A, int64_t lda,
-                               const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc, void *s)
-{
-    using namespace mpr;
-    hipStream_t st = (hipStream_t)s;
-    switch (cfg) {
-    case 0: return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
-    case 1: return level_launch<LCfg1>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
-    case 2: return level_launch<LCfg2>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
-    case 4: return level_launch<LCfg4>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
-    default: return level_launch<LCfg3>(M, N, K, A, lda, B, ldb, C, ldc, st, 0);
-    }
-}
-#endif

@@ -1,7 +1,7 @@
 // rowops.hip -- the memory-bound kernels around the product: row-min
 // normalisation (canonical form), operand folding for products of powers,
-// input validation, traces (Corollary 7), the class hash and exact compare of
-// the period search, and small fills.  All of them stream rows with 16-byte
+// input validation, traces (Corollary 7), the exact compare of the period
+// search, and small fills.  All of them stream rows with 16-byte
 // loads and are bounded by HBM bandwidth.
 #include <algorithm>
 
@@ -47,13 +47,6 @@ __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, uint64_t *sh)
     return r;
 }
 
-// Key of entry (i, j) with value v in the class hash; injective for
-// i, j < 2^24.
-__device__ __forceinline__ uint64_t entry_hash(int64_t i, int64_t j, uint32_t v)
-{
-    return mix64(((uint64_t)i << 40) ^ ((uint64_t)j << 16) ^ (uint64_t)v ^ 0x6A09E667F3BCC909ull);
-}
-
 // Subtract r from a packed pair, keeping infinity; flags results > FMAX.
 __device__ __forceinline__ uint32_t sub_pair(uint32_t w, uint32_t r, bool &over)
 {
@@ -74,7 +67,7 @@ constexpr int NCH = 12;  // 16-byte chunks a thread keeps in registers
 // twice.
 __global__ __launch_bounds__(RB) void normalise_kernel(u16 *C, int64_t ldc, int64_t N, const int64_t *R_in,
                                                        const int64_t *add_scalar, int64_t *R_out, int32_t *st,
-                                                       uint64_t *row_hash, int vec)
+                                                       int vec)
 {
     __shared__ uint64_t sh[RB / 64];
     const int64_t i = blockIdx.x;
@@ -121,7 +114,6 @@ __global__ __launch_bounds__(RB) void normalise_kernel(u16 *C, int64_t ldc, int6
         const bool none = r == 0xFFFFu || rin == ROW_NONE || add == ROW_NONE;
         R_out[i] = none ? ROW_NONE : rin + (int64_t)r + add;
     }
-    uint64_t h = 0;
     bool over = false;
     if (r != 0xFFFFu) {
         if (resident) {
@@ -131,13 +123,7 @@ __global__ __launch_bounds__(RB) void normalise_kernel(u16 *C, int64_t ldc, int6
                 if (c >= N) continue;
                 uint32_t w[4] = {keep[q].x, keep[q].y, keep[q].z, keep[q].w};
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    w[e] = sub_pair(w[e], r, over);
-                    if (row_hash) {
-                        if (c + 2 * e < N) h += entry_hash(i, c + 2 * e, w[e] & 0xFFFFu);
-                        if (c + 2 * e + 1 < N) h += entry_hash(i, c + 2 * e + 1, w[e] >> 16);
-                    }
-                }
+                for (int e = 0; e < 4; e++) w[e] = sub_pair(w[e], r, over);
                 if (c + 8 <= N) {
                     *(uint4 *)(row + c) = make_uint4(w[0], w[1], w[2], w[3]);
                 } else {
@@ -150,18 +136,13 @@ __global__ __launch_bounds__(RB) void normalise_kernel(u16 *C, int64_t ldc, int6
                     uint4 v = *(const uint4 *)(row + c);
                     uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        w[q] = sub_pair(w[q], r, over);
-                        if (row_hash)
-                            h += entry_hash(i, c + 2 * q, w[q] & 0xFFFFu) + entry_hash(i, c + 2 * q + 1, w[q] >> 16);
-                    }
+                    for (int q = 0; q < 4; q++) w[q] = sub_pair(w[q], r, over);
                     *(uint4 *)(row + c) = make_uint4(w[0], w[1], w[2], w[3]);
                 } else {
                     for (int64_t j = c; j < N; j++) {
                         uint32_t x = row[j];
                         x = x == 0xFFFFu ? x : x - r;
                         over |= x != 0xFFFFu && x > FMAX16;
-                        if (row_hash) h += entry_hash(i, j, x);
                         row[j] = (u16)x;
                     }
                 }
@@ -171,36 +152,27 @@ __global__ __launch_bounds__(RB) void normalise_kernel(u16 *C, int64_t ldc, int6
                 uint32_t x = row[j];
                 x = x == 0xFFFFu ? x : x - r;
                 over |= x != 0xFFFFu && x > FMAX16;
-                if (row_hash) h += entry_hash(i, j, x);
                 row[j] = (u16)x;
             }
         }
-    } else if (row_hash) {
-        for (int64_t j = threadIdx.x; j < N; j += RB) h += entry_hash(i, j, 0xFFFFu);
     }
     if (over) set_status(st, MPR_EOVERFLOW);
-    if (row_hash) {
-        const uint64_t t = block_sum_u64(h, sh);
-        if (threadIdx.x == 0) row_hash[i] = t;
-    }
 }
 
 mpr_status normalise_launch(int64_t M, int64_t N, u16 *C, int64_t ldc, const int64_t *R_in,
-                            const int64_t *add_scalar, int64_t *R_out, int32_t *st, uint64_t *row_hash,
-                            hipStream_t s)
+                            const int64_t *add_scalar, int64_t *R_out, int32_t *st, hipStream_t s)
 {
     if (M == 0) return MPR_OK;
     if (M > INT32_MAX) return MPR_EUNSUPPORTED;
     const int vec = aligned16(C) && ldc % 8 == 0;
-    hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)M), dim3(RB), 0, s, C, ldc, N, R_in, add_scalar, R_out, st,
-                       row_hash, vec);
+    hipLaunchKernelGGL(normalise_kernel, dim3((unsigned)M), dim3(RB), 0, s, C, ldc, N, R_in, add_scalar, R_out, st, vec);
     return check_launch();
 }
 
 // The elementwise passes walk whole rows, one block a row at a time, in
 // 16-byte chunks where the rows allow it (one entry per thread and a 64-bit
 // division each took 58 us to check, 81 us to copy and 185 us to compare
-// matrices of 7411 states; now ELEMS).
+// matrices of 7411 states; now 19, 36 and 62).
 constexpr int64_t kRowBlocks = 8192;
 static unsigned row_blocks(int64_t rows) { return (unsigned)std::min<int64_t>(rows, kRowBlocks); }
 
@@ -451,31 +423,6 @@ mpr_status transpose_launch(const u16 *src, int64_t lds, u16 *dst, int64_t ldd, 
     const int64_t tiles = (n + 63) / 64;
     if (tiles * tiles > INT32_MAX) return MPR_EUNSUPPORTED;
     hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(tiles * tiles)), dim3(256), 0, s, src, lds, dst, ldd, n);
-    return check_launch();
-}
-
-// Class hash of a canonical form up to a scalar shift:
-// sum of the row hashes of N plus a term per row for R[i] - min R.
-__global__ __launch_bounds__(1024) void class_hash_kernel(const uint64_t *row_hash, const int64_t *R, int64_t n,
-                                                          uint64_t *out)
-{
-    __shared__ int64_t shm[16];
-    __shared__ uint64_t shs[16];
-    int64_t v = ROW_NONE;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) v = R[i] < v ? R[i] : v;
-    const int64_t base = block_min_i64(v, shm);
-    uint64_t h = 0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint64_t rel = R[i] == ROW_NONE ? 0xFFFFFFFFFFFFFFFFull : (uint64_t)(R[i] - base);
-        h += row_hash[i] + mix64(mix64((uint64_t)i ^ 0xBB67AE8584CAA73Bull) + rel);
-    }
-    h = block_sum_u64(h, shs);
-    if (threadIdx.x == 0) *out = h;
-}
-
-mpr_status class_hash_launch(const uint64_t *row_hash, const int64_t *R, int64_t n, uint64_t *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(class_hash_kernel, dim3(1), dim3(1024), 0, s, row_hash, R, n, out);
     return check_launch();
 }
 

@@ -500,7 +500,7 @@ static mpr_status enqueue_giants(Server &S, Ladder &L, int upto)
             : n >= kBigLadder ? product_launch_spare(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s)
                               : product_launch(-1, n, n, n, L.Ng[i - 1], ld, L.Bp, ld, L.Ng[i], ld, s);
         if (e == MPR_OK)
-            e = normalise_launch(n, n, L.Ng[i], ld, L.Rg[i - 1], L.scal, L.Rg[i], L.status_dev, nullptr, s);
+            e = normalise_launch(n, n, L.Ng[i], ld, L.Rg[i - 1], L.scal, L.Rg[i], L.status_dev, s);
         if (e == MPR_OK) e = pack_build(S, L, L.Ng[i], L.Ng8[i]);
         if (e == MPR_OK) e = publish_build(S, L);
         if (e == MPR_OK && hipEventRecord(L.step_ev[i], s) != hipSuccess) e = MPR_EHIP;
@@ -579,12 +579,12 @@ static mpr_status start_build(Server &S, Ladder &L)
         int64_t *R[2] = {L.Rg[1], Rp};
         int b = (B - 1) & 1;
         if (e == MPR_OK) e = copy_launch(A, ld, buf[b], ld, n, n, s);
-        if (e == MPR_OK) e = normalise_launch(n, n, buf[b], ld, nullptr, nullptr, R[b], L.status_dev, nullptr, s);
+        if (e == MPR_OK) e = normalise_launch(n, n, buf[b], ld, nullptr, nullptr, R[b], L.status_dev, s);
         if (e == MPR_OK && B >= 2) e = sparse_plan_launch(A, n, ld, plan, plan_bytes, L.status_dev, s);
         for (int k = 2; k <= B && e == MPR_OK; k++) {
             e = sparse_step_launch(buf[b], ld, n, plan, plan_bytes, buf[b ^ 1], ld, s);
             if (e == MPR_OK)
-                e = normalise_launch(n, n, buf[b ^ 1], ld, R[b], nullptr, R[b ^ 1], L.status_dev, nullptr, s);
+                e = normalise_launch(n, n, buf[b ^ 1], ld, R[b], nullptr, R[b ^ 1], L.status_dev, s);
             b ^= 1;
         }
     }
@@ -592,11 +592,11 @@ static mpr_status start_build(Server &S, Ladder &L)
     // on A^T (plan built from the raw A^T before it is normalised in place).
     if (e == MPR_OK) e = transpose_launch(A, ld, L.Nb[1], ld, n, s);
     if (e == MPR_OK && B >= 2) e = sparse_plan_launch(L.Nb[1], n, ld, plan, plan_bytes, L.status_dev, s);
-    if (e == MPR_OK) e = normalise_launch(n, n, L.Nb[1], ld, nullptr, nullptr, L.Rb[1], L.status_dev, nullptr, s);
+    if (e == MPR_OK) e = normalise_launch(n, n, L.Nb[1], ld, nullptr, nullptr, L.Rb[1], L.status_dev, s);
     for (int j = 2; j <= B && e == MPR_OK; j++) {
         e = sparse_step_launch(L.Nb[j - 1], ld, n, plan, plan_bytes, L.Nb[j], ld, s);
         if (e == MPR_OK)
-            e = normalise_launch(n, n, L.Nb[j], ld, L.Rb[j - 1], nullptr, L.Rb[j], L.status_dev, nullptr, s);
+            e = normalise_launch(n, n, L.Nb[j], ld, L.Rb[j - 1], nullptr, L.Rb[j], L.status_dev, s);
     }
     for (int j = 1; j <= B && e == MPR_OK; j++) e = trace_launch(L.Nb[j], n, ld, L.Rb[j], L.trace_dev + (j - 1), s);
     for (int j = 1; j <= B && e == MPR_OK; j++) e = pack(L.Nb[j], L.Nb8[j]);

@@ -32,7 +32,7 @@ constexpr int SBK = SCfg::BK;
 // x 64 columns with one 16-byte load per lane (whole 128-byte lines, PU groups
 // in flight), so a pass reads A once, coalesced; one thread per row, each
 // walking its own line, took 0.57 ms to count and 1.80 ms to fill at m = 9
-// (0.10 and 0.50 at m = 8; TIMES).
+// (0.10 and 0.50 at m = 8); now 0.45 and 0.47 (0.056 and 0.070).
 constexpr int PT = 1024;       // threads
 constexpr int PW = PT / 64;    // waves
 constexpr int PWIN = 8 * PT;   // groups per window (65536 rows)

@@ -114,7 +114,7 @@ __device__ __forceinline__ uint64_t blocked(uint32_t w, int m)
 // of its rows and columns is unranked once, into LDS; an entry is then two
 // ANDs and a compare, and the kernel is bound by its writes (one thread per
 // entry, unranking both words each time, took 10.2 ms at m = 9 and 1.10 ms at
-// m = 8; now TIMES).
+// m = 8; now 0.24 and 0.06).
 constexpr int TROWS = 64, TCOLS = 256 * 8;
 __global__ __launch_bounds__(256) void transfer_kernel(WordTable t, int64_t n, u16 *A, int64_t lda, int vec)
 {
