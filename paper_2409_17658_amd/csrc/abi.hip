@@ -744,7 +744,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK || (r = fill_i32_launch(big, 1, 0, s)) != MPR_OK) return r;
         if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
         // the counts that sized the plan lie where it begins (same carving)
-        if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, st, s)) != MPR_OK) return r;
+        if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, bytes, st, s)) != MPR_OK) return r;
     }
     if (traces_host) traces_host[0] = MPR_ROW_NONE;
 

@@ -720,8 +720,10 @@ struct LevelLds {
     static constexpr int CHUNKS = C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK;
 };
 
-// sparse.hip: the rows of a plan whose counts sparse_plan_rows left in ws.
-mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st, hipStream_t s);
+// sparse.hip: the rows of a plan whose counts sparse_plan_rows left in ws, as
+// values or (for sparse_step8_launch) as level images.
+mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, bool images, int32_t *st,
+                            hipStream_t s);
 
 // period.hip: one pass over a power of a period search (canonical form to dst,
 // offsets, and into rec the class hash, trace, status and seq), and the

@@ -154,11 +154,20 @@ __global__ __launch_bounds__(PT) void sp_scan_kernel(const int64_t *counts, int6
 // Bp[(off[J] + t) * SBN + c] = A[l][j0 + c]; padding rows are row 0 / infinite.
 // A plan whose rows (off[nblk]) exceed the capacity `cap` of its workspace
 // is not written: *st = MPR_ENOMEM, and the step kernel then does nothing.
+// IMAGES (the step in bytes): Bp holds the images of the values instead, 8 rows
+// of a column to a 16-byte chunk, as the matrix instruction reads them, and
+// top[J] the largest finite value of the block.
+template <bool IMAGES>
 __global__ __launch_bounds__(PT) void sp_fill_kernel(const u16 *A, int64_t lda, int64_t n, const int64_t *off,
                                                      int64_t nblk, int64_t cap, int32_t *idx, u16 *Bp, int vec,
-                                                     int32_t *st)
+                                                     int32_t *top, int32_t *st)
 {
     __shared__ uint8_t rows[PWIN];
+    typedef u32x4 __attribute__((may_alias)) chunk_bits;
+    __shared__ __attribute__((aligned(16))) u16 turn[IMAGES ? PW : 1][8 * SBN];  // a wave's 8 rows
+    __shared__ int most;
+    uint32_t mx = 0;  // largest finite value + 1
+    if (threadIdx.x == 0) most = 0;
     __shared__ int pos[PWIN];
     __shared__ int wsum[PW];
     if (off[nblk] > cap) {  // uniform over the grid
@@ -189,17 +198,44 @@ __global__ __launch_bounds__(PT) void sp_fill_kernel(const u16 *A, int64_t lda, 
             for (int u = 0; u < PU; u++)
                 if (g + u < cnt && (lane >> 3) < rows[g + u]) {
                     const int64_t t = base + run + pos[g + u] + (lane >> 3);
-                    gstore16(glob(Bp) + t * SBN + (lane & 7) * 8, v[u]);
+                    if constexpr (!IMAGES) gstore16(glob(Bp) + t * SBN + (lane & 7) * 8, v[u]);
                     if ((lane & 7) == 0) idx[t] = (int32_t)((g0 + g + u) * 8 + (lane >> 3));
                 }
+            if constexpr (IMAGES) {
+#pragma unroll
+                for (int u = 0; u < PU; u++)
+                    if (g + u < cnt && rows[g + u]) {  // uniform in the wave; rows past n were loaded as infinite
+                        ((chunk_bits *)turn[w])[lane] = (u32x4){v[u].x, v[u].y, v[u].z, v[u].w};
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        const u16 *col = turn[w] + lane;
+                        uint32_t x[4];
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            const uint32_t lo = col[2 * q * SBN], hi = col[(2 * q + 1) * SBN];
+                            mx = max(mx, max((lo + 1) & 0xFFFFu, (hi + 1) & 0xFFFFu));
+                            x[q] = level_image(lo | hi << 16);
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        gstore16(glob(Bp) + (base + run + pos[g + u]) * SBN + lane * 8, make_uint4(x[0], x[1], x[2], x[3]));
+                    }
+            }
         }
         run += total;
         __syncthreads();
     }
     // padding up to the multiple of SBK
+    const uint32_t none = IMAGES ? 0u : 0xFFFFFFFFu;
+    const int64_t filled = IMAGES ? (run + 7) & ~(int64_t)7 : run;
     for (int64_t e = (base + run) * 8 + threadIdx.x; e < end * 8; e += PT) {
-        gstore16(glob(Bp) + e * 8, make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu));
+        if (e >= (base + filled) * 8) gstore16(glob(Bp) + e * 8, make_uint4(none, none, none, none));
         if (e % 8 == 0) idx[e / 8] = 0;
+    }
+    if constexpr (IMAGES) {
+        if (mx) atomicMax(&most, (int)mx - 1);
+        __syncthreads();
+        if (threadIdx.x == 0) top[J] = most;
     }
 }
 
@@ -736,17 +772,57 @@ struct LevelGather8 {
     }
 };
 
+// Staging of the right operand from its images: two 16-byte loads a thread and
+// slice and no conversion, where values took eight loads of 4 bytes and 24
+// instructions of the 113 (whole searches of m = 8 6.55 ms, now 5.98; m = 9
+// 72.2, now 65.3).
+template <class C>
+struct LevelImages {
+    gbytes *base, *at;
+    int64_t K;
+    uint4 r[C::B_COLS];
+    static __device__ __forceinline__ int chunk(int j) { return C::tid() + j * C::GT; }  // (k / 8) * BN + column
+    __device__ __forceinline__ LevelImages(const u16 *p, int64_t K_) : base((gbytes *)glob(p)), K(K_) {}
+    __device__ __forceinline__ void seek(int64_t k0) { at = base + k0 * (C::BN * 2); }
+    __device__ __forceinline__ void load()
+    {
+#pragma unroll
+        for (int j = 0; j < C::B_COLS; j++) r[j] = gload16((const gu16 *)(at + chunk(j) * 16));
+        at -= C::BK * C::KS * C::BN * 2;
+    }
+    __device__ __forceinline__ void load_tail(int64_t k0)
+    {
+#pragma unroll
+        for (int j = 0; j < C::B_COLS; j++) {
+            const bool in = k0 + chunk(j) / C::BN * 8 < K;
+            r[j] = in ? gload16((const gu16 *)(base + k0 * (C::BN * 2) + chunk(j) * 16)) : make_uint4(0, 0, 0, 0);
+        }
+    }
+    __device__ __forceinline__ void settle() {}
+    __device__ __forceinline__ void store_chunk(uint4 *bs, int j) const
+    {
+        const int n = chunk(j) % C::BN;
+        bs[chunk(j) / C::BN * C::PB + (n ^ ((n >> 3) & 3))] = r[j];
+    }
+};
+
 // Row panels that run side by side over the column blocks (whole searches with
 // 1, 2, 3, 4: m = 8 7.45, 6.79, 6.87, 6.62 ms, m = 9 85.4, 79.8, 82.1, 80.3).  A
 // block that took 2 neighbouring column blocks, the second's first loads ahead
 // of the first's stores, left too few blocks: 8.40 and 91.8 ms.
 constexpr int PANELS8 = 2;
+// Rows are staged in order, so the pitch need not be odd; at an odd one a fifth
+// of the LDS cycles were bank conflicts of the operand reads (m = 9 65.6 ms, now
+// 63.5; m = 8 6.05 and 5.89).
+struct P8Cfg : PCfg {
+    static constexpr int PA = BM, STAGE = KC * (PA + PB), LDS_CHUNKS = 2 * STAGE * KS;
+};
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level8_kernel(
     const uint8_t *__restrict__ N, int64_t group8, int64_t n, const int64_t *__restrict__ off,
     const int32_t *__restrict__ idx, const u16 *__restrict__ Bp, uint8_t *__restrict__ O, int tiles_m, int nblk,
-    int64_t cap, int32_t *wide, const int32_t *big)
+    int64_t cap, const int32_t *top, int32_t *wide, const int32_t *big)
 {
-    using C = PCfg;
+    using C = P8Cfg;
     __shared__ uint4 lds[C::LDS_CHUNKS];
     const int nb = (int)gridDim.x;  // a multiple of 8
     const int t = ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
@@ -758,19 +834,12 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     LevelAcc<C> acc;
     if (K > 0) {
         LevelGather8<C> aop(N + m0 * 8, group8, rows, idx + kbeg, K);
-        LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
+        LevelImages<C> bop(Bp + kbeg * SBN, K);
         level_kloop<C>(K, aop, bop, lds, acc);
         if (!level_sure<C>(acc, rows, cols)) {
             // exact when the largest values of N and of these columns sum to
             // what the float range holds
-            const int b = level_largest<C>(lds, [&](i16x2 m) {
-                for (int64_t e = threadIdx.x; e < K * SBN / 8; e += C::NT) {
-                    const uint4 v = gload16(glob(Bp) + kbeg * SBN + e * 8);
-#pragma unroll
-                    for (int q = 0; q < 4; q++) m = __builtin_elementwise_max(m, __builtin_bit_cast(i16x2, comp(v, q)));
-                }
-                return m;
-            });
+            const int b = top[J];
             if (threadIdx.x == 0 && (b > (int)LV_MAX || *big + b > (int)LV_SUM)) set_status(wide, 1);
         }
     } else {  // no finite entry in these columns, or a plan that did not fit
@@ -882,12 +951,15 @@ mpr_status sparse_plan_rows(const u16 *A, int64_t n, int64_t lda, void *ws, hipS
     return w;
 }
 
-mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st, hipStream_t s)
+mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, bool images, int32_t *st,
+                            hipStream_t s)
 {
     SparsePlan p = carve_plan(ws, n, bytes);
     const int vec = aligned16(A) && lda % 8 == 0;
-    hipLaunchKernelGGL(sp_fill_kernel, dim3((unsigned)p.nblk), dim3(PT), 0, s, A, lda, n, (const int64_t *)p.off,
-                       p.nblk, p.cap, p.idx, p.Bp, vec, st);
+    // with images, the blocks' largest values take the place of their order,
+    // which only the VALU forms read
+    hipLaunchKernelGGL(images ? sp_fill_kernel<true> : sp_fill_kernel<false>, dim3((unsigned)p.nblk), dim3(PT), 0, s, A,
+                       lda, n, (const int64_t *)p.off, p.nblk, p.cap, p.idx, p.Bp, vec, p.order, st);
     return check_launch();
 }
 
@@ -896,7 +968,7 @@ mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, si
 {
     const SparsePlan p = carve_plan(ws, n, bytes);
     plan_count(A, n, lda, p, nullptr, s);
-    return sparse_plan_fill(A, n, lda, ws, bytes, st, s);
+    return sparse_plan_fill(A, n, lda, ws, bytes, false, st, s);
 }
 
 static std::atomic<int> g_sparse_arith{MPR_ARITH_U16};  // process-wide, set from any thread
@@ -926,7 +998,7 @@ mpr_status sparse_step8_launch(const uint8_t *N, int64_t n, void *ws, size_t byt
     if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
     hipLaunchKernelGGL(sp_level8_kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, N, level_group8(n), n,
                        (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, O, (int)tiles_m, (int)p.nblk,
-                       p.cap, wide, big);
+                       p.cap, (const int32_t *)p.order, wide, big);
     return check_launch();
 }
 
