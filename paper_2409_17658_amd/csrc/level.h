@@ -66,14 +66,19 @@ struct LevelCfg {
         return KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / GT);
     }
     static constexpr int BK = 64, KC = BK / 8;
-    // Chunks per k group.  The A pitch is odd, so the 8 lanes that stage the
-    // 8 k groups of one row write to 8 different 16-byte bank groups.
-    static constexpr int PA = BM + 1, PB = BN;
+    // Chunks per k group.  Row r of A lies at r ^ (k group) when SWZ, so the 8
+    // lanes that stage the 8 k groups of one row write to 8 different 16-byte
+    // bank groups, and the rows of a read stay in whole groups of 4 (an odd
+    // pitch instead left reads of two k groups in conflict: 12 chains 33.8 ms,
+    // now 33.4; N = 16384 10.3 and 10.2).
+    static constexpr int PA = BM, PB = BN;
+    static constexpr bool SWZ = true;
     static constexpr int STAGE = KC * (PA + PB);
     static constexpr int LDS_CHUNKS = 2 * STAGE * KS;
     static constexpr int A_CPT = BM * KC / GT;   // A chunks a thread stages
     static constexpr int B_COLS = BN * KC / GT;  // columns of 8 k a thread stages
     static_assert(NI % 2 == 0, "level_store pairs neighbouring tiles");
+    static_assert(GT / KC % 8 == 0, "a thread's rows differ above the swizzle");
     static_assert(BM * KC % GT == 0 && (B_COLS == 2 || B_COLS == 4), "staging split");
 };
 
@@ -174,7 +179,7 @@ struct LevelA {
     }
     __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
-        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+        as[(C::tid() % C::KC) * C::PA + (C::tid() / C::KC ^ C::tid() % C::KC) + q * (C::GT / C::KC)] =
             make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
                        level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
@@ -320,8 +325,8 @@ __device__ __forceinline__ void level_first(int64_t K, AOp &aop, BOp &bop)
 // outputs a SIMD needs 162 VALU instructions and 32 x 2 slots: that, not the
 // matrix core, is the bound, and the clock falls to 1.95 GHz under this load.
 template <class C, bool STORE, bool LOAD, class AOp, class BOp>
-__device__ __forceinline__ void level_slice(const uint4 *as, const uint4 *bs0, const uint4 *bs1, uint4 *next, AOp &aop,
-                                            BOp &bop, LevelAcc<C> &acc)
+__device__ __forceinline__ void level_slice(const uint4 *as0, const uint4 *as1, const uint4 *bs0, const uint4 *bs1,
+                                            uint4 *next, AOp &aop, BOp &bop, LevelAcc<C> &acc)
 {
     constexpr int T = C::MI * C::NI, PIECES = C::A_CPT + C::B_COLS, LAG = 2;
     bf16x8 bf[C::NI][2], af[2][2];
@@ -332,7 +337,7 @@ __device__ __forceinline__ void level_slice(const uint4 *as, const uint4 *bs0, c
     };
     readb(0);
 #pragma unroll
-    for (int ks = 0; ks < 2; ks++) af[0][ks] = __builtin_bit_cast(bf16x8, as[4 * ks * C::PA]);
+    for (int ks = 0; ks < 2; ks++) af[0][ks] = __builtin_bit_cast(bf16x8, (ks ? as1 : as0)[0]);
     f32x4 t[LAG + 1][2];
     if (STORE) bop.settle();
     int piece = 0;
@@ -348,7 +353,7 @@ __device__ __forceinline__ void level_slice(const uint4 *as, const uint4 *bs0, c
         if (i < T && ni == 0 && mi + 1 < C::MI) {  // the next row of tiles' operand, a row ahead
 #pragma unroll
             for (int ks = 0; ks < 2; ks++)
-                af[(mi + 1) & 1][ks] = __builtin_bit_cast(bf16x8, as[4 * ks * C::PA + 16 * (mi + 1)]);
+                af[(mi + 1) & 1][ks] = __builtin_bit_cast(bf16x8, (ks ? as1 : as0)[16 * (mi + 1)]);
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ks++) {
@@ -391,7 +396,9 @@ __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
 {
     const int lane = (int)(threadIdx.x & 63);
     const int wm = C::wave() / C::WN, wn = C::wave() % C::WN;
-    const int aoff = (lane >> 4) * C::PA + wm * 16 * C::MI + (lane & 15);
+    // k groups 0..3 and 4..7 of A
+    const int aoff0 = (lane >> 4) * C::PA + wm * 16 * C::MI + ((lane & 15) ^ (C::SWZ ? lane >> 4 : 0));
+    const int aoff1 = (aoff0 ^ (C::SWZ ? 4 : 0)) + 4 * C::PA;
     // even and odd tiles of 16 columns (LevelB's order of the chunks)
     const int boff0 = C::KC * C::PA + (lane >> 4) * C::PB + wn * 16 * C::NI + ((lane & 15) ^ ((lane >> 3) & 1));
     const int boff1 = boff0 ^ 2;
@@ -422,13 +429,13 @@ __device__ __forceinline__ void level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
     for (int cur = 0;; cur ^= 1) {
         left--;  // slices of the group after this one
         uint4 *next = lds + (cur ^ 1) * C::STAGE;
-        const uint4 *st = lds + cur * C::STAGE, *as = st + aoff, *b0 = st + boff0, *b1 = st + boff1;
+        const uint4 *st = lds + cur * C::STAGE, *a0 = st + aoff0, *a1 = st + aoff1, *b0 = st + boff0, *b1 = st + boff1;
         if (left > 1)
-            level_slice<C, true, true>(as, b0, b1, next, aop, bop, acc);
+            level_slice<C, true, true>(a0, a1, b0, b1, next, aop, bop, acc);
         else if (left == 1)
-            level_slice<C, true, false>(as, b0, b1, next, aop, bop, acc);
+            level_slice<C, true, false>(a0, a1, b0, b1, next, aop, bop, acc);
         else if (left == 0)
-            level_slice<C, false, false>(as, b0, b1, next, aop, bop, acc);
+            level_slice<C, false, false>(a0, a1, b0, b1, next, aop, bop, acc);
         __syncthreads();
         if (--trips == 0) break;
     }

@@ -636,7 +636,7 @@ struct LevelGather {
     }
     __device__ __forceinline__ void store_chunk(uint4 *as, int q) const
     {
-        as[(C::tid() % C::KC) * C::PA + C::tid() / C::KC + q * (C::GT / C::KC)] =
+        as[(C::tid() % C::KC) * C::PA + (C::tid() / C::KC ^ C::tid() % C::KC) + q * (C::GT / C::KC)] =
             make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
                        level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
@@ -811,11 +811,8 @@ struct LevelImages {
 // block that took 2 neighbouring column blocks, the second's first loads ahead
 // of the first's stores, left too few blocks: 8.40 and 91.8 ms.
 constexpr int PANELS8 = 2;
-// Rows are staged in order, so the pitch need not be odd; at an odd one a fifth
-// of the LDS cycles were bank conflicts of the operand reads (m = 9 65.6 ms, now
-// 63.5; m = 8 6.05 and 5.89).
 struct P8Cfg : PCfg {
-    static constexpr int PA = BM, STAGE = KC * (PA + PB), LDS_CHUNKS = 2 * STAGE * KS;
+    static constexpr bool SWZ = false;  // rows are staged in order
 };
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level8_kernel(
     const uint8_t *__restrict__ N, int64_t group8, int64_t n, const int64_t *__restrict__ off,
