@@ -39,8 +39,8 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     LevelB<C> bop(glob(B) + n0, ldb, cols, K);
     {
         LevelAcc<C> acc;
-        level_kloop<C>(K, aop, bop, lds, acc);
-        if (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds)) {
+        if (level_kloop<C, true>(K, aop, bop, lds, acc) &&
+            (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds))) {
             level_store<C>(glob(Cm) + m0 * ldc + n0, ldc, rows, cols, acc);
             return;
         }

@@ -228,3 +228,20 @@ def test_period_search_byte_passes(mpr, n):
     got = mpr.find_period(A, kmax, slots=9, sparse=True, pipeline=True)
     assert got[:3] == want[:3] and got[3].tolist() == want[3].tolist()
     assert any(t != mpr.ROW_NONE for t in got[3][1:])
+
+
+@pytest.mark.parametrize("shape", [(300, 260, 1000), (2048, 2048, 193), (64, 70, 257), (2304, 2050, 128)])
+@pytest.mark.parametrize("late", [False, True])
+def test_blocks_that_give_up_early(mpr, shape, late):
+    """Blocks whose first slices hold values past the levels leave the pass over
+    K at once, or (late: only the first columns of K hold small values) after
+    it; the product is the same."""
+    M, N, K = shape
+    X, Y = synth.random_matrix(M, K, 31, 0, 3000, 0.25), synth.random_matrix(K, N, 32, 0, 3000, 0.25)
+    if late:
+        X[:, : K // 2] = np.minimum(X[:, : K // 2], 9)
+        Y[: K // 2] = np.minimum(Y[: K // 2], 9)
+    A, B = mpr.to_device(X), mpr.to_device(Y)
+    want = mpr.minplus_gemm(A, B, cfg=0, check=False)
+    got = mpr.minplus_gemm(A, B, check=False)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
