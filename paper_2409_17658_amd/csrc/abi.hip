@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <thread>
 #include <unordered_map>
@@ -96,42 +97,56 @@ int device_cu_count()
 // ------------------------------------------------------------ host records
 // At most kRecords pinned records stay allocated while no call uses them.
 static std::mutex g_records_mu;
-static std::vector<int64_t *> g_records;
 constexpr size_t kRecords = 16;
+static int64_t *g_records[kRecords];
+static size_t g_records_free = 0;
+static std::atomic<int64_t> g_tickets{0};
 
-HostRecord::HostRecord() : p(nullptr)
+HostRecord::HostRecord(hipStream_t stream) : p(nullptr), s(stream)
 {
     {
         std::lock_guard<std::mutex> lk(g_records_mu);
-        if (!g_records.empty()) {
-            p = g_records.back();
-            g_records.pop_back();
-        }
+        if (g_records_free > 0) p = g_records[--g_records_free];
     }
-    if (!p && hipHostMalloc((void **)&p, 16 * sizeof(int64_t), hipHostMallocPortable) != hipSuccess) p = nullptr;
+    if (!p && hipHostMalloc((void **)&p, 16 * sizeof(int64_t), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
     if (p) p[7] = p[15] = 0;  // no record yet
 }
 
 HostRecord::~HostRecord()
 {
-    if (!p || failed) return;
+    if (!p) return;
+    // a writer may still be on its way (a failed launch behind it, a failed
+    // wait): a stream that can not be drained keeps the record
+    if (seen != newest && hipStreamSynchronize(s) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
     {
         std::lock_guard<std::mutex> lk(g_records_mu);
-        if (g_records.size() < kRecords) {
-            g_records.push_back(p);
+        if (g_records_free < kRecords) {
+            g_records[g_records_free++] = p;
             return;
         }
     }
     (void)hipHostFree(p);
 }
 
-// Waits until a kernel on stream s has written `seq` (never 0) into the
-// record: a look at host memory (6 us from launch to here, 21 us with a copy
-// and a synchronisation).  A stream that ends or fails without writing it is
-// an error, so the wait ends in every case.
-mpr_status HostRecord::wait(const int64_t *rec, int64_t seq, hipStream_t s)
+int64_t HostRecord::ticket() { return newest = ++g_tickets; }
+
+// Waits until a kernel on the stream has written `seq` into the record: a look
+// at host memory (6 us from launch to here, 21 us with a copy and a
+// synchronisation).  A stream that ends or fails without writing it is an
+// error, so the wait ends in every case.
+mpr_status HostRecord::wait(const int64_t *rec, int64_t seq)
 {
-    auto there = [&] { return __atomic_load_n(&rec[7], __ATOMIC_ACQUIRE) == seq; };
+    auto there = [&] {
+        if (__atomic_load_n(&rec[7], __ATOMIC_ACQUIRE) != seq) return false;
+        seen = seq;
+        return true;
+    };
     for (;;) {
         for (int k = 0; k < 4096; k++) {
             if (there()) return MPR_OK;
@@ -144,7 +159,6 @@ mpr_status HostRecord::wait(const int64_t *rec, int64_t seq, hipStream_t s)
         }
         if (e == hipSuccess && there()) return MPR_OK;
         (void)hipGetLastError();
-        failed = true;
         return MPR_EHIP;
     }
 }
@@ -657,7 +671,10 @@ extern "C" mpr_status mpr_sparse_plan_bytes(const uint16_t *A, int64_t n, int64_
     hipStream_t s = as_stream(stream);
     const size_t tmp_bytes = sparse_plan_bytes_rows(n, 0);
     void *tmp = nullptr;
-    if (hipMallocAsync(&tmp, tmp_bytes, s) != hipSuccess) return MPR_ENOMEM;
+    if (hipMallocAsync(&tmp, tmp_bytes, s) != hipSuccess) {
+        (void)hipGetLastError();  // do not leave the error for the next launch check
+        return MPR_ENOMEM;
+    }
     int64_t rows = 0;
     r = sparse_plan_rows(A, n, lda, tmp, s, &rows);
     if (hipFreeAsync(tmp, s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
@@ -779,16 +796,17 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         c = no_rows ? 0 : cmp[1];
         return MPR_OK;
     };
-    HostRecord host;  // two records of 8 words, powers in turn
+    HostRecord host(s);  // two records, powers in turn
+    int64_t ticket[2];
     if (!host.p) return MPR_ENOMEM;
     // Power k into slot (k - 1) % M, its record on the way to the host.
     auto enqueue = [&](int64_t k, int64_t M) -> mpr_status {
-        const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M;
+        const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M, seq = ticket[k & 1] = host.ticket();
         u16 *Nk = slot_N(w, slot);
         int64_t *Rk = slot_R(w, slot), *rec = host.p + 8 * (k & 1);
         if (small)
             return period_small_launch(A, lda, k == 1 ? nullptr : (const uint8_t *)slot_N(w, ps), (uint8_t *)Nk, ld8, n,
-                                       k == 1 ? nullptr : slot_R(w, ps), Rk, rec, k, s);
+                                       k == 1 ? nullptr : slot_R(w, ps), Rk, rec, seq, s);
         if (bytes) {
             uint8_t *N8 = (uint8_t *)Nk;
             mpr_status e = k == 1 ? MPR_OK
@@ -796,13 +814,13 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
                                                         wide, big, s);
             if (e == MPR_OK)
                 e = period_rows8_launch(k == 1 ? A : nullptr, lda, N8, n, k == 1 ? nullptr : slot_R(w, ps), Rk,
-                                        w.acc, st, wide, big, rec, k, s);
+                                        w.acc, st, wide, big, rec, seq, s);
             return e;
         }
-        if (k == 1) return period_rows_launch(A, lda, Nk, w.ld, n, nullptr, Rk, true, w.acc, st, rec, k, s);
+        if (k == 1) return period_rows_launch(A, lda, Nk, w.ld, n, nullptr, Rk, true, w.acc, st, rec, seq, s);
         mpr_status e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
                               : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
-        if (e == MPR_OK) e = period_rows_launch(Nk, w.ld, Nk, w.ld, n, slot_R(w, ps), Rk, false, w.acc, st, rec, k, s);
+        if (e == MPR_OK) e = period_rows_launch(Nk, w.ld, Nk, w.ld, n, slot_R(w, ps), Rk, false, w.acc, st, rec, seq, s);
         return e;
     };
     if (pipeline) {
@@ -820,7 +838,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         for (int64_t k = 1; k <= kmax; k++) {
             if (k + 1 <= kmax && (r = enqueue(k + 1, M)) != MPR_OK) return finish(r);
             const int64_t *rec = host.p + 8 * (k & 1);
-            if ((r = host.wait(rec, k, s)) != MPR_OK) return finish(r);
+            if ((r = host.wait(rec, ticket[k & 1])) != MPR_OK) return finish(r);
             const int64_t hash = rec[0], trace = rec[1];
             const int32_t stv = (int32_t)rec[2];
             if (stv != 0) return finish((mpr_status)stv);
@@ -870,7 +888,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         u16 *Nk = slot_N(w, slot);
         int64_t *Rk = slot_R(w, slot);
         const int64_t *rec = host.p + 8 * (k & 1);
-        if ((r = enqueue(k, w.slots)) != MPR_OK || (r = host.wait(rec, k, s)) != MPR_OK) return r;
+        if ((r = enqueue(k, w.slots)) != MPR_OK || (r = host.wait(rec, ticket[k & 1])) != MPR_OK) return r;
         const int64_t hash = rec[0], trace = rec[1];
         if ((int32_t)rec[2] != 0) return (mpr_status)(int32_t)rec[2];
         if (bytes && rec[3] != 0) {

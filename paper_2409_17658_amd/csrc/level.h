@@ -786,20 +786,25 @@ mpr_status sparse_step8_launch(const uint8_t *N, int64_t n, void *ws, size_t byt
 mpr_status period_rows_launch(const u16 *src, int64_t lds_, u16 *dst, int64_t ldd, int64_t n, const int64_t *R_in,
                               int64_t *R_out, bool raw, void *acc, int32_t *st, int64_t *rec, int64_t seq, hipStream_t s);
 
-// abi.hip: 16 words of pinned host memory that a kernel writes records of 8
-// words to (the last one, word 7, when the others are in place), and the wait
+// abi.hip: 16 words of pinned host memory, two records of 8 words that kernels
+// on stream s write (word 7 last, when the others are in place), and the wait
 // for one.  A few stay allocated between calls (a pinned allocation and its
-// release take 50 us); taken and given back from any thread.
+// release take 50 us); taken and given back from any thread.  Every writer has
+// a ticket of its own, taken before its launch: no other call's late write can
+// be taken for it, and a record whose newest ticket has not been seen is given
+// back only once the stream is idle.
 struct HostRecord {
     int64_t *p;
-    HostRecord();
+    explicit HostRecord(hipStream_t stream);
     ~HostRecord();
     HostRecord(const HostRecord &) = delete;
     HostRecord &operator=(const HostRecord &) = delete;
-    mpr_status wait(const int64_t *rec, int64_t seq, hipStream_t s);
+    int64_t ticket();
+    mpr_status wait(const int64_t *rec, int64_t seq);
 
 private:
-    bool failed = false;  // a kernel of a failed stream could still write here: not used again
+    hipStream_t s;
+    int64_t newest = 0, seen = 0;
 };
 
 // The compressed-K step (sparse.hip) in the same way; p.A is not read.

@@ -208,7 +208,7 @@ namespace mpr {
 // block also ends the record; more blocks leave that to check_end_kernel.
 __global__ __launch_bounds__(1024) void check_kernel(const u16 *A, int64_t rows_a, int64_t cols_a, int64_t lda,
                                                      const u16 *B, int64_t rows_b, int64_t cols_b, int64_t ldb,
-                                                     int64_t *rec)
+                                                     int64_t *rec, int64_t seq)
 {
     const int64_t step = (int64_t)gridDim.x * blockDim.x, t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool over = false;
@@ -228,11 +228,11 @@ __global__ __launch_bounds__(1024) void check_kernel(const u16 *A, int64_t rows_
     const bool any = __syncthreads_or(over);
     if (threadIdx.x != 0) return;
     if (any) __hip_atomic_store(&rec[0], (int64_t)MPR_EOVERFLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (gridDim.x == 1) __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (gridDim.x == 1) __hip_atomic_store(&rec[7], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__global__ void check_end_kernel(int64_t *rec)
+__global__ void check_end_kernel(int64_t *rec, int64_t seq)
 {
-    __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&rec[7], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace mpr
@@ -258,19 +258,17 @@ extern "C" mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, in
     if ((e = ensure_init()) != MPR_OK) return e;
     const int64_t values = M * K + K * N;
     if (values == 0) return product();
-    HostRecord rec;
+    hipStream_t s = as_stream(stream);
+    HostRecord rec(s);
     if (!rec.p) return MPR_ENOMEM;
     rec.p[0] = 0;
-    hipStream_t s = as_stream(stream);
+    const int64_t seq = rec.ticket();
     const unsigned blocks = (unsigned)std::min<int64_t>(values / (8 * 8192) + 1, 2048);
-    hipLaunchKernelGGL(check_kernel, dim3(blocks), dim3(1024), 0, s, A, M, K, lda, B, K, N, ldb, rec.p);
-    if (blocks > 1) hipLaunchKernelGGL(check_end_kernel, dim3(1), dim3(1), 0, s, rec.p);
-    if ((e = check_launch()) != MPR_OK) {
-        (void)hipStreamSynchronize(s);  // nothing writes the record any more
-        return e;
-    }
+    hipLaunchKernelGGL(check_kernel, dim3(blocks), dim3(1024), 0, s, A, M, K, lda, B, K, N, ldb, rec.p, seq);
+    if (blocks > 1) hipLaunchKernelGGL(check_end_kernel, dim3(1), dim3(1), 0, s, rec.p, seq);
+    if ((e = check_launch()) != MPR_OK) return e;
     e = product();
-    const mpr_status w = rec.wait(rec.p, 1, s);
+    const mpr_status w = rec.wait(rec.p, seq);
     if (e == MPR_OK) e = w;
     if (w == MPR_OK) *status_host = (int32_t)rec.p[0];
     return e;

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(PT) void sp_count_kernel(const u16 *A, int64_t lda,
 // counts in LDS when they fit; the total also goes to rec when given.
 constexpr int PCOUNTS = 8 * PT;
 __global__ __launch_bounds__(PT) void sp_scan_kernel(const int64_t *counts, int64_t nblk, int64_t *off, int32_t *order,
-                                                     int64_t *rec)
+                                                     int64_t *rec, int64_t seq)
 {
     __shared__ int wsum[PW];
     __shared__ int cs[PCOUNTS];
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(PT) void sp_scan_kernel(const int64_t *counts, int6
         off[nblk] = run;
         if (rec) {
             rec[0] = run;
-            __hip_atomic_store(&rec[7], (int64_t)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&rec[7], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     __syncthreads();
@@ -927,23 +927,25 @@ static SparsePlan carve_plan(void *ws, int64_t n, size_t bytes)
 
 // The counts, their prefix sums (off[nblk] = the plan's rows) and the order
 // of the blocks: the part of a plan that needs no room for rows.
-static void plan_count(const u16 *A, int64_t n, int64_t lda, const SparsePlan &p, int64_t *rec, hipStream_t s)
+static void plan_count(const u16 *A, int64_t n, int64_t lda, const SparsePlan &p, int64_t *rec, int64_t seq,
+                       hipStream_t s)
 {
     const int vec = aligned16(A) && lda % 8 == 0;
     hipLaunchKernelGGL(sp_count_kernel, dim3((unsigned)p.nblk), dim3(PT), 0, s, A, lda, n, p.counts, vec);
     hipLaunchKernelGGL(sp_scan_kernel, dim3(1), dim3(PT), 0, s, (const int64_t *)p.counts, p.nblk, p.off,
-                       p.order, rec);
+                       p.order, rec, seq);
 }
 
 mpr_status sparse_plan_rows(const u16 *A, int64_t n, int64_t lda, void *ws, hipStream_t s, int64_t *rows)
 {
     SparsePlan p = carve_plan(ws, n, 0);
-    HostRecord rec;
+    HostRecord rec(s);
     if (!rec.p) return MPR_ENOMEM;
-    plan_count(A, n, lda, p, rec.p, s);
+    const int64_t seq = rec.ticket();
+    plan_count(A, n, lda, p, rec.p, seq, s);
     const mpr_status e = check_launch();
     if (e != MPR_OK) return e;
-    const mpr_status w = rec.wait(rec.p, 1, s);
+    const mpr_status w = rec.wait(rec.p, seq);
     if (w == MPR_OK) *rows = rec.p[0];
     return w;
 }
@@ -964,7 +966,7 @@ mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, si
                               hipStream_t s)
 {
     const SparsePlan p = carve_plan(ws, n, bytes);
-    plan_count(A, n, lda, p, nullptr, s);
+    plan_count(A, n, lda, p, nullptr, 0, s);
     return sparse_plan_fill(A, n, lda, ws, bytes, false, st, s);
 }
 
