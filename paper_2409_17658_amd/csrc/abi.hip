@@ -677,7 +677,8 @@ extern "C" mpr_status mpr_sparse_plan_bytes(const uint16_t *A, int64_t n, int64_
     }
     int64_t rows = 0;
     r = sparse_plan_rows(A, n, lda, tmp, s, &rows);
-    if (hipFreeAsync(tmp, s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
+    // the record that gives the rows is written before the kernel has retired
+    if (hipFreeAsync(tmp, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) r = r != MPR_OK ? r : MPR_EHIP;
     if (r == MPR_OK) *bytes_host = sparse_plan_bytes_rows(n, rows) + (n >= 8 ? level_chain_bytes(n) : 0);
     return r;
 }
@@ -830,21 +831,17 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         // the ring of M buffers, so a repeat of power j is confirmed while
         // k - j < M - 1: the workspace of `slots` holds M = slots + 1.
         const int64_t M = w.slots;
-        auto finish = [&](mpr_status e) {
-            if (hipStreamSynchronize(s) != hipSuccess && e == MPR_OK) e = MPR_EHIP;  // the power computed ahead
-            return e;
-        };
-        if ((r = enqueue(1, M)) != MPR_OK) return finish(r);
+        if ((r = enqueue(1, M)) != MPR_OK) return r;
         for (int64_t k = 1; k <= kmax; k++) {
-            if (k + 1 <= kmax && (r = enqueue(k + 1, M)) != MPR_OK) return finish(r);
+            if (k + 1 <= kmax && (r = enqueue(k + 1, M)) != MPR_OK) return r;
             const int64_t *rec = host.p + 8 * (k & 1);
-            if ((r = host.wait(rec, ticket[k & 1])) != MPR_OK) return finish(r);
+            if ((r = host.wait(rec, ticket[k & 1])) != MPR_OK) return r;
             const int64_t hash = rec[0], trace = rec[1];
             const int32_t stv = (int32_t)rec[2];
-            if (stv != 0) return finish((mpr_status)stv);
+            if (stv != 0) return (mpr_status)stv;
             if (bytes && rec[3] != 0) {
                 *restart = true;
-                return finish(MPR_OK);
+                return MPR_OK;
             }
             if (traces_host) traces_host[k] = trace;
             if (k > *reported) report_progress(*reported = k, trace);
@@ -858,7 +855,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
                     bool eq = false;
                     int64_t c = 0;
                     if ((r = same_class(slot_N(w, sj), slot_R(w, sj), slot_N(w, sk), slot_R(w, sk), eq, c)) != MPR_OK)
-                        return finish(r);
+                        return r;
                     if (eq) {
                         found = true;
                         mu = j;
@@ -876,7 +873,6 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
                 break;
             }
         }
-        if ((r = finish(MPR_OK)) != MPR_OK) return r;
         if (!found) return MPR_ENOTFOUND;
         *mu_host = mu;
         *lam_host = lam;
@@ -974,14 +970,19 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     // In bytes where the steps allow it (and A, which a restart reads again,
     // is not given up): half the traffic of every step and pass.
     int64_t reported = 0;
+    bool again = true;
+    mpr_status e = MPR_OK;
     if (sparse && !reuse_a && sparse_step_late(n, lda, lda)) {
-        bool restart = false;
-        const mpr_status e = find_period_impl(A, n, lda, kmax, flags, true, &restart, &reported, mu_host, lam_host,
-                                              c_host, traces_host, ws, ws_bytes, stream);
-        if (!restart) return e;
+        again = false;
+        e = find_period_impl(A, n, lda, kmax, flags, true, &again, &reported, mu_host, lam_host, c_host, traces_host, ws,
+                             ws_bytes, stream);
     }
-    return find_period_impl(A, n, lda, kmax, flags, false, nullptr, &reported, mu_host, lam_host, c_host, traces_host,
-                            ws, ws_bytes, stream);
+    if (again)
+        e = find_period_impl(A, n, lda, kmax, flags, false, nullptr, &reported, mu_host, lam_host, c_host, traces_host,
+                             ws, ws_bytes, stream);
+    // a record tells of a power before the kernel that wrote it has retired
+    if (hipStreamSynchronize(as_stream(stream)) != hipSuccess && (e == MPR_OK || e == MPR_ENOTFOUND)) e = MPR_EHIP;
+    return e;
 }
 
 extern "C" mpr_status mpr_set_period_progress(void (*fn)(int64_t k, int64_t trace, void *user), void *user)

@@ -29,3 +29,10 @@ def test_failed_launch_leaves_no_writer_behind(driver):
     allocation is not reported again by the next call."""
     p = driver("errors")
     assert p.returncode == 0, p.stdout
+
+
+def test_synchronous_calls_return_with_the_stream_drained(driver):
+    """mpr_find_period and mpr_sparse_plan_bytes are synchronous: the kernel
+    that wrote the record a call waited for has retired when they return."""
+    p = driver("idle")
+    assert p.returncode == 0, p.stdout
