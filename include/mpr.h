@@ -156,8 +156,8 @@ mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K,
 /* The product of mpr_minplus_gemm_cfg (spare = 0) or mpr_minplus_gemm_spare
  * (spare != 0) with its inputs checked and the verdict given to the host:
  * *status_host = 0, or MPR_EOVERFLOW when a finite input exceeds MPR_FMAX.
- * Waits for the check only (the product may still run when the call
- * returns); allocates no device memory.  Not for captured streams. */
+ * Waits for the product and the check; allocates no device memory.  Not for
+ * captured streams. */
 mpr_status mpr_minplus_gemm_checked(int cfg, int spare, int64_t M, int64_t N, int64_t K,
                                     const uint16_t *A, int64_t lda,
                                     const uint16_t *B, int64_t ldb,

@@ -120,10 +120,7 @@ HostRecord::~HostRecord()
     if (!p) return;
     // a writer may still be on its way (a failed launch behind it, a failed
     // wait): a stream that can not be drained keeps the record
-    if (seen != newest && hipStreamSynchronize(s) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
-    }
+    if (seen != newest && drain() != MPR_OK) return;
     {
         std::lock_guard<std::mutex> lk(g_records_mu);
         if (g_records_free < kRecords) {
@@ -135,6 +132,16 @@ HostRecord::~HostRecord()
 }
 
 int64_t HostRecord::ticket() { return newest = ++g_tickets; }
+
+mpr_status HostRecord::drain()
+{
+    if (hipStreamSynchronize(s) != hipSuccess) {
+        (void)hipGetLastError();
+        return MPR_EHIP;
+    }
+    seen = newest;
+    return MPR_OK;
+}
 
 // Waits until a kernel on the stream has written `seq` into the record: a look
 // at host memory (6 us from launch to here, 21 us with a copy and a
@@ -731,8 +738,8 @@ extern "C" mpr_status mpr_period_workspace_size(int64_t n, int64_t slots, size_t
 // The search; bytes: the powers are kept in bytes (sparse.hip), and *restart
 // tells that a value left their range, so that the search has to start again
 // without.  reported: powers the observer has heard of.
-static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, int64_t kmax, int flags, bool bytes,
-                                   bool *restart, int64_t *reported, int64_t *mu_host, int64_t *lam_host,
+static mpr_status find_period_impl(HostRecord &host, const uint16_t *A, int64_t n, int64_t lda, int64_t kmax, int flags,
+                                   bool bytes, bool *restart, int64_t *reported, int64_t *mu_host, int64_t *lam_host,
                                    int64_t *c_host, int64_t *traces_host, void *ws, size_t ws_bytes, mpr_stream stream)
 {
     const bool sparse = (flags & MPR_PERIOD_SPARSE) != 0;
@@ -797,9 +804,7 @@ static mpr_status find_period_impl(const uint16_t *A, int64_t n, int64_t lda, in
         c = no_rows ? 0 : cmp[1];
         return MPR_OK;
     };
-    HostRecord host(s);  // two records, powers in turn
-    int64_t ticket[2];
-    if (!host.p) return MPR_ENOMEM;
+    int64_t ticket[2];  // two records, powers in turn
     // Power k into slot (k - 1) % M, its record on the way to the host.
     auto enqueue = [&](int64_t k, int64_t M) -> mpr_status {
         const int64_t slot = (k - 1) % M, ps = (k - 2 + M) % M, seq = ticket[k & 1] = host.ticket();
@@ -969,20 +974,22 @@ extern "C" mpr_status mpr_find_period_ex(const uint16_t *A, int64_t n, int64_t l
     if (r != MPR_OK) return r;
     // In bytes where the steps allow it (and A, which a restart reads again,
     // is not given up): half the traffic of every step and pass.
+    HostRecord host(as_stream(stream));
+    if (!host.p) return MPR_ENOMEM;
     int64_t reported = 0;
     bool again = true;
     mpr_status e = MPR_OK;
     if (sparse && !reuse_a && sparse_step_late(n, lda, lda)) {
         again = false;
-        e = find_period_impl(A, n, lda, kmax, flags, true, &again, &reported, mu_host, lam_host, c_host, traces_host, ws,
-                             ws_bytes, stream);
+        e = find_period_impl(host, A, n, lda, kmax, flags, true, &again, &reported, mu_host, lam_host, c_host,
+                             traces_host, ws, ws_bytes, stream);
     }
     if (again)
-        e = find_period_impl(A, n, lda, kmax, flags, false, nullptr, &reported, mu_host, lam_host, c_host, traces_host,
-                             ws, ws_bytes, stream);
+        e = find_period_impl(host, A, n, lda, kmax, flags, false, nullptr, &reported, mu_host, lam_host, c_host,
+                             traces_host, ws, ws_bytes, stream);
     // a record tells of a power before the kernel that wrote it has retired
-    if (hipStreamSynchronize(as_stream(stream)) != hipSuccess && (e == MPR_OK || e == MPR_ENOTFOUND)) e = MPR_EHIP;
-    return e;
+    const mpr_status d = host.drain();
+    return e == MPR_OK || e == MPR_ENOTFOUND ? (d != MPR_OK ? d : e) : e;
 }
 
 extern "C" mpr_status mpr_set_period_progress(void (*fn)(int64_t k, int64_t trace, void *user), void *user)

@@ -801,6 +801,7 @@ struct HostRecord {
     HostRecord &operator=(const HostRecord &) = delete;
     int64_t ticket();
     mpr_status wait(const int64_t *rec, int64_t seq);
+    mpr_status drain();  // waits for the stream
 
 private:
     hipStream_t s;

@@ -65,6 +65,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
     static int64_t hash = 1;
     if (k.find("14sp_scan_kernel") != k.npos) record(4, 32);
     else if (k.find("12check_kernel") != k.npos && grid.x == 1) record(8, 0);
+    else if (k.find("19tiny_checked_kernel") != k.npos) record(9, 0);
     else if (k.find("16check_end_kernel") != k.npos) record(0, 0);
     else if (k.find("19period_small_kernel") != k.npos) record(8, hash++);
     else if (k.find("18period_rows_kernel") != k.npos) record(10, hash++);
@@ -152,7 +153,7 @@ int main(int argc, char **argv)
     auto look = [&](const Case &k, const char *when) {
         size_t left = 0;
         for (const Kernel &q : queued) left += !errors || q.writes;
-        const bool runs = !errors && retiring;
+        const bool runs = !errors && retiring && k.name[0] != 'c';  // the check's record is the product's end
         if (!left && !runs && !verdict) return;
         printf("%s, %s: %zu kernels still queued, %s, verdict %d\n", k.name.c_str(), when, left,
                runs ? "one running" : "none running", verdict);
@@ -160,7 +161,6 @@ int main(int argc, char **argv)
         (void)hipStreamSynchronize(nullptr);
     };
     for (const Case &k : cases) {
-        if (!errors && k.name[0] == 'c') continue;
         fail_at = -1, checks = 0;
         const mpr_status ok = k.call();
         if (ok != MPR_OK && ok != MPR_ENOTFOUND) printf("%s: status %d\n", k.name.c_str(), ok), bad++;

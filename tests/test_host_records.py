@@ -33,6 +33,8 @@ def test_failed_launch_leaves_no_writer_behind(driver):
 
 def test_synchronous_calls_return_with_the_stream_drained(driver):
     """mpr_find_period and mpr_sparse_plan_bytes are synchronous: the kernel
-    that wrote the record a call waited for has retired when they return."""
+    that wrote the record a call waited for has retired when they return.
+    A checked product has run as well: only its check, which runs behind it and
+    wrote the record, may still be retiring."""
     p = driver("idle")
     assert p.returncode == 0, p.stdout
