@@ -411,7 +411,7 @@ static PeriodWs carve_period(void *ws, int64_t n, size_t ws_bytes, int64_t slots
     PeriodWs w{};
     w.ld = round_up(n > 0 ? n : 1, 8);
     Carver c(ws);
-    w.acc = c.take<char>(period_acc_bytes());
+    w.acc = c.take<int64_t>((size_t)n);
     w.scal = c.take<int64_t>(8);
     w.hold_R = (flags & MPR_PERIOD_REUSE_A) ? c.take<int64_t>((size_t)n) : nullptr;
     if (flags & MPR_PERIOD_SPARSE) {
@@ -767,7 +767,7 @@ static mpr_status find_period_impl(HostRecord &host, const uint16_t *A, int64_t 
     const bool small = bytes && n <= PERIOD_SMALL_N;
     if (!small) {
         if ((r = fill_i32_launch(st, 2, 0, s)) != MPR_OK || (r = fill_i32_launch(big, 1, 0, s)) != MPR_OK) return r;
-        if ((r = period_clear_launch(w.acc, s)) != MPR_OK) return r;
+        if ((r = period_clear_launch(w.acc, n, s)) != MPR_OK) return r;
         // the counts that sized the plan lie where it begins (same carving)
         if (sparse && (r = sparse_plan_fill(A, n, lda, w.plan, w.plan_bytes, bytes, st, s)) != MPR_OK) return r;
     }

@@ -757,9 +757,9 @@ mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size
 
 // period.hip: one pass over a power of a period search (canonical form to dst,
 // offsets, and into rec the class hash, trace, status and seq), and the
-// accumulator it folds into (cleared once; every pass leaves it clear).
-size_t period_acc_bytes();
-mpr_status period_clear_launch(void *acc, hipStream_t s);
+// accumulator of 8 n bytes, rounded up to 256, that it folds into (cleared
+// once; every pass leaves it clear).
+mpr_status period_clear_launch(void *acc, int64_t n, hipStream_t s);
 // The same over a power in bytes, in groups of 8 columns: [column / 8][row]
 // [column % 8], the rows padded to whole lines, at most as large as its n rows
 // of u16.  Raw sums with 255 = infinity (or, first not null, the u16 matrix

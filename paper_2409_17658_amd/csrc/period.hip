@@ -9,11 +9,13 @@
 // words with keys by position (the NH hash of UMAC, Black et al. 1999), one
 // multiply-add per 4 entries instead of two 64-bit multiplications per entry,
 // and for the offsets a linear sum, whose shift by the least offset can be
-// taken off at the end.  Each block folds its row into one of PSLOTS records
+// taken off at the end.  Each block folds its row into one of PSLOTS slots
 // and the last block combines them, where two more kernels of one block used
 // to read n words each (m = 8: 68 + 13 + 9 us, in bytes 30; m = 9: 410 + 51 +
 // 24 us, in bytes 246; m = 3: 6.0 + 3.4 + 3.3 us and a copy to the host, now
 // within the 6.7 us of a whole power).
+#include <algorithm>
+
 #include "level.h"
 
 namespace mpr {
@@ -28,21 +30,26 @@ struct PeriodSlot {
 };
 static_assert(sizeof(PeriodSlot) == 64, "a slot to a half line");
 struct PeriodAcc {
-    PeriodSlot slot[PSLOTS];
     uint32_t full, pad[15];  // slots complete
+    PeriodSlot slot[PSLOTS];
 };
-size_t period_acc_bytes() { return sizeof(PeriodAcc); }
-
-__device__ __forceinline__ void period_clear(PeriodAcc *a, int t)
+// Slots in use: as many as fit the 8 n bytes, rounded up to 256, that a
+// workspace has for the accumulator.
+static int period_slots(int64_t n)
 {
-    if (t < PSLOTS) {
+    return (int)std::min<int64_t>(PSLOTS, round_up(8 * n, 256) / (int64_t)sizeof(PeriodSlot) - 1);
+}
+
+__device__ __forceinline__ void period_clear(PeriodAcc *a, int t, int slots)
+{
+    if (t < slots) {
         PeriodSlot z{};
         z.least = z.trace = ROW_NONE;
         a->slot[t] = z;
     }
     if (t == 0) a->full = 0;
 }
-__global__ void period_clear_kernel(PeriodAcc *a) { period_clear(a, (int)threadIdx.x); }
+__global__ void period_clear_kernel(PeriodAcc *a, int slots) { period_clear(a, (int)threadIdx.x, slots); }
 
 template <class X>
 __device__ __forceinline__ X agent_add(X *p, X v)
@@ -100,12 +107,12 @@ __device__ __forceinline__ RowPart period_row(int64_t i, uint32_t m, uint32_t di
 // Folds a block's rows into the power, called by every thread (x and refuse
 // of thread 0; refuse: 1 out of range, 2 wide).  wide: a second status word
 // for the record, or null.
-__device__ __forceinline__ void period_fold(const RowPart &x, int refuse, PeriodAcc *acc, int32_t *st, int32_t *wide,
-                                            int64_t *rec, int64_t seq, int *last)
+__device__ __forceinline__ void period_fold(const RowPart &x, int refuse, PeriodAcc *acc, int nslots, int32_t *st,
+                                            int32_t *wide, int64_t *rec, int64_t seq, int *last)
 {
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
     if (threadIdx.x == 0) {
-        PeriodSlot *s = &acc->slot[blockIdx.x % PSLOTS];
+        PeriodSlot *s = &acc->slot[blockIdx.x % (uint32_t)nslots];
         // every fold completes (its old value arrives) before the block counts
         uint64_t seen = agent_add(&s->hash, x.hash);
         if (x.least != ROW_NONE) {
@@ -117,8 +124,8 @@ __device__ __forceinline__ void period_fold(const RowPart &x, int refuse, Period
             seen |= (uint64_t)__hip_atomic_exchange(st, MPR_EOVERFLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (refuse & 2) seen |= (uint64_t)__hip_atomic_exchange(wide, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" : : "v"(seen) : "memory");
-        const uint32_t blocks = ((uint32_t)gridDim.x + PSLOTS - 1 - blockIdx.x % PSLOTS) / PSLOTS;  // of this slot
-        const uint32_t slots = min((uint32_t)gridDim.x, (uint32_t)PSLOTS);
+        const uint32_t blocks = ((uint32_t)gridDim.x + nslots - 1 - blockIdx.x % (uint32_t)nslots) / nslots;  // of this slot
+        const uint32_t slots = min((uint32_t)gridDim.x, (uint32_t)nslots);
         *last = 0;
         if (agent_add(&s->done, 1u) + 1 == blocks) *last = agent_add(&acc->full, 1u) + 1 == slots;
     }
@@ -126,17 +133,17 @@ __device__ __forceinline__ void period_fold(const RowPart &x, int refuse, Period
     if (!*last || w != 0) return;
     // The last block of the power: one lane per slot (reads at the place where
     // the folds happened), then the record and a clear accumulator.
-    PeriodSlot *s = &acc->slot[lane % PSLOTS];
-    uint64_t hs = lane < PSLOTS ? agent_add(&s->hash, (uint64_t)0) : 0;
-    uint64_t os = lane < PSLOTS ? agent_add(&s->offsets, (uint64_t)0) : 0;
-    uint64_t ks = lane < PSLOTS ? agent_add(&s->keys, (uint64_t)0) : 0;
+    PeriodSlot *s = &acc->slot[lane < nslots ? lane : 0];
+    uint64_t hs = lane < nslots ? agent_add(&s->hash, (uint64_t)0) : 0;
+    uint64_t os = lane < nslots ? agent_add(&s->offsets, (uint64_t)0) : 0;
+    uint64_t ks = lane < nslots ? agent_add(&s->keys, (uint64_t)0) : 0;
     const int64_t lo = wave_min_i64(agent_min(&s->least, ROW_NONE));
     const int64_t tr = wave_min_i64(agent_min(&s->trace, ROW_NONE));
     hs = wave_sum_u64(hs);
     os = wave_sum_u64(os);
     ks = wave_sum_u64(ks);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    period_clear(acc, lane);
+    period_clear(acc, lane, nslots);
     if (lane != 0) return;
     const int32_t code = __hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     rec[0] = (int64_t)mix64(hs + mix64(os - (lo == ROW_NONE ? 0 : (uint64_t)lo * ks)));
@@ -154,7 +161,7 @@ __device__ __forceinline__ void period_fold(const RowPart &x, int refuse, Period
 template <int NCH>
 __global__ __launch_bounds__(RT) void period_rows_kernel(const u16 *src, int64_t lds_, u16 *dst, int64_t ldd, int64_t n,
                                                          const int64_t *R_in, int64_t *R_out, int raw, PeriodAcc *acc,
-                                                         int32_t *st, int64_t *rec, int64_t seq)
+                                                         int nslots, int32_t *st, int64_t *rec, int64_t seq)
 {
     __shared__ uint32_t least[RT / 64];
     __shared__ uint64_t hsum[RT / 64];
@@ -233,7 +240,7 @@ __global__ __launch_bounds__(RT) void period_rows_kernel(const u16 *src, int64_t
     __syncthreads();
     RowPart x{};
     if (threadIdx.x == 0) x = period_row(i, m, diag, hsum[0] + hsum[1] + hsum[2] + hsum[3], R_in, R_out);
-    period_fold(x, refuse, acc, st, nullptr, rec, seq, &last);
+    period_fold(x, refuse, acc, nslots, st, nullptr, rec, seq, &last);
 }
 
 // The same in bytes (level bytes in column groups, sparse.hip), 16 rows to a
@@ -246,7 +253,7 @@ constexpr int GROWS = 16;
 template <int T, int NCH, bool FIRST>
 __global__ __launch_bounds__(T) void period_rows8_kernel(const u16 *X, int64_t ldx, uint8_t *N, int64_t group8, int64_t n,
                                                          const int64_t *R_in, int64_t *R_out, PeriodAcc *acc,
-                                                         int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
+                                                         int nslots, int32_t *st, int32_t *wide, int32_t *big, int64_t *rec,
                                                          int64_t seq)
 {
     constexpr int W = T / 64, GSTEP = T / 8;  // groups of a sweep
@@ -433,7 +440,7 @@ __global__ __launch_bounds__(T) void period_rows8_kernel(const u16 *X, int64_t l
         if (lane == 0 && (int)v > __hip_atomic_load(big, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             atomicMax(big, (int)v);
     }
-    period_fold(x, refuse, acc, st, wide, rec, seq, &last);
+    period_fold(x, refuse, acc, nslots, st, wide, rec, seq, &last);
 }
 
 mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_t n, const int64_t *R_in,
@@ -445,7 +452,7 @@ mpr_status period_rows8_launch(const u16 *first, int64_t lda, uint8_t *N, int64_
     const int64_t group8 = level_group8(n), groups = (n + 7) / 8;
 #define ROWS8(T, NCH, FIRST)                                                                                           \
     hipLaunchKernelGGL((period_rows8_kernel<T, NCH, FIRST>), grid, dim3(T), 0, s, first, lda, N, group8, n, R_in, R_out, \
-                       (PeriodAcc *)acc, st, wide, big, rec, seq)
+                       (PeriodAcc *)acc, period_slots(n), st, wide, big, rec, seq)
     // the forms keep a row's groups in registers (m = 9: 1024 threads spilled,
     // 301 us; 512 with twice the groups each do not, 246)
     if (first)
@@ -546,9 +553,9 @@ mpr_status period_small_launch(const u16 *A, int64_t lda, const uint8_t *N, uint
     return check_launch();
 }
 
-mpr_status period_clear_launch(void *acc, hipStream_t s)
+mpr_status period_clear_launch(void *acc, int64_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(period_clear_kernel, dim3(1), dim3(64), 0, s, (PeriodAcc *)acc);
+    hipLaunchKernelGGL(period_clear_kernel, dim3(1), dim3(64), 0, s, (PeriodAcc *)acc, period_slots(n));
     return check_launch();
 }
 
@@ -561,7 +568,7 @@ mpr_status period_rows_launch(const u16 *src, int64_t lds_, u16 *dst, int64_t ld
                   : n <= 12 * RT * 8 ? period_rows_kernel<12>
                                      : period_rows_kernel<0>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(RT), 0, s, src, lds_, dst, ldd, n, R_in, R_out, raw ? 1 : 0,
-                       (PeriodAcc *)acc, st, rec, seq);
+                       (PeriodAcc *)acc, period_slots(n), st, rec, seq);
     return check_launch();
 }
 

@@ -68,8 +68,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
     else if (k.find("19tiny_checked_kernel") != k.npos) record(9, 0);
     else if (k.find("16check_end_kernel") != k.npos) record(0, 0);
     else if (k.find("19period_small_kernel") != k.npos) record(8, hash++);
-    else if (k.find("18period_rows_kernel") != k.npos) record(10, hash++);
-    else if (k.find("19period_rows8_kernel") != k.npos) record(11, hash++);
+    else if (k.find("18period_rows_kernel") != k.npos) record(11, hash++);
+    else if (k.find("19period_rows8_kernel") != k.npos) record(12, hash++);
     else queued.push_back({[] {}, false});
     return hipSuccess;
 }
