@@ -1,0 +1,106 @@
+"""The block shapes that products, chain steps and batches take between 160
+and 255 tiles of 128 x 128, and 128 x 256 blocks with ragged edges, with values
+in the levels, past them, and past 2048: against the uint16 configuration 0
+(itself checked against the oracle)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1700, 1730, 135), (1000, 3333, 300), (2500, 2570, 135), (2049, 6200, 192)]
+LAWS = [(0, 15, 0.3), (0, 200, 0.25), (22, 23, 0.99), (14, 40, 0.3), (0, 3000, 0.25), (1000, 10000, 0.2),
+        (1500, 0x7FFF, 0.2), (0, 1, 1.0)]
+
+
+@pytest.fixture(scope="module")
+def mpr():
+    import paper_2409_17658_amd as m
+
+    m.lib()
+    m.init(0)
+    return m
+
+
+def _same(a, b):
+    return torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("law", LAWS)
+def test_products(mpr, law):
+    for i, (M, N, K) in enumerate(SHAPES):
+        print("blocks", law, (M, N, K), flush=True)
+        lo, hi, inf = law
+        X, Y = synth.random_matrix(M, K, 1 + i, lo, hi, inf), synth.random_matrix(K, N, 50 + i, lo, hi, inf)
+        A = mpr.to_device(X) if i % 2 else torch.from_numpy(X).cuda()
+        B = mpr.to_device(Y)
+        ref = mpr.minplus_gemm(A, B, cfg=0)
+        assert _same(mpr.minplus_gemm(A, B), ref)
+        assert _same(mpr.minplus_gemm(A, B, spare=True), ref)
+        rows = [0, 127, 128, M - 1]
+        assert np.array_equal(ref.cpu().numpy()[rows], O.to_u16(O.minplus(O.from_u16(X[rows]), O.from_u16(Y))))
+
+
+def test_products_of_mixed_blocks(mpr):
+    """Rows past the levels in some blocks only, columns in others."""
+    for M, N, K in SHAPES:
+        X, Y = synth.random_matrix(M, K, 3, 0, 9, 0.4), synth.random_matrix(K, N, 4, 0, 9, 0.4)
+        X[130:300] = np.where(X[130:300] == mpr.INF, mpr.INF, X[130:300] + 2500)
+        Y[:, 900:1100] = np.where(Y[:, 900:1100] == mpr.INF, mpr.INF, Y[:, 900:1100] + 700)
+        X[M - 1], Y[:, N - 2] = mpr.INF, mpr.INF
+        A, B = mpr.to_device(X), mpr.to_device(Y)
+        assert _same(mpr.minplus_gemm(A, B), mpr.minplus_gemm(A, B, cfg=0))
+
+
+STEP_LAWS = [(0, 31, 0.25), (0, 60, 0.9), (2100, 3000, 0.2), (0x7000, 0x7FFF, 0.3), (0, 3000, 0.2)]
+
+
+def _chain(mpr, A, e):
+    """A^e by products of configuration 0 and normalisations."""
+    N = A.clone()
+    R = mpr.normalise(N)
+    for _ in range(e - 1):
+        N = mpr.minplus_gemm(N, A, cfg=0, check=False)
+        R = mpr.normalise(N, R_in=R)
+    return N, R
+
+
+@pytest.mark.parametrize("n", [900, 1700, 2100])
+@pytest.mark.parametrize("law", STEP_LAWS)
+def test_chain_steps(mpr, n, law):
+    """Chain steps normalised late (a workspace with room for their minima)."""
+    lo, hi, inf = law
+    A = mpr.to_device(synth.random_matrix(n, n, n, lo, hi, inf))
+    for e in (2, 4):
+        ws = mpr.workspace(mpr.power_workspace_size(n, e, mpr.CHAIN) + 32 * n + 4096)
+        N, R = mpr.minplus_power(A, e, mpr.CHAIN, ws=ws)
+        Nr, Rr = _chain(mpr, A, e)
+        assert _same(N, Nr) and torch.equal(R, Rr)
+
+
+@pytest.mark.parametrize("law", STEP_LAWS)
+def test_batch_steps(mpr, law):
+    """A batch of more than 256 tiles of 128 x 256, beside small chains."""
+    lo, hi, inf = law
+    chains, want = [], []
+    for i, (n, e) in enumerate([(4101, 3), (300, 5), (1300, 2), (9, 4)]):
+        A = mpr.to_device(synth.random_matrix(n, n, 70 + i, lo, hi, inf))
+        chains.append((A, e, mpr.alloc_matrix(n, n), torch.empty(n, dtype=torch.int64, device="cuda")))
+        want.append(_chain(mpr, A, e))
+    mpr.batch_power(chains)
+    for (_, _, N, R), (Nr, Rr) in zip(chains, want):
+        assert _same(N, Nr) and torch.equal(R, Rr)
+
+
+def test_batch_overflow_is_reported(mpr):
+    n, e = 4101, 3
+    X = np.full((n, n), mpr.INF, dtype=np.uint16)
+    X[np.arange(n), (np.arange(n) + 1) % n] = 0x7FFF
+    X[np.arange(n), np.arange(n)] = 0
+    chain = (mpr.to_device(X), e, mpr.alloc_matrix(n, n), torch.empty(n, dtype=torch.int64, device="cuda"))
+    with pytest.raises(mpr.MprError) as err:
+        mpr.batch_power([chain])
+    assert err.value.status == 3
