@@ -140,13 +140,16 @@ mpr_status mpr_build_border_transfer(int m, uint16_t *A, int64_t lda, int64_t *s
  * [0, 0xFFFE].  M, N, K >= 0 (an empty K gives an all-MPR_INF C).  C must
  * not overlap A or B.  Fast path: A, B, C 16-byte aligned and lda, ldb, ldc
  * multiples of 8; any other layout takes a slower element-wise path.  The
- * product runs on the matrix cores when K >= 128 (values 0..30 as powers of
- * two, the least sum read off the exponent of a sum of products; a block
- * with a larger minimum is computed again in the f16 form), else in the
- * configuration of the tile table of the process-wide arithmetic
- * (mpr_set_arith): packed uint16 by default; in the f16 form the result is
- * the same, but tiles whose minima reach 2048 are computed twice (about
- * 1.75x the uint16 time for such tiles).  The same bits in every form. */
+ * product runs on the matrix cores when K >= 128 and N >= 4 (values 0..30 as
+ * powers of two, the least sum read off the exponent of a sum of products).
+ * A block of it whose minima pass that range is computed in the f16 form or,
+ * where its values say that minima reach 2048, in uint16; a large product
+ * whose values say so as a whole, in the configuration of the tile table.
+ * Other products run in the configuration of the tile table of the
+ * process-wide arithmetic (mpr_set_arith; mpr_gemm_pick_config names it):
+ * packed uint16 by default; in the f16 form the result is the same, but tiles
+ * whose minima reach 2048 are computed twice (about 1.75x the uint16 time for
+ * such tiles).  The same bits in every form. */
 mpr_status mpr_minplus_gemm(int64_t M, int64_t N, int64_t K,
                             const uint16_t *A, int64_t lda,
                             const uint16_t *B, int64_t ldb,

@@ -6,7 +6,7 @@
 #include <mutex>
 #include <vector>
 
-#include "tile.h"
+#include "level.h"
 
 namespace mpr {
 
@@ -22,11 +22,10 @@ using Cfg6 = TileCfg<256, 128, 32, 8, 8>;    // 512 threads, 8x8 per lane
 // Blocks are handed to the 8 XCDs round-robin (block b runs on XCD b % 8).
 // Renumber so that each XCD receives a contiguous run of tiles, and walk the
 // tiles in groups of G tile-rows so that the blocks resident on one XCD share
-// A row panels and B column panels in that XCD's L2.
-__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int &tm, int &tn)
+// A row panels and B column panels in that XCD's L2.  b: block of nb, a multiple
+// of 8.
+__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int &tm, int &tn, int b, int nb)
 {
-    const int nb = (int)gridDim.x;  // a multiple of 8
-    const int b = (int)blockIdx.x;
     const int t = (b & 7) * (nb >> 3) + (b >> 3);
     if (t >= tiles_m * tiles_n) return false;
     constexpr int G = 8;
@@ -54,11 +53,36 @@ __global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(GemmWaves
 {
     __shared__ __attribute__((aligned(16))) u16 lds[T::LDS_ELEMS];
     int tm, tn;
-    if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+    if (!tile_of_block(tiles_m, tiles_n, tm, tn, (int)blockIdx.x, (int)gridDim.x)) return;
     const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
     TileAcc<T> acc;
     tile_mainloop<T, H>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, lds, acc);
     tile_store<T>(C, ldc, M, N, m0, n0, vec != 0, acc);
+}
+
+// The same tiles of a product whose values are out of the level form's range
+// (level_sample), in the f16 form or uint16 by those values; of another one,
+// nothing, which a block a tile takes 100 us to find out at N = 16384: so no
+// more than four times the blocks that the chip holds, which share the nb tiles
+// (one time: N = 3350 1434 us, with all of them 1376).
+template <class T>
+__global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(GemmWaves<T>::value))) void gemm_past_kernel(
+    const u16 *__restrict__ A, int64_t lda, const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ C, int64_t ldc,
+    int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int vec)
+{
+    __shared__ __attribute__((aligned(16))) u16 lds[T::LDS_ELEMS];
+    __shared__ int seen;
+    const LevelView view = level_sample(A, lda, B, ldb, M, N, K, &seen);
+    if (view <= LEVEL_PAST) return;
+    const int nb = (tiles_m * tiles_n + 7) / 8 * 8;
+    for (int b = (int)blockIdx.x; b < nb; b += (int)gridDim.x) {
+        int tm, tn;
+        if (!tile_of_block(tiles_m, tiles_n, tm, tn, b, nb)) continue;
+        const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
+        TileAcc<T> acc;
+        tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, lds, acc, view == LEVEL_U16);
+        tile_store<T>(C, ldc, M, N, m0, n0, vec != 0, acc);
+    }
 }
 
 // An empty inner dimension: every entry of C is infinite.
@@ -69,17 +93,20 @@ __global__ void fill_inf_kernel(u16 *C, int64_t ldc, int64_t M, int64_t N)
         C[(t / N) * ldc + t % N] = 0xFFFF;
 }
 
-template <class T, bool H>
+template <class T, bool H, bool PAST = false>
 static mpr_status launch_cfg(int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                              int64_t ldb, u16 *C, int64_t ldc, hipStream_t s, size_t pad_lds = 0)
 {
     const int64_t tiles_m = (M + T::BM - 1) / T::BM, tiles_n = (N + T::BN - 1) / T::BN;
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
-    const int64_t blocks = round_up(tiles, 8);
+    int64_t blocks = round_up(tiles, 8);
+    if (PAST) blocks = std::min<int64_t>(blocks, 4 * round_up(device_cu_count(), 8) * GemmWaves<T>::value * 256 / T::NT);
     const bool vec = aligned16(A) && aligned16(B) && aligned16(C) && lda % 8 == 0 && ldb % 8 == 0 && ldc % 8 == 0;
-    hipLaunchKernelGGL((gemm_kernel<T, H>), dim3((unsigned)blocks), dim3(T::NT), pad_lds, s, A, lda, B, ldb, C, ldc, M,
-                       N, K, (int)tiles_m, (int)tiles_n, vec ? 1 : 0);
+    auto kernel = gemm_kernel<T, H>;
+    if constexpr (PAST) kernel = gemm_past_kernel<T>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(T::NT), pad_lds, s, A, lda, B, ldb, C, ldc, M, N, K,
+                       (int)tiles_m, (int)tiles_n, vec ? 1 : 0);
     return check_launch();
 }
 
@@ -98,10 +125,11 @@ static void residency(int *blocks, size_t *lds)
     *lds = fa.sharedSizeBytes;
 }
 
+typedef mpr_status (*GemmLaunch)(int64_t, int64_t, int64_t, const u16 *, int64_t, const u16 *, int64_t, u16 *, int64_t,
+                                 hipStream_t, size_t);
 struct CfgInfo {
     int bm, bn, bk, tm, tn, nt, arith;
-    mpr_status (*launch)(int64_t, int64_t, int64_t, const u16 *, int64_t, const u16 *, int64_t, u16 *, int64_t,
-                         hipStream_t, size_t);
+    GemmLaunch launch, past;
     void (*residency)(int *, size_t *);
 };
 
@@ -111,7 +139,7 @@ struct CfgInfo {
 // 512-thread tile in uint16, 13 the same in the f16 form.
 #define MPR_CFG(T, H)                                                                                 \
     {T::BM, T::BN, T::BK, T::TM, T::TN, T::NT, H ? MPR_ARITH_F16 : MPR_ARITH_U16, launch_cfg<T, H>,       \
-     residency<T, H>}
+     launch_cfg<T, H, true>, residency<T, H>}
 static const CfgInfo kCfgs[] = {MPR_CFG(Cfg0, false), MPR_CFG(Cfg1, false), MPR_CFG(Cfg2, false),
                                 MPR_CFG(Cfg3, false), MPR_CFG(Cfg4, false), MPR_CFG(Cfg5, false),
                                 MPR_CFG(Cfg0, true),  MPR_CFG(Cfg1, true),  MPR_CFG(Cfg2, true),
@@ -163,12 +191,10 @@ mpr_status gemm_launch(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, i
 // LDS of one CU on gfx950.
 constexpr size_t kLdsPerCU = 160 * 1024;
 
-mpr_status gemm_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
-                             int64_t ldb, u16 *C, int64_t ldc, hipStream_t s)
+// The configuration that a launch which leaves room on every CU runs cfg as,
+// and the dynamic LDS of its workgroups.
+static size_t spare_config(int &cfg)
 {
-    if (M == 0 || N == 0 || K == 0) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
-    if (cfg < 0) cfg = pick_config(M, N, K);
-    if (cfg >= kNumCfgs) return MPR_EINVAL;
     // The plain launch, with extra dynamic LDS per workgroup so that one
     // workgroup fewer fits on a CU than registers and static LDS allow: the
     // blocks still retire and refill as usual, and the slot left over (its
@@ -194,12 +220,31 @@ mpr_status gemm_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16
         cfg = kCfgs[cfg].arith == MPR_ARITH_F16 ? 6 : 0;  // Cfg0 in either arithmetic
         info(cfg, blocks, lds);
     }
-    if (blocks < 3) return kCfgs[cfg].launch(M, N, K, A, lda, B, ldb, C, ldc, s, 0);
+    if (blocks < 3) return 0;
     // (blocks - 1) workgroups of `per` bytes fit with 4 KB to spare, blocks do not
     const size_t per = ((kLdsPerCU - 4096) / (size_t)(blocks - 1)) & ~(size_t)1023;
-    const size_t pad = per > lds ? per - lds : 0;
+    return per > lds ? per - lds : 0;
+}
+
+mpr_status gemm_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                             int64_t ldb, u16 *C, int64_t ldc, hipStream_t s)
+{
+    if (M == 0 || N == 0 || K == 0) return gemm_launch(cfg, M, N, K, A, lda, B, ldb, C, ldc, s);
+    if (cfg < 0) cfg = pick_config(M, N, K);
+    if (cfg >= kNumCfgs) return MPR_EINVAL;
+    const size_t pad = spare_config(cfg);
     return kCfgs[cfg].launch(M, N, K, A, lda, B, ldb, C, ldc, s, pad);
 }
+
+mpr_status gemm_past_launch(bool spare, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                            int64_t ldb, u16 *C, int64_t ldc, hipStream_t s)
+{
+    if (!level_sampled(M, N, K)) return MPR_EUNSUPPORTED;
+    int cfg = pick_config(M, N, K);
+    const size_t pad = spare ? spare_config(cfg) : 0;
+    return kCfgs[cfg].past(M, N, K, A, lda, B, ldb, C, ldc, s, pad);
+}
+
 
 }  // namespace mpr
 

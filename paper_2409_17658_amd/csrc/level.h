@@ -183,7 +183,14 @@ struct LevelA {
             make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
                        level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
-    __device__ __forceinline__ uint32_t first() const { return value2(r[0].x, 0) & 0xFFFFu; }  // any one value
+    // one value, of another k by row (rows past the end are all the last one)
+    __device__ __forceinline__ uint32_t first() const
+    {
+        const int row = C::tid() / C::KC;
+        const uint64_t lo = (uint64_t)r[0].y << 32 | r[0].x, hi = (uint64_t)r[0].w << 32 | r[0].z;
+        const uint32_t v = value2((uint32_t)(((row & 2) ? hi : lo) >> (row & 1) * 32), 0);
+        return v >> (row & 4) * 4 & 0xFFFFu;
+    }
     // largest finite value (signed: infinity is negative)
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {
@@ -291,6 +298,88 @@ struct LevelAcc {
     uint32_t v[C::MI][C::NI][4];
 };
 
+// What a look at a block's values says: all that it saw are in the levels; a
+// finite one is past LV_MAX, so its results can not all be proved by
+// level_clean; so few are in range that the block gives up, for the f16 form or
+// (minima of 2048 and more to be expected) the uint16 form of tile.h; the whole
+// product gives up, and a launch of its own computes it.
+enum LevelView { LEVEL_IN, LEVEL_PAST, LEVEL_F16, LEVEL_U16, LEVEL_ELSEWHERE };
+// Counts among n values of an operand: up to LV_MAX, up to LV_HALF, and finite
+// ones past that.
+struct LevelCount {
+    int64_t in, half, over, n;
+};
+// The view that the counts of A and B give.  About half of the a.in b.in K /
+// (a.n b.n) pairs of an output with both values in range sum to at most
+// LV_MAX, and some ten of them are needed for all outputs of a block to have
+// one.  A pass over K in vain costs a tenth of the VALU form that follows, and
+// the VALU form in vain ten times the pass: so a block, which counts few
+// values, gives up below NEED = 8 such pairs, and a product, from LEVEL_SAMPLE
+// values, below 20.  Likewise the f16 form, which is exact but for results of
+// 2048 and more: uint16 where few pairs are of values up to LV_HALF and it is not
+// infinity that takes their place.
+template <int NEED>
+__device__ __forceinline__ LevelView level_view(const LevelCount &a, const LevelCount &b, int64_t K)
+{
+    const int64_t need = NEED * a.n * b.n;
+    if (a.in * b.in * K >= need) return LEVEL_PAST;
+    return a.half * b.half * K < need && (4 * a.over > a.half || 4 * b.over > b.half) ? LEVEL_U16 : LEVEL_F16;
+}
+constexpr int LEVEL_COUNTS = 6;  // words of LDS for a block's counts
+constexpr int LEVEL_NEED = 8, LEVEL_NEED_ALL = 20, LEVEL_DOUBT = 40;
+constexpr uint32_t LV_HALF = 1023;
+__device__ __forceinline__ int lanes_up_to(uint32_t v, uint32_t most) { return (int)__popcll(__ballot(v <= most)); }
+
+
+// The view of a whole product from LEVEL_SAMPLE values of each operand in runs of
+// 8 (K and N are at least 8: level_sampled), the same for every block of every
+// kernel that asks; seen: a word of LDS.  One wave looks: with all 8 waves of 800
+// blocks looking, a launch that finds nothing to do took 12 us, now 5.
+constexpr int LEVEL_SAMPLE = 1024;
+inline bool level_sampled(int64_t M, int64_t N, int64_t K) { return M > 0 && N >= 8 && K >= 8; }
+__device__ __forceinline__ LevelView level_sample(const u16 *A, int64_t lda, const u16 *B, int64_t ldb, int64_t M,
+                                                  int64_t N, int64_t K, int *seen)
+{
+    constexpr int PER = LEVEL_SAMPLE / 8 / 64;
+    if (threadIdx.x >= 64) {
+        __syncthreads();
+        return (LevelView)*seen;
+    }
+    uint4 v[2 * PER];
+#pragma unroll
+    for (int q = 0; q < PER; q++) {
+        const uint32_t s = (threadIdx.x & 63) * PER + q;
+        // four independent fractions of 2^32
+        const uint64_t x = mix64(2 * (uint64_t)s + 1), y = mix64(2 * (uint64_t)s + 2);
+        const uint64_t i = (x >> 32) * (uint64_t)M >> 32, k = (x & 0xFFFFFFFFu) * (uint64_t)(K - 7) >> 32;
+        const uint64_t l = (y >> 32) * (uint64_t)K >> 32, j = (y & 0xFFFFFFFFu) * (uint64_t)(N - 7) >> 32;
+        v[q] = uload16((gbytes *)(glob(A) + (int64_t)i * lda + (int64_t)k), 0);
+        v[PER + q] = uload16((gbytes *)(glob(B) + (int64_t)l * ldb + (int64_t)j), 0);
+    }
+    LevelCount t[2];
+#pragma unroll
+    for (int o = 0; o < 2; o++) {
+        uint32_t c = 0, over = 0;  // c: up to LV_MAX, and up to LV_HALF in the upper half
+#pragma unroll
+        for (int q = 0; q < PER; q++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const uint32_t w = comp(v[o * PER + q], e >> 1), x = (e & 1) ? w >> 16 : w & 0xFFFFu;
+                c += (x <= LV_MAX ? 1u : 0u) + (x <= LV_HALF ? 0x10000u : 0u);
+                over += x > LV_HALF && x != 0xFFFFu ? 1u : 0u;
+            }
+        for (int off = 1; off < 64; off <<= 1) {
+            c += (uint32_t)__shfl_xor((int)c, off, 64);
+            over += (uint32_t)__shfl_xor((int)over, off, 64);
+        }
+        t[o] = LevelCount{c & 0xFFFFu, c >> 16, over, LEVEL_SAMPLE};
+    }
+    const LevelView view = level_view<LEVEL_NEED_ALL>(t[0], t[1], K);
+    if (threadIdx.x == 0) *seen = view;
+    __syncthreads();
+    return view;
+}
+
 // The slices of K: slice 0 is the partial one at the end of K when there is
 // one, so that no loop has an edge, and the others follow from the end to the
 // start; group g of a block takes slices g, g + KS, ...
@@ -392,15 +481,19 @@ __device__ __forceinline__ void level_slice(const uint4 *as0, const uint4 *as1, 
 
 // The k loop: acc = the largest 32-term sum of each output (its f32 bits),
 // complete in group 0.  The product is taken transposed (D = B^T A^T): a lane
-// then holds one row of C and runs of 4 consecutive columns.  With CHECK, a
-// block whose first slice holds values past LV_MAX takes one value per thread
-// of each operand's next slice, and gives up (false) when so few of them are
-// in range that fewer than 8 pairs of an output can be expected to be: the
-// stand-in then has to run anyway, and the pass over K is saved (values 0..3000,
-// 2200 x 2500 x 9000: 2.34 ms, now 2.10, and 2.47 in the uint16 form; values
-// 0..15 at N = 16384: no difference).
-template <class C, bool CHECK = false, class AOp, class BOp>
-__device__ __forceinline__ bool level_kloop(int64_t K, AOp &aop, BOp &bop, uint4 *lds, LevelAcc<C> &acc)
+// then holds one row of C and runs of 4 consecutive columns.  With CHECK (and
+// `check`, block-uniform), a block whose first slice holds values past LV_MAX
+// takes one value per thread of each operand there (cnt: LEVEL_COUNTS words of LDS) and
+// returns what level_view makes of them, or of the whole product (whole(), asked
+// in doubt): given up, the rest of the pass over K is saved
+// (values 0..3000, 2200 x 2500 x 9000: 2.34 ms, now 2.10; values 0..15 at N =
+// 16384: no difference).
+struct LevelAlone {
+    __device__ __forceinline__ LevelView operator()() const { return LEVEL_PAST; }
+};
+template <class C, bool CHECK = false, class AOp, class BOp, class Whole = LevelAlone>
+__device__ __forceinline__ LevelView level_kloop(int64_t K, AOp &aop, BOp &bop, uint4 *lds, LevelAcc<C> &acc,
+                                                 int *cnt = nullptr, bool check = true, Whole whole = Whole())
 {
     const int lane = (int)(threadIdx.x & 63);
     const int wm = C::wave() / C::WN, wn = C::wave() % C::WN;
@@ -423,10 +516,15 @@ __device__ __forceinline__ bool level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
     lds += C::group() * 2 * C::STAGE;
     level_first<C>(K, aop, bop);
     bool past = false;
+    uint32_t va = 0xFFFFu, vb = 0xFFFFu;
     if (left > 0) {
         if constexpr (CHECK) {
-            const i16x2 m = bop.largest(aop.largest((i16x2){-1, -1}));
-            past = max(m.x, m.y) > (int)LV_MAX;
+            if (check) {
+                const i16x2 m = bop.largest(aop.largest((i16x2){-1, -1}));
+                past = max(m.x, m.y) > (int)LV_MAX;
+                va = aop.first();
+                vb = bop.first();
+            }
         }
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) aop.store_chunk(lds, q);
@@ -438,11 +536,24 @@ __device__ __forceinline__ bool level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
         aop.load();
         bop.load();
     }
+    LevelView view = LEVEL_IN;
     if constexpr (CHECK) {
-        // with more than 2 KS slices every group has loaded a second one
-        if (__syncthreads_or(past) && slices > 2 * C::KS) {
-            const int64_t a = __syncthreads_count(aop.first() <= LV_MAX), b = __syncthreads_count(bop.first() <= LV_MAX);
-            if (a * b * K < (int64_t)8 * C::NT * C::NT) return false;
+        if (threadIdx.x < LEVEL_COUNTS) cnt[threadIdx.x] = 0;
+        if (__syncthreads_or(past)) {
+            const auto finite = [](uint32_t v) { return v < 0x8000u ? v : 0u; };
+            const int c[6] = {lanes_up_to(va, LV_MAX),       lanes_up_to(va, LV_HALF), 64 - lanes_up_to(finite(va), LV_HALF),
+                              lanes_up_to(vb, LV_MAX),       lanes_up_to(vb, LV_HALF), 64 - lanes_up_to(finite(vb), LV_HALF)};
+            if (lane == 0)
+#pragma unroll
+                for (int q = 0; q < 6; q++) atomicAdd(&cnt[q], c[q]);
+            __syncthreads();
+            // the partial slice of group 0 has infinity past K
+            const int64_t groups = slices < C::KS ? slices : C::KS, part = K % C::BK ? K % C::BK : C::BK;
+            const LevelCount ca{cnt[0], cnt[1], cnt[2], C::GT * (groups - 1) + C::GT * part / C::BK};
+            const LevelCount cb{cnt[3], cnt[4], cnt[5], C::GT * groups};
+            if (level_view<LEVEL_DOUBT>(ca, cb, K) > LEVEL_PAST && whole() > LEVEL_PAST) return LEVEL_ELSEWHERE;
+            view = level_view<LEVEL_NEED>(ca, cb, K);
+            if (view > LEVEL_PAST) return view;
         }
     } else {
         __syncthreads();
@@ -479,7 +590,7 @@ __device__ __forceinline__ bool level_kloop(int64_t K, AOp &aop, BOp &bop, uint4
             __syncthreads();
         }
     }
-    return true;
+    return view;
 }
 
 // Block row, and first of the 4 block columns, that the accumulators of wave
@@ -671,6 +782,7 @@ template <class T>
 __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, int64_t n0, int rows, bool vec,
                                                 const TileAcc<T> &acc)
 {
+    if (T::group() != 0) return;
     tile_store<T>(p.O, p.ldo, p.n, p.n, m0, n0, vec, acc);
 #pragma unroll
     for (int r = 0; r < T::TM; r++) {
@@ -688,7 +800,7 @@ __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, 
             x = max(x, (uint32_t)__shfl_xor((int)x, off, 64));
         }
         const int row = tile_row<T>(r);
-        if (threadIdx.x % T::TX == 0 && row < rows && x) {
+        if (T::tid() % T::TX == 0 && row < rows && x) {
             atomicMin(&p.low_out[m0 + row], m);
             atomicMax(&p.big_out[m0 + row], x - 1);
         }
@@ -700,14 +812,17 @@ __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, 
 template <class C, class T>
 __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0, int64_t n0, uint4 *lds, int32_t *st)
 {
+    __shared__ int cnt[LEVEL_COUNTS];
     const int rows = (int)min<int64_t>(C::BM, p.n - m0), cols = (int)min<int64_t>(C::BN, p.n - n0);
+    LevelView view = LEVEL_F16;
     if (!level_step_rows<C>(p, m0, rows, n0 == 0, st)) {
         LevelA<C, true> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, p.n, p.low_in + m0);
         LevelB<C> bop(glob(p.A) + n0, p.lda, cols, p.n);
         LevelAcc<C> acc;
         // (small blocks: the check costs a step of n = 848 3 % and saves little)
-        if (level_kloop<C, (C::MI > 2)>(p.n, aop, bop, lds, acc) &&
-            (level_sure<C>(acc, rows, cols) || level_clean<C>(p.n, aop, bop, lds))) {
+        view = level_kloop<C, (C::MI > 2)>(p.n, aop, bop, lds, acc, cnt);
+        if (view <= LEVEL_PAST &&
+            (level_sure<C>(acc, rows, cols) || (view == LEVEL_IN && level_clean<C>(p.n, aop, bop, lds)))) {
             level_row_low<C>(acc, rows, cols, p.low_out + m0);
             level_store<C>(glob(p.O) + m0 * p.ldo + n0, p.ldo, rows, cols, acc);
             return;
@@ -716,7 +831,7 @@ __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0,
     const bool vec = (uintptr_t)p.L % 16 == 0 && (uintptr_t)p.A % 16 == 0 && (uintptr_t)p.O % 16 == 0 &&
                      p.ldl % 8 == 0 && p.lda % 8 == 0 && p.ldo % 8 == 0;
     TileAcc<T> acc;
-    tile_mainloop_with<T, true>(
+    tile_split<T>(
         (p.n + T::BK - 1) / T::BK,
         [&](int64_t k0, int row, int kc) {
             const uint4 v = load8(p.L, p.ldl, m0 + row, k0 + kc, p.n, p.n, vec);
@@ -724,7 +839,7 @@ __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0,
             return make_uint4(take_low(v.x, l), take_low(v.y, l), take_low(v.z, l), take_low(v.w, l));
         },
         [&](int64_t k0, int kr, int jc) { return load8(p.A, p.lda, k0 + kr, n0 + jc, p.n, p.n, vec); }, (u16 *)lds,
-        acc);
+        acc, view == LEVEL_U16);
     level_step_back<T>(p, m0, n0, rows, vec, acc);
 }
 
@@ -737,16 +852,16 @@ using LCfg3 = LevelCfg<2, 2, 2, 2, 2>;  // 512 threads, 64 x 64
 using LCfg4 = LevelCfg<4, 4, 2, 4>;     // 512 threads, 128 x 256
 template <class C> struct LevelBack;
 template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
-template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 32, 2, 8>; };
-template <> struct LevelBack<LCfg2> { using T = TileCfg<128, 128, 32, 4, 8>; };
+template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 16, 4, 8, 2>; };
+template <> struct LevelBack<LCfg2> { using T = TileCfg<128, 128, 32, 8, 8, 2>; };
 template <> struct LevelBack<LCfg4> { using T = TileCfg<128, 256, 32, 8, 8>; };
-template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 32, 1, 8>; };
+template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 16, 4, 8, 4>; };
 // LDS of a block (16-byte chunks): its own, or the VALU tile's if larger.
 template <class C>
 struct LevelLds {
     using T = typename LevelBack<C>::T;
-    static_assert(T::NT == C::NT && C::BM == T::BM && C::BN == T::BN, "stand-in tile");
-    static constexpr int BACK = (T::LDS_ELEMS + 7) / 8;
+    static_assert(T::NT * T::G == C::NT && C::BM == T::BM && C::BN == T::BN, "stand-in tile");
+    static constexpr int BACK = (T::G * T::LDS_ELEMS + 7) / 8;
     static constexpr int CHUNKS = C::LDS_CHUNKS > BACK ? C::LDS_CHUNKS : BACK;
 };
 
@@ -824,6 +939,11 @@ int level_shape(int64_t M, int64_t N);
 // reads one third, writes the next and clears the last).
 mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s);
 mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStream_t s);
+
+// gemm.hip: the product in the tile table's configuration, unless level_sample
+// finds its values in the levels: then nothing.
+mpr_status gemm_past_launch(bool spare, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
+                            int64_t ldb, u16 *C, int64_t ldc, hipStream_t s);
 
 // The product C = A (x) B: configuration cfg of gemm.hip, or (cfg = -1) the
 // level form where it applies and the tile table's configuration elsewhere.

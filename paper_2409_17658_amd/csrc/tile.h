@@ -31,12 +31,20 @@
 
 namespace mpr {
 
-template <int BM_, int BN_, int BK_, int TM_, int TN_>
+// G > 1: a workgroup holds G groups of NT threads, each with a tile routine of
+// its own (and its own LDS), which share the slices of K (tile_split).
+template <int BM_, int BN_, int BK_, int TM_, int TN_, int G_ = 1>
 struct TileCfg {
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, TM = TM_, TN = TN_;
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, TM = TM_, TN = TN_, G = G_;
     static constexpr int TX = BN / TN;  // lanes along columns
     static constexpr int TY = BM / TM;  // lanes along rows
-    static constexpr int NT = TX * TY;  // threads per workgroup
+    static constexpr int NT = TX * TY;  // threads per group
+    // Thread in its group, and its group.
+    static __device__ __forceinline__ int tid() { return G == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT; }
+    static __device__ __forceinline__ int group()
+    {
+        return G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    }
     static_assert(TN % 8 == 0 && BK % 8 == 0, "16-byte fragments");
     static_assert(NT % 64 == 0, "whole wavefronts");
     // Padded LDS row strides (elements).  A rows are BK + 8 long (a 16-byte
@@ -102,7 +110,7 @@ struct ChunkA {
     {
 #pragma unroll
         for (int q = 0; q < T::A_CPT; q++) {
-            const int c = threadIdx.x + q * T::NT;
+            const int c = T::tid() + q * T::NT;
             if (T::A_CH % T::NT == 0 || c < T::A_CH) r[q] = f(k0, c / (T::BK / 8), (c % (T::BK / 8)) * 8);
         }
     }
@@ -111,7 +119,7 @@ struct ChunkA {
     {
 #pragma unroll
         for (int q = 0; q < T::A_CPT; q++) {
-            const int c = threadIdx.x + q * T::NT;
+            const int c = T::tid() + q * T::NT;
             if (T::A_CH % T::NT == 0 || c < T::A_CH)
                 *(uint4 *)(as + (c / (T::BK / 8)) * T::LDA_S + (c % (T::BK / 8)) * 8) = image<H>(r[q]);
         }
@@ -126,7 +134,7 @@ struct ChunkB {
     {
 #pragma unroll
         for (int q = 0; q < T::B_CPT; q++) {
-            const int c = threadIdx.x + q * T::NT;
+            const int c = T::tid() + q * T::NT;
             if (T::B_CH % T::NT == 0 || c < T::B_CH) r[q] = f(k0, c / (T::BN / 8), (c % (T::BN / 8)) * 8);
         }
     }
@@ -135,7 +143,7 @@ struct ChunkB {
     {
 #pragma unroll
         for (int q = 0; q < T::B_CPT; q++) {
-            const int c = threadIdx.x + q * T::NT;
+            const int c = T::tid() + q * T::NT;
             if (T::B_CH % T::NT == 0 || c < T::B_CH)
                 *(uint4 *)(bs + (c / (T::BN / 8)) * T::LDB_S + (c % (T::BN / 8)) * 8) = image<H>(r[q]);
         }
@@ -157,7 +165,7 @@ __device__ __forceinline__ ChunkB<T, F> chunk_b(F f)
 template <class T, bool H, class AOp, class BOp>
 __device__ __forceinline__ void tile_kloop(int64_t nk, AOp &aop, BOp &bop, u16 *lds, TileAcc<T> &acc)
 {
-    const int tid = threadIdx.x;
+    const int tid = T::tid();
     const int tx = tid % T::TX, ty = tid / T::TX;
     // Stage s holds A at lds + s*STAGE and B at lds + s*STAGE + A_STAGE.
     constexpr int STAGE = T::A_STAGE + T::B_STAGE;
@@ -307,30 +315,75 @@ __device__ __forceinline__ bool tile_from_h16(TileAcc<T> &acc)
 
 // The (min,+) block product: form H, with the uint16 recomputation for the
 // blocks whose f16 results are not all exact (block-uniform decision).
+// skip (block-uniform): the f16 pass is known to be of no use.
 template <class T, bool H, class AOp, class BOp>
-__device__ __forceinline__ void tile_product(int64_t nk, AOp &aop, BOp &bop, u16 *lds, TileAcc<T> &acc)
+__device__ __forceinline__ void tile_product(int64_t nk, AOp &aop, BOp &bop, u16 *lds, TileAcc<T> &acc,
+                                             bool skip = false)
 {
     if constexpr (H) {
-        tile_kloop<T, true>(nk, aop, bop, lds, acc);
-        if (!__syncthreads_or(tile_from_h16<T>(acc))) return;
+        if (!skip) {
+            tile_kloop<T, true>(nk, aop, bop, lds, acc);
+            if (!__syncthreads_or(tile_from_h16<T>(acc))) return;
+        }
     }
     tile_kloop<T, false>(nk, aop, bop, lds, acc);
 }
 
-// uint16 form only (kept for callers that stage operands themselves).
-template <class T, class AOp, class BOp>
-__device__ __forceinline__ void tile_mainloop_ops(int64_t nk, AOp &aop, BOp &bop, u16 *lds, TileAcc<T> &acc)
+// The minima of a workgroup's groups into group 0 (lds is free).
+template <class T>
+__device__ __forceinline__ void tile_join(u16 *lds, TileAcc<T> &acc)
 {
-    tile_kloop<T, false>(nk, aop, bop, lds, acc);
+    uint32_t *sh = (uint32_t *)lds + T::tid();
+    for (int g = 1; g < T::G; g++) {
+        if (T::group() == g) {
+#pragma unroll
+            for (int r = 0; r < T::TM; r++)
+#pragma unroll
+                for (int c = 0; c < T::NACC; c++) sh[(r * T::NACC + c) * T::NT] = as_u32(acc.v[r][c]);
+        }
+        __syncthreads();
+        if (T::group() == 0) {
+#pragma unroll
+            for (int r = 0; r < T::TM; r++)
+#pragma unroll
+                for (int c = 0; c < T::NACC; c++) acc.v[r][c] = min2(acc.v[r][c], as_u16x2(sh[(r * T::NACC + c) * T::NT]));
+        }
+        __syncthreads();
+    }
 }
 
 // Functor form of the k loop (16-byte chunk producers for both operands).
 template <class T, bool H = false, class ALoad, class BLoad>
-__device__ __forceinline__ void tile_mainloop_with(int64_t nk, ALoad aload, BLoad bload, u16 *lds, TileAcc<T> &acc)
+__device__ __forceinline__ void tile_mainloop_with(int64_t nk, ALoad aload, BLoad bload, u16 *lds, TileAcc<T> &acc,
+                                                   bool skip = false)
 {
     auto aop = chunk_a<T>(aload);
     auto bop = chunk_b<T>(bload);
-    tile_product<T, H>(nk, aop, bop, lds, acc);
+    tile_product<T, H>(nk, aop, bop, lds, acc, skip);
+}
+
+// The same with the slices dealt to the workgroup's G groups in turn; the
+// product is complete in group 0.  Past the last slice the loaders return
+// infinity.  (min of f16 bit patterns: nonnegative, so they order as integers.)
+template <class T, class ALoad, class BLoad>
+__device__ __forceinline__ void tile_split(int64_t nk, ALoad aload, BLoad bload, u16 *lds, TileAcc<T> &acc, bool skip)
+{
+    if constexpr (T::G == 1) {
+        tile_mainloop_with<T, true>(nk, aload, bload, lds, acc, skip);
+    } else {
+        const int64_t mine = (nk + T::G - 1) / T::G, at = (int64_t)T::group() * T::BK;
+        auto aop = chunk_a<T>([&](int64_t k0, int row, int kc) { return aload(k0 * T::G + at, row, kc); });
+        auto bop = chunk_b<T>([&](int64_t k0, int kr, int jc) { return bload(k0 * T::G + at, kr, jc); });
+        u16 *part = lds + T::group() * T::LDS_ELEMS;
+        if (!skip) {
+            tile_kloop<T, true>(mine, aop, bop, part, acc);
+            tile_join<T>(lds, acc);
+            const bool off = tile_from_h16<T>(acc);
+            if (!__syncthreads_or(T::group() == 0 && off)) return;
+        }
+        tile_kloop<T, false>(mine, aop, bop, part, acc);
+        tile_join<T>(lds, acc);
+    }
 }
 
 // The plain product's k loop: A is M x K (lda), B is K x N (ldb), block at (m0, n0).
@@ -338,25 +391,29 @@ template <class T, bool H = false>
 __device__ __forceinline__ void tile_mainloop(const u16 *__restrict__ A, int64_t lda,
                                               const u16 *__restrict__ B, int64_t ldb,
                                               int64_t M, int64_t N, int64_t K, int64_t m0, int64_t n0,
-                                              bool vec, u16 *lds, TileAcc<T> &acc)
+                                              bool vec, u16 *lds, TileAcc<T> &acc, bool skip = false)
 {
     const int64_t nk = (K + T::BK - 1) / T::BK;
-    tile_mainloop_with<T, H>(
-        nk, [&](int64_t k0, int row, int kc) { return load8(A, lda, m0 + row, k0 + kc, M, K, vec); },
-        [&](int64_t k0, int kr, int jc) { return load8(B, ldb, k0 + kr, n0 + jc, K, N, vec); }, lds, acc);
+    auto aload = [&](int64_t k0, int row, int kc) { return load8(A, lda, m0 + row, k0 + kc, M, K, vec); };
+    auto bload = [&](int64_t k0, int kr, int jc) { return load8(B, ldb, k0 + kr, n0 + jc, K, N, vec); };
+    if constexpr (T::G > 1)
+        tile_split<T>(nk, aload, bload, lds, acc, skip);
+    else
+        tile_mainloop_with<T, H>(nk, aload, bload, lds, acc, skip);
 }
 
 // Row of the block that accumulator row r of this lane holds.
 template <class T>
-__device__ __forceinline__ int tile_row(int r) { return (int)(threadIdx.x / T::TX) + r * T::TY; }
+__device__ __forceinline__ int tile_row(int r) { return T::tid() / T::TX + r * T::TY; }
 // First of the 8 block columns that accumulator group c8 of this lane holds.
 template <class T>
-__device__ __forceinline__ int tile_col(int c8) { return c8 * (T::TX * 8) + (int)(threadIdx.x % T::TX) * 8; }
+__device__ __forceinline__ int tile_col(int c8) { return c8 * (T::TX * 8) + T::tid() % T::TX * 8; }
 
 template <class T>
 __device__ __forceinline__ void tile_store(u16 *__restrict__ C, int64_t ldc, int64_t M, int64_t N, int64_t m0,
                                            int64_t n0, bool vec, const TileAcc<T> &acc)
 {
+    if (T::group() != 0) return;
 #pragma unroll
     for (int r = 0; r < T::TM; r++) {
         const int64_t row = m0 + tile_row<T>(r);

@@ -55,6 +55,29 @@ def test_products_of_mixed_blocks(mpr):
         assert _same(mpr.minplus_gemm(A, B), mpr.minplus_gemm(A, B, cfg=0))
 
 
+# Sizes whose products past the levels have a launch of their own (128 x 256
+# blocks would leave CUs idle), and, launched to leave room, outputs of few
+# columns down to fewer than a sample's run of 8.
+PAST_SHAPES = [(3000, 3001, 136, False), (3050, 2900, 128, False), (33000, 9, 137, True), (33000, 8, 128, True),
+               (33000, 7, 130, True), (2300, 2200, 200, True)]
+
+
+@pytest.mark.parametrize("shape", PAST_SHAPES)
+def test_products_past_the_levels(mpr, shape):
+    """Whole products past the levels, mostly infinite ones, and ones of which
+    some or most rows are: the same bits whichever launch takes a block."""
+    M, N, K, spare = shape
+    for law in LAWS + [(0, 20, 0.97), (900, 1100, 0.9)]:
+        print("past the levels", shape, law, flush=True)
+        lo, hi, inf = law
+        X, Y = synth.random_matrix(M, K, 5, lo, hi, inf), synth.random_matrix(K, N, 6, lo, hi, inf)
+        small = synth.random_matrix(M, K, 7, 0, 9, 0.2)
+        for rows in (0, M // 10, 9 * M // 10):
+            X[:rows] = small[:rows]
+            A, B = mpr.to_device(X), mpr.to_device(Y)
+            assert _same(mpr.minplus_gemm(A, B, spare=spare), mpr.minplus_gemm(A, B, cfg=0))
+
+
 STEP_LAWS = [(0, 31, 0.25), (0, 60, 0.9), (2100, 3000, 0.2), (0x7000, 0x7FFF, 0.3), (0, 3000, 0.2)]
 
 
