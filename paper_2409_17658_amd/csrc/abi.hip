@@ -231,7 +231,7 @@ struct PowerWs {
 // saving while a step is short (a third of it at n = 848; past 4096 the pass
 // is below a tenth of the step, and the workspace stays what it was).
 static bool level_chain(int64_t n) { return n >= 33 && n <= 4096; }
-static size_t level_chain_bytes(int64_t n) { return (size_t)round_up(6 * n * 4, 256) + 256; }
+static size_t level_chain_bytes(int64_t n) { return (size_t)round_up(6 * n * 4, 256) + 256; }  // 6 n words, 3 LEVEL_PASTS and the alignment
 
 // Workspace layout of mpr_minplus_power.  The compressed-K plan takes the
 // rest of a workspace of ws_bytes, up to its worst case; ws_bytes = 0 (or
@@ -267,7 +267,7 @@ static PowerWs carve_power(void *ws, int64_t n, int schedule, size_t ws_bytes = 
         }
     }
     w.bytes = c.used + 256;
-    if (schedule == MPR_CHAIN && level_chain(n) && ws_bytes >= w.bytes + level_chain_bytes(n)) w.low = c.take<uint32_t>(6 * (size_t)n);
+    if (schedule == MPR_CHAIN && level_chain(n) && ws_bytes >= w.bytes + level_chain_bytes(n)) w.low = c.take<uint32_t>(6 * (size_t)n + 3 * LEVEL_PASTS);
     return w;
 }
 
@@ -310,14 +310,15 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
     if (r == MPR_OK && sparse && e >= 2) r = sparse_plan_launch(A, n, lda, w.plan, w.plan_bytes, st, s);
     if (r == MPR_OK && w.low && e >= 2 &&
         (sparse ? sparse_step_late(n, w.ld, ldo) : level_strides(lda, ldo) && level_strides(w.ld, ldo))) {
-        uint32_t *low = w.low, *big = w.low + 3 * n;
-        r = level_prepare_launch(low, big, n, s);
+        uint32_t *low = w.low, *big = w.low + 3 * n, *past = w.low + 6 * n;
+        r = level_prepare_launch(low, big, past, n, s);
         for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
             const int nb = b ^ 1;
             const int64_t in = (k - 2) % 3 * n, out = (k - 1) % 3 * n, next = k % 3 * n;
             const LevelStep p{buf[b], A, buf[nb], ld[b], lda, ld[nb], n, R_out, low + in, big + in, low + out,
-                              big + out, low + next, big + next};
-            r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, st, s) : level_step_launch(p, st, s);
+                              big + out, low + next, big + next, past + (k - 2) % 3 * LEVEL_PASTS, past + (k - 1) % 3 * LEVEL_PASTS,
+                              past + k % 3 * LEVEL_PASTS};
+            r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, st, s) : level_step_launch(p, k == 2, st, s);
             b = nb;
         }
         if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, s);

@@ -326,9 +326,10 @@ struct LevelItem {
 };
 
 // Row minima and maxima of the steps: three buffers in rotation (a step reads
-// one, writes the next and clears the third), `rows` words each.
+// one, writes the next and clears the third), `rows` words each, and
+// LEVEL_PASTS words a chain.
 struct LowBufs {
-    uint32_t *low, *big;
+    uint32_t *low, *big, *past;
     int64_t rows;
 };
 
@@ -367,6 +368,9 @@ __global__ __launch_bounds__(256) void batch_rows_kernel(const DevChain *__restr
             lb.low[blockIdx.x] = lb.big[blockIdx.x] = 0;  // the first power is canonical
             lb.low[lb.rows + blockIdx.x] = LOW_NONE;
             lb.big[lb.rows + blockIdx.x] = 0;
+            if (i == 0)
+                for (int q = 0; q < LEVEL_PASTS; q++)
+                    lb.past[inst * LEVEL_PASTS + q] = lb.past[(count + inst) * LEVEL_PASTS + q] = 0;
         }
     }
     __syncthreads();
@@ -376,10 +380,10 @@ __global__ __launch_bounds__(256) void batch_rows_kernel(const DevChain *__restr
 }
 
 // Power k of every chain with e >= k: one tile per block.
-template <class C>
+template <class C, bool FIRST>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void batch_step_kernel(
     const DevChain *__restrict__ chains, const int64_t *__restrict__ row0, const LevelItem *__restrict__ items,
-    int64_t k, LowBufs lb, int32_t *st)
+    int count, int64_t k, LowBufs lb, int32_t *st)
 {
     __shared__ uint4 lds[LevelLds<C>::CHUNKS];
     const LevelItem it = items[blockIdx.x];
@@ -390,8 +394,10 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void
                   next = k % 3 * lb.rows + r0;
     const LevelStep p{in_p ? c.P : c.N_out, c.A, in_p ? c.N_out : c.P, in_p ? c.ldp : c.ldo, c.lda,
                       in_p ? c.ldo : c.ldp, c.n, c.R_out, lb.low + in, lb.big + in, lb.low + out, lb.big + out,
-                      lb.low + next, lb.big + next};
-    level_step_block<C, typename LevelBack<C>::T>(p, (int64_t)it.tm * C::BM, (int64_t)it.tn * C::BN, lds, st);
+                      lb.low + next, lb.big + next, lb.past + ((k - 2) % 3 * count + it.inst) * LEVEL_PASTS,
+                      lb.past + ((k - 1) % 3 * count + it.inst) * LEVEL_PASTS,
+                      lb.past + (k % 3 * count + it.inst) * LEVEL_PASTS};
+    level_step_block<C, typename LevelBack<C>::T, FIRST>(p, (int64_t)it.tm * C::BM, (int64_t)it.tn * C::BN, lds, st);
 }
 
 // ------------------------------------------------------------ host side
@@ -534,7 +540,7 @@ static LevelLayout level_layout(const mpr_chain_desc *d, int count, size_t from)
     L.row0_off = take(8 * (size_t)(count + 1));
     L.items_off[0] = take(sizeof(LevelItem) * level_item_count(d, count, BStep0::BM, BStep0::BN));
     L.items_off[1] = take(sizeof(LevelItem) * level_item_count(d, count, BStep1::BM, BStep1::BN));
-    L.low_off = take(6 * 4 * (size_t)L.rows);
+    L.low_off = take(4 * (6 * (size_t)L.rows + 3 * LEVEL_PASTS * (size_t)count));
     L.bytes = off + 256;
     return L;
 }
@@ -761,7 +767,8 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
                 return MPR_EHIP;
             level->count = count;
             level->row0 = (const int64_t *)(base + V.row0_off);
-            level->low = LowBufs{(uint32_t *)(base + V.low_off), (uint32_t *)(base + V.low_off) + 3 * V.rows, V.rows};
+            uint32_t *low = (uint32_t *)(base + V.low_off);
+            level->low = LowBufs{low, low + 3 * V.rows, low + 6 * V.rows, V.rows};
         }
     }
     if (count && hipMemcpyAsync(base + L.chains_off, chains.data(), sizeof(DevChain) * count, hipMemcpyHostToDevice,
@@ -796,11 +803,12 @@ static mpr_status level_batch_launch(const BatchPlan &p, int32_t *st, hipStream_
                        (const DevChain *)p.chains, v.row0, v.count, v.low, st);
     for (size_t k = 2; k < v.active[0].size(); k++) {
         if (v.active[0][k] >= fill)
-            hipLaunchKernelGGL(batch_step_kernel<BStep0>, dim3(v.active[0][k]), dim3(BStep0::NT), 0, s,
-                               (const DevChain *)p.chains, v.row0, v.items[0], (int64_t)k, v.low, st);
+            hipLaunchKernelGGL((batch_step_kernel<BStep0, true>), dim3(v.active[0][k]), dim3(BStep0::NT), 0, s,
+                               (const DevChain *)p.chains, v.row0, v.items[0], v.count, (int64_t)k, v.low, st);
         else
-            hipLaunchKernelGGL(batch_step_kernel<BStep1>, dim3(v.active[1][k]), dim3(BStep1::NT), 0, s,
-                               (const DevChain *)p.chains, v.row0, v.items[1], (int64_t)k, v.low, st);
+            hipLaunchKernelGGL((k == 2 ? batch_step_kernel<BStep1, true> : batch_step_kernel<BStep1, false>),
+                               dim3(v.active[1][k]), dim3(BStep1::NT), 0, s,
+                               (const DevChain *)p.chains, v.row0, v.items[1], v.count, (int64_t)k, v.low, st);
     }
     hipLaunchKernelGGL(batch_rows_kernel<false>, dim3((unsigned)v.low.rows), dim3(256), 0, s,
                        (const DevChain *)p.chains, v.row0, v.count, v.low, st);

@@ -725,7 +725,16 @@ struct LevelStep {
     int64_t *R;
     const uint32_t *low_in, *big_in;
     uint32_t *low_out, *big_out, *low_next, *big_next;
+    // Outputs, in tiles of 64 x 64, of blocks that had a finite result past
+    // LV_MAX in the step before, and of those with one past 2047; the same of
+    // this step; the words to clear (rotated in the same way).  Where most of
+    // the step before was past the levels, a block goes to the VALU tile at
+    // once (n = 848, entries 0..3000: 57 us a step with the pass over K in
+    // vain, 42 without).  The first step has 0 and 0, and looks at its values.
+    const uint32_t *past_in;
+    uint32_t *past_out, *past_next;
 };
+constexpr int LEVEL_PASTS = 2;
 constexpr uint32_t LOW_NONE = 0xFFFFu;  // no finite value in the row
 
 // Row minima of the block into low (the block's first row), from the largest
@@ -777,50 +786,64 @@ __device__ __forceinline__ uint32_t take_low(uint32_t x, uint32_t l)
     return (lo == 0xFFFFu ? lo : lo - l) | (hi == 0xFFFFu ? hi : hi - l) << 16;
 }
 
-// A block that the VALU tile computed: its results, row minima and maxima.
+// A block that the VALU tile computed: its results, row minima and maxima, and
+// what they tell the next step (past_out, when given; called by every thread).
 template <class T>
 __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, int64_t n0, int rows, bool vec,
                                                 const TileAcc<T> &acc)
 {
-    if (T::group() != 0) return;
-    tile_store<T>(p.O, p.ldo, p.n, p.n, m0, n0, vec, acc);
+    uint32_t most = 0;  // largest finite value + 1
+    if (T::group() == 0) {
+        tile_store<T>(p.O, p.ldo, p.n, p.n, m0, n0, vec, acc);
 #pragma unroll
-    for (int r = 0; r < T::TM; r++) {
-        // columns and rows past the end are infinite
-        u16x2 mn = {0xFFFF, 0xFFFF}, mx = {0, 0};  // mx: largest finite value + 1
+        for (int r = 0; r < T::TM; r++) {
+            // columns and rows past the end are infinite
+            u16x2 mn = {0xFFFF, 0xFFFF}, mx = {0, 0};  // mx: largest finite value + 1
 #pragma unroll
-        for (int q = 0; q < T::NACC; q++) {
-            mn = min2(mn, acc.v[r][q]);
-            mx = __builtin_elementwise_max(mx, (u16x2)(acc.v[r][q] + (u16x2){1, 1}));
-        }
-        uint32_t m = min((uint32_t)mn.x, (uint32_t)mn.y), x = max((uint32_t)mx.x, (uint32_t)mx.y);
+            for (int q = 0; q < T::NACC; q++) {
+                mn = min2(mn, acc.v[r][q]);
+                mx = __builtin_elementwise_max(mx, (u16x2)(acc.v[r][q] + (u16x2){1, 1}));
+            }
+            uint32_t m = min((uint32_t)mn.x, (uint32_t)mn.y), x = max((uint32_t)mx.x, (uint32_t)mx.y);
 #pragma unroll
-        for (int off = 1; off < T::TX; off <<= 1) {
-            m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
-            x = max(x, (uint32_t)__shfl_xor((int)x, off, 64));
-        }
-        const int row = tile_row<T>(r);
-        if (T::tid() % T::TX == 0 && row < rows && x) {
-            atomicMin(&p.low_out[m0 + row], m);
-            atomicMax(&p.big_out[m0 + row], x - 1);
+            for (int off = 1; off < T::TX; off <<= 1) {
+                m = min(m, (uint32_t)__shfl_xor((int)m, off, 64));
+                x = max(x, (uint32_t)__shfl_xor((int)x, off, 64));
+            }
+            most = max(most, x);
+            const int row = tile_row<T>(r);
+            if (T::tid() % T::TX == 0 && row < rows && x) {
+                atomicMin(&p.low_out[m0 + row], m);
+                atomicMax(&p.big_out[m0 + row], x - 1);
+            }
         }
     }
+    if (!p.past_out) return;
+    constexpr uint32_t AREA = T::BM * T::BN / (64 * 64);
+    const bool past = __syncthreads_or(most > LV_MAX + 1), deep = __syncthreads_or(most > 0x800);
+    if (threadIdx.x != 0) return;
+    if (past) atomicAdd(&p.past_out[0], AREA);
+    if (deep) atomicAdd(&p.past_out[1], AREA);
 }
 
 // The block of rows m0.. and columns n0.. of a step; T is the VALU tile of
 // the same shape and threads for blocks whose values leave the level range.
-template <class C, class T>
+// FIRST: the first step of a chain.
+template <class C, class T, bool FIRST>
 __device__ __forceinline__ void level_step_block(const LevelStep &p, int64_t m0, int64_t n0, uint4 *lds, int32_t *st)
 {
     __shared__ int cnt[LEVEL_COUNTS];
     const int rows = (int)min<int64_t>(C::BM, p.n - m0), cols = (int)min<int64_t>(C::BN, p.n - n0);
-    LevelView view = LEVEL_F16;
-    if (!level_step_rows<C>(p, m0, rows, n0 == 0, st)) {
+    const uint32_t past = p.past_in[0], deep = p.past_in[1];
+    if (m0 == 0 && n0 == 0 && threadIdx.x < LEVEL_PASTS) p.past_next[threadIdx.x] = 0;
+    const bool far = level_step_rows<C>(p, m0, rows, n0 == 0, st);
+    LevelView view = 2 * deep > past ? LEVEL_U16 : LEVEL_F16;
+    if (!far && 2 * 64 * 64 * (int64_t)past <= p.n * p.n) {
         LevelA<C, true> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, p.n, p.low_in + m0);
         LevelB<C> bop(glob(p.A) + n0, p.lda, cols, p.n);
         LevelAcc<C> acc;
-        // (small blocks: the check costs a step of n = 848 3 % and saves little)
-        view = level_kloop<C, (C::MI > 2)>(p.n, aop, bop, lds, acc, cnt);
+        // (a look in every step costs one of n = 848 3 %; large blocks nothing)
+        view = level_kloop<C, FIRST || (C::MI > 2)>(p.n, aop, bop, lds, acc, cnt);
         if (view <= LEVEL_PAST &&
             (level_sure<C>(acc, rows, cols) || (view == LEVEL_IN && level_clean<C>(p.n, aop, bop, lds)))) {
             level_row_low<C>(acc, rows, cols, p.low_out + m0);
@@ -855,7 +878,7 @@ template <> struct LevelBack<LCfg0> { using T = TileCfg<128, 128, 32, 8, 8>; };
 template <> struct LevelBack<LCfg1> { using T = TileCfg<64, 64, 16, 4, 8, 2>; };
 template <> struct LevelBack<LCfg2> { using T = TileCfg<128, 128, 32, 8, 8, 2>; };
 template <> struct LevelBack<LCfg4> { using T = TileCfg<128, 256, 32, 8, 8>; };
-template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 16, 4, 8, 4>; };
+template <> struct LevelBack<LCfg3> { using T = TileCfg<64, 64, 32, 4, 8, 4>; };
 // LDS of a block (16-byte chunks): its own, or the VALU tile's if larger.
 template <class C>
 struct LevelLds {
@@ -936,9 +959,10 @@ int level_shape(int64_t M, int64_t N);
 
 // A chain step in the shape for its size, and the row minima and maxima of
 // the first power and for its first step (3 n words each in rotation: a step
-// reads one third, writes the next and clears the last).
-mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s);
-mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStream_t s);
+// reads one third, writes the next and clears the last), and likewise the 3
+// LEVEL_PASTS words.  first: the first step of a chain.
+mpr_status level_step_launch(const LevelStep &p, bool first, int32_t *st, hipStream_t s);
+mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, uint32_t *past, int64_t n, hipStream_t s);
 
 // gemm.hip: the product in the tile table's configuration, unless level_sample
 // finds its values in the levels: then nothing.

@@ -189,7 +189,7 @@ mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const 
 }
 
 // One step of a chain (LevelStep).
-template <class C>
+template <class C, bool FIRST>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void level_step_kernel(LevelStep p,
                                                                                                   int tiles,
                                                                                                   int32_t *st)
@@ -197,39 +197,40 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     __shared__ uint4 lds[LevelLds<C>::CHUNKS];
     int tm, tn;
     if (!level_tile(tiles, tiles, tm, tn)) return;
-    level_step_block<C, typename LevelBack<C>::T>(p, (int64_t)tm * C::BM, (int64_t)tn * C::BN, lds, st);
+    level_step_block<C, typename LevelBack<C>::T, FIRST>(p, (int64_t)tm * C::BM, (int64_t)tn * C::BN, lds, st);
 }
 
 template <class C>
-static mpr_status step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
+static mpr_status step_launch(const LevelStep &p, bool first, int32_t *st, hipStream_t s)
 {
     const int64_t side = (p.n + C::BM - 1) / C::BM;
-    hipLaunchKernelGGL(level_step_kernel<C>, dim3((unsigned)round_up(side * side, 8)), dim3(C::NT), 0, s, p, (int)side,
-                       st);
+    auto kernel = first ? level_step_kernel<C, true> : level_step_kernel<C, (C::MI > 2)>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)round_up(side * side, 8)), dim3(C::NT), 0, s, p, (int)side, st);
     return check_launch();
 }
 
-mpr_status level_step_launch(const LevelStep &p, int32_t *st, hipStream_t s)
+mpr_status level_step_launch(const LevelStep &p, bool first, int32_t *st, hipStream_t s)
 {
     switch (level_shape(p.n, p.n)) {
-    case 0: case 4: return step_launch<LCfg0>(p, st, s);
-    case 2: return step_launch<LCfg2>(p, st, s);
-    default: return step_launch<LCfg3>(p, st, s);
+    case 0: case 4: return step_launch<LCfg0>(p, first, st, s);
+    case 2: return step_launch<LCfg2>(p, first, st, s);
+    default: return step_launch<LCfg3>(p, first, st, s);
     }
 }
 
-__global__ void level_prepare_kernel(uint32_t *low, uint32_t *big, int64_t n)
+__global__ void level_prepare_kernel(uint32_t *low, uint32_t *big, uint32_t *past, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 2 * LEVEL_PASTS) past[i] = 0;
     if (i >= n) return;
     low[i] = big[i] = 0;  // the first power is canonical
     low[n + i] = LOW_NONE;
     big[n + i] = 0;
 }
 
-mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, int64_t n, hipStream_t s)
+mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, uint32_t *past, int64_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(level_prepare_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, low, big, n);
+    hipLaunchKernelGGL(level_prepare_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, low, big, past, n);
     return check_launch();
 }
 
