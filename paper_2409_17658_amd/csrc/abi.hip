@@ -318,7 +318,7 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
             const LevelStep p{buf[b], A, buf[nb], ld[b], lda, ld[nb], n, R_out, low + in, big + in, low + out,
                               big + out, low + next, big + next, past + (k - 2) % 3 * LEVEL_PASTS, past + (k - 1) % 3 * LEVEL_PASTS,
                               past + k % 3 * LEVEL_PASTS};
-            r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, st, s) : level_step_launch(p, k == 2, st, s);
+            r = sparse ? sparse_step_late_launch(p, w.plan, w.plan_bytes, k - 2, st, s) : level_step_launch(p, k == 2, st, s);
             b = nb;
         }
         if (r == MPR_OK) r = normalise_launch(n, n, buf[b], ld[b], R_out, nullptr, R_out, st, s);
@@ -326,7 +326,7 @@ static mpr_status power_chain(const u16 *A, int64_t n, int64_t lda, int64_t e, u
     }
     for (int64_t k = 2; k <= e && r == MPR_OK; k++) {
         const int nb = b ^ 1;
-        r = sparse ? sparse_step_launch(buf[b], ld[b], n, w.plan, w.plan_bytes, buf[nb], ld[nb], s)
+        r = sparse ? sparse_step_launch(buf[b], ld[b], n, w.plan, w.plan_bytes, buf[nb], ld[nb], k - 2, s)
                    : product_launch(-1, n, n, n, buf[b], ld[b], A, lda, buf[nb], ld[nb], s);
         if (r == MPR_OK) r = normalise_launch(n, n, buf[nb], ld[nb], R_out, nullptr, R_out, st, s);
         b = nb;
@@ -825,7 +825,7 @@ static mpr_status find_period_impl(HostRecord &host, const uint16_t *A, int64_t 
             return e;
         }
         if (k == 1) return period_rows_launch(A, lda, Nk, w.ld, n, nullptr, Rk, true, w.acc, st, rec, seq, s);
-        mpr_status e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, s)
+        mpr_status e = sparse ? sparse_step_launch(slot_N(w, ps), w.ld, n, w.plan, w.plan_bytes, Nk, w.ld, k - 2, s)
                               : product_launch(-1, n, n, n, slot_N(w, ps), w.ld, A, lda, Nk, w.ld, s);
         if (e == MPR_OK) e = period_rows_launch(Nk, w.ld, Nk, w.ld, n, slot_R(w, ps), Rk, false, w.acc, st, rec, seq, s);
         return e;

@@ -144,7 +144,7 @@ mpr_status sparse_plan_rows(const u16 *A, int64_t n, int64_t lda, void *ws, hipS
 mpr_status sparse_plan_launch(const u16 *A, int64_t n, int64_t lda, void *ws, size_t bytes, int32_t *st,
                               hipStream_t s);
 mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, size_t bytes, u16 *C, int64_t ldc,
-                              hipStream_t s);
+                              int64_t step, hipStream_t s);  // step: 0, 1, ... since the plan was made
 
 // rowops.hip
 mpr_status validate_launch(const u16 *X, int64_t rows, int64_t cols, int64_t ld, int32_t *st, hipStream_t s);

@@ -787,8 +787,9 @@ __device__ __forceinline__ uint32_t take_low(uint32_t x, uint32_t l)
 }
 
 // A block that the VALU tile computed: its results, row minima and maxima, and
-// what they tell the next step (past_out, when given; called by every thread).
-template <class T>
+// what they tell the next step (called by every thread).  LOW: the minima and
+// maxima are wanted.
+template <class T, bool LOW = true>
 __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, int64_t n0, int rows, bool vec,
                                                 const TileAcc<T> &acc)
 {
@@ -812,13 +813,12 @@ __device__ __forceinline__ void level_step_back(const LevelStep &p, int64_t m0, 
             }
             most = max(most, x);
             const int row = tile_row<T>(r);
-            if (T::tid() % T::TX == 0 && row < rows && x) {
+            if (LOW && T::tid() % T::TX == 0 && row < rows && x) {
                 atomicMin(&p.low_out[m0 + row], m);
                 atomicMax(&p.big_out[m0 + row], x - 1);
             }
         }
     }
-    if (!p.past_out) return;
     constexpr uint32_t AREA = T::BM * T::BN / (64 * 64);
     const bool past = __syncthreads_or(most > LV_MAX + 1), deep = __syncthreads_or(most > 0x800);
     if (threadIdx.x != 0) return;
@@ -948,7 +948,8 @@ private:
 
 // The compressed-K step (sparse.hip) in the same way; p.A is not read.
 bool sparse_step_late(int64_t n, int64_t ldl, int64_t ldo);  // whether it applies
-mpr_status sparse_step_late_launch(const LevelStep &p, void *ws, size_t bytes, int32_t *st, hipStream_t s);
+mpr_status sparse_step_late_launch(const LevelStep &p, void *ws, size_t bytes, int64_t step, int32_t *st,
+                                   hipStream_t s);
 
 // abi.hip: the argument checks of a product.
 mpr_status mpr_gemm_args(int cfg, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B, int64_t ldb,

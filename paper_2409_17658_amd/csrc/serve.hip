@@ -582,7 +582,7 @@ static mpr_status start_build(Server &S, Ladder &L)
         if (e == MPR_OK) e = normalise_launch(n, n, buf[b], ld, nullptr, nullptr, R[b], L.status_dev, s);
         if (e == MPR_OK && B >= 2) e = sparse_plan_launch(A, n, ld, plan, plan_bytes, L.status_dev, s);
         for (int k = 2; k <= B && e == MPR_OK; k++) {
-            e = sparse_step_launch(buf[b], ld, n, plan, plan_bytes, buf[b ^ 1], ld, s);
+            e = sparse_step_launch(buf[b], ld, n, plan, plan_bytes, buf[b ^ 1], ld, k - 2, s);
             if (e == MPR_OK)
                 e = normalise_launch(n, n, buf[b ^ 1], ld, R[b], nullptr, R[b ^ 1], L.status_dev, s);
             b ^= 1;
@@ -594,7 +594,7 @@ static mpr_status start_build(Server &S, Ladder &L)
     if (e == MPR_OK && B >= 2) e = sparse_plan_launch(L.Nb[1], n, ld, plan, plan_bytes, L.status_dev, s);
     if (e == MPR_OK) e = normalise_launch(n, n, L.Nb[1], ld, nullptr, nullptr, L.Rb[1], L.status_dev, s);
     for (int j = 2; j <= B && e == MPR_OK; j++) {
-        e = sparse_step_launch(L.Nb[j - 1], ld, n, plan, plan_bytes, L.Nb[j], ld, s);
+        e = sparse_step_launch(L.Nb[j - 1], ld, n, plan, plan_bytes, L.Nb[j], ld, j - 2, s);
         if (e == MPR_OK)
             e = normalise_launch(n, n, L.Nb[j], ld, L.Rb[j - 1], nullptr, L.Rb[j], L.status_dev, s);
     }

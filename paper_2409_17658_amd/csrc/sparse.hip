@@ -160,8 +160,9 @@ __global__ __launch_bounds__(PT) void sp_scan_kernel(const int64_t *counts, int6
 template <bool IMAGES>
 __global__ __launch_bounds__(PT) void sp_fill_kernel(const u16 *A, int64_t lda, int64_t n, const int64_t *off,
                                                      int64_t nblk, int64_t cap, int32_t *idx, u16 *Bp, int vec,
-                                                     int32_t *top, int32_t *st)
+                                                     int32_t *top, uint32_t *past, int32_t *st)
 {
+    if (blockIdx.x == 0 && threadIdx.x < 3 * LEVEL_PASTS) past[threadIdx.x] = 0;  // (SparsePlan)
     __shared__ uint8_t rows[PWIN];
     typedef u32x4 __attribute__((may_alias)) chunk_bits;
     __shared__ __attribute__((aligned(16))) u16 turn[IMAGES ? PW : 1][8 * SBN];  // a wave's 8 rows
@@ -334,7 +335,8 @@ __global__ __launch_bounds__(SCfg::NT) __attribute__((amdgpu_waves_per_eu(4))) v
 }
 
 // ------------------------------------------- entry-list form of the step
-// (by request: MPR_SPARSE_ENTRIES.)  The tile above multiplies whole 64-column rows of A[L_J, J]; for a
+// (by request, MPR_SPARSE_ENTRIES, and for the tiles that the level form leaves.)
+// The tile above multiplies whole 64-column rows of A[L_J, J]; for a
 // transfer matrix about nine in ten of those entries are infinite (a
 // column has 25 to 120 finite entries, its block's L_J ten times as many),
 // so nine in ten of its pairs cannot win.  This form visits the finite
@@ -368,12 +370,16 @@ constexpr int kEntryDense = 12;          // more entries than this in a column's
 constexpr int ESV = EBM / ERP;           // values a thread stages per slice
 
 // One 512-row tile of the entry-list step; FULL: every row of the tile is
-// < n (so the gathers need no row test).
-template <bool FULL>
-__device__ __forceinline__ void entry_tile(const u16 *__restrict__ Np, int64_t ldn, int64_t n, int64_t m0,
+// < n (so the gathers need no row test).  LATE: the rows lose their offsets
+// low[row of the tile] on the way in, and leave their minima and maxima (low_out,
+// big_out, the tile's first row).  COUNT: returns the largest finite result + 1
+// of this thread's row.
+template <bool FULL, bool LATE, bool COUNT>
+__device__ __forceinline__ uint32_t entry_tile(const u16 *__restrict__ Np, int64_t ldn, int64_t n, int64_t m0,
                                            int64_t j0, const int32_t *__restrict__ idx, const u16 *__restrict__ Bp,
                                            int64_t kbeg, int64_t nk, u16 *__restrict__ C, int64_t ldc, int vec,
-                                           u16 *nt)
+                                           u16 *nt, const uint32_t *low, uint32_t *low_out, uint32_t *big_out,
+                                           u16 *low_lds)
 {
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
     u16x2 acc[ECOLS][ERL / 2];
@@ -422,6 +428,11 @@ __device__ __forceinline__ void entry_tile(const u16 *__restrict__ Np, int64_t l
             if (!FULL) {
                 lo = row_of(2 * e) < nloc ? lo : 0xFFFFu;
                 hi = row_of(2 * e + 1) < nloc ? hi : 0xFFFFu;
+            }
+            if constexpr (LATE) {
+                const uint32_t l = *(const uint32_t *)(low_lds + row_of(2 * e));  // of the pair of rows
+                lo = lo == 0xFFFFu ? lo : lo - (l & 0xFFFFu);
+                hi = hi == 0xFFFFu ? hi : hi - (l >> 16);
             }
             *(uint32_t *)(q + 2 * ERP * e) = lo | (hi << 16);
         }
@@ -473,6 +484,11 @@ __device__ __forceinline__ void entry_tile(const u16 *__restrict__ Np, int64_t l
             }
         }
     };
+    if constexpr (LATE) {  // 0xFFFF (no finite value) takes nothing off infinity
+        const int r = (int)threadIdx.x;
+        low_lds[r] = (u16)(r < nloc ? low[r] : 0u);
+        __syncthreads();
+    }
     if (nk > 0) {
         uint32_t col = (uint32_t)gi[sk];
         load(0, col);
@@ -504,13 +520,21 @@ __device__ __forceinline__ void entry_tile(const u16 *__restrict__ Np, int64_t l
     __syncthreads();
     const int r = (int)threadIdx.x;
     const int64_t i = m0 + r;
-    if (i >= n) return;
+    if (i >= n) return 0;
     gu16 *crow = glob(C) + i * ldc + j0;
+    uint32_t least = 0xFFFFu, most = 0;
 #pragma unroll
     for (int c8 = 0; c8 < SBN; c8 += 8) {
         uint32_t v[8];
 #pragma unroll
         for (int q = 0; q < 8; q++) v[q] = ct[(c8 + q) * ELDN + r];
+        if constexpr (LATE || COUNT) {  // columns past n are infinite
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                least = min(least, v[q]);
+                most = max(most, (v[q] + 1) & 0xFFFFu);
+            }
+        }
         if (vec && j0 + c8 + 8 <= n) {
             gstore16(crow + c8, make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16),
                                            v[6] | (v[7] << 16)));
@@ -519,6 +543,11 @@ __device__ __forceinline__ void entry_tile(const u16 *__restrict__ Np, int64_t l
                 if (j0 + c8 + q < n) crow[c8 + q] = (u16)v[q];
         }
     }
+    if (LATE && most) {
+        atomicMin(&low_out[r], least);
+        atomicMax(&big_out[r], most - 1);
+    }
+    return most;
 }
 
 __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void sp_entry_kernel(
@@ -539,9 +568,9 @@ __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void s
     const int64_t kbeg = off[J];
     const int64_t nk = off[nblk] > cap ? 0 : (off[J + 1] - kbeg) / SBK;
     if (m0 + EBM <= n)
-        entry_tile<true>(Np, ldn, n, m0, j0, idx, Bp, kbeg, nk, C, ldc, vec, nt);
+        entry_tile<true, false, false>(Np, ldn, n, m0, j0, idx, Bp, kbeg, nk, C, ldc, vec, nt, nullptr, nullptr, nullptr, nullptr);
     else
-        entry_tile<false>(Np, ldn, n, m0, j0, idx, Bp, kbeg, nk, C, ldc, vec, nt);
+        entry_tile<false, false, false>(Np, ldn, n, m0, j0, idx, Bp, kbeg, nk, C, ldc, vec, nt, nullptr, nullptr, nullptr, nullptr);
 }
 
 // ------------------------------------------- level form of the step
@@ -640,6 +669,13 @@ struct LevelGather {
             make_uint4(level_image(value2(r[q].x, q)), level_image(value2(r[q].y, q)),
                        level_image(value2(r[q].z, q)), level_image(value2(r[q].w, q)));
     }
+    __device__ __forceinline__ uint32_t first() const  // as LevelA's
+    {
+        const int row = C::tid() / C::KC;
+        const uint64_t lo = (uint64_t)r[0].y << 32 | r[0].x, hi = (uint64_t)r[0].w << 32 | r[0].z;
+        const uint32_t v = value2((uint32_t)(((row & 2) ? hi : lo) >> (row & 1) * 32), 0);
+        return v >> (row & 4) * 4 & 0xFFFFu;
+    }
     __device__ __forceinline__ i16x2 largest(i16x2 m) const
     {
 #pragma unroll
@@ -653,8 +689,12 @@ struct LevelGather {
 
 // One 128 x 64 tile of a step.  LATE: the rows of p.L are normalised on the
 // way in and their minima left behind (LevelStep); otherwise p.L is canonical
-// and only L, O, their strides and n of p are used.
-template <bool LATE>
+// and only L, O, their strides, n and the past words of p are used.  FIRST: the first
+// step of a chain, which looks at its values; the others go by the step before
+// (LevelStep).  ELSEWHERE: a tile past the levels is marked, by a first value that
+// no tile in the levels has, and left to sp_entry_kernel.
+constexpr u16 TILE_MARK = 0xFFFE;
+template <bool LATE, bool FIRST, bool ELSEWHERE>
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level_kernel(
     LevelStep p, const int64_t *__restrict__ off, const int32_t *__restrict__ idx, const u16 *__restrict__ Bp,
     int tiles_m, int nblk, int64_t cap, int vec, int32_t *st)
@@ -670,6 +710,9 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
     const int rows = (int)min<int64_t>(C::BM, n - m0), cols = (int)min<int64_t>(SBN, n - j0);
     const int64_t kbeg = off[J], K = off[nblk] > cap ? 0 : off[J + 1] - kbeg;
     gu16 *out = glob(p.O) + m0 * p.ldo + j0;
+    __shared__ int cnt[LEVEL_COUNTS];
+    const uint32_t past = p.past_in[0], deep = p.past_in[1];
+    if (t == 0 && threadIdx.x < LEVEL_PASTS) p.past_next[threadIdx.x] = 0;
     bool far = false;
     if constexpr (LATE) far = level_step_rows<C>(p, m0, rows, J == 0, st);
     if (K == 0) {  // no finite entry in these columns, or a plan that did not fit: infinite
@@ -677,26 +720,56 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
             if (e % SBN < cols) out[(int64_t)(e / SBN) * p.ldo + e % SBN] = 0xFFFF;
         return;
     }
-    if (!far) {
+    LevelView view = 2 * deep > past ? LEVEL_U16 : LEVEL_F16;
+    if (!far && (int64_t)past <= (int64_t)tiles_m * nblk) {  // 2 tiles of 64 x 64 each
         LevelGather<C, LATE> aop(glob(p.L) + m0 * p.ldl, p.ldl, rows, n, idx + kbeg, K, LATE ? p.low_in + m0 : nullptr);
         LevelB<C> bop(glob(Bp) + kbeg * SBN, SBN, SBN, K);
         LevelAcc<C> acc;
-        level_kloop<C>(K, aop, bop, lds, acc);
-        if (level_sure<C>(acc, rows, cols) || level_clean<C>(K, aop, bop, lds)) {
+        view = level_kloop<C, FIRST>(K, aop, bop, lds, acc, cnt);
+        if (view <= LEVEL_PAST &&
+            (level_sure<C>(acc, rows, cols) || (view == LEVEL_IN && level_clean<C>(K, aop, bop, lds)))) {
             if constexpr (LATE) level_row_low<C>(acc, rows, cols, p.low_out + m0);
             level_store<C>(out, p.ldo, rows, cols, acc);
             return;
         }
     }
+    if constexpr (ELSEWHERE) {
+        if (threadIdx.x == 0) out[0] = TILE_MARK;
+        return;
+    }
     const gu16 *gB = glob(Bp) + kbeg * SBN;
     TileAcc<PBack> acc;
     GatherA<PBack> aop{glob(p.L), p.ldl, n, m0, glob(idx) + kbeg, rows == C::BM, LATE ? p.low_in + m0 : nullptr, {}};
     auto bop = chunk_b<PBack>([&](int64_t k0, int kr, int jc) { return gload16(gB + (k0 + kr) * SBN + jc); });
-    tile_product<PBack, true>(K / PBack::BK, aop, bop, (u16 *)lds, acc);
-    if constexpr (LATE)
-        level_step_back<PBack>(p, m0, j0, rows, vec != 0, acc);
+    tile_product<PBack, true>(K / PBack::BK, aop, bop, (u16 *)lds, acc, view == LEVEL_U16);
+    level_step_back<PBack, LATE>(p, m0, j0, rows, vec != 0, acc);
+}
+
+// The marked tiles of a step (sp_level_kernel) in the entry-list form, which
+// takes a fraction of the tile form's pairs.  Where none is marked, as in the
+// steps of a transfer matrix, a block ends after 4 reads (m = 8: 5 us of a step of 285).
+constexpr int EPARTS = EBM / PCfg::BM;
+template <bool LATE>
+__global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void sp_entry_past_kernel(
+    LevelStep p, const int64_t *__restrict__ off, const int32_t *__restrict__ order, const int32_t *__restrict__ idx,
+    const u16 *__restrict__ Bp, int tiles_m, int nblk, int vec)
+{
+    __shared__ __attribute__((aligned(16))) u16 nt[2 * E_NT];
+    __shared__ __attribute__((aligned(4))) u16 low[LATE ? EBM : 2];
+    const int t = (int)blockIdx.x, J = order[t / tiles_m];
+    const int64_t n = p.n, m0 = (int64_t)(t % tiles_m) * EBM, j0 = (int64_t)J * SBN;
+    const int64_t row = m0 + (int64_t)(threadIdx.x % EPARTS) * PCfg::BM;
+    if (!__syncthreads_or(threadIdx.x < EPARTS && row < n && glob(p.O)[row * p.ldo + j0] == TILE_MARK)) return;
+    const int64_t kbeg = off[J], nk = (off[J + 1] - kbeg) / SBK;
+    const uint32_t *li = LATE ? p.low_in + m0 : nullptr;
+    uint32_t *lo = LATE ? p.low_out + m0 : nullptr, *bo = LATE ? p.big_out + m0 : nullptr;
+    uint32_t most;
+    if (m0 + EBM <= n)
+        most = entry_tile<true, LATE, true>(p.L, p.ldl, n, m0, j0, idx, Bp, kbeg, nk, p.O, p.ldo, vec, nt, li, lo, bo, low);
     else
-        tile_store<PBack>(p.O, p.ldo, n, n, m0, j0, vec != 0, acc);
+        most = entry_tile<false, LATE, true>(p.L, p.ldl, n, m0, j0, idx, Bp, kbeg, nk, p.O, p.ldo, vec, nt, li, lo, bo, low);
+    if (__syncthreads_or(most > LV_MAX + 1) && threadIdx.x == 0)  // (the form has no use for the other word)
+        atomicAdd(&p.past_out[0], 2u * (uint32_t)min<int64_t>(EPARTS, (n - m0 + PCfg::BM - 1) / PCfg::BM));
 }
 
 // ------------------------------------------- the step in bytes
@@ -902,7 +975,8 @@ static int64_t plan_capacity(int64_t n, size_t bytes)
 
 struct SparsePlan {
     int64_t nblk, cap;
-    int64_t *counts, *off;
+    int64_t *counts;  // of rows; of a finished plan, the 3 x LEVEL_PASTS words of its steps (level_step)
+    int64_t *off;
     int32_t *order, *idx;
     u16 *Bp;
 };
@@ -958,7 +1032,7 @@ mpr_status sparse_plan_fill(const u16 *A, int64_t n, int64_t lda, void *ws, size
     // with images, the blocks' largest values take the place of their order,
     // which only the VALU forms read
     hipLaunchKernelGGL(images ? sp_fill_kernel<true> : sp_fill_kernel<false>, dim3((unsigned)p.nblk), dim3(PT), 0, s, A,
-                       lda, n, (const int64_t *)p.off, p.nblk, p.cap, p.idx, p.Bp, vec, p.order, st);
+                       lda, n, (const int64_t *)p.off, p.nblk, p.cap, p.idx, p.Bp, vec, p.order, (uint32_t *)p.counts, st);
     return check_launch();
 }
 
@@ -978,14 +1052,31 @@ bool sparse_step_late(int64_t n, int64_t ldl, int64_t ldo)
     return g_sparse_form == MPR_SPARSE_AUTO && n >= 8 && level_strides(ldl, ldo);
 }
 
+// From so many states on, tiles past the levels are left to the entry-list form
+// (a launch more a step): below, the tile form is as fast or faster on them.
+constexpr int64_t ENTRY_MIN_N = 7000;
+
+// Step `step` (from 0) over a plan's lists; the past words lie where the plan's
+// counts were, which its other parts replace.
 template <bool LATE>
-static mpr_status level_step(const LevelStep &q, const SparsePlan &p, int vec, int32_t *st, hipStream_t s)
+static mpr_status level_step(LevelStep q, const SparsePlan &p, int64_t step, int vec, int32_t *st, hipStream_t s)
 {
+    uint32_t *past = (uint32_t *)p.counts;
+    q.past_in = past + step % 3 * LEVEL_PASTS;
+    q.past_out = past + (step + 1) % 3 * LEVEL_PASTS;
+    q.past_next = past + (step + 2) % 3 * LEVEL_PASTS;
+    const bool elsewhere = q.n >= ENTRY_MIN_N && g_sparse_arith == MPR_ARITH_U16 && (int64_t)EBM * q.ldl * 2 < ((int64_t)1 << 32);
     const int64_t tiles_m = (q.n + PCfg::BM - 1) / PCfg::BM, tiles = tiles_m * p.nblk;
     if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
-    hipLaunchKernelGGL(sp_level_kernel<LATE>, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, q,
-                       (const int64_t *)p.off, (const int32_t *)p.idx, (const u16 *)p.Bp, (int)tiles_m, (int)p.nblk,
-                       p.cap, vec, st);
+    auto kernel = elsewhere ? (step == 0 ? sp_level_kernel<LATE, true, true> : sp_level_kernel<LATE, false, true>)
+                            : (step == 0 ? sp_level_kernel<LATE, true, false> : sp_level_kernel<LATE, false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)round_up(tiles, 8)), dim3(PCfg::NT), 0, s, q, (const int64_t *)p.off,
+                       (const int32_t *)p.idx, (const u16 *)p.Bp, (int)tiles_m, (int)p.nblk, p.cap, vec, st);
+    if (elsewhere) {
+        const int64_t rows = (q.n + EBM - 1) / EBM;  // fewer tiles than above
+        hipLaunchKernelGGL(sp_entry_past_kernel<LATE>, dim3((unsigned)(rows * p.nblk)), dim3(ENT), 0, s, q,
+                           (const int64_t *)p.off, (const int32_t *)p.order, (const int32_t *)p.idx, (const u16 *)p.Bp, (int)rows, (int)p.nblk, vec);
+    }
     return check_launch();
 }
 
@@ -1001,13 +1092,13 @@ mpr_status sparse_step8_launch(const uint8_t *N, int64_t n, void *ws, size_t byt
     return check_launch();
 }
 
-mpr_status sparse_step_late_launch(const LevelStep &q, void *ws, size_t bytes, int32_t *st, hipStream_t s)
+mpr_status sparse_step_late_launch(const LevelStep &q, void *ws, size_t bytes, int64_t step, int32_t *st, hipStream_t s)
 {
-    return level_step<true>(q, carve_plan(ws, q.n, bytes), aligned16(q.O) && q.ldo % 8 == 0, st, s);
+    return level_step<true>(q, carve_plan(ws, q.n, bytes), step, aligned16(q.O) && q.ldo % 8 == 0, st, s);
 }
 
 mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, size_t bytes, u16 *C, int64_t ldc,
-                              hipStream_t s)
+                              int64_t step, hipStream_t s)
 {
     SparsePlan p = carve_plan(ws, n, bytes);
     const int vec = aligned16(C) && ldc % 8 == 0;
@@ -1019,7 +1110,7 @@ mpr_status sparse_step_launch(const u16 *Np, int64_t ldn, int64_t n, void *ws, s
         q.ldl = ldn;
         q.ldo = ldc;
         q.n = n;
-        return level_step<false>(q, p, vec, nullptr, s);
+        return level_step<false>(q, p, step, vec, nullptr, s);
     }
     if (form == MPR_SPARSE_ENTRIES && g_sparse_arith == MPR_ARITH_U16 && (int64_t)EBM * ldn * 2 < ((int64_t)1 << 32)) {
         const int64_t tiles_m = (n + EBM - 1) / EBM;
