@@ -315,7 +315,8 @@ void batch_kernel(const DevChain *__restrict__ chains, const BatchItem *__restri
 __global__ void reset_counter_kernel(int *counter) { *counter = 0; }
 
 // ------------------------------------------------ the batch step by step
-// Tiles of a step: 128 x 256 while they fill the CUs, else 64 x 64 (12 chains
+// Tiles of a step: 128 x 256 while they fill the CUs and are not mostly empty
+// (1.5 times the area in 64 x 64: chains of 192 states), else 64 x 64 (12 chains
 // of 256 to 4096 states: 33.7 ms; with 128 x 128 instead 37.3; with 128 x 256
 // and 128 x 128 34.0, and 6 chains up to 1500 states 2.73 / 2.97 / 3.98 ms).
 using BStep0 = LCfg4;
@@ -389,6 +390,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void
     const LevelItem it = items[blockIdx.x];
     if (it.inst < 0) return;
     const DevChain c = chains[it.inst];
+    if (k > c.e) return;
     const bool in_p = ((c.e - k + 1) & 1) != 0;  // step k writes buffer (e - k) % 2
     const int64_t r0 = row0[it.inst], in = (k - 2) % 3 * lb.rows + r0, out = (k - 1) % 3 * lb.rows + r0,
                   next = k % 3 * lb.rows + r0;
@@ -422,7 +424,8 @@ struct LevelPlan {
     int count;
     const int64_t *row0;
     const LevelItem *items[2];            // tiles of BStep0, of BStep1
-    std::vector<unsigned> active[2];      // [k]: leading items whose chains reach power k
+    std::vector<unsigned> active[2];      // [k]: leading items with all chains that reach power k
+    std::vector<char> large;              // [k]: power k in tiles of BStep0
     LowBufs low;
 };
 
@@ -470,53 +473,81 @@ static BatchLayout batch_layout(const mpr_chain_desc *d, int count, int bm)
     return L;
 }
 
-// Step-by-step batches: the matrix cores take any size, but below about 200
-// states a step is a few tiles, and its launch costs more than the panel form
-// (which keeps all steps of a panel in one workgroup) spends on it.  A step is
-// a launch, so very long chains (and captures of them) keep the panel form.
+// Step-by-step batches: the matrix cores take any size, but a batch of chains
+// below about 200 states keeps every step of a panel in one workgroup.  A step
+// is a launch, 6.3 us and more, so very long chains (and captures of them) keep the
+// panel form, and so does a batch whose longest chain of panels is shorter
+// than its launches: few steps of a larger chain beside thousands of a tiny one
+// (192 states to A^2 with 16 chains of 8 states to A^4096: 21.4 ms in panels, 25.8
+// step by step).  A step of a panel takes about 5 us and 0.00066 n^2 (n = 8 5.2,
+// 64 9.2, 192 39, 512 178).
 constexpr int64_t LEVEL_MIN_N = 192, LEVEL_MAX_E = 4096;
 
 static bool level_batch(const mpr_chain_desc *d, int count)
 {
-    int64_t most = 0;
+    int64_t most = 0, steps = 0;
+    double panel = 0;
     for (int i = 0; i < count; i++) {
         most = std::max(most, d[i].n);
+        steps = std::max(steps, d[i].e);
+        panel = std::max(panel, (double)d[i].e * (5 + 0.00066 * (double)d[i].n * (double)d[i].n));
         if (d[i].n < 8 || d[i].e > LEVEL_MAX_E) return false;
     }
-    return most >= LEVEL_MIN_N;
+    return most >= LEVEL_MIN_N && panel >= 6.5 * (double)steps;
 }
 
-// bm x bn tiles of the chains in `order`, 8 streams interleaved: block b
-// runs on XCD b % 8, and each XCD gets an eighth of every chain's tiles, a
-// contiguous run in groups of 8 tile rows, so the blocks of one XCD share
-// panels in its L2 and all XCDs have equal work.
+static int64_t level_tiles(int64_t n, int64_t bm, int64_t bn) { return ((n + bm - 1) / bm) * ((n + bn - 1) / bn); }
+
+// bm x bn tiles of the chains in `order`, 8 streams interleaved: block b runs
+// on XCD b % 8.  Each XCD gets an eighth of a chain's tiles, a contiguous run in
+// groups of 8 tile rows, so the blocks of one XCD share panels in its L2 and
+// all XCDs have equal work.  Eight chains in a row of fewer than XCD_TILES tiles
+// each go one to an XCD instead: spread over all of them, every XCD read every
+// operand (256 chains of 192 states 118 us a step, now 23).  ends[o]: items up to
+// the last of the o-th chain's (a step takes a prefix, and its blocks look
+// whether their chain is done).
+constexpr int64_t XCD_TILES = 64;
 static std::vector<LevelItem> level_items(const mpr_chain_desc *d, const std::vector<int> &order, int64_t bm,
                                           int64_t bn, std::vector<unsigned> *ends)
 {
     std::vector<LevelItem> out;
-    for (size_t o = 0; o < order.size(); o++) {
+    const int count = (int)order.size();
+    auto tiles_of = [&](int o) { return level_tiles(d[order[o]].n, bm, bn); };
+    auto push = [&](int o, int64_t at) {
         const int64_t n = d[order[o]].n, down = (n + bm - 1) / bm, across = (n + bn - 1) / bn;
-        const int64_t tiles = down * across, per = (tiles + 7) / 8;
-        for (int64_t q = 0; q < per * 8; q++) {
-            const int64_t at = (q % 8) * per + q / 8;
-            if (at >= tiles) {
-                out.push_back(LevelItem{-1, 0, 0});
-                continue;
-            }
-            const int64_t first = at / (8 * across) * 8, gs = std::min<int64_t>(down - first, 8),
-                          w = at - first * across;
-            out.push_back(LevelItem{(int32_t)o, (int16_t)(first + w % gs), (int16_t)(w / gs)});
+        if (at >= down * across) {
+            out.push_back(LevelItem{-1, 0, 0});
+            return;
         }
-        if (ends) ends->push_back((unsigned)out.size());
+        const int64_t first = at / (8 * across) * 8, gs = std::min<int64_t>(down - first, 8), w = at - first * across;
+        out.push_back(LevelItem{(int32_t)o, (int16_t)(first + w % gs), (int16_t)(w / gs)});
+    };
+    ends->clear();
+    for (int o = 0; o < count;) {
+        int64_t most = 0;
+        int run = 0;
+        while (run < 8 && o + run < count && tiles_of(o + run) < XCD_TILES) most = std::max(most, tiles_of(o + run++));
+        if (run == 8) {
+            for (int64_t at = 0; at < most; at++)
+                for (int x = 0; x < 8; x++) push(o + x, at);
+        } else {
+            run = 1;
+            const int64_t per = (tiles_of(o) + 7) / 8;
+            for (int64_t q = 0; q < per * 8; q++) push(o, (q % 8) * per + q / 8);
+        }
+        for (; run > 0; run--, o++) ends->push_back((unsigned)out.size());
     }
     return out;
 }
 
-// Items of bm x bn tiles of the whole batch.
+// Room for the items of bm x bn tiles of the whole batch, in any order.
 static size_t level_item_count(const mpr_chain_desc *d, int count, int64_t bm, int64_t bn)
 {
     size_t c = 0;
-    for (int i = 0; i < count; i++) c += (size_t)round_up((d[i].n + bm - 1) / bm * ((d[i].n + bn - 1) / bn), 8);
+    for (int i = 0; i < count; i++) {
+        const int64_t tiles = level_tiles(d[i].n, bm, bn);
+        c += (size_t)(tiles < XCD_TILES ? 8 * tiles : round_up(tiles, 8));
+    }
     return c;
 }
 
@@ -765,6 +796,15 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
             if (hipMemcpyAsync(base + V.row0_off, row0.data(), 8 * row0.size(), hipMemcpyHostToDevice, s) !=
                 hipSuccess)
                 return MPR_EHIP;
+            const int64_t cus = device_cu_count();
+            int64_t wide = 0, narrow = 0;  // tiles of the chains that reach power k
+            level->large.assign((size_t)chains[0].e + 1, 0);
+            for (int o = 0; o < count; o++) {
+                wide += level_tiles(chains[o].n, BStep0::BM, BStep0::BN);
+                narrow += level_tiles(chains[o].n, BStep1::BM, BStep1::BN);
+                for (int64_t k = o + 1 < count ? chains[o + 1].e + 1 : 2; k <= chains[o].e; k++)
+                    level->large[k] = wide >= cus && 2 * 8 * wide <= 3 * narrow;
+            }
             level->count = count;
             level->row0 = (const int64_t *)(base + V.row0_off);
             uint32_t *low = (uint32_t *)(base + V.low_off);
@@ -798,11 +838,10 @@ extern "C" mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count
 static mpr_status level_batch_launch(const BatchPlan &p, int32_t *st, hipStream_t s)
 {
     const LevelPlan &v = *p.level;
-    const unsigned fill = (unsigned)device_cu_count();
     hipLaunchKernelGGL(batch_rows_kernel<true>, dim3((unsigned)v.low.rows), dim3(256), 0, s,
                        (const DevChain *)p.chains, v.row0, v.count, v.low, st);
     for (size_t k = 2; k < v.active[0].size(); k++) {
-        if (v.active[0][k] >= fill)
+        if (v.large[k])
             hipLaunchKernelGGL((batch_step_kernel<BStep0, true>), dim3(v.active[0][k]), dim3(BStep0::NT), 0, s,
                                (const DevChain *)p.chains, v.row0, v.items[0], v.count, (int64_t)k, v.low, st);
         else

@@ -127,3 +127,32 @@ def test_batch_overflow_is_reported(mpr):
     with pytest.raises(mpr.MprError) as err:
         mpr.batch_power([chain])
     assert err.value.status == 3
+
+
+@pytest.mark.parametrize("count", [7, 8, 21, 33])
+def test_batch_of_many_small_chains(mpr, count):
+    """Chains that go eight at a time, one to an XCD, beside ones that do not;
+    within an eight they end at different powers and differ in size."""
+    rng = np.random.default_rng(count)
+    chains, want = [], []
+    for i in range(count):
+        n, e = (int(rng.integers(8, 400)), int(rng.integers(1, 7))) if i != 3 else (900, 4)
+        X = synth.random_matrix(n, n, 100 * count + i, 0, 25 if i % 5 else 2600, 0.25)
+        A = mpr.to_device(X)
+        chains.append((A, e, mpr.alloc_matrix(n, n), torch.empty(n, dtype=torch.int64, device="cuda")))
+        want.append(_chain(mpr, A, e))
+    ws = mpr.workspace(mpr.batch_workspace_size(chains)).fill_(255)
+    mpr.batch_plan(chains, ws)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    stream = torch.cuda.Stream()
+    graph = mpr.batch_graph_create(ws, st, stream)
+    for launch in (lambda: mpr.batch_launch(ws, st), lambda: (torch.cuda.synchronize(), mpr.graph_launch(graph, stream))) * 2:
+        for _, _, N, R in chains:
+            N.view(torch.int16).fill_(9)
+            R.fill_(9)
+        launch()
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        for (_, _, N, R), (Nr, Rr) in zip(chains, want):
+            assert _same(N, Nr) and torch.equal(R, Rr)
+    mpr.graph_destroy(graph)
