@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <mutex>
 #include <thread>
 #include <unordered_map>
@@ -146,22 +147,33 @@ mpr_status HostRecord::drain()
 // Waits until a kernel on the stream has written `seq` into the record: a look
 // at host memory (6 us from launch to here, 21 us with a copy and a
 // synchronisation).  A stream that ends or fails without writing it is an
-// error, so the wait ends in every case.
+// error, so the wait ends in every case.  A wait of more than kSpinMs sleeps
+// between looks, for a 64th of the time that it has lasted (at most 1 ms): a
+// search of m = 11, 1 s a power, held a core for its 40 s.
 mpr_status HostRecord::wait(const int64_t *rec, int64_t seq)
 {
+    using clock = std::chrono::steady_clock;
+    constexpr std::chrono::milliseconds kSpinMs{10};
+    const auto from = clock::now();
     auto there = [&] {
         if (__atomic_load_n(&rec[7], __ATOMIC_ACQUIRE) != seq) return false;
         seen = seq;
         return true;
     };
-    for (;;) {
-        for (int k = 0; k < 4096; k++) {
+    for (int looks = 4096;;) {
+        for (int k = 0; k < looks; k++) {
             if (there()) return MPR_OK;
             __builtin_ia32_pause();
         }
         const hipError_t e = hipStreamQuery(s);
         if (e == hipErrorNotReady) {
-            std::this_thread::yield();
+            const clock::duration waited = clock::now() - from;
+            if (waited < kSpinMs) {
+                std::this_thread::yield();
+            } else {
+                looks = 1;
+                std::this_thread::sleep_for(std::min<clock::duration>(waited / 64, std::chrono::milliseconds(1)));
+            }
             continue;
         }
         if (e == hipSuccess && there()) return MPR_OK;

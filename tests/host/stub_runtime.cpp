@@ -5,11 +5,15 @@
 // leaves behind on its error paths can be looked at without a GPU.
 //   stub_runtime <libmpr.so> errors   every launch check of every call fails once
 //   stub_runtime <libmpr.so> idle     synchronous calls return with the stream drained
+//   stub_runtime <libmpr.so> wait     a wait of 400 ms leaves the processor to others
 #include <dlfcn.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
+#include <time.h>
+
+#include <chrono>
 #include <deque>
 #include <functional>
 #include <map>
@@ -25,6 +29,7 @@ struct Kernel { std::function<void()> run; bool writes; };  // writes: a host re
 static std::deque<Kernel> queued;
 static bool retiring = false;  // the last kernel has written its record and still runs
 static int fail_at = -1, checks = 0, allocations_fail = 0;
+static std::chrono::steady_clock::time_point hold;  // nothing runs before
 static bool sticky = false;  // an error that hipGetLastError has yet to report
 struct Call { dim3 grid, block; size_t shared; hipStream_t stream; };
 static Call call;
@@ -82,6 +87,7 @@ hipError_t hipGetLastError(void)
 hipError_t hipStreamQuery(hipStream_t)
 {
     if (queued.empty()) return retiring = false, hipSuccess;
+    if (std::chrono::steady_clock::now() < hold) return hipErrorNotReady;
     retiring = true;
     run_one();
     return hipErrorNotReady;
@@ -133,6 +139,14 @@ int main(int argc, char **argv)
     int64_t mu, lam, c;
     size_t bytes;
     int32_t verdict = 0;
+    if (!strcmp(argv[2], "wait")) {
+        hold = std::chrono::steady_clock::now() + std::chrono::milliseconds(400);
+        const clock_t busy = clock();
+        const mpr_status e = plan(A.data(), 300, 300, &bytes, nullptr);
+        const double part = (double)(clock() - busy) / CLOCKS_PER_SEC / 0.4;
+        printf(e == MPR_OK && part < 0.25 ? "ok\n" : "status %d, %.0f %% of the wait busy\n", e, 100 * part);
+        return e != MPR_OK || part >= 0.25;
+    }
     struct Case { std::string name; std::function<mpr_status()> call; };
     std::vector<Case> cases;
     for (int64_t n : {20, 300})

@@ -38,3 +38,10 @@ def test_synchronous_calls_return_with_the_stream_drained(driver):
     wrote the record, may still be retiring."""
     p = driver("idle")
     assert p.returncode == 0, p.stdout
+
+
+def test_long_waits_sleep(driver):
+    """A call that waits for a record for 400 ms uses the processor for less than
+    a quarter of them (the first 10 are spent looking)."""
+    p = driver("wait")
+    assert p.returncode == 0, p.stdout
