@@ -748,10 +748,10 @@ def leg_config1(mpr, torch):
 
 def leg_config2(mpr, torch, args):
     """N = 8192: one product, and A^64 by the chain (63 products, each
-    normalised); the f16 form of the chain as a labelled experiment; the
-    oracle's row-restricted chain on sampled rows (row i of A^k depends only
-    on row i of A^(k-1) and on A, so this is exact) as CPU baseline and
-    parity check."""
+    normalised), as the library chooses them; the product in the f16
+    configuration as a labelled experiment; the oracle's row-restricted chain
+    on sampled rows (row i of A^k depends only on row i of A^(k-1) and on A, so
+    this is exact) as CPU baseline and parity check."""
     import oracle as O
     import synth
 
@@ -770,30 +770,30 @@ def leg_config2(mpr, torch, args):
     t_single = float(np.mean([e0.elapsed_time(e1) for e0, e1 in ev])) * 1e-3
     ws = mpr.workspace(mpr.power_workspace_size(n, e, mpr.CHAIN))
     st = torch.zeros(1, dtype=torch.int32, device="cuda")
-    out = {}
-    for arith in ("u16", "f16"):
-        N = mpr.alloc_matrix(n, n)
-        R = torch.empty(n, dtype=torch.int64, device="cuda")
-        with mpr.arith_scope(arith):
-            mpr.minplus_power(A, 3, mpr.CHAIN, N, R, ws, check=False, d_status=st)
-            _, t = _timed(torch, lambda: mpr.minplus_power(A, e, mpr.CHAIN, N, R, ws, check=False, d_status=st))
-        mpr.check_status(st)
-        out[arith] = ((N, R), t)
+    Nu = mpr.alloc_matrix(n, n)
+    Ru = torch.empty(n, dtype=torch.int64, device="cuda")
+    mpr.minplus_power(A, 3, mpr.CHAIN, Nu, Ru, ws, check=False, d_status=st)
+    _, t_chain = _timed(torch, lambda: mpr.minplus_power(A, e, mpr.CHAIN, Nu, Ru, ws, check=False, d_status=st))
+    mpr.check_status(st)
+    with mpr.arith_scope("f16"):
+        fcfg = mpr.gemm_pick_config(n, n, n)
+    F = mpr.alloc_matrix(n, n)
+    mpr.minplus_gemm(A, A, F, check=False, cfg=fcfg)
+    _, t_f16 = _timed(torch, lambda: mpr.minplus_gemm(A, A, F, check=False, cfg=fcfg))
+    f16_same = torch.equal(F.view(torch.int16), C.view(torch.int16))
     pairs = float(n) ** 3
     rng = np.random.default_rng(3)
     rows = np.sort(rng.choice(n, args.config2_rows, replace=False))
     t0 = time.perf_counter()
     Nr, Rr = O.chain_rows(O.from_u16(X), rows, e)
     t_cpu = time.perf_counter() - t0
-    (Nu, Ru), t_chain = out["u16"]
     ok = np.array_equal(_rows(torch, Nu, rows), O.to_u16(Nr)) and np.array_equal(Ru.cpu().numpy()[rows], Rr)
     return {"workload": "N=8192 uint16 (seed 3, U[0,15], 30% inf): one product, A^64 by the chain",
             "value": round(63 * pairs / t_chain / 1e9, 1), "unit": "G pairs/s", "dtype": "uint16",
             "chain_s": round(t_chain, 3), "single_product_ms": round(t_single * 1e3, 3),
             "single_product_gpairs": round(pairs / t_single / 1e9, 1),
-            "f16_form": {"chain_s": round(out["f16"][1], 3),
-                         "gpairs": round(63 * pairs / out["f16"][1] / 1e9, 1),
-                         "bit_identical": _same(torch, out["u16"][0], out["f16"][0])},
+            "f16_form": {"tile_config": fcfg, "single_product_ms": round(t_f16 * 1e3, 3),
+                         "gpairs": round(pairs / t_f16 / 1e9, 1), "bit_identical": bool(f16_same)},
             "sampled_rows_match_oracle": bool(ok),
             "cpu_baseline": {"value": round(len(rows) * (e - 1) * float(n) * n / t_cpu / 1e9, 3),
                              "unit": "G pairs/s", "cores": O.threads(), "kind": "oracle",
@@ -869,10 +869,10 @@ def leg_config3(mpr, torch, goldens, args):
 
 
 def leg_config4(mpr, torch, args):
-    """256 chains in one graph-captured launch (configuration picked by the
-    library's model with the autotuner's weights), the f16 form of it, and
-    the plain per-instance path (one chain after another) on the same GPU;
-    the oracle on sampled rows of three chains."""
+    """256 chains as one HIP graph (as the library runs them, step by step on
+    the matrix cores), the same batch in the f16 panel configuration that its
+    model picks, and the plain per-instance path (one chain after another) on
+    the same GPU; the oracle on sampled rows of three chains."""
     import oracle as O
     import synth
 
@@ -890,10 +890,14 @@ def leg_config4(mpr, torch, args):
     st = torch.zeros(1, dtype=torch.int32, device="cuda")
     stream = torch.cuda.Stream()
     forms = {}
-    for arith in ("u16", "f16"):
-        with mpr.arith_scope(arith):
+    with mpr.arith_scope("f16"):
+        mpr.batch_plan(chains, ws, stream)
+    for name, cfg in (("steps", -1), ("f16", mpr.batch_plan_info(ws)[0])):
+        mpr.set_batch_config(cfg)
+        try:
             mpr.batch_plan(chains, ws, stream)
-        cfg = mpr.batch_plan_info(ws)[0]
+        finally:
+            mpr.set_batch_config(-1)
         g = mpr.batch_graph_create(ws, st, stream)
         mpr.graph_launch(g, stream)
         stream.synchronize()
@@ -904,7 +908,7 @@ def leg_config4(mpr, torch, args):
         t = (time.perf_counter() - t0) / args.batch_reps
         mpr.graph_destroy(g)
         mpr.check_status(st)
-        forms[arith] = (cfg, t, [(N.clone(), R.clone()) for (_, _, N, R) in chains])
+        forms[name] = (cfg, t, [(N.clone(), R.clone()) for (_, _, N, R) in chains])
     wsi = mpr.workspace(max(mpr.power_workspace_size(d["n"], d["e"], mpr.CHAIN) for d in inst))
 
     def solo():
@@ -913,8 +917,8 @@ def leg_config4(mpr, torch, args):
 
     _, t_solo = _timed(torch, solo)
     mpr.check_status(st)
-    same = all(_same(torch, (N, R), b) for (_, _, N, R), b in zip(chains, forms["u16"][2]))
-    same_f16 = all(_same(torch, a, b) for a, b in zip(forms["u16"][2], forms["f16"][2]))
+    same = all(_same(torch, (N, R), b) for (_, _, N, R), b in zip(chains, forms["steps"][2]))
+    same_f16 = all(_same(torch, a, b) for a, b in zip(forms["steps"][2], forms["f16"][2]))
     order = sorted(range(len(inst)), key=lambda i: -inst[i]["n"])
     picks = [order[0], order[len(order) // 2], order[-1]]
     t0 = time.perf_counter()
@@ -923,22 +927,21 @@ def leg_config4(mpr, torch, args):
         n, e = inst[i]["n"], inst[i]["e"]
         rows = np.sort(np.random.default_rng(i).choice(n, args.config4_rows, replace=False))
         Nr, Rr = O.chain_rows(O.from_u16(mats[i]), rows, e)
-        N, R = forms["u16"][2][i]
+        N, R = forms["steps"][2][i]
         ok = ok and np.array_equal(_rows(torch, N, rows), O.to_u16(Nr)) and np.array_equal(R.cpu().numpy()[rows], Rr)
         sampled += len(rows) * (e - 1) * float(n) * n
     t_cpu = time.perf_counter() - t0
-    cfg, t_batch, _ = forms["u16"]
+    t_batch = forms["steps"][1]
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    binfo = mpr.batch_config_info(cfg)
     return {"workload": "256 chains, N log-uniform [256,4096], e uniform [8,128], U[0,31] 25% inf (seed 4)",
             "value": round(pairs / t_batch / 1e9, 1), "unit": "G pairs/s", "dtype": "uint16",
-            "total_pairs": pairs, "batch_config": cfg, "panel_rows": binfo["panel_rows"],
-            "batched_s": round(t_batch, 3), "pct_valu_peak": round(100 * pairs / t_batch / 1e9 /
-                                                                   valu_peak_gpairs(cus, "u16"), 2),
+            "total_pairs": pairs, "batched_s": round(t_batch, 3),
+            "pct_matrix_core_peak": round(100 * pairs / t_batch / 1e9 / mfma_peak_gpairs(cus), 2),
             "per_instance_s": round(t_solo, 3), "per_instance_gpairs": round(pairs / t_solo / 1e9, 1),
             "speedup_vs_per_instance": round(t_solo / t_batch, 2),
             "batched_equals_per_instance": bool(same),
-            "f16_form": {"batch_config": forms["f16"][0], "batched_s": round(forms["f16"][1], 3),
+            "f16_form": {"batch_config": forms["f16"][0],
+                         "panel_rows": mpr.batch_config_info(forms["f16"][0])["panel_rows"], "batched_s": round(forms["f16"][1], 3),
                          "gpairs": round(pairs / forms["f16"][1] / 1e9, 1),
                          "pct_of_f16_peak": round(100 * pairs / forms["f16"][1] / 1e9 /
                                                   valu_peak_gpairs(cus, "f16"), 2),

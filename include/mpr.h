@@ -224,11 +224,13 @@ mpr_status mpr_minplus_gemm_norm(int64_t M, int64_t N, int64_t K,
 /* ------------------------------------------------------------------ */
 
 /* Workspace bytes for mpr_minplus_power on an n x n matrix.  For
- * MPR_CHAIN on a matrix of few tiles (fewer than about two 64 x 64 output
- * tiles per CU) this includes room in which the steps keep their row minima,
- * so that each step normalises the power it reads and no pass of its own
- * does (the same bits); a workspace of only the layout, n * round_up(n, 8) *
- * 2 + 256 bytes, normalises after every step. */
+ * MPR_CHAIN on a matrix of 256 states and more but few tiles (fewer than
+ * about two 64 x 64 output tiles per CU, n < 1450 or so) this includes room
+ * in which the steps keep their row minima, so that each step normalises the
+ * power it reads and no pass of its own does (the same bits); so does any
+ * workspace with 24 n + 512 bytes past the layout, n * round_up(n, 8) * 2 +
+ * 256 bytes, for 33 <= n <= 4096.  A smaller one normalises after every
+ * step. */
 mpr_status mpr_power_workspace_size(int64_t n, int64_t e, int schedule, size_t *bytes_host);
 
 /* Canonical form (N_out, R_out) of A^e for the n x n matrix A, e >= 1.
@@ -285,9 +287,10 @@ mpr_status mpr_minplus_power_noalloc(const uint16_t *A, int64_t n, int64_t lda, 
                                      mpr_stream stream);
 
 /* Bytes of the compressed-K plan of the n x n device matrix A (row stride
- * lda): for every block J of 64 columns, the rows of A with a finite entry
- * in J (rounded up to 32 per block) and their packed entries -- a few per
- * cent of the worst case that mpr_power_workspace_size and
+ * lda): for every block J of 64 columns, the aligned groups of 8 rows of A
+ * with a finite entry in J (rounded up to 32 rows per block) and their packed
+ * entries, and 24 n bytes and some for the steps' row minima -- a few per cent
+ * of the worst case that mpr_power_workspace_size and
  * mpr_period_workspace_size_ex assume (a dense A) for transfer matrices.
  * A workspace of mpr_power_workspace_size(n, e, MPR_CHAIN) + this many bytes
  * serves mpr_minplus_power(..., MPR_CHAIN_SPARSE) on this A (a d_status is
@@ -445,7 +448,8 @@ mpr_status mpr_batch_plan(const mpr_chain_desc *descs_host, int count,
  * states, every chain at least 8 and no exponent past 4096, planned with no
  * explicit configuration, not persistent and in a workspace of the size
  * mpr_batch_workspace_size gives, runs on the matrix cores power by power
- * instead: one launch per power over the tiles of all chains that reach it.
+ * instead: one launch per power over the tiles of all chains that reach it
+ * (unless a tiny chain's panels would be done before so many launches).
  * No memset node, no host sync, so the launches can be captured into a HIP
  * graph.  Results land in each N_out / R_out, the same bits in every form. */
 mpr_status mpr_batch_launch(void *ws, int32_t *d_status, mpr_stream stream);
@@ -480,8 +484,9 @@ mpr_status mpr_set_sparse_arith(int arith);
  * MPR_SPARSE_ENTRIES (uint16 arithmetic only; the f16 form always takes
  * the tiles) visits only the finite entries of A[L_J, J], one output
  * column per wave; MPR_SPARSE_AUTO (the default) multiplies the tiles on the
- * matrix cores, as mpr_minplus_gemm does.  All give the same powers bit for
- * bit.  MPR_EINVAL for other values.  Process-wide setting. */
+ * matrix cores, as mpr_minplus_gemm does, and leaves those whose values are
+ * out of range there to f16 or uint16 tiles or, from 7000 states on in uint16
+ * arithmetic, to the entries form.  All give the same powers bit for bit.  MPR_EINVAL for other values.  Process-wide setting. */
 #define MPR_SPARSE_AUTO 0
 #define MPR_SPARSE_TILES 1
 #define MPR_SPARSE_ENTRIES 2
@@ -653,7 +658,8 @@ int mpr_gemm_config_count(void);
 mpr_status mpr_gemm_config_info(int cfg, int *bm, int *bn, int *bk, int *tm, int *tn, int *threads,
                                 int *arith);
 /* The configuration the tile table of the process-wide arithmetic gives an
- * M x N x K product (cfg = -1). */
+ * M x N x K product: what cfg = -1 runs where it does not run on the matrix
+ * cores (mpr_minplus_gemm). */
 int mpr_gemm_pick_config(int64_t M, int64_t N, int64_t K);
 /* Installs a size -> configuration table used when cfg = -1: entry t
  * applies to problems whose largest dimension is <= max_dim_host[t]

@@ -61,6 +61,8 @@ __device__ __forceinline__ int64_t agent_min(int64_t *p, int64_t v)
     return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Keys by position: multiples of 2^32 / phi, told apart by multipliers of
+// MurmurHash3's finaliser and of xxHash (any odd constants would do).
 __device__ __forceinline__ uint64_t nh4(const uint32_t w[4], uint32_t pos)
 {
     const uint32_t k = (pos + 1u) * 0x9E3779B1u;
