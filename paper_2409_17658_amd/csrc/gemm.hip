@@ -22,10 +22,11 @@ using Cfg6 = TileCfg<256, 128, 32, 8, 8>;    // 512 threads, 8x8 per lane
 // Blocks are handed to the 8 XCDs round-robin (block b runs on XCD b % 8).
 // Renumber so that each XCD receives a contiguous run of tiles, and walk the
 // tiles in groups of G tile-rows so that the blocks resident on one XCD share
-// A row panels and B column panels in that XCD's L2.  b: block of nb, a multiple
-// of 8.
-__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int &tm, int &tn, int b, int nb)
+// A row panels and B column panels in that XCD's L2.
+__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int &tm, int &tn)
 {
+    const int nb = (int)gridDim.x;  // a multiple of 8
+    const int b = (int)blockIdx.x;
     const int t = (b & 7) * (nb >> 3) + (b >> 3);
     if (t >= tiles_m * tiles_n) return false;
     constexpr int G = 8;
@@ -53,36 +54,34 @@ __global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(GemmWaves
 {
     __shared__ __attribute__((aligned(16))) u16 lds[T::LDS_ELEMS];
     int tm, tn;
-    if (!tile_of_block(tiles_m, tiles_n, tm, tn, (int)blockIdx.x, (int)gridDim.x)) return;
+    if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
     TileAcc<T> acc;
     tile_mainloop<T, H>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, lds, acc);
     tile_store<T>(C, ldc, M, N, m0, n0, vec != 0, acc);
 }
 
-// The same tiles of a product whose values are out of the level form's range
-// (level_sample), in the f16 form or uint16 by those values; of another one,
-// nothing, which a block a tile takes 100 us to find out at N = 16384: so no
-// more than four times the blocks that the chip holds, which share the nb tiles
-// (one time: N = 3350 1434 us, with all of them 1376).
+// Those of the tiles that hold a marked cell (level.h), in the f16 form or uint16
+// by their marks.  Where none is marked it takes 18 us at N = 16384; with blocks
+// that stay for several tiles, whose kernel spills registers on entry, 43.
 template <class T>
 __global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(GemmWaves<T>::value))) void gemm_past_kernel(
     const u16 *__restrict__ A, int64_t lda, const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ C, int64_t ldc,
     int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int vec)
 {
     __shared__ __attribute__((aligned(16))) u16 lds[T::LDS_ELEMS];
-    __shared__ int seen;
-    const LevelView view = level_sample(A, lda, B, ldb, M, N, K, &seen);
-    if (view <= LEVEL_PAST) return;
-    const int nb = (tiles_m * tiles_n + 7) / 8 * 8;
-    for (int b = (int)blockIdx.x; b < nb; b += (int)gridDim.x) {
-        int tm, tn;
-        if (!tile_of_block(tiles_m, tiles_n, tm, tn, b, nb)) continue;
-        const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
-        TileAcc<T> acc;
-        tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, lds, acc, view == LEVEL_U16);
-        tile_store<T>(C, ldc, M, N, m0, n0, vec != 0, acc);
-    }
+    static_assert(T::BM % MARK_CELL == 0 && T::BN % MARK_CELL == 0, "whole cells");
+    constexpr int ACROSS = T::BN / MARK_CELL, CELLS = T::BM / MARK_CELL * ACROSS;
+    int tm, tn;
+    if (!tile_of_block(tiles_m, tiles_n, tm, tn)) return;
+    const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
+    const int64_t row = m0 + (int)threadIdx.x / ACROSS * MARK_CELL, col = n0 + (int)threadIdx.x % ACROSS * MARK_CELL;
+    const u16 mark = (int)threadIdx.x < CELLS && row < M && col < N ? glob(C)[row * ldc + col] : 0;
+    if (!__syncthreads_or(mark == MARK_F16 || mark == MARK_U16)) return;
+    const bool wide = !__syncthreads_or(mark == MARK_F16);
+    TileAcc<T> acc;
+    tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, lds, acc, wide);
+    tile_store<T>(C, ldc, M, N, m0, n0, vec != 0, acc);
 }
 
 // An empty inner dimension: every entry of C is infinite.
@@ -100,8 +99,7 @@ static mpr_status launch_cfg(int64_t M, int64_t N, int64_t K, const u16 *A, int6
     const int64_t tiles_m = (M + T::BM - 1) / T::BM, tiles_n = (N + T::BN - 1) / T::BN;
     const int64_t tiles = tiles_m * tiles_n;
     if (tiles > (int64_t)INT32_MAX - 8) return MPR_EUNSUPPORTED;
-    int64_t blocks = round_up(tiles, 8);
-    if (PAST) blocks = std::min<int64_t>(blocks, 4 * round_up(device_cu_count(), 8) * GemmWaves<T>::value * 256 / T::NT);
+    const int64_t blocks = round_up(tiles, 8);
     const bool vec = aligned16(A) && aligned16(B) && aligned16(C) && lda % 8 == 0 && ldb % 8 == 0 && ldc % 8 == 0;
     auto kernel = gemm_kernel<T, H>;
     if constexpr (PAST) kernel = gemm_past_kernel<T>;
@@ -239,7 +237,6 @@ mpr_status gemm_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const u16
 mpr_status gemm_past_launch(bool spare, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                             int64_t ldb, u16 *C, int64_t ldc, hipStream_t s)
 {
-    if (!level_sampled(M, N, K)) return MPR_EUNSUPPORTED;
     int cfg = pick_config(M, N, K);
     const size_t pad = spare ? spare_config(cfg) : 0;
     return kCfgs[cfg].past(M, N, K, A, lda, B, ldb, C, ldc, s, pad);

@@ -301,9 +301,8 @@ struct LevelAcc {
 // What a look at a block's values says: all that it saw are in the levels; a
 // finite one is past LV_MAX, so its results can not all be proved by
 // level_clean; so few are in range that the block gives up, for the f16 form or
-// (minima of 2048 and more to be expected) the uint16 form of tile.h; the whole
-// product gives up, and a launch of its own computes it.
-enum LevelView { LEVEL_IN, LEVEL_PAST, LEVEL_F16, LEVEL_U16, LEVEL_ELSEWHERE };
+// (minima of 2048 and more to be expected) the uint16 form of tile.h.
+enum LevelView { LEVEL_IN, LEVEL_PAST, LEVEL_F16, LEVEL_U16 };
 // Counts among n values of an operand: up to LV_MAX, up to LV_HALF, and finite
 // ones past that.
 struct LevelCount {
@@ -314,71 +313,25 @@ struct LevelCount {
 // LV_MAX, and some ten of them are needed for all outputs of a block to have
 // one.  A pass over K in vain costs a tenth of the VALU form that follows, and
 // the VALU form in vain ten times the pass: so a block, which counts few
-// values, gives up below NEED = 8 such pairs, and a product, from LEVEL_SAMPLE
-// values, below 20.  Likewise the f16 form, which is exact but for results of
-// 2048 and more: uint16 where few pairs are of values up to LV_HALF and it is not
-// infinity that takes their place.
-template <int NEED>
+// values, gives up below LEVEL_NEED = 8 such pairs.  Likewise the f16 form, which is
+// exact but for results of 2048 and more: uint16 where few pairs are of values
+// up to LV_HALF and it is not infinity that takes their place.
+constexpr int LEVEL_NEED = 8;
 __device__ __forceinline__ LevelView level_view(const LevelCount &a, const LevelCount &b, int64_t K)
 {
-    const int64_t need = NEED * a.n * b.n;
+    const int64_t need = LEVEL_NEED * a.n * b.n;
     if (a.in * b.in * K >= need) return LEVEL_PAST;
     return a.half * b.half * K < need && (4 * a.over > a.half || 4 * b.over > b.half) ? LEVEL_U16 : LEVEL_F16;
 }
 constexpr int LEVEL_COUNTS = 6;  // words of LDS for a block's counts
-constexpr int LEVEL_NEED = 8, LEVEL_NEED_ALL = 20, LEVEL_DOUBT = 40;
 constexpr uint32_t LV_HALF = 1023;
 __device__ __forceinline__ int lanes_up_to(uint32_t v, uint32_t most) { return (int)__popcll(__ballot(v <= most)); }
 
-
-// The view of a whole product from LEVEL_SAMPLE values of each operand in runs of
-// 8 (K and N are at least 8: level_sampled), the same for every block of every
-// kernel that asks; seen: a word of LDS.  One wave looks: with all 8 waves of 800
-// blocks looking, a launch that finds nothing to do took 12 us, now 5.
-constexpr int LEVEL_SAMPLE = 1024;
-inline bool level_sampled(int64_t M, int64_t N, int64_t K) { return M > 0 && N >= 8 && K >= 8; }
-__device__ __forceinline__ LevelView level_sample(const u16 *A, int64_t lda, const u16 *B, int64_t ldb, int64_t M,
-                                                  int64_t N, int64_t K, int *seen)
-{
-    constexpr int PER = LEVEL_SAMPLE / 8 / 64;
-    if (threadIdx.x >= 64) {
-        __syncthreads();
-        return (LevelView)*seen;
-    }
-    uint4 v[2 * PER];
-#pragma unroll
-    for (int q = 0; q < PER; q++) {
-        const uint32_t s = (threadIdx.x & 63) * PER + q;
-        // four independent fractions of 2^32
-        const uint64_t x = mix64(2 * (uint64_t)s + 1), y = mix64(2 * (uint64_t)s + 2);
-        const uint64_t i = (x >> 32) * (uint64_t)M >> 32, k = (x & 0xFFFFFFFFu) * (uint64_t)(K - 7) >> 32;
-        const uint64_t l = (y >> 32) * (uint64_t)K >> 32, j = (y & 0xFFFFFFFFu) * (uint64_t)(N - 7) >> 32;
-        v[q] = uload16((gbytes *)(glob(A) + (int64_t)i * lda + (int64_t)k), 0);
-        v[PER + q] = uload16((gbytes *)(glob(B) + (int64_t)l * ldb + (int64_t)j), 0);
-    }
-    LevelCount t[2];
-#pragma unroll
-    for (int o = 0; o < 2; o++) {
-        uint32_t c = 0, over = 0;  // c: up to LV_MAX, and up to LV_HALF in the upper half
-#pragma unroll
-        for (int q = 0; q < PER; q++)
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const uint32_t w = comp(v[o * PER + q], e >> 1), x = (e & 1) ? w >> 16 : w & 0xFFFFu;
-                c += (x <= LV_MAX ? 1u : 0u) + (x <= LV_HALF ? 0x10000u : 0u);
-                over += x > LV_HALF && x != 0xFFFFu ? 1u : 0u;
-            }
-        for (int off = 1; off < 64; off <<= 1) {
-            c += (uint32_t)__shfl_xor((int)c, off, 64);
-            over += (uint32_t)__shfl_xor((int)over, off, 64);
-        }
-        t[o] = LevelCount{c & 0xFFFFu, c >> 16, over, LEVEL_SAMPLE};
-    }
-    const LevelView view = level_view<LEVEL_NEED_ALL>(t[0], t[1], K);
-    if (threadIdx.x == 0) *seen = view;
-    __syncthreads();
-    return view;
-}
+// First values of the 64 x 64 cells of a block that leaves its outputs to
+// another launch, for the f16 form or for uint16 at once: no block in the levels
+// has such values (up to LV_SUM, or infinity).
+constexpr u16 MARK_F16 = 0xFFFE, MARK_U16 = 0xFFFD;
+constexpr int MARK_CELL = 64;
 
 // The slices of K: slice 0 is the partial one at the end of K when there is
 // one, so that no loop has an edge, and the others follow from the end to the
@@ -481,19 +434,15 @@ __device__ __forceinline__ void level_slice(const uint4 *as0, const uint4 *as1, 
 
 // The k loop: acc = the largest 32-term sum of each output (its f32 bits),
 // complete in group 0.  The product is taken transposed (D = B^T A^T): a lane
-// then holds one row of C and runs of 4 consecutive columns.  With CHECK (and
-// `check`, block-uniform), a block whose first slice holds values past LV_MAX
-// takes one value per thread of each operand there (cnt: LEVEL_COUNTS words of LDS) and
-// returns what level_view makes of them, or of the whole product (whole(), asked
-// in doubt): given up, the rest of the pass over K is saved
-// (values 0..3000, 2200 x 2500 x 9000: 2.34 ms, now 2.10; values 0..15 at N =
-// 16384: no difference).
-struct LevelAlone {
-    __device__ __forceinline__ LevelView operator()() const { return LEVEL_PAST; }
-};
-template <class C, bool CHECK = false, class AOp, class BOp, class Whole = LevelAlone>
+// then holds one row of C and runs of 4 consecutive columns.  With CHECK, a
+// block whose first slice holds values past LV_MAX takes one value per thread
+// of each operand there (cnt: LEVEL_COUNTS words of LDS) and returns what
+// level_view makes of them: given up, the rest of the pass over K is saved
+// (values 0..3000, 2200 x 2500 x 9000: 2.34 ms without, 2.10 with; values
+// 0..15 at N = 16384: no difference).
+template <class C, bool CHECK = false, class AOp, class BOp>
 __device__ __forceinline__ LevelView level_kloop(int64_t K, AOp &aop, BOp &bop, uint4 *lds, LevelAcc<C> &acc,
-                                                 int *cnt = nullptr, bool check = true, Whole whole = Whole())
+                                                 int *cnt = nullptr)
 {
     const int lane = (int)(threadIdx.x & 63);
     const int wm = C::wave() / C::WN, wn = C::wave() % C::WN;
@@ -519,12 +468,10 @@ __device__ __forceinline__ LevelView level_kloop(int64_t K, AOp &aop, BOp &bop, 
     uint32_t va = 0xFFFFu, vb = 0xFFFFu;
     if (left > 0) {
         if constexpr (CHECK) {
-            if (check) {
-                const i16x2 m = bop.largest(aop.largest((i16x2){-1, -1}));
-                past = max(m.x, m.y) > (int)LV_MAX;
-                va = aop.first();
-                vb = bop.first();
-            }
+            const i16x2 m = bop.largest(aop.largest((i16x2){-1, -1}));
+            past = max(m.x, m.y) > (int)LV_MAX;
+            va = aop.first();
+            vb = bop.first();
         }
 #pragma unroll
         for (int q = 0; q < C::A_CPT; q++) aop.store_chunk(lds, q);
@@ -551,8 +498,7 @@ __device__ __forceinline__ LevelView level_kloop(int64_t K, AOp &aop, BOp &bop, 
             const int64_t groups = slices < C::KS ? slices : C::KS, part = K % C::BK ? K % C::BK : C::BK;
             const LevelCount ca{cnt[0], cnt[1], cnt[2], C::GT * (groups - 1) + C::GT * part / C::BK};
             const LevelCount cb{cnt[3], cnt[4], cnt[5], C::GT * groups};
-            if (level_view<LEVEL_DOUBT>(ca, cb, K) > LEVEL_PAST && whole() > LEVEL_PAST) return LEVEL_ELSEWHERE;
-            view = level_view<LEVEL_NEED>(ca, cb, K);
+            view = level_view(ca, cb, K);
             if (view > LEVEL_PAST) return view;
         }
     } else {
@@ -965,8 +911,7 @@ int level_shape(int64_t M, int64_t N);
 mpr_status level_step_launch(const LevelStep &p, bool first, int32_t *st, hipStream_t s);
 mpr_status level_prepare_launch(uint32_t *low, uint32_t *big, uint32_t *past, int64_t n, hipStream_t s);
 
-// gemm.hip: the product in the tile table's configuration, unless level_sample
-// finds its values in the levels: then nothing.
+// gemm.hip: the tiles of C with a marked cell, in the tile table's configuration.
 mpr_status gemm_past_launch(bool spare, int64_t M, int64_t N, int64_t K, const u16 *A, int64_t lda, const u16 *B,
                             int64_t ldb, u16 *C, int64_t ldc, hipStream_t s);
 

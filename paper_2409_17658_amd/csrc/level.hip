@@ -21,38 +21,41 @@ __device__ __forceinline__ bool level_tile(int tiles_m, int tiles_n, int &tm, in
 }
 
 // A block that the levels can not hold is computed in the f16 form or in
-// uint16, by its values (level_view); ELSEWHERE, a block that finds such values
-// leaves when the whole product's are, to the launch behind this one
-// (gemm_past_launch).
+// uint16, by its values (level_view): here, or, ELSEWHERE, by the launch behind
+// this one, which its cells are marked for (gemm_past_launch).
 template <class C, bool ELSEWHERE>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) void level_gemm_kernel(
     const u16 *__restrict__ A, int64_t lda, const u16 *__restrict__ B, int64_t ldb, u16 *__restrict__ Cm, int64_t ldc,
     int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int vec)
 {
     using T = typename LevelBack<C>::T;
-    __shared__ uint4 lds[LevelLds<C>::CHUNKS];
-    __shared__ int cnt[LEVEL_COUNTS], seen;
+    __shared__ uint4 lds[ELSEWHERE ? C::LDS_CHUNKS : LevelLds<C>::CHUNKS];
+    __shared__ int cnt[LEVEL_COUNTS];
     int tm, tn;
     if (!level_tile(tiles_m, tiles_n, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int rows = (int)min<int64_t>(C::BM, M - m0), cols = (int)min<int64_t>(C::BN, N - n0);
     LevelA<C> aop(glob(A) + m0 * lda, lda, rows, K);
     LevelB<C> bop(glob(B) + n0, ldb, cols, K);
-    auto whole = [&] { return ELSEWHERE ? level_sample(A, lda, B, ldb, M, N, K, &seen) : LEVEL_PAST; };
     LevelView view;
     {
         LevelAcc<C> acc;
-        view = level_kloop<C, true>(K, aop, bop, lds, acc, cnt, true, whole);
+        view = level_kloop<C, true>(K, aop, bop, lds, acc, cnt);
         if (view <= LEVEL_PAST &&
             (level_sure<C>(acc, rows, cols) || (view == LEVEL_IN && level_clean<C>(K, aop, bop, lds)))) {
             level_store<C>(glob(Cm) + m0 * ldc + n0, ldc, rows, cols, acc);
             return;
         }
     }
-    if (view == LEVEL_ELSEWHERE || whole() > LEVEL_PAST) return;
-    TileAcc<T> acc;
-    tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, (u16 *)lds, acc, view == LEVEL_U16);
-    tile_store<T>(Cm, ldc, M, N, m0, n0, vec != 0, acc);
+    if constexpr (ELSEWHERE) {
+        constexpr int ACROSS = C::BN / MARK_CELL;
+        const int r = (int)threadIdx.x / ACROSS * MARK_CELL, c = (int)threadIdx.x % ACROSS * MARK_CELL;
+        if (r < rows && c < cols) glob(Cm)[(m0 + r) * ldc + n0 + c] = view == LEVEL_U16 ? MARK_U16 : MARK_F16;
+    } else {
+        TileAcc<T> acc;
+        tile_mainloop<T, true>(A, lda, B, ldb, M, N, K, m0, n0, vec != 0, (u16 *)lds, acc, view == LEVEL_U16);
+        tile_store<T>(Cm, ldc, M, N, m0, n0, vec != 0, acc);
+    }
 }
 
 template <class C, bool ELSEWHERE = false>
@@ -130,20 +133,20 @@ __global__ __launch_bounds__(256) void tiny_product_kernel(const u16 *__restrict
 // Up to so many outputs (K < 128: the level form takes the others).
 constexpr int64_t TINY_OUTPUTS = 1 << 14;
 
-// Whether a product whose values leave the levels is computed by a launch of
-// its own behind the level form's, in the configuration that the tile table has
-// for its size, and not block by block in the level form's shape.  Where a CU
-// would get more of the work in blocks of 128 x 256 than in 128 x 128, the
-// stand-in loses to quantisation (entries 1000..10000, N = 3000: 1586 us,
-// in its own launch 1009, without the level form 996); elsewhere to its two
-// waves a SIMD, some 4 % (N = 2700: 765 us, 731 without the level form; N =
-// 4096 with its own launch 1970 and 1946).  The launch costs a product in the
-// levels 4 to 6 us (N = 3000, entries 0..40: 122 us without, 126.5), so short
+// Whether the blocks of a product whose values leave the levels are computed by
+// a launch of their own behind the level form's, in the configuration that the
+// tile table has for its size, and not where they are, in the level form's
+// shape.  Where a CU would get more of the work in blocks of 128 x 256 than in
+// 128 x 128, the stand-in loses to quantisation (entries 1000..10000, N = 3000:
+// 1586 us, in its own launch 1003, without the level form 996); elsewhere to its
+// two waves a SIMD, some 5 % (N = 2700: 770 us, 731 without the level form; N =
+// 4096 with its own launch 1967 and 1946).  The launch costs a product in the
+// levels 3 to 4 us (N = 3000, entries 0..40: 122 us without, 124.6), so short
 // ones that quantisation spares go without.
 static bool past_elsewhere(int64_t M, int64_t N, int64_t K)
 {
     const int64_t rows = (M + 127) / 128, tiles = rows * ((N + 127) / 128), cus = device_cu_count();
-    if (tiles < cus || !level_sampled(M, N, K)) return false;
+    if (tiles < cus) return false;
     const int64_t wide = (rows * ((N + 255) / 256) + cus - 1) / cus, square = (tiles + cus - 1) / cus;
     return (level_shape(M, N) == 4 && 2 * wide > square) || (double)M * (double)N * (double)K >= 3e10;
 }
@@ -181,7 +184,6 @@ mpr_status product_launch_spare(int cfg, int64_t M, int64_t N, int64_t K, const 
     // that a second one does not fit, the other half stays free
     const size_t pad = 84 * 1024 - sizeof(uint4) * LCfg0::LDS_CHUNKS;
     if (level_shape(M, N) % 4 == 0) {  // and one wave a SIMD is too few for the VALU forms
-        if (!level_sampled(M, N, K)) return level_launch<LCfg0>(M, N, K, A, lda, B, ldb, Cm, ldc, s, pad);
         const mpr_status e = level_launch<LCfg0, true>(M, N, K, A, lda, B, ldb, Cm, ldc, s, pad);
         return e != MPR_OK ? e : gemm_past_launch(true, M, N, K, A, lda, B, ldb, Cm, ldc, s);
     }

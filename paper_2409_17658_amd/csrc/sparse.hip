@@ -691,9 +691,8 @@ struct LevelGather {
 // way in and their minima left behind (LevelStep); otherwise p.L is canonical
 // and only L, O, their strides, n and the past words of p are used.  FIRST: the first
 // step of a chain, which looks at its values; the others go by the step before
-// (LevelStep).  ELSEWHERE: a tile past the levels is marked, by a first value that
-// no tile in the levels has, and left to sp_entry_kernel.
-constexpr u16 TILE_MARK = 0xFFFE;
+// (LevelStep).  ELSEWHERE: a tile past the levels is marked by its first value and
+// left to sp_entry_past_kernel.
 template <bool LATE, bool FIRST, bool ELSEWHERE>
 __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) void sp_level_kernel(
     LevelStep p, const int64_t *__restrict__ off, const int32_t *__restrict__ idx, const u16 *__restrict__ Bp,
@@ -734,7 +733,7 @@ __global__ __launch_bounds__(PCfg::NT) __attribute__((amdgpu_waves_per_eu(3))) v
         }
     }
     if constexpr (ELSEWHERE) {
-        if (threadIdx.x == 0) out[0] = TILE_MARK;
+        if (threadIdx.x == 0) out[0] = MARK_F16;
         return;
     }
     const gu16 *gB = glob(Bp) + kbeg * SBN;
@@ -759,7 +758,7 @@ __global__ __launch_bounds__(ENT) __attribute__((amdgpu_waves_per_eu(4))) void s
     const int t = (int)blockIdx.x, J = order[t / tiles_m];
     const int64_t n = p.n, m0 = (int64_t)(t % tiles_m) * EBM, j0 = (int64_t)J * SBN;
     const int64_t row = m0 + (int64_t)(threadIdx.x % EPARTS) * PCfg::BM;
-    if (!__syncthreads_or(threadIdx.x < EPARTS && row < n && glob(p.O)[row * p.ldo + j0] == TILE_MARK)) return;
+    if (!__syncthreads_or(threadIdx.x < EPARTS && row < n && glob(p.O)[row * p.ldo + j0] == MARK_F16)) return;
     const int64_t kbeg = off[J], nk = (off[J + 1] - kbeg) / SBK;
     const uint32_t *li = LATE ? p.low_in + m0 : nullptr;
     uint32_t *lo = LATE ? p.low_out + m0 : nullptr, *bo = LATE ? p.big_out + m0 : nullptr;

@@ -57,7 +57,7 @@ def test_products_of_mixed_blocks(mpr):
 
 # Sizes whose products past the levels have a launch of their own (128 x 256
 # blocks would leave CUs idle), and, launched to leave room, outputs of few
-# columns down to fewer than a sample's run of 8.
+# columns, also fewer than 8.
 PAST_SHAPES = [(3000, 3001, 136, False), (3050, 2900, 128, False), (33000, 9, 137, True), (33000, 8, 128, True),
                (33000, 7, 130, True), (2300, 2200, 200, True)]
 
@@ -76,6 +76,20 @@ def test_products_past_the_levels(mpr, shape):
             X[:rows] = small[:rows]
             A, B = mpr.to_device(X), mpr.to_device(Y)
             assert _same(mpr.minplus_gemm(A, B, spare=spare), mpr.minplus_gemm(A, B, cfg=0))
+
+
+@pytest.mark.parametrize("shape", PAST_SHAPES[:2])
+def test_products_partly_past_the_levels(mpr, shape):
+    """Blocks in the levels beside ones for either VALU form, whose borders are no
+    tile's: the launch behind computes whole tiles of them."""
+    M, N, K, spare = shape
+    X, Y = synth.random_matrix(M, K, 8, 0, 9, 0.2), synth.random_matrix(K, N, 9, 0, 9, 0.2)
+    for at, size, more in [(100, 300, 600), (500, 700, 20000), (1300, 65, 600), (1500, 1, 20000), (M - 130, 130, 600)]:
+        X[at : at + size] = np.where(X[at : at + size] == mpr.INF, mpr.INF, X[at : at + size] + more)
+        Y[:, at + 90 : at + 90 + size] = np.where(
+            Y[:, at + 90 : at + 90 + size] == mpr.INF, mpr.INF, Y[:, at + 90 : at + 90 + size] + more)
+    A, B = mpr.to_device(X), mpr.to_device(Y)
+    assert _same(mpr.minplus_gemm(A, B, spare=spare), mpr.minplus_gemm(A, B, cfg=0))
 
 
 STEP_LAWS = [(0, 31, 0.25), (0, 60, 0.9), (2100, 3000, 0.2), (0x7000, 0x7FFF, 0.3), (0, 3000, 0.2)]
