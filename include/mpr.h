@@ -143,8 +143,8 @@ mpr_status mpr_build_border_transfer(int m, uint16_t *A, int64_t lda, int64_t *s
  * product runs on the matrix cores when K >= 128 and N >= 4 (values 0..30 as
  * powers of two, the least sum read off the exponent of a sum of products).
  * A block of it whose minima pass that range is computed in the f16 form or,
- * where its values say that minima reach 2048, in uint16; a large product
- * whose values say so as a whole, in the configuration of the tile table.
+ * where its values say that minima reach 2048, in uint16; in a large product
+ * by a launch behind it, in the configuration of the tile table.
  * Other products run in the configuration of the tile table of the
  * process-wide arithmetic (mpr_set_arith; mpr_gemm_pick_config names it):
  * packed uint16 by default; in the f16 form the result is the same, but tiles
